@@ -201,7 +201,9 @@ int st_head_forward(const st_head_desc* desc, const void* features, const float*
  * ST_NOALLOC_MAX_WORKSPACE_MIB MiB per GPU the library runs on, held from the first call on that
  * GPU until the process ends (enough for the 1280x720 head 256 -> 128 -> 128 -> 19, which needs
  * 75 MiB).  The call allocates nothing, on the device or through any library; shapes with
- * st_workspace_bytes(desc) above the limit are refused with ST_ERR_TOO_LARGE before any GPU work.
+ * st_workspace_bytes(desc) above the limit are refused with ST_ERR_TOO_LARGE before any GPU work
+ * (float32 heads, and those with channel counts that are no multiples of 64: only where the
+ * buffers of the forward pass alone exceed it).
  * The first call on a device looks the array's address up (hipGetSymbolAddress); make that call
  * outside a capture.  Every call on a GPU uses that GPU's one array: calls that overlap on one
  * GPU (two streams, two threads) race -- serialise them.  The event profile (st_profile_enable)
@@ -302,7 +304,8 @@ const char* st_version(void);
 /* ---- introspection for tests and tools (no part of the training path) -------------------- */
 
 /* Byte offsets of the library's internal buffers inside `workspace`, so that a test can look
- * at intermediate tensors after a call.  Offsets are 0 for buffers this shape does not use. */
+ * at intermediate tensors after a call.  Offsets are 0 for buffers this shape does not use.  On
+ * the bfloat16 path the channels of feat .. da2 are padded with zeros to a multiple of 64. */
 typedef struct st_workspace_layout {
     size_t feat;      /* features, position-major [n, h+2, row_pitch, c_in], zero border    */
     size_t a1, a2;    /* activations after ReLU, same layout, c1 / c2 channels              */

@@ -17,8 +17,6 @@ namespace st {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-bool conv3_mfma_supported(int c2, int C) { return (c2 == 64 || c2 == 128 || c2 == 256) && C <= 32; }
-
 // ------------------------------------------------------------------ backward
 // One block = C3B_BP consecutive padded positions (g is zero on the border).  The block first
 // forms g = d loss / d z for its cells from what the loss kernel left behind -- the per-tile slots
@@ -35,6 +33,8 @@ bool conv3_mfma_supported(int c2, int C) { return (c2 == 64 || c2 == 128 || c2 =
 // tile is loaded once, position-major, before the first barrier (its latency overlaps the
 // staging of g) and kept in LDS: the ReLU mask is read from it directly, the dW3 operand
 // through the transposing LDS read.
+// A block takes C2 channels of the layer: all of them, or (RUNS, heads with more than 256) the run of
+// channels that blockIdx.y names, each run forming g for itself.
 // The work per position is small and every phase is a chain of dependent memory round trips, so
 // the block is kept small: the grid then covers the whole chip and each chain is short.
 constexpr int C3B_BP = 64;
@@ -46,7 +46,7 @@ constexpr int C3B_BP = 64;
 // bookkeeping of the forward pass that came before (finish_block: loss, per-frame mean IoU, the
 // metric for the host) instead -- it touches nothing this kernel reads or writes, and riding
 // along saves that pass a launch of its own.
-template <int C2, bool FIN>
+template <int C2, bool RUNS, bool FIN>
 __global__ void __launch_bounds__(256, 1)
 k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
                  const unsigned long long* __restrict__ n_valid, int CP, LossTiling lt,
@@ -55,7 +55,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
                  float* __restrict__ part, Geo g, int PPT, int guard, int grp_blocks, int main_blocks, FinishArgs fin)
 {
     if (FIN && (int)blockIdx.x >= main_blocks) {
-        finish_block<true>(fin, (int)blockIdx.x - main_blocks, 0);
+        if (!RUNS || blockIdx.y == 0) finish_block<true>(fin, (int)blockIdx.x - main_blocks, 0);
         return;
     }
     constexpr int BP = C3B_BP;
@@ -80,7 +80,8 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     const int head = g.grouped ? blockIdx.x / grp_blocks : 0;
     const int m0 = g.grouped ? head * frame + (blockIdx.x - head * grp_blocks) * BP : blockIdx.x * BP;
     const int m_end = g.grouped ? (head + 1) * frame : PP;
-    W3T += (size_t)head * C2 * 32;
+    const int k2 = RUNS ? g.k2 : C2, ch0 = RUNS ? blockIdx.y * C2 : 0;     // channel pitch; first channel of this block
+    W3T += ((size_t)head * k2 + ch0) * 32;
 
     // ---- early loads: the block's a2 tile (position-major, 16 bytes per load) on its way to LDS.
     //      Both uses take it from there: the ReLU mask of the da2 part, and the dW3 part, whose
@@ -95,7 +96,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     for (int k = 0; k < A2_CHUNKS; ++k) {
         const int q = tid + 256 * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
         // (rows past the last position repeat it: d loss / d z is zero there)
-        a2v[k] = *(const u32x4*)(a2 + (size_t)min(m0 + p, PP - 1) * C2 + part8 * 8);
+        a2v[k] = *(const u32x4*)(a2 + (size_t)min(m0 + p, PP - 1) * k2 + ch0 + part8 * 8);
     }
     // W3^T fragments of this wavefront's da2 tiles: rows = channels, k = 16 classes per step
     bf16x8 wfr[OH][2];
@@ -199,7 +200,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     }
 
     // ---- dW3: D[c][o] = sum_pos g[c][pos] * a2[pos][o] over this block's positions
-    float* slot = part + (size_t)blockIdx.x * (32 * C2 + 32);
+    float* slot = part + (size_t)blockIdx.x * (32 * k2 + 32);
 #pragma unroll
     for (int d = 0; d < DW; ++d) {
         const int t = wave + 4 * d;
@@ -222,14 +223,14 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
-                if (c < g.C) slot[c * C2 + t * 32 + l32] = acc[r];    // (rows beyond the classes are never read)
+                if (c < g.C) slot[c * k2 + ch0 + t * 32 + l32] = acc[r];    // (rows beyond the classes are never read)
             }
         }
     }
-    if (tid < 32) {
+    if (tid < 32 && ch0 == 0) {
         float s = 0.f;
         for (int p = 0; p < BP; ++p) s += (float)g_cp[tid * GP + p];
-        if (tid < g.C) slot[32 * C2 + tid] = s;
+        if (tid < g.C) slot[32 * k2 + tid] = s;
     }
     __syncthreads();
 
@@ -237,7 +238,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     for (int q = tid; q < BP * (C2 / 8); q += 256) {
         const int p = q / (C2 / 8), part8 = q % (C2 / 8);
         if (m0 + p < m_end)
-            *(uint4*)(da2 + (size_t)(m0 + p) * C2 + part8 * 8) = *(const uint4*)(Os + p * OLD + part8 * 8);
+            *(uint4*)(da2 + (size_t)(m0 + p) * k2 + ch0 + part8 * 8) = *(const uint4*)(Os + p * OLD + part8 * 8);
     }
     for (int q = tid; q < (BP / 8) * C2; q += 256) {
         const int o = q % C2, pg = q / C2;
@@ -245,13 +246,13 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
         bf16x8 ov;
 #pragma unroll
         for (int e = 0; e < 8; ++e) ov[e] = Os[(pg * 8 + e) * OLD + o];
-        *(bf16x8*)(da2T + xt_index(o, guard + m0 + pg * 8, PPT / 8)) = ov;
+        *(bf16x8*)(da2T + xt_index(ch0 + o, guard + m0 + pg * 8, PPT / 8)) = ov;
     }
 }
 
 // blocks (and partial-sum slots) per head
 int conv3_bwd_blocks(const Geo& g) { return cdiv(g.padded_positions() / g.heads(), C3B_BP); }
-size_t conv3_bwd_slot_floats(const Geo& g) { return (size_t)32 * g.c2 + 32; }
+size_t conv3_bwd_slot_floats(const Geo& g) { return (size_t)32 * g.k2 + 32; }
 
 void conv3_bwd_mfma(Ctx& c, const Plan& p, const float* slots, const float* T,
                     const unsigned long long* n_valid, const bf16* a2, const bf16* W3T,
@@ -268,22 +269,26 @@ void conv3_bwd_mfma(Ctx& c, const Plan& p, const float* slots, const float* T,
         fin = *finish;
     }
     // with `finish`: one more block per frame and one for the loss
-    const dim3 grid(main_blocks + (finish ? fin.fph + 1 : 0));
-#define ST_C3B(C2)                                                                                             \
+    const int run = g.k2 <= 256 ? g.k2 : g.k2 % 128 == 0 ? 128 : 64;     // channels per block
+    const dim3 grid(main_blocks + (finish ? fin.fph + 1 : 0), g.k2 / run);
+#define ST_C3B(C2, RUNS)                                                                                       \
     do {                                                                                                       \
         if (finish)                                                                                            \
-            ST_LAUNCH(c, "conv3_bwd_mfma+finish_pass", (k_conv3_bwd_mfma<C2, true>), grid, dim3(256), 0, slots, T,   \
+            ST_LAUNCH(c, "conv3_bwd_mfma+finish_pass", (k_conv3_bwd_mfma<C2, RUNS, true>), grid, dim3(256), 0, slots, T, \
                       n_valid, CP, p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin); \
         else                                                                                                   \
-            ST_LAUNCH(c, "conv3_bwd_mfma", (k_conv3_bwd_mfma<C2, false>), grid, dim3(256), 0, slots, T, n_valid, CP, \
+            ST_LAUNCH(c, "conv3_bwd_mfma", (k_conv3_bwd_mfma<C2, RUNS, false>), grid, dim3(256), 0, slots, T, n_valid, CP, \
                       p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin);    \
     } while (0)
-    switch (g.c2) {
-    case 64: ST_C3B(64); break;
-    case 128: ST_C3B(128); break;
-    case 256: ST_C3B(256); break;
-    default: c.status = ST_ERR_SHAPE;
-    }
+    if (run == g.k2) {
+        switch (run) {
+        case 64: ST_C3B(64, false); break;
+        case 128: ST_C3B(128, false); break;
+        case 192: ST_C3B(192, false); break;
+        default: ST_C3B(256, false); break;
+        }
+    } else if (run == 128) ST_C3B(128, true);
+    else ST_C3B(64, true);
 #undef ST_C3B
 }
 

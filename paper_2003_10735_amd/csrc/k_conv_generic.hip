@@ -1,8 +1,5 @@
 // Plain tiled GEMM kernels for every contraction of the head (forward, data-gradient and
-// weight-gradient of the 3x3 and 1x1 convolutions), templated on the element type of the
-// activations and weights.  With float elements this is the reference-precision path; with
-// bfloat16 elements it computes what the matrix-core kernels compute (bf16 x bf16 products are
-// exact in float32, sums in float32) and serves shapes those kernels do not cover.
+// weight-gradient of the 3x3 and 1x1 convolutions) of the float32 path.
 //
 //   C[m][n] = sum_k A(m, k) * B(k, n),   64 x 64 tile per block, 4 x 4 per thread, K step 16.
 //
@@ -406,29 +403,21 @@ static void bwd_impl(Ctx& c, const Plan& p, char* ws, const WE* W2, const WE* W3
 void generic_forward(Ctx& c, const Plan& p, char* ws, float* z)
 {
     const float* theta = (const float*)(ws + p.theta);
-    if (p.bf16)
-        fwd_impl<bf16, bf16>(c, p, ws, (const bf16*)(ws + p.wq1), (const bf16*)(ws + p.wq2),
-                             (const bf16*)(ws + p.wq3), theta, z);
-    else
-        fwd_impl<float, float>(c, p, ws, theta + p.po.W1, theta + p.po.W2, theta + p.po.W3, theta, z);
+    fwd_impl<float, float>(c, p, ws, theta + p.po.W1, theta + p.po.W2, theta + p.po.W3, theta, z);
 }
 
 // d loss / d features [n, c_in, h, w] float32 from da1 (run after generic_backward)
 void generic_feature_grad(Ctx& c, const Plan& p, char* ws, float* dfeat)
 {
     const float* theta = (const float*)(ws + p.theta);
-    if (p.bf16) feat_grad_impl<bf16, bf16>(c, p, ws, (const bf16*)(ws + p.wq1), dfeat);
-    else feat_grad_impl<float, float>(c, p, ws, theta + p.po.W1, dfeat);
+    feat_grad_impl<float, float>(c, p, ws, theta + p.po.W1, dfeat);
 }
 
 void generic_backward(Ctx& c, const Plan& p, char* ws)
 {
     const float* theta = (const float*)(ws + p.theta);
     float* grad = (float*)(ws + p.grad);
-    if (p.bf16)
-        bwd_impl<bf16, bf16>(c, p, ws, (const bf16*)(ws + p.wq2), (const bf16*)(ws + p.wq3), grad);
-    else
-        bwd_impl<float, float>(c, p, ws, theta + p.po.W2, theta + p.po.W3, grad);
+    bwd_impl<float, float>(c, p, ws, theta + p.po.W2, theta + p.po.W3, grad);
 }
 
 }  // namespace st

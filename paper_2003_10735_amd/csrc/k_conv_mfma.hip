@@ -68,7 +68,7 @@ struct ConvArgs {
     float* zpart;
     int n_cls, zpitch;
     // EPI 3: the plain sums go, as float32, straight to a dense [n][cout][h][w] tensor
-    float* dense;
+    float* dense; int dense_c;   // (channels of that tensor: cout without the padding)
     int PP, Hp, Wp, h, w, cin, cout, PPT, guard;
     int m_tiles, n_tiles, tiles_per_xcd;
     // Several heads: positions [k * grp_pp, (k + 1) * grp_pp) use weight set k (Wq, bias and W3q
@@ -288,11 +288,11 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         const int mp = m0 + kgrp * 32 + l32;
         const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
         if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) {
-            float* dst = a.dense + ((size_t)img * a.cout * a.h + (y - 1)) * a.w + (x - 1);
+            float* dst = a.dense + ((size_t)img * a.dense_c * a.h + (y - 1)) * a.w + (x - 1);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int ch = n0 + wn * 32 + (r >> 2) * 8 + lhi * 4 + (r & 3);
-                if (ch < a.cout) dst[(size_t)ch * a.h * a.w] = mine[r];
+                if (ch < a.dense_c) dst[(size_t)ch * a.h * a.w] = mine[r];
             }
         }
         return;
@@ -387,8 +387,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     }
 }
 
-bool conv3x3_mfma_supported(int cin, int cout) { return cin % CV_BK == 0 && cout % 32 == 0 && cout >= 32; }
-
+// (cin and cout are multiples of 64 here: Geo::ki, k1, k2)
 // epi 0: Y = relu(conv + bias); epi 1: Y = conv * [mask > 0]; with W3q / zpart (epi 0, cout a
 // multiple of 64) the block also leaves its share of the classifier's logits; epi 3: the plain
 // sums as float32 to the dense tensor `dense` [n][cout][h][w]
@@ -399,7 +398,7 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     const Geo& g = p.g;
     ConvArgs a;
     a.X = X; a.Wq = Wq; a.bias = bias; a.mask = mask; a.Y = Y; a.YT = YT;
-    a.W3q = W3q; a.zpart = zpart; a.n_cls = p.g.C; a.zpitch = (p.g.C + 3) / 4 * 4; a.dense = dense;
+    a.W3q = W3q; a.zpart = zpart; a.n_cls = p.g.C; a.zpitch = (p.g.C + 3) / 4 * 4; a.dense = dense; a.dense_c = g.c_in;
     a.PP = p.g.padded_positions(); a.Hp = p.g.Hp; a.Wp = p.g.Wp; a.h = p.g.h; a.w = p.g.w;
     a.cin = cin; a.cout = cout;
     a.PPT = p.PPT; a.guard = p.guard;

@@ -103,7 +103,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             const int lc = cell % CW, r = cell / CW;
             const int cx = min(max(cx0 + lc, 0), g.w - 1), cy = min(max(cy0 + r, 0), g.h - 1);
             const size_t mp = ((size_t)img * g.Hp + cy + 1) * g.Wp + cx + 1;
-            // one, two or four shares (64, 128, 256 channels); within a group of two an absent
+            // up to four shares (one per 64 channels); within a group of two an absent
             // share re-reads the last one (it is then not added), so that the loads of a group are
             // issued together.  Only loaded here: the sums wait until every load of the prologue
             // is on its way.
@@ -113,7 +113,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             zr[k][1] = *(const f32x4*)(zp + (zs.n_parts > 1 ? share : 0));
             if (zs.n_parts > 2) {
                 zr[k][2] = *(const f32x4*)(zp + 2 * share);
-                zr[k][3] = *(const f32x4*)(zp + 3 * share);
+                zr[k][3] = *(const f32x4*)(zp + (zs.n_parts > 3 ? 3 : 2) * share);
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) bq[k][e] = zs.b3[g.head_of(img) * zs.b3_stride + min(chunk * 4 + e, C - 1)];
@@ -208,7 +208,17 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             }
             if (zs.n_parts > 2) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(1.f, zr[k][3][e], __builtin_fmaf(1.f, zr[k][2][e], acc[e]));
+                for (int e = 0; e < 4; ++e) {
+                    acc[e] = __builtin_fmaf(1.f, zr[k][2][e], acc[e]);
+                    if (zs.n_parts > 3) acc[e] = __builtin_fmaf(1.f, zr[k][3][e], acc[e]);
+                }
+                // (heads with more than 256 channels in the second layer)
+                for (int s = 4; s < zs.n_parts; ++s) {
+                    const int ii = min(i, CH * CW * QC - 1), cl = ii / QC, ch = ii - cl * QC;
+                    const int cx = min(max(cx0 + cl % CW, 0), g.w - 1), cy = min(max(cy0 + cl / CW, 0), g.h - 1);
+                    const size_t mp = ((size_t)img * g.Hp + cy + 1) * g.Wp + cx + 1;
+                    acc += *(const f32x4*)(zs.parts + ((size_t)s * g.padded_positions() + mp) * CP + ch * 4);
+                }
             }
             if (i < CH * CW * QC) {
 #pragma unroll

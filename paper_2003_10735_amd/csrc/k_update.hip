@@ -26,19 +26,18 @@ namespace st {
 //      block: the tile losses added in a fixed order (float64) over the number of valid pixels.
 //
 // Roles (1) and (2) also refresh the bfloat16 copies of the new weights:
-//   wq1, wq2, wq3 : for the forward convolutions
+//   wq1, wq2, wq3 : for the forward convolutions; bq1, bq2: their biases, where padded channels follow
 //   wq2t          : W2 with the roles of o and i exchanged and the taps mirrored (tap' = 8 - tap),
 //                   for the data-gradient of layer 2 run as a forward convolution
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
-//   wq3t          : W3 transposed, [c2][32] with zero columns beyond the classes: the A fragments of
+//   wq3t          : W3 transposed, [k2][32] with zero columns beyond the classes: the A fragments of
 //                   the classifier's backward kernel, read straight from memory
-// wq3 has theta's order.  So do wq1 and wq2 for the plain tiled kernels (frag == 0); the
-// matrix-core convolutions read wq1, wq2 and wq2t in fragment order (wfrag_index).
+// wq3 is [class][k2]; wq1, wq2 and wq2t are in fragment order (wfrag_index).  Rows and columns of
+// padded channels are cleared when the call opens and never written.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; const float* grad; size_t stride; int splits1, splits2, splits3;
-    bf16* wq1; bf16* wq1t; bf16* wq2; bf16* wq2t; bf16* wq3; bf16* wq3t;
-    ParamOffsets po; int c_in, c1, c2;
-    int frag;        // wq1 / wq2 / wq2t in fragment order
+    bf16* wq1; bf16* wq1t; bf16* wq2; bf16* wq2t; bf16* wq3; bf16* wq3t; float* bq1; float* bq2;
+    ParamOffsets po; int c_in, c1, c2, ki, k1, k2;   // k: channel pitches of the operand copies
     float lr, mu;
     int adam; AdamStep ad;   // adam != 0: vel = first moment m, vel2 = second moment v
     int do_step;     // 0: only refresh the bfloat16 copies
@@ -59,16 +58,26 @@ struct UpdateArgs {
 };
 
 
-// index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
-__device__ __forceinline__ size_t external_index(const UpdateArgs& a, size_t j)
+// Where an internal parameter index j ([o][kh][kw][i]) of a 3x3 block lies.  (A head has fewer than
+// 2^30 parameters: 32-bit divisions, a 64-bit one is some forty instructions longer.)
+struct Weight3x3 { unsigned o, tap, i; };
+__device__ __forceinline__ Weight3x3 weight3x3(unsigned r, unsigned cin)
 {
-    if (j < a.po.b1) {
-        const size_t r = j - a.po.W1, i = r % a.c_in, tap = (r / a.c_in) % 9, o = r / ((size_t)a.c_in * 9);
-        return a.po.W1 + (o * a.c_in + i) * 9 + tap;
+    const unsigned row = r / cin, o = row / 9u;
+    return Weight3x3{o, row - o * 9u, r - row * cin};
+}
+
+// index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
+__device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned j)
+{
+    if (j < (unsigned)a.po.b1) {
+        const Weight3x3 k = weight3x3(j, a.c_in);
+        return (k.o * a.c_in + k.i) * 9u + k.tap;
     }
-    if (j >= a.po.W2 && j < a.po.b2) {
-        const size_t r = j - a.po.W2, i = r % a.c1, tap = (r / a.c1) % 9, o = r / ((size_t)a.c1 * 9);
-        return a.po.W2 + (o * a.c1 + i) * 9 + tap;
+    const unsigned w2 = (unsigned)a.po.W2;
+    if (j >= w2 && j < (unsigned)a.po.b2) {
+        const Weight3x3 k = weight3x3(j - w2, a.c1);
+        return w2 + (k.o * a.c1 + k.i) * 9u + k.tap;
     }
     return j;
 }
@@ -76,7 +85,7 @@ __device__ __forceinline__ size_t external_index(const UpdateArgs& a, size_t j)
 // (EE: the early-exit form's extras -- save_old here, the host copy of the metric in finish_block --
 //  are compiled in; the kernels of the fixed-step form never look at those fields)
 template <bool EE>
-__device__ __forceinline__ void apply_update(const UpdateArgs& a, size_t j, float g)
+__device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, float g)
 {
     float w = a.ext_in ? a.ext_in[external_index(a, j)] : a.theta[j];
     if (a.ext_in) a.theta[j] = w;
@@ -101,31 +110,30 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, size_t j, floa
     if (a.wq1) {
         const bf16 q = (bf16)w;
         if (j < a.po.b1) {
-            const size_t r = j - a.po.W1;
-            if (a.frag) {
-                const int i = (int)(r % a.c_in), tap = (int)((r / a.c_in) % 9), o = (int)(r / ((size_t)a.c_in * 9));
-                a.wq1[wfrag_index(o, tap, i, a.c_in)] = q;
-                if (a.wq1t) a.wq1t[wfrag_index(i, 8 - tap, o, a.c1)] = q;
-            } else a.wq1[r] = q;
-        } else if (j >= a.po.W2 && j < a.po.b2) {
-            const size_t r = j - a.po.W2;
-            if (a.frag) {
-                const int i = (int)(r % a.c1), tap = (int)((r / a.c1) % 9), o = (int)(r / ((size_t)a.c1 * 9));
-                a.wq2[wfrag_index(o, tap, i, a.c1)] = q;
-                a.wq2t[wfrag_index(i, 8 - tap, o, a.c2)] = q;
-            } else a.wq2[r] = q;
-        } else if (j >= a.po.W3 && j < a.po.b3) {
-            const size_t r = j - a.po.W3;
-            a.wq3[r] = q;
-            if (a.wq3t) a.wq3t[(r % a.c2) * 32 + r / a.c2] = q;
+            const Weight3x3 k = weight3x3(j, a.c_in);
+            a.wq1[wfrag_index(k.o, k.tap, k.i, a.ki)] = q;
+            if (a.wq1t) a.wq1t[wfrag_index(k.i, 8 - k.tap, k.o, a.k1)] = q;
+        } else if (j < a.po.W2) {
+            if (a.bq1) a.bq1[j - a.po.b1] = w;
+        } else if (j < a.po.b2) {
+            const Weight3x3 k = weight3x3(j - (unsigned)a.po.W2, a.c1);
+            a.wq2[wfrag_index(k.o, k.tap, k.i, a.k1)] = q;
+            if (a.wq2t) a.wq2t[wfrag_index(k.i, 8 - k.tap, k.o, a.k2)] = q;
+        } else if (j < a.po.W3) {
+            if (a.bq2) a.bq2[j - a.po.b2] = w;
+        } else if (j < a.po.b3) {
+            const unsigned r = j - (unsigned)a.po.W3;
+            const unsigned cl = r / (unsigned)a.c2, o = r - cl * a.c2;
+            a.wq3[cl * a.k2 + o] = q;
+            if (a.wq3t) a.wq3t[o * 32 + cl] = q;
         }
     }
 }
 
-// Four consecutive parameters (all block boundaries below W3 are multiples of four here, so
-// the four lie in the same block).
+// Four consecutive parameters (all block boundaries below W3 are multiples of four here, and so are
+// the channel counts: the four lie in the same block and under the same tap).
 template <bool EE>
-__device__ __forceinline__ void apply_update4(const UpdateArgs& a, size_t j, f32x4 g)
+__device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f32x4 g)
 {
     f32x4 w;
     if (a.ext_in) {
@@ -165,24 +173,22 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, size_t j, f32
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[e] = (bf16)w[e];
         if (j < a.po.b1) {
-            const size_t r = j - a.po.W1;
-            if (a.frag) {
-                const int i = (int)(r % a.c_in), tap = (int)((r / a.c_in) % 9), o = (int)(r / ((size_t)a.c_in * 9));
-                *(bf16x4*)(a.wq1 + wfrag_index(o, tap, i, a.c_in)) = q;
-                if (a.wq1t) {
+            const Weight3x3 k = weight3x3(j, a.c_in);
+            *(bf16x4*)(a.wq1 + wfrag_index(k.o, k.tap, k.i, a.ki)) = q;
+            if (a.wq1t) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) a.wq1t[wfrag_index(i + e, 8 - tap, o, a.c1)] = q[e];
-                }
-            } else *(bf16x4*)(a.wq1 + r) = q;
-        } else if (j >= a.po.W2 && j < a.po.b2) {
-            const size_t r = j - a.po.W2;
-            if (a.frag) {
-                const int i = (int)(r % a.c1), tap = (int)((r / a.c1) % 9), o = (int)(r / ((size_t)a.c1 * 9));
-                *(bf16x4*)(a.wq2 + wfrag_index(o, tap, i, a.c1)) = q;
+                for (int e = 0; e < 4; ++e) a.wq1t[wfrag_index(k.i + e, 8 - k.tap, k.o, a.k1)] = q[e];
+            }
+        } else if (j < a.po.W2) {
+            if (a.bq1) *(f32x4*)(a.bq1 + (j - a.po.b1)) = w;
+        } else if (j < a.po.b2) {
+            const Weight3x3 k = weight3x3(j - (unsigned)a.po.W2, a.c1);
+            *(bf16x4*)(a.wq2 + wfrag_index(k.o, k.tap, k.i, a.k1)) = q;
+            if (a.wq2t) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a.wq2t[wfrag_index(i + e, 8 - tap, o, a.c2)] = q[e];
-            } else *(bf16x4*)(a.wq2 + r) = q;
-        }
+                for (int e = 0; e < 4; ++e) a.wq2t[wfrag_index(k.i + e, 8 - k.tap, k.o, a.k2)] = q[e];
+            }
+        } else if (a.bq2) *(f32x4*)(a.bq2 + (j - a.po.b2)) = w;
     }
 }
 
@@ -196,7 +202,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         if (a.wq1) { a.wq1 += head * a.hs_wq1; a.wq2 += head * a.hs_wq2; a.wq3 += head * a.hs_wq3; }
         if (a.wq1t) a.wq1t += head * a.hs_wq1;
         if (a.wq2t) a.wq2t += head * a.hs_wq2;
-        if (a.wq3t) a.wq3t += head * (size_t)a.c2 * 32;
+        if (a.wq3t) a.wq3t += head * (size_t)a.k2 * 32;
         if (a.ext_in) a.ext_in += head * a.hs_ext;
         if (a.ext_out) a.ext_out += head * a.hs_ext;
         if (a.part3) a.part3 += head * a.hs_part3;
@@ -205,7 +211,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         // role (1), four parameters per thread over [0, W3): the partial gradients are added in
         // ascending order of the split, four loads in flight at a time
         if (a.vec) {
-            const size_t j = ((size_t)b * 256 + threadIdx.x) * 4;
+            const unsigned j = ((unsigned)b * 256 + threadIdx.x) * 4;
             if (j >= a.po.W3) return;
             f32x4 g = {0.f, 0.f, 0.f, 0.f};
             if (a.do_step) {
@@ -226,7 +232,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
             return;
         }
         // role (1), one parameter per thread; W3/b3 are left to role (2) when it is active
-        const size_t j = (size_t)b * 256 + threadIdx.x;
+        const unsigned j = (unsigned)b * 256 + threadIdx.x;
         const size_t limit = a.nb_l3 ? a.po.W3 : a.po.total;
         if (j >= limit) return;
         float g = 0.f;
@@ -238,7 +244,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         apply_update<EE>(a, j, g);
     } else if (b < a.nb_main + a.nb_tail) {
         // [W3, total) one by one (only when role (2) is not active)
-        const size_t j = a.po.W3 + (size_t)(b - a.nb_main) * 256 + threadIdx.x;
+        const unsigned j = (unsigned)a.po.W3 + (unsigned)(b - a.nb_main) * 256 + threadIdx.x;
         if (j >= a.po.total) return;
         float g = 0.f;
         if (a.do_step) {
@@ -247,7 +253,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         }
         apply_update<EE>(a, j, g);
     } else if (b < a.nb_main + a.nb_tail + a.nb_l3) {
-        // role (2): slot layout [32 classes][c2] weights, then [32] biases.  The slots were
+        // role (2): slot layout [32 classes][k2] weights, then [32] biases.  The slots were
         // written by other compute units, so every load is a round trip to memory: the role is
         // laid out for few of them.  A block takes 16 consecutive values; its 256 threads split
         // the slots into 16 contiguous runs (thread = value + 16 * run), every thread adds its
@@ -260,7 +266,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         const bool live = k < n_w + a.C;
         float acc = 0.f;
         if (a.do_step && live) {
-            const float* src = a.part3 + (k < n_w ? (size_t)k : (size_t)32 * a.c2 + (k - n_w));
+            const float* src = a.part3 + (k < n_w ? (size_t)(k / a.c2) * a.k2 + k % a.c2 : (size_t)32 * a.k2 + (k - n_w));
             const int per = (a.blocks3 + 15) / 16;
             const int s1 = min((run + 1) * per, a.blocks3);
             int s = run * per;
@@ -286,13 +292,13 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
             float total = run_sum[0][kk];
 #pragma unroll
             for (int r = 1; r < 16; ++r) total += run_sum[r][kk];
-            apply_update<EE>(a, a.po.W3 + k, total);
+            apply_update<EE>(a, (unsigned)a.po.W3 + k, total);
         }
     } else if (b < a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish) {
         finish_block<EE>(f, b - a.nb_main - a.nb_tail - a.nb_l3, head);
     } else {
         // parameters back to the caller's order
-        const size_t j = (size_t)(b - a.nb_main - a.nb_tail - a.nb_l3 - a.nb_finish) * 256 + threadIdx.x;
+        const unsigned j = (unsigned)(b - a.nb_main - a.nb_tail - a.nb_l3 - a.nb_finish) * 256 + threadIdx.x;
         if (j < a.po.total) a.ext_out[external_index(a, j)] = a.theta[j];
     }
 }
@@ -378,9 +384,9 @@ static void head_strides(UpdateArgs& a, const Plan& p)
     a.hs_param = p.head_stride;
     a.hs_ext = p.po.total;
     a.hs_grad = p.grad_stride * p.grad_copies;
-    a.hs_wq1 = p.po.b1 - p.po.W1;
-    a.hs_wq2 = p.po.b2 - p.po.W2;
-    a.hs_wq3 = p.po.b3 - p.po.W3;
+    a.hs_wq1 = (size_t)p.g.k1 * 9 * p.g.ki;
+    a.hs_wq2 = (size_t)p.g.k2 * 9 * p.g.k1;
+    a.hs_wq3 = (size_t)p.g.C * p.g.k2;
     a.hs_part3 = (size_t)p.blocks3 * conv3_bwd_slot_floats(p.g);
 }
 
@@ -404,19 +410,20 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.wq1 = p.bf16 ? (bf16*)(ws + p.wq1) : nullptr;
     a.wq1t = (p.mfma && w1t) ? (bf16*)(ws + p.wq1t) : nullptr;
     a.wq2 = p.bf16 ? (bf16*)(ws + p.wq2) : nullptr;
-    a.wq2t = (p.bf16 && p.wq2t) ? (bf16*)(ws + p.wq2t) : nullptr;
+    a.wq2t = p.wq2t ? (bf16*)(ws + p.wq2t) : nullptr;
     a.wq3 = p.bf16 ? (bf16*)(ws + p.wq3) : nullptr;
     a.wq3t = p.wq3t ? (bf16*)(ws + p.wq3t) : nullptr;
-    a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2;
-    a.frag = p.mfma ? 1 : 0;
+    a.bq1 = p.bq1 ? (float*)(ws + p.bq1) : nullptr;
+    a.bq2 = p.bq2 ? (float*)(ws + p.bq2) : nullptr;
+    a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2; a.ki = p.g.ki; a.k1 = p.g.k1; a.k2 = p.g.k2;
     a.lr = lr; a.mu = mu; a.do_step = do_step ? 1 : 0;
     a.part3 = (const float*)(ws + p.grad3);
     a.blocks3 = p.blocks3; a.slot3 = conv3_bwd_slot_floats(p.g); a.C = p.g.C;
     const bool params = do_step || p.bf16 || a.ext_in;
     const bool l3 = params && p.mfma && do_step;
-    // four parameters per thread when every block below W3 starts at a multiple of four and the
-    // split copies keep 16-byte alignment
-    a.vec = (p.po.b1 % 4 == 0 && p.po.W2 % 4 == 0 && p.po.b2 % 4 == 0 && p.po.W3 % 4 == 0) ? 1 : 0;
+    // four parameters per thread when every block below W3, and every row under one tap, starts at a
+    // multiple of four
+    a.vec = (p.g.c_in % 4 == 0 && p.g.c1 % 4 == 0 && p.g.c2 % 4 == 0) ? 1 : 0;
     if (a.vec) {
         a.nb_main = params ? cdiv(p.po.W3 / 4, 256) : 0;
         a.nb_tail = (params && !l3) ? cdiv(p.po.total - p.po.W3, 256) : 0;
@@ -448,7 +455,7 @@ void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamSte
 // are multiples of 16 bytes from a 16-byte aligned start, in the [n, c_in, h, w] order.
 bool pack_covers_borders(const Plan& p, const void* features, int feat_dtype)
 {
-    return p.mfma && !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && p.g.c_in % 64 == 0 &&
+    return p.mfma && !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && p.g.c_in % 64 == 0 && !p.g.padded() &&
            ((uintptr_t)features & 15) == 0;
 }
 

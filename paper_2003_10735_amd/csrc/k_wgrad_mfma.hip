@@ -35,7 +35,8 @@ struct WgradArgs {
     float* dW;         // [splits][stride] : this layer's weight block, [o][9][cin]
     float* db;         // [splits][stride] : this layer's bias block
     size_t split_stride;
-    int cin, cout, PPT, guard, Wp;
+    int cin, cout;        // channels of the gradient itself; the operands' are padded to multiples of 32
+    int PPT, guard, Wp;
     int units_per_wave;   // 16-position units per wavefront
     int n_units;          // units of one head's positions
     int o_tiles, i_tiles, splits, items_per_xcd;
@@ -290,24 +291,36 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     if (want_bias && lhi == 0) redb[wave * 32 + l32] = acc[9][0];
     __syncthreads();
     float* dW = a.dW + head * a.head_out_stride + (size_t)split * a.split_stride;
-    for (int q = tid; q < 9 * 32 * 8; q += 256) {
+    auto sum_of = [&](int q) {
         const int row = q >> 3, part = q & 7;
-        const int t = row >> 5, ol = row & 31;
-        const int chunk = (part ^ ((ol >> 1) & 7)) << 2;
+        const int chunk = (part ^ (((row & 31) >> 1) & 7)) << 2;
         const f32x4 v0 = *(const f32x4*)(red + ((0 * 9 * 32 + row) * 32 + chunk));
         const f32x4 v1 = *(const f32x4*)(red + ((1 * 9 * 32 + row) * 32 + chunk));
         const f32x4 v2 = *(const f32x4*)(red + ((2 * 9 * 32 + row) * 32 + chunk));
         const f32x4 v3 = *(const f32x4*)(red + ((3 * 9 * 32 + row) * 32 + chunk));
-        const f32x4 sum = ((v0 + v1) + v2) + v3;
-        *(f32x4*)(dW + ((size_t)(o0 + ol) * 9 + t) * a.cin + i0 + part * 4) = sum;
+        return ((v0 + v1) + v2) + v3;
+    };
+    auto place_of = [&](int q) {
+        const int t = q >> 8, ol = (q >> 3) & 31, part = q & 7;
+        return dW + ((size_t)(o0 + ol) * 9 + t) * a.cin + i0 + part * 4;
+    };
+    if (o0 + 32 <= a.cout && i0 + 32 <= a.cin && ((a.cin | (int)((uintptr_t)dW >> 2)) & 3) == 0) {
+        for (int q = tid; q < 9 * 32 * 8; q += 256) *(f32x4*)place_of(q) = sum_of(q);
+    } else {
+        // a tile with padded channels of a narrow head: those have no gradient to store
+        for (int q = tid; q < 9 * 32 * 8; q += 256) {
+            const f32x4 sum = sum_of(q);
+            float* dst = place_of(q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (o0 + ((q >> 3) & 31) < a.cout && i0 + (q & 7) * 4 + e < a.cin) dst[e] = sum[e];
+        }
     }
-    if (want_bias && tid < 32) {
+    if (want_bias && tid < 32 && o0 + tid < a.cout) {
         float* db = a.db + head * a.head_out_stride + (size_t)split * a.split_stride;
         db[o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
     }
 }
-
-bool wgrad3x3_mfma_supported(int cin, int cout) { return cin % 32 == 0 && cout % 32 == 0; }
 
 // Position splits of the two layers for the shared launch.  Every block pays a fixed cost (ring
 // fill, the reduction through LDS, the partial-result store: about 22 units' worth) on top of its
@@ -317,7 +330,7 @@ bool wgrad3x3_mfma_supported(int cin, int cout) { return cin % 32 == 0 && cout %
 void wgrad_splits_for(const Geo& g, int* s1_out, int* s2_out)
 {
     constexpr int n_cu = 256, fixed_units = 22, reread_units_per_chip = 13;
-    const int tiles1 = g.heads() * (g.c1 / 32) * (g.c_in / 32), tiles2 = g.heads() * (g.c2 / 32) * (g.c1 / 32);
+    const int tiles1 = g.heads() * cdiv(g.c1, 32) * cdiv(g.c_in, 32), tiles2 = g.heads() * cdiv(g.c2, 32) * cdiv(g.c1, 32);
     const int n_units = cdiv(g.padded_positions() / g.heads(), 16);
     int best1 = 1, best2 = 1;
     long best_cost = -1;
@@ -372,7 +385,7 @@ static WgradArgs wgrad_args(const Plan& p, const bf16* dYT, const bf16* XT, floa
     a.head_groups8 = p.g.Hp * p.g.Wp / 8;
     a.head_out_stride = p.grad_stride * p.grad_copies;
     a.units_per_wave = cdiv(a.n_units, splits * 4);
-    a.o_tiles = cout / 32; a.i_tiles = cin / 32;
+    a.o_tiles = cdiv(cout, 32); a.i_tiles = cdiv(cin, 32);
     a.splits = splits;
     a.items_per_xcd = cdiv(a.o_tiles * a.i_tiles * splits * a.heads, 8);
     return a;

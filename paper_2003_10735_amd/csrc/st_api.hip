@@ -99,8 +99,8 @@ static int validate(const st_head_desc* d)
     if ((long long)d->c1 * d->c_in * 9 >= (1ll << 28) || (long long)d->c2 * d->c1 * 9 >= (1ll << 28))
         return ST_ERR_SHAPE;
     if (d->grouped) {
-        // one head per frame: matrix-core kernels only, and all heads' parameters in 32-bit reach
-        if (!make_plan(*d).mfma) return ST_ERR_SHAPE;
+        // one head per frame: matrix-core kernels without padded channels only, and all heads' parameters in 32-bit reach
+        if (d->compute != ST_COMPUTE_BF16 || make_geo(*d).padded() || (d->c2 != 64 && d->c2 != 128 && d->c2 != 256)) return ST_ERR_SHAPE;
         if ((long long)d->n * ((long long)d->c1 * d->c_in * 9 + (long long)d->c2 * d->c1 * 9) >= (1ll << 30))
             return ST_ERR_SHAPE;
     }
@@ -114,7 +114,7 @@ static size_t take(size_t& off, size_t bytes)
     return at;
 }
 
-Plan make_plan(const st_head_desc& d)
+Plan make_plan(const st_head_desc& d, PlanKind kind)
 {
     Plan p;
     memset(&p, 0, sizeof(p));
@@ -124,9 +124,7 @@ Plan make_plan(const st_head_desc& d)
     p.bf16 = d.compute == ST_COMPUTE_BF16;
     p.esz = p.bf16 ? 2 : 4;
     const Geo& g = p.g;
-    p.mfma = p.bf16 && conv3x3_mfma_supported(g.c_in, g.c1) && conv3x3_mfma_supported(g.c1, g.c2) &&
-             wgrad3x3_mfma_supported(g.c_in, g.c1) && wgrad3x3_mfma_supported(g.c1, g.c2) &&
-             conv3_mfma_supported(g.c2, g.C);
+    p.mfma = p.bf16;
     p.splits1 = p.splits2 = p.splits3 = 1;
     if (p.mfma) wgrad_splits_for(g, &p.splits1, &p.splits2);
     else generic_wgrad_splits(g, &p.splits1, &p.splits2, &p.splits3);
@@ -145,44 +143,54 @@ Plan make_plan(const st_head_desc& d)
         const size_t base = take(off, (PP + 2 * (size_t)p.guard) * C * p.esz);
         return base + (size_t)p.guard * C * p.esz;
     };
-    p.feat = act(g.c_in);
-    p.a1 = act(g.c1);
-    p.a2 = act(g.c2);
-    p.da1 = act(g.c1);
-    p.da2 = act(g.c2);
+    // a buffer that only training needs
+    auto train = [&](auto&& taker) -> size_t {
+        if (kind == PLAN_COMPACT) return 0;
+        const size_t at = taker();
+        return kind == PLAN_FULL ? at : 0;
+    };
+    auto train_act = [&](int C) { return train([&] { return act(C); }); };
+    auto train_take = [&](size_t bytes) { return train([&] { return take(off, bytes); }); };
+    p.feat = act(g.ki);
+    p.a1 = act(g.k1);
+    p.a2 = p.mfma ? train_act(g.k2) : act(g.k2);     // (the classifier-fused convolution keeps it to itself)
+    p.da1 = train_act(g.k1);
+    p.da2 = train_act(g.k2);
     if (p.mfma) {
-        p.featT = take(off, (size_t)g.c_in * p.PPT * 2);
-        p.a1T = take(off, (size_t)g.c1 * p.PPT * 2);
-        p.da1T = take(off, (size_t)g.c1 * p.PPT * 2);
-        p.da2T = take(off, (size_t)g.c2 * p.PPT * 2);
+        p.featT = train_take((size_t)g.ki * p.PPT * 2);
+        p.a1T = train_take((size_t)g.k1 * p.PPT * 2);
+        p.da1T = train_take((size_t)g.k1 * p.PPT * 2);
+        p.da2T = train_take((size_t)g.k2 * p.PPT * 2);
     }
     p.zero_end = off;
     const size_t hw = (size_t)g.h * g.w;
     const size_t heads = (size_t)g.heads();
     p.z = take(off, (size_t)g.n * g.C * hw * 4);
-    p.gz = take(off, (size_t)g.n * g.C * hw * 4);
-    p.tadj = take(off, (size_t)g.n * g.C * hw * 4);
-    p.lab8 = take(off, (size_t)g.pixels());
-    p.z_parts = p.mfma ? g.c2 / 64 : 0;
+    p.gz = train_take((size_t)g.n * g.C * hw * 4);
+    p.tadj = train_take((size_t)g.n * g.C * hw * 4);
+    p.lab8 = train_take((size_t)g.pixels());
+    p.z_parts = p.mfma ? g.k2 / 64 : 0;
     if (p.mfma) p.zpart = take(off, (size_t)p.z_parts * PP * ((g.C + 3) / 4 * 4) * 4);
-    p.g_slots = take(off, loss_slot_floats(g) * 4);
+    p.g_slots = train_take(loss_slot_floats(g) * 4);
     p.grad_stride = (p.po.total + 3) / 4 * 4;
     p.head_stride = p.grad_stride;
     p.theta = take(off, heads * p.head_stride * 4);
-    p.vel = take(off, heads * p.head_stride * 4);
-    p.vel2 = take(off, heads * p.head_stride * 4);
-    p.grad = take(off, heads * p.grad_stride * 4 * p.grad_copies);
-    p.grad3 = take(off, heads * std::max(p.blocks3, 1) * conv3_bwd_slot_floats(g) * 4);
-    p.best = take(off, heads * p.head_stride * 4);
+    p.vel = train_take(heads * p.head_stride * 4);
+    p.vel2 = train_take(heads * p.head_stride * 4);
+    p.grad = train_take(heads * p.grad_stride * 4 * p.grad_copies);
+    p.grad3 = train_take(heads * std::max(p.blocks3, 1) * conv3_bwd_slot_floats(g) * 4);
+    p.best = train_take(heads * p.head_stride * 4);
     if (p.bf16) {
-        p.wq1 = take(off, heads * (p.po.b1 - p.po.W1) * 2);
-        p.wq1t = take(off, heads * (p.po.b1 - p.po.W1) * 2);
-        p.wq2 = take(off, heads * (p.po.b2 - p.po.W2) * 2);
-        p.wq2t = take(off, heads * (p.po.b2 - p.po.W2) * 2);
-        p.wq3 = take(off, heads * (p.po.b3 - p.po.W3) * 2);
-        if (p.mfma) p.wq3t = take(off, heads * (size_t)g.c2 * 32 * 2);
+        const size_t w1 = (size_t)g.k1 * 9 * g.ki, w2 = (size_t)g.k2 * 9 * g.k1;
+        p.wq1 = take(off, heads * w1 * 2);
+        p.wq1t = train_take(heads * w1 * 2);
+        p.wq2 = take(off, heads * w2 * 2);
+        p.wq2t = train_take(heads * w2 * 2);
+        p.wq3 = take(off, heads * (size_t)g.C * g.k2 * 2);
+        p.wq3t = train_take(heads * (size_t)g.k2 * 32 * 2);
+        if (g.padded()) { p.bq1 = take(off, (size_t)g.k1 * 4); p.bq2 = take(off, (size_t)g.k2 * 4); }
     }
-    p.loss_part = take(off, (size_t)loss_blocks(g) * 4);
+    p.loss_part = train_take((size_t)loss_blocks(g) * 4);
     p.counters = take(off, std::max((size_t)256, heads * 8));   // valid pixels (their weights), one count per head
     p.conf = take(off, (size_t)g.n * g.C * g.C * 8);
     p.scal = take(off, (size_t)g.n * 8);               // per-frame mean IoU of the last pass (double)
@@ -317,36 +325,44 @@ static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered
 {
     ZeroList z;
     const Geo& g = p.g;
-    const int n_regions = 2 + 8 + 2 * 2 * (g.c1 / 32 + g.c2 / 32) + 2 * (g.c_in / 32) + 3;
+    const int n_regions = 2 + 8 + 2 * 2 * (g.k1 / 32 + g.k2 / 32) + 2 * (g.ki / 32) + 3 + 7;
     if (!p.mfma || n_regions > ZeroList::MAX) {
         z.add(ws + p.zero_begin, p.zero_end - p.zero_begin);
     } else {
         const size_t PP = (size_t)g.padded_positions(), G = (size_t)p.guard;
         if (!feat_covered) {
-            z.add(ws + p.feat - G * g.c_in * 2, (PP + 2 * G) * g.c_in * 2);
-            z.add(ws + p.featT, (size_t)g.c_in * p.PPT * 2);
+            z.add(ws + p.feat - G * g.ki * 2, (PP + 2 * G) * g.ki * 2);
+            if (p.featT) z.add(ws + p.featT, (size_t)g.ki * p.PPT * 2);
         }
         const size_t pm[5] = {p.a1, p.a2, p.da1, p.da2, p.feat};
-        const int pc[5] = {g.c1, g.c2, g.c1, g.c2, g.c_in};
+        const int pc[5] = {g.k1, g.k2, g.k1, g.k2, g.ki};
         const int nbuf = feat_covered ? 5 : 4;
         for (int i = 0; i < nbuf; ++i) {
+            if (!pm[i]) continue;
             z.add(ws + pm[i] - G * pc[i] * 2, G * pc[i] * 2);
             z.add(ws + pm[i] + PP * pc[i] * 2, G * pc[i] * 2);
         }
         // channel-major copies [C/32][PPT/8][32][8]: per channel block, the column groups of the
         // head guard and those from the end of the positions (rounded down to a group) on
         const size_t tm[4] = {p.a1T, p.da1T, p.da2T, p.featT};
-        const int tc[4] = {g.c1, g.c1, g.c2, g.c_in};
+        const int tc[4] = {g.k1, g.k1, g.k2, g.ki};
         const size_t blk = (size_t)p.PPT * 32 * 2;                 // bytes of one channel block
         const size_t head = G * 32 * 2;                            // guard columns (a multiple of 8)
         const size_t tail_at = (G + PP / 8 * 8) * 32 * 2;
         for (int i = 0; i < nbuf - 1; ++i)
-            for (int b = 0; b < tc[i] / 32; ++b) {
+            for (int b = 0; tm[i] && b < tc[i] / 32; ++b) {
                 z.add(ws + tm[i] + b * blk, head);
                 z.add(ws + tm[i] + b * blk + tail_at, blk - tail_at);
             }
     }
-    if (p.wq3t) z.add(ws + p.wq3t, (size_t)g.heads() * g.c2 * 32 * 2);      // rows of the classes beyond C stay zero
+    if (p.wq3t) z.add(ws + p.wq3t, (size_t)g.heads() * g.k2 * 32 * 2);      // rows of the classes beyond C stay zero
+    if (p.mfma && g.padded()) {     // ... and so do the weights and biases of the channels beyond the caller's
+        const size_t w1 = (size_t)g.k1 * 9 * g.ki * 2, w2 = (size_t)g.k2 * 9 * g.k1 * 2;
+        z.add(ws + p.wq1, w1); z.add(ws + p.wq2, w2);
+        if (p.wq1t) { z.add(ws + p.wq1t, w1); z.add(ws + p.wq2t, w2); }
+        z.add(ws + p.wq3, (size_t)g.C * g.k2 * 2);
+        z.add(ws + p.bq1, (size_t)g.k1 * 4); z.add(ws + p.bq2, (size_t)g.k2 * 4);
+    }
     z.add(ws + p.counters, std::max((size_t)256, (size_t)g.heads() * 8));
     z.add(ws + p.conf, (size_t)g.n * g.C * g.C * 8);
     zero_regions(c, z);
@@ -361,10 +377,12 @@ static void forward(Ctx& c, const Plan& p, char* ws, float* z)
     if (!p.mfma) { generic_forward(c, p, ws, z); return; }
     const Geo& g = p.g;
     const float* theta = (const float*)(ws + p.theta);
-    conv3x3_mfma(c, "conv1_fwd_mfma", p, (const bf16*)(ws + p.feat), (const bf16*)(ws + p.wq1), theta + p.po.b1,
-                 nullptr, (bf16*)(ws + p.a1), (bf16*)(ws + p.a1T), g.c_in, g.c1, 0, 1);
+    const float* b1 = p.bq1 ? (const float*)(ws + p.bq1) : theta + p.po.b1;
+    const float* b2 = p.bq2 ? (const float*)(ws + p.bq2) : theta + p.po.b2;
+    conv3x3_mfma(c, "conv1_fwd_mfma", p, (const bf16*)(ws + p.feat), (const bf16*)(ws + p.wq1), b1,
+                 nullptr, (bf16*)(ws + p.a1), p.a1T ? (bf16*)(ws + p.a1T) : nullptr, g.ki, g.k1, 0, 1);
     conv3x3_mfma(c, "conv2_fwd_logits_mfma", p, (const bf16*)(ws + p.a1), (const bf16*)(ws + p.wq2),
-                 theta + p.po.b2, nullptr, (bf16*)(ws + p.a2), nullptr, g.c1, g.c2, 0, 2,
+                 b2, nullptr, p.a2 ? (bf16*)(ws + p.a2) : nullptr, nullptr, g.k1, g.k2, 0, 2,
                  (const bf16*)(ws + p.wq3), (float*)(ws + p.zpart));
 }
 
@@ -398,10 +416,10 @@ static void backward(Ctx& c, const Plan& p, char* ws, float* dfeat, const Finish
                    (const unsigned long long*)(ws + p.counters), (const bf16*)(ws + p.a2),
                    (const bf16*)(ws + p.wq3t), (bf16*)(ws + p.da2), (bf16*)(ws + p.da2T), (float*)(ws + p.grad3), finish);
     conv3x3_mfma(c, "conv2_dgrad_mfma", p, (const bf16*)(ws + p.da2), (const bf16*)(ws + p.wq2t), nullptr,
-                 (const bf16*)(ws + p.a1), dfeat ? (bf16*)(ws + p.da1) : nullptr, (bf16*)(ws + p.da1T), g.c2, g.c1, 1, 2);
+                 (const bf16*)(ws + p.a1), dfeat ? (bf16*)(ws + p.da1) : nullptr, (bf16*)(ws + p.da1T), g.k2, g.k1, 1, 2);
     if (dfeat)
         conv3x3_mfma(c, "conv1_dgrad_mfma", p, (const bf16*)(ws + p.da1), (const bf16*)(ws + p.wq1t), nullptr, nullptr,
-                     nullptr, nullptr, g.c1, g.c_in, 3, 1, nullptr, nullptr, dfeat);
+                     nullptr, nullptr, g.k1, g.ki, 3, 1, nullptr, nullptr, dfeat);
     wgrad3x3_mfma(c, p, (const bf16*)(ws + p.da1T), (const bf16*)(ws + p.featT), (const bf16*)(ws + p.da2T),
                   (const bf16*)(ws + p.a1T), grad);
 }
@@ -486,7 +504,7 @@ int st_head_forward(const st_head_desc* desc, const void* features, const float*
     if (v != ST_OK) return v;
     if (!features || !head_params) return ST_ERR_NULL;
     if (!workspace || !aligned(workspace, 256)) return ST_ERR_WORKSPACE;
-    const Plan p = make_plan(*desc);
+    const Plan p = make_plan(*desc, PLAN_FORWARD);
     return head_forward_launches(desc, p, features, head_params, logits_lowres, pred, (char*)workspace, stream, false);
 }
 
@@ -496,7 +514,10 @@ int st_head_forward_noalloc(const st_head_desc* desc, const void* features, cons
     const int v = validate(desc);
     if (v != ST_OK) return v;
     if (!features || !head_params) return ST_ERR_NULL;
-    const Plan p = make_plan(*desc);
+    Plan p = make_plan(*desc, PLAN_FORWARD);
+    // (heads whose internal buffers hold padded channels, and float32 ones: what the forward pass
+    //  itself needs is what counts)
+    if (p.total > NOALLOC_SCRATCH_BYTES && (!p.bf16 || p.g.padded())) p = make_plan(*desc, PLAN_COMPACT);
     if (p.total > NOALLOC_SCRATCH_BYTES) return ST_ERR_TOO_LARGE;
     char* ws = nullptr;
     const int sr = scratch_of_current_device(&ws);
@@ -634,8 +655,6 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
 
     const Plan p = make_plan(*desc);
     const Geo& g = p.g;
-    // (the matrix-core kernel of the feature gradient needs c1 in multiples of 64)
-    if (feature_grad && p.mfma && !conv3x3_mfma_supported(g.c1, g.c_in)) return ST_ERR_SHAPE;
     char* ws = (char*)workspace;
     Ctx c{as_stream(stream), ST_OK};
 

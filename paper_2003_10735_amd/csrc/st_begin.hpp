@@ -30,7 +30,7 @@ __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E
             float v = 0.f;
             if (c < g.c_in && x < g.w) {
                 v = to_f32(f[(((size_t)img * g.h + y) * g.w + x) * g.c_in + c]);
-                out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.c_in + c] = from_f32<E>(v);
+                out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<E>(v);
             }
             tile[tx][k] = v;
         }
@@ -55,7 +55,7 @@ __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E
     for (int k = ty; k < 32; k += 8) {
         const int x = x0 + k, c = c0 + tx;
         if (c < g.c_in && x < g.w)
-            out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.c_in + c] = from_f32<E>(tile[tx][k]);
+            out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<E>(tile[tx][k]);
     }
 }
 
@@ -112,7 +112,7 @@ __device__ __forceinline__ void pack_features_vec_block(const bf16* __restrict__
         }
         {   // channel-major: 8 positions of one channel
             const int ch = i >> 3, g8 = i & 7;
-            if (xp0 + 8 * g8 < g.Wp)
+            if (outT && xp0 + 8 * g8 < g.Wp)
                 *(bf16x8*)(outT + xt_index(c0 + ch, guard + (int)prow + xp0 + 8 * g8, PPT / 8)) =
                     *(const bf16x8*)(tile + ch * PACKV_PITCH + 8 * g8);
         }

@@ -26,9 +26,14 @@ struct Geo {
     int Hp, Wp;      // padded grid: h + 2 rows of pitch Wp >= w + 2
     int H, W;        // frame resolution: 8h, 8w
     int c_in, c1, c2, C;
+    // Channel pitches of the internal buffers (activations, gradients, operand copies of the weights):
+    // c_in, c1, c2 rounded up to what the kernels of the compute path take in one piece.  The channels
+    // beyond the caller's count are zero everywhere, and so are the weights that touch them.
+    int ki, k1, k2;
     int ignore_index;
     int grouped;     // 1: frame f has a head (parameters, loss, pixel count) of its own
     int nhwc;        // 1: the caller's features are [n, h, w, c_in] instead of [n, c_in, h, w]
+    bool padded() const { return ki != c_in || k1 != c1 || k2 != c2; }
     __host__ __device__ int heads() const { return grouped ? n : 1; }
     __host__ __device__ int head_of(int img) const { return grouped ? img : 0; }
     __host__ __device__ int positions() const { return n * h * w; }
@@ -43,6 +48,11 @@ inline Geo make_geo(const st_head_desc& d)
     g.Hp = d.h + 2; g.Wp = (d.w + 2 + 7) / 8 * 8;
     g.H = d.h * UP; g.W = d.w * UP;
     g.c_in = d.c_in; g.c1 = d.c1; g.c2 = d.c2; g.C = d.n_classes;
+    // matrix-core kernels: whole 64-channel stages.  (A narrow head costs up to the work of a 64-channel
+    // one, but that is matrix-core work on a chip such a head cannot fill anyway: 96 -> 48 -> 48 on
+    // 60 x 107 cells went from 3.12 ms per 4-step call on plain kernels to the time of the launches.)
+    const int q = d.compute == ST_COMPUTE_BF16 ? 64 : 1;
+    g.ki = (d.c_in + q - 1) / q * q; g.k1 = (d.c1 + q - 1) / q * q; g.k2 = (d.c2 + q - 1) / q * q;
     g.ignore_index = d.ignore_index;
     g.grouped = d.grouped ? 1 : 0;
     g.nhwc = d.feat_layout == ST_NHWC ? 1 : 0;
@@ -104,7 +114,7 @@ struct Plan {
     LossTiling lt;
     bool bf16;          // compute path
     size_t esz;         // bytes per activation element
-    bool mfma;          // bf16 path on the matrix-core kernels (else the plain tiled kernels)
+    bool mfma;          // bf16 path: matrix-core kernels (else the plain tiled kernels)
     // With several heads (Geo::grouped) every per-head buffer holds heads() consecutive blocks:
     // theta, vel, vel2, best (head_stride floats apart), grad (grad_copies * grad_stride floats
     // apart), grad3 (blocks3 slots apart), the bfloat16 weight copies (their own size apart),
@@ -129,13 +139,17 @@ struct Plan {
     size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution
     size_t theta, vel, vel2, grad, best;   // vel: velocity or Adam's m; vel2: Adam's v
     size_t wq1, wq1t, wq2, wq2t, wq3;      // bfloat16 operand copies of the weights
-    size_t wq3t;                           // W3 transposed, [c2][32 classes] (zero beyond C): MFMA A fragments of its backward
+    size_t bq1, bq2;                       // biases followed by zeros up to k1 / k2, where the pitches exceed the counts
+    size_t wq3t;                           // W3 transposed, [k2][32 classes] (zero beyond C): MFMA A fragments of its backward
     size_t loss_part, counters, conf, scal;
     size_t losses, mious;            // staging when the caller passes no result arrays
     size_t total;
 };
 
-Plan make_plan(const st_head_desc& d);
+// PLAN_FORWARD: the offsets of the full plan, with those of buffers that only training needs set to 0
+// (absent), so that no kernel fills them.  PLAN_COMPACT: the same buffers without room for the others.
+enum PlanKind { PLAN_FULL, PLAN_FORWARD, PLAN_COMPACT };
+Plan make_plan(const st_head_desc& d, PlanKind kind = PLAN_FULL);
 
 // ------------------------------------------------------------------ launch bookkeeping
 // Each kernel launch goes through Launch: it records the kernel's name for the optional event

@@ -18,22 +18,19 @@ void zero_regions(Ctx& c, const ZeroList& z);
 void zero_u64(Ctx& c, unsigned long long* p, size_t n);
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
 
-// k_conv_generic.hip -- plain tiled kernels (float32 path; bfloat16 shapes the MFMA kernels skip)
+// k_conv_generic.hip -- plain tiled kernels of the float32 path
 void generic_forward(Ctx& c, const Plan& p, char* ws, float* z);
 void generic_backward(Ctx& c, const Plan& p, char* ws);
 void generic_feature_grad(Ctx& c, const Plan& p, char* ws, float* dfeat);
 
 // k_conv_mfma.hip, k_wgrad_mfma.hip, k_conv3_mfma.hip -- matrix-core kernels of the bfloat16 path
-bool conv3x3_mfma_supported(int cin, int cout);
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
                   const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, int layer,
                   const bf16* W3q = nullptr, float* zpart = nullptr, float* dense = nullptr);
-bool wgrad3x3_mfma_supported(int cin, int cout);
 void wgrad_splits_for(const Geo& g, int* splits1, int* splits2);
 void generic_wgrad_splits(const Geo& g, int* splits1, int* splits2, int* splits3);
 void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, const bf16* da2T,
                    const bf16* a1T, float* grad);
-bool conv3_mfma_supported(int c2, int C);
 int conv3_bwd_blocks(const Geo& g);
 size_t conv3_bwd_slot_floats(const Geo& g);
 // finish: the bookkeeping of the pass that precedes this backward pass rides on the launch (a few more blocks)
