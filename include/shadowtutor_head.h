@@ -305,7 +305,8 @@ const char* st_version(void);
 
 /* Byte offsets of the library's internal buffers inside `workspace`, so that a test can look
  * at intermediate tensors after a call.  Offsets are 0 for buffers this shape does not use.  On
- * the bfloat16 path the channels of feat .. da2 are padded with zeros to a multiple of 64. */
+ * the bfloat16 path the channels of feat .. da2 are padded with zeros to a multiple of 64; on the
+ * float32 path these buffers hold runs of eight channels, [c / 8][position][8]. */
 typedef struct st_workspace_layout {
     size_t feat;      /* features, position-major [n, h+2, row_pitch, c_in], zero border    */
     size_t a1, a2;    /* activations after ReLU, same layout, c1 / c2 channels              */
@@ -316,13 +317,13 @@ typedef struct st_workspace_layout {
     size_t grad;      /* parameter gradient, internal order, as partial sums: grad_copies   */
                       /* copies grad_stride floats apart (the weight-gradient kernels split  */
                       /* the positions; a layer may use fewer copies than grad_copies: the   */
-                      /* unused ones are not written).  On the matrix-core path the          */
-                      /* classifier's share lies elsewhere (one slot per block).             */
+                      /* unused ones are not written).  The classifier's share lies          */
+                      /* elsewhere (one slot per block); float32 path: its sum in copy 0.    */
     size_t elem_size; /* bytes per activation element: 4 (float32 path) or 2 (bfloat16)     */
     size_t total;     /* == st_workspace_bytes                                              */
     size_t row_pitch; /* cells per padded row: w + 2 rounded up to a multiple of 8          */
     size_t grad_copies, grad_stride;      /* see grad                                        */
-    size_t splits[3]; /* copies the 3x3 layers 1, 2 and (plain kernels) the classifier use   */
+    size_t splits[3]; /* copies the 3x3 layers 1, 2 and the classifier use                   */
 } st_workspace_layout;
 
 int st_get_workspace_layout(const st_head_desc* desc, st_workspace_layout* out);

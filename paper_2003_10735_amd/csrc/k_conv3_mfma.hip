@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include "st_kernels.hpp"
+#include "st_gather.hpp"
 #include "st_mfma.hpp"
 #include "st_finish.hpp"
 
@@ -74,7 +75,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int PP = g.padded_positions(), frame = g.Hp * g.Wp, hw = g.h * g.w;
+    const int PP = g.padded_positions(), frame = g.Hp * g.Wp;
     // several heads: blocks are counted per frame (grp_blocks each), so that no block mixes the
     // positions -- and with them W3 and the partial sums -- of two heads
     const int head = g.grouped ? blockIdx.x / grp_blocks : 0;
@@ -108,52 +109,12 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     {
         const int p = tid & (BP - 1), cq = tid / BP;     // this thread: one position, every fourth class
         constexpr int NQ = 256 / BP;
-        const int mp = m0 + p;
-        const int img = min(mp / frame, g.n - 1), rr = mp - img * frame, y = rr / g.Wp, x = rr - y * g.Wp;
-        const bool inside = mp < m_end && y >= 1 && y <= g.h && x >= 1 && x <= g.w;
-        const int cy = inside ? y - 1 : 0, cx = inside ? x - 1 : 0;
-        const unsigned long long nv = n_valid[head];
-        const float inv_n = (inside && nv) ? 1.0f / (float)nv : 0.f;
-        // the tiles whose cell window contains (cy, cx): up to 3 tile rows x 2 tile columns
-        const int ty_hi = min((cy + 1) / LOSS_TY, lt.tiles_y - 1), tx_hi = min((cx + 1) / LOSS_TX, lt.tiles_x - 1);
-        // slot offset of class 0 and a 0/1 weight: tiles that do not exist or do not touch the
-        // cell read slot element 0 with weight 0, so that every load is unconditional
-        int off[3][2];
-        float wgt[3][2];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int ty = ty_hi - 2 + a, tx = tx_hi - 1 + b;
-                const int r = cy - (ty * LOSS_TY - 1), lc = cx - (tx * LOSS_TX - 1);
-                const bool ok = inside && ty >= 0 && tx >= 0 && r >= 0 && r < LOSS_CH && lc >= 0 && lc < LOSS_CW;
-                off[a][b] = ok ? (((img * lt.tiles() + ty * lt.tiles_x + tx) * CP) * LOSS_CH + r) * LOSS_CW + lc : 0;
-                wgt[a][b] = ok ? 1.f : 0.f;
-            }
-        const int cstride = LOSS_CH * LOSS_CW;
-        const size_t tbase = (size_t)img * g.C * hw + cy * g.w + cx;
-        // all loads of the gather first (their addresses do not depend on each other), then the sums
-        float sv[32 / NQ][6], tv[32 / NQ];
-#pragma unroll
-        for (int k = 0; k < 32 / NQ; ++k) {
-            const int c = min(cq + NQ * k, g.C - 1);     // classes beyond C re-read the last one, unused
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) sv[k][a * 2 + b] = slots[(size_t)off[a][b] + (size_t)c * cstride];
-            tv[k] = T[tbase + (size_t)c * hw];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        float v[32 / NQ];
+        gather_g<32 / NQ, NQ>(slots, T, n_valid[head], CP, lt, g, m0 + p, m_end, cq, v);
 #pragma unroll
         for (int k = 0; k < 32 / NQ; ++k) {
             const int cc = cq + NQ * k;
-            float v = 0.f;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) v = __builtin_fmaf(wgt[a][b], sv[k][a * 2 + b], v);
-            v = (v - tv[k]) * inv_n;
-            const bf16 q = (cc < g.C) ? (bf16)v : (bf16)0.f;
+            const bf16 q = (cc < g.C) ? (bf16)v[k] : (bf16)0.f;
             g_cp[cc * GP + p] = q;
             g_pc[p * GC + cc] = q;
         }

@@ -89,12 +89,10 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
     // ---- stage the touched cells (edge replication = clamped read); padded classes get a
     //      large negative logit: they never win, their softmax term is exactly 0.
     //      All global loads of the prologue are issued before anything waits for one of them.
-    constexpr int NZ = (CP * CH * CW + NT - 1) / NT;
     constexpr int QC = CP / 4;                            // 16-byte chunks of a cell's row of CP classes
     constexpr int NZQ = (CH * CW * QC + NT - 1) / NT;
-    float zv[NZ];
     f32x4 zr[NZQ][4], bq[NZQ];
-    if (zs.parts) {
+    {
         const size_t PP = (size_t)g.padded_positions();
 #pragma unroll
         for (int k = 0; k < NZQ; ++k) {
@@ -117,14 +115,6 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) bq[k][e] = zs.b3[g.head_of(img) * zs.b3_stride + min(chunk * 4 + e, C - 1)];
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NZ; ++k) {
-            const int i = min(tid + k * NT, CP * CH * CW - 1);
-            const int lc = i % CW, r = (i / CW) % CH, c = i / (CW * CH);
-            const int cx = min(max(cx0 + lc, 0), g.w - 1), cy = min(max(cy0 + r, 0), g.h - 1);
-            zv[k] = zs.planar[((size_t)img * C + min(c, C - 1)) * hw + cy * g.w + cx];
         }
     }
     // T over the cells this tile owns, for the  - <T, z>  part of the loss (see the header)
@@ -193,7 +183,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             if (i / LOSS_TX >= C || tile_x * LOSS_TX + i % LOSS_TX >= g.w) tv[k] = 0.f;
         }
     }
-    if (zs.parts) {
+    {
 #pragma unroll
         for (int k = 0; k < NZQ; ++k) {
             const int i = tid + k * NT;
@@ -228,17 +218,10 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
                 }
             }
         }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NZ; ++k) {
-            const int i = tid + k * NT;
-            const int lc = i % CW, r = (i / CW) % CH, c = i / (CW * CH);
-            if (i < CP * CH * CW) zt[c][r][lc] = c < C ? zv[k] : -1e30f;
-        }
     }
     __syncthreads();
     // the logits of this tile's own cells, as used below, for whoever wants the planar tensor
-    if (zs.parts && zs.z_out) {
+    if (zs.z_out) {
         for (int i = tid; i < C * LOSS_TX; i += NT) {
             const int lc = i % LOSS_TX, c = i / LOSS_TX;
             const int cx = tile_x * LOSS_TX + lc;
@@ -395,36 +378,6 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
     }
 }
 
-// g[img][c][cy][cx] = ( sum of the slots of the tiles that touch the cell, tile rows first,  - T ) / N_valid
-template <int CP>
-__global__ void __launch_bounds__(256)
-k_assemble_g(const float* __restrict__ slots, const float* __restrict__ T,
-             const unsigned long long* __restrict__ n_valid, float* __restrict__ gz, Geo g, LossTiling lt)
-{
-    constexpr int CW = LOSS_CW, CH = LOSS_CH;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    const int hw = g.h * g.w;
-    if (idx >= g.n * g.C * hw) return;
-    const int cx = idx % g.w, cy = (idx / g.w) % g.h, c = (idx / hw) % g.C, img = idx / (hw * g.C);
-    float v = 0.f;
-    // tiles whose cell window [t*T - 1, t*T + T] contains the cell: the last candidate is
-    // (cell + 1) / T, and a window of T + 2 cells can overlap at most 3 tiles
-    const int ty_hi = min((cy + 1) / LOSS_TY, lt.tiles_y - 1), tx_hi = min((cx + 1) / LOSS_TX, lt.tiles_x - 1);
-    for (int ty = max(ty_hi - 2, 0); ty <= ty_hi; ++ty) {
-        const int r = cy - (ty * LOSS_TY - 1);
-        if (r < 0 || r >= CH) continue;
-        for (int tx = max(tx_hi - 2, 0); tx <= tx_hi; ++tx) {
-            const int lc = cx - (tx * LOSS_TX - 1);
-            if (lc < 0 || lc >= CW) continue;
-            const size_t tile = (size_t)img * lt.tiles() + ty * lt.tiles_x + tx;
-            v += slots[((tile * CP + c) * CH + r) * CW + lc];
-        }
-    }
-    const unsigned long long nv = *n_valid;
-    const float inv_n = nv ? 1.0f / (float)nv : 0.f;
-    gz[idx] = (v - T[idx]) * inv_n;
-}
-
 static int padded_classes(int C) { return (C + 3) / 4 * 4; }
 
 size_t loss_slot_floats(const Geo& g)
@@ -437,9 +390,7 @@ int loss_blocks(const Geo& g) { return g.n * loss_tiling(g).tiles(); }
 
 template <int CP, int CA>
 static void loss_launch(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels, const uint8_t* wmap,
-                        const float* T,
-                        uint8_t* pred, float* slots, float* gz, float* loss_part, unsigned long long* conf,
-                        const unsigned long long* n_valid, bool grad, bool assemble)
+                        const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad)
 {
     const LossTiling lt = loss_tiling(g);
     const int n_tiles = g.n * lt.tiles();
@@ -447,10 +398,6 @@ static void loss_launch(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* lab
     if (grad) {
         ST_LAUNCH(c, "upsample_ce_grad", (k_loss<CP, CA, true>), dim3(blocks), dim3(LOSS_THREADS), 0, zs, labels, wmap, T, pred,
                   slots, loss_part, conf, g, lt, n_tiles);
-        // the matrix-core backward kernel adds the slots itself; the plain path wants g assembled
-        if (assemble)
-            ST_LAUNCH(c, "assemble_dz", (k_assemble_g<CP>), dim3(cdiv((long long)g.n * g.C * g.h * g.w, 256)),
-                      dim3(256), 0, (const float*)slots, T, n_valid, gz, g, lt);
     } else {
         ST_LAUNCH(c, "upsample_ce", (k_loss<CP, CA, false>), dim3(blocks), dim3(LOSS_THREADS), 0, zs, labels, wmap, T, pred, slots,
                   loss_part, conf, g, lt, n_tiles);
@@ -471,11 +418,9 @@ static void loss_launch(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* lab
     }
 
 void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels, const uint8_t* wmap, const float* T,
-               uint8_t* pred,
-               float* slots, float* gz, float* loss_part, unsigned long long* conf,
-               const unsigned long long* n_valid, bool grad, bool assemble)
+               uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad)
 {
-#define ST_ARGS c, g, zs, labels, wmap, T, pred, slots, gz, loss_part, conf, n_valid, grad, assemble
+#define ST_ARGS c, g, zs, labels, wmap, T, pred, slots, loss_part, conf, grad
 #define ST_CALL(CP)                                                                           \
     switch (CP - g.C) {                                                                       \
     case 0: loss_launch<CP, CP>(ST_ARGS); break;                                              \

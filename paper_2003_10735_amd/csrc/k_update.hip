@@ -14,40 +14,41 @@ namespace st {
 
 // One kernel closes a training step; its blocks play three roles (block index ranges):
 //
-//  (1) optimiser step over the flat parameter buffer: theta <- theta - lr * v, v <- mu * v + g
-//      (mu == 0: v is not touched), or an Adam step (Section 5.2 of the paper; AdamStep).  g is the sum, in ascending order, of the partial gradients
-//      the backward kernels left behind: `splits1` copies for W1/b1, `splits2` for W2/b2 and, on
-//      the plain kernels, `splits3` for W3/b3 (position splits of the weight-gradient kernels,
+//  (1) optimiser step over the parameters in front of the classifier: theta <- theta - lr * v,
+//      v <- mu * v + g (mu == 0: v is not touched), or an Adam step (Section 5.2 of the paper;
+//      AdamStep).  g is the sum, in ascending order, of the partial gradients the weight-gradient
+//      kernel left behind: `splits1` copies for W1/b1, `splits2` for W2/b2 (its position splits,
 //      `stride` floats apart).
-//  (2) the same for W3/b3 when the classifier's backward kernel left one slot per block: 16
+//  (2) the same for W3/b3, of which the classifier's backward kernel left one slot per block: 16
 //      threads per parameter, each adding a contiguous run of the slots, then the runs in order.
 //  (3) bookkeeping of the forward pass that preceded the step: block f: mean IoU of frame f from
 //      its confusion counts (copied out when asked, then cleared for the next pass); one more
 //      block: the tile losses added in a fixed order (float64) over the number of valid pixels.
 //
-// Roles (1) and (2) also refresh the bfloat16 copies of the new weights:
+// Roles (1) and (2) also refresh the operand copies of the new weights:
 //   wq1, wq2, wq3 : for the forward convolutions; bq1, bq2: their biases, where padded channels follow
 //   wq2t          : W2 with the roles of o and i exchanged and the taps mirrored (tap' = 8 - tap),
 //                   for the data-gradient of layer 2 run as a forward convolution
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
-//   wq3t          : W3 transposed, [k2][32] with zero columns beyond the classes: the A fragments of
-//                   the classifier's backward kernel, read straight from memory
-// wq3 is [class][k2]; wq1, wq2 and wq2t are in fragment order (wfrag_index).  Rows and columns of
-// padded channels are cleared when the call opens and never written.
+//   wq3t          : W3 transposed, for the classifier's backward kernel
+// bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
+// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in the order of wfrag32_index,
+// wq3t likewise with one tap, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
+// classes are cleared when the call opens and never written.
 struct UpdateArgs {
-    float* theta; float* vel; float* vel2; const float* grad; size_t stride; int splits1, splits2, splits3;
-    bf16* wq1; bf16* wq1t; bf16* wq2; bf16* wq2t; bf16* wq3; bf16* wq3t; float* bq1; float* bq2;
+    float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
+    void *wq1, *wq1t, *wq2, *wq2t, *wq3, *wq3t; float* bq1; float* bq2;   // (bf16 or float elements)
     ParamOffsets po; int c_in, c1, c2, ki, k1, k2;   // k: channel pitches of the operand copies
     float lr, mu;
     int adam; AdamStep ad;   // adam != 0: vel = first moment m, vel2 = second moment v
-    int do_step;     // 0: only refresh the bfloat16 copies
+    int do_step;     // 0: only refresh the operand copies
     // parameter hand-over riding along: with ext_in (do_step == 0) theta is first taken from the
     // caller's vector (its OIHW order); with ext_out, nb_out more blocks copy theta out to it
     const float* ext_in; float* ext_out; int nb_out;
     // role (2)
     const float* part3; int blocks3; size_t slot3; int C;
-    // block ranges; vec: role (1) handles four parameters per thread over [0, W3) and nb_tail
-    // blocks handle [W3, total) one by one unless role (2) does
+    // block ranges; vec: role (1) handles four parameters per thread over [0, W3); nb_tail blocks handle
+    // [W3, total) one by one unless role (2) does
     int nb_main, nb_tail, nb_l3, nb_finish, vec;
     // several heads (blockIdx.y): floats / elements from one head's block to the next in the
     // parameter-like vectors (theta, vel, vel2), the caller's vectors, the partial gradients,
@@ -82,9 +83,37 @@ __device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned
     return j;
 }
 
+// the operand copies of W1 (layer 1) or W2 for the parameter (o, tap, i) and, with N == 4, the three behind
+// it along i
+template <bool F32, int N>
+__device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, const Weight3x3& k, const float (&w)[N])
+{
+    void* fwd = layer == 1 ? a.wq1 : a.wq2;
+    void* bwd = layer == 1 ? a.wq1t : a.wq2t;
+    const int kin = layer == 1 ? a.ki : a.k1, kout = layer == 1 ? a.k1 : a.k2;
+    if (F32) {
+        float* f = (float*)fwd + wfrag32_index<9>(k.o, k.tap, k.i, kin);
+        if (N == 4) *(f32x4*)f = f32x4{w[0], w[N > 1 ? 1 : 0], w[N > 2 ? 2 : 0], w[N > 3 ? 3 : 0]};
+        else f[0] = w[0];
+        if (bwd)
+#pragma unroll
+            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag32_index<9>(k.i + e, 8 - k.tap, k.o, kout)] = w[e];
+    } else {
+        bf16* f = (bf16*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
+        bf16 q[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) q[e] = (bf16)w[e];
+        if (N == 4) *(bf16x4*)f = bf16x4{q[0], q[N > 1 ? 1 : 0], q[N > 2 ? 2 : 0], q[N > 3 ? 3 : 0]};
+        else f[0] = q[0];
+        if (bwd)
+#pragma unroll
+            for (int e = 0; e < N; ++e) ((bf16*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = q[e];
+    }
+}
+
 // (EE: the early-exit form's extras -- save_old here, the host copy of the metric in finish_block --
 //  are compiled in; the kernels of the fixed-step form never look at those fields)
-template <bool EE>
+template <bool EE, bool F32>
 __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, float g)
 {
     float w = a.ext_in ? a.ext_in[external_index(a, j)] : a.theta[j];
@@ -107,32 +136,30 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
         }
         a.theta[j] = w;
     }
-    if (a.wq1) {
-        const bf16 q = (bf16)w;
-        if (j < a.po.b1) {
-            const Weight3x3 k = weight3x3(j, a.c_in);
-            a.wq1[wfrag_index(k.o, k.tap, k.i, a.ki)] = q;
-            if (a.wq1t) a.wq1t[wfrag_index(k.i, 8 - k.tap, k.o, a.k1)] = q;
-        } else if (j < a.po.W2) {
-            if (a.bq1) a.bq1[j - a.po.b1] = w;
-        } else if (j < a.po.b2) {
-            const Weight3x3 k = weight3x3(j - (unsigned)a.po.W2, a.c1);
-            a.wq2[wfrag_index(k.o, k.tap, k.i, a.k1)] = q;
-            if (a.wq2t) a.wq2t[wfrag_index(k.i, 8 - k.tap, k.o, a.k2)] = q;
-        } else if (j < a.po.W3) {
-            if (a.bq2) a.bq2[j - a.po.b2] = w;
-        } else if (j < a.po.b3) {
-            const unsigned r = j - (unsigned)a.po.W3;
-            const unsigned cl = r / (unsigned)a.c2, o = r - cl * a.c2;
-            a.wq3[cl * a.k2 + o] = q;
-            if (a.wq3t) a.wq3t[o * 32 + cl] = q;
+    if (j < a.po.b1) {
+        copy_weights<F32>(a, 1, weight3x3(j, a.c_in), {w});
+    } else if (j < a.po.W2) {
+        if (a.bq1) a.bq1[j - a.po.b1] = w;
+    } else if (j < a.po.b2) {
+        copy_weights<F32>(a, 2, weight3x3(j - (unsigned)a.po.W2, a.c1), {w});
+    } else if (j < a.po.W3) {
+        if (a.bq2) a.bq2[j - a.po.b2] = w;
+    } else if (j < a.po.b3) {
+        const unsigned r = j - (unsigned)a.po.W3;
+        const unsigned cl = r / (unsigned)a.c2, o = r - cl * a.c2;
+        if (F32) {
+            ((float*)a.wq3)[cl * ((a.c2 + 31) & ~31) + o] = w;
+            if (a.wq3t) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, cl, 32)] = w;
+        } else {
+            ((bf16*)a.wq3)[cl * a.k2 + o] = (bf16)w;
+            if (a.wq3t) ((bf16*)a.wq3t)[o * 32 + cl] = (bf16)w;
         }
     }
 }
 
 // Four consecutive parameters (all block boundaries below W3 are multiples of four here, and so are
 // the channel counts: the four lie in the same block and under the same tap).
-template <bool EE>
+template <bool EE, bool F32>
 __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f32x4 g)
 {
     f32x4 w;
@@ -168,41 +195,25 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f
         }
         *(f32x4*)(a.theta + j) = w;
     }
-    if (a.wq1) {
-        bf16x4 q;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) q[e] = (bf16)w[e];
-        if (j < a.po.b1) {
-            const Weight3x3 k = weight3x3(j, a.c_in);
-            *(bf16x4*)(a.wq1 + wfrag_index(k.o, k.tap, k.i, a.ki)) = q;
-            if (a.wq1t) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a.wq1t[wfrag_index(k.i + e, 8 - k.tap, k.o, a.k1)] = q[e];
-            }
-        } else if (j < a.po.W2) {
-            if (a.bq1) *(f32x4*)(a.bq1 + (j - a.po.b1)) = w;
-        } else if (j < a.po.b2) {
-            const Weight3x3 k = weight3x3(j - (unsigned)a.po.W2, a.c1);
-            *(bf16x4*)(a.wq2 + wfrag_index(k.o, k.tap, k.i, a.k1)) = q;
-            if (a.wq2t) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a.wq2t[wfrag_index(k.i + e, 8 - k.tap, k.o, a.k2)] = q[e];
-            }
-        } else if (a.bq2) *(f32x4*)(a.bq2 + (j - a.po.b2)) = w;
-    }
+    if (j < a.po.b1) copy_weights<F32>(a, 1, weight3x3(j, a.c_in), {w[0], w[1], w[2], w[3]});
+    else if (j < a.po.W2) {
+        if (a.bq1) *(f32x4*)(a.bq1 + (j - a.po.b1)) = w;
+    } else if (j < a.po.b2) copy_weights<F32>(a, 2, weight3x3(j - (unsigned)a.po.W2, a.c1), {w[0], w[1], w[2], w[3]});
+    else if (a.bq2) *(f32x4*)(a.bq2 + (j - a.po.b2)) = w;
 }
 
-template <bool EE>
+template <bool EE, bool F32>
 __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f, int b, int head)
 {
     if (head) {
         if (a.theta) { a.theta += head * a.hs_param; a.vel += head * a.hs_param; a.vel2 += head * a.hs_param; }
         if (EE && a.save_old) a.save_old += head * a.hs_param;
         if (a.grad) a.grad += head * a.hs_grad;
-        if (a.wq1) { a.wq1 += head * a.hs_wq1; a.wq2 += head * a.hs_wq2; a.wq3 += head * a.hs_wq3; }
-        if (a.wq1t) a.wq1t += head * a.hs_wq1;
-        if (a.wq2t) a.wq2t += head * a.hs_wq2;
-        if (a.wq3t) a.wq3t += head * (size_t)a.k2 * 32;
+        // (several heads: bfloat16 path only)
+        auto move = [](void*& q, size_t by) { if (q) q = (bf16*)q + by; };
+        move(a.wq1, head * a.hs_wq1); move(a.wq1t, head * a.hs_wq1);
+        move(a.wq2, head * a.hs_wq2); move(a.wq2t, head * a.hs_wq2);
+        move(a.wq3, head * a.hs_wq3); move(a.wq3t, head * (size_t)a.k2 * 32);
         if (a.ext_in) a.ext_in += head * a.hs_ext;
         if (a.ext_out) a.ext_out += head * a.hs_ext;
         if (a.part3) a.part3 += head * a.hs_part3;
@@ -228,30 +239,23 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
                 }
                 for (; s < splits; ++s) g += *(const f32x4*)(gp + (size_t)s * a.stride);
             }
-            apply_update4<EE>(a, j, g);
+            apply_update4<EE, F32>(a, j, g);
             return;
         }
-        // role (1), one parameter per thread; W3/b3 are left to role (2) when it is active
+        // role (1), one parameter per thread
         const unsigned j = (unsigned)b * 256 + threadIdx.x;
-        const size_t limit = a.nb_l3 ? a.po.W3 : a.po.total;
-        if (j >= limit) return;
+        if (j >= a.po.W3) return;
         float g = 0.f;
         if (a.do_step) {
-            const int splits = j < a.po.W2 ? a.splits1 : (j < a.po.W3 ? a.splits2 : a.splits3);
+            const int splits = j < a.po.W2 ? a.splits1 : a.splits2;
             g = a.grad[j];
             for (int s = 1; s < splits; ++s) g += a.grad[(size_t)s * a.stride + j];
         }
-        apply_update<EE>(a, j, g);
+        apply_update<EE, F32>(a, j, g);
     } else if (b < a.nb_main + a.nb_tail) {
-        // [W3, total) one by one (only when role (2) is not active)
+        // [W3, total) one by one (no step: only the copies)
         const unsigned j = (unsigned)a.po.W3 + (unsigned)(b - a.nb_main) * 256 + threadIdx.x;
-        if (j >= a.po.total) return;
-        float g = 0.f;
-        if (a.do_step) {
-            g = a.grad[j];
-            for (int s = 1; s < a.splits3; ++s) g += a.grad[(size_t)s * a.stride + j];
-        }
-        apply_update<EE>(a, j, g);
+        if (j < a.po.total) apply_update<EE, F32>(a, j, 0.f);
     } else if (b < a.nb_main + a.nb_tail + a.nb_l3) {
         // role (2): slot layout [32 classes][k2] weights, then [32] biases.  The slots were
         // written by other compute units, so every load is a round trip to memory: the role is
@@ -292,7 +296,8 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
             float total = run_sum[0][kk];
 #pragma unroll
             for (int r = 1; r < 16; ++r) total += run_sum[r][kk];
-            apply_update<EE>(a, (unsigned)a.po.W3 + k, total);
+            if (F32 && a.do_step) a.grad[a.po.W3 + k] = total;      // (the float32 path's gradient can be looked at as a whole)
+            apply_update<EE, F32>(a, (unsigned)a.po.W3 + k, total);
         }
     } else if (b < a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish) {
         finish_block<EE>(f, b - a.nb_main - a.nb_tail - a.nb_l3, head);
@@ -303,21 +308,21 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
     }
 }
 
-template <bool EE>
+template <bool EE, bool F32>
 __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 {
-    step_end_block<EE>(a, f, blockIdx.x, blockIdx.y);
+    step_end_block<EE, F32>(a, f, blockIdx.x, blockIdx.y);
 }
 
 // The launch that opens a call: three kinds of blocks that do not depend on each other,
 //   first   U^T of the label map and the pixel counts (label_adjoint_block),
-//   then    the caller's parameters into theta and the bfloat16 operand copies: the blocks of
+//   then    the caller's parameters into theta and the operand copies: the blocks of
 //           k_step_end, head by head,
 //   last    feature packing (pack_features_block).
 // Run one after the other they are three short launches, each of which leaves most of the chip
 // idle for most of its time.
 struct BeginArgs {
-    const void* features; void* feat; void* featT; int in_bf16, out_bf16, PPT, guard;
+    const void* features; void* feat; void* featT; int in_bf16, PPT, guard;
     int pack_vec;                          // the 16-byte packing role over the padded grid
     int pack_x, pack_y, nb_pack;           // pack grid: pack_x column tiles x pack_y channel tiles x rows
     const int32_t* labels; const uint8_t* wmap; float* T; unsigned long long* n_valid; int CP, nb_label;
@@ -326,6 +331,7 @@ struct BeginArgs {
     Geo g;
 };
 
+template <bool F32>
 __global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, FinishArgs f)
 {
     extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
@@ -341,22 +347,22 @@ __global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, F
     b -= q.nb_label;
     if (b >= q.nb_update_all) {
         b -= q.nb_update_all;
-        float (*tile)[33] = (float (*)[33])dyn_lds;
         const int bx = b % q.pack_x, by = (b / q.pack_x) % q.pack_y, bz = b / (q.pack_x * q.pack_y);
+        if (F32) {
+            if (q.in_bf16) pack_features_f32_block((const bf16*)q.features, (float*)q.feat, q.g, q.PPT, q.guard, bx, by);
+            else pack_features_f32_block((const float*)q.features, (float*)q.feat, q.g, q.PPT, q.guard, bx, by);
+            return;
+        }
         if (q.pack_vec) {
             pack_features_vec_block((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, (bf16*)dyn_lds);
             return;
         }
-        if (q.out_bf16) {
-            if (q.in_bf16) pack_features_block<bf16, bf16>((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
-            else pack_features_block<float, bf16>((const float*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
-        } else {
-            if (q.in_bf16) pack_features_block<bf16, float>((const bf16*)q.features, (float*)q.feat, (float*)nullptr, q.g, 0, 0, bx, by, bz, tile);
-            else pack_features_block<float, float>((const float*)q.features, (float*)q.feat, (float*)nullptr, q.g, 0, 0, bx, by, bz, tile);
-        }
+        float (*tile)[33] = (float (*)[33])dyn_lds;
+        if (q.in_bf16) pack_features_block((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
+        else pack_features_block((const float*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
         return;
     }
-    step_end_block<false>(a, f, b % q.nb_update, b / q.nb_update);
+    step_end_block<false, F32>(a, f, b % q.nb_update, b / q.nb_update);
 }
 
 FinishArgs finish_args(const Plan& p, char* ws, float* loss_out, double* miou_out, long long* conf_out,
@@ -390,7 +396,7 @@ static void head_strides(UpdateArgs& a, const Plan& p)
     a.hs_part3 = (size_t)p.blocks3 * conv3_bwd_slot_floats(p.g);
 }
 
-// do_step: optimiser step (else only the bfloat16 copies are refreshed);
+// do_step: optimiser step (else only the operand copies are refreshed);
 // finish: also close the forward pass that preceded it (loss, per-frame mIoU, counts)
 static int step_end_args(const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool do_step, bool finish,
                          const float* ext_in, bool w1t, const FinishArgs& f, UpdateArgs& a, float* save_old = nullptr)
@@ -402,36 +408,25 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.ext_in = do_step ? nullptr : ext_in; a.ext_out = nullptr; a.nb_out = 0;
     a.adam = adam ? 1 : 0;
     if (adam) a.ad = *adam; else memset(&a.ad, 0, sizeof(a.ad));
-    a.grad = (const float*)(ws + p.grad);
+    a.grad = (float*)(ws + p.grad);
     a.stride = p.grad_stride;
     a.splits1 = p.splits1;
     a.splits2 = p.splits2;
-    a.splits3 = p.splits3;
-    a.wq1 = p.bf16 ? (bf16*)(ws + p.wq1) : nullptr;
-    a.wq1t = (p.mfma && w1t) ? (bf16*)(ws + p.wq1t) : nullptr;
-    a.wq2 = p.bf16 ? (bf16*)(ws + p.wq2) : nullptr;
-    a.wq2t = p.wq2t ? (bf16*)(ws + p.wq2t) : nullptr;
-    a.wq3 = p.bf16 ? (bf16*)(ws + p.wq3) : nullptr;
-    a.wq3t = p.wq3t ? (bf16*)(ws + p.wq3t) : nullptr;
-    a.bq1 = p.bq1 ? (float*)(ws + p.bq1) : nullptr;
-    a.bq2 = p.bq2 ? (float*)(ws + p.bq2) : nullptr;
+    auto at = [&](size_t off) -> void* { return off ? ws + off : nullptr; };
+    a.wq1 = at(p.wq1); a.wq1t = w1t ? at(p.wq1t) : nullptr;
+    a.wq2 = at(p.wq2); a.wq2t = at(p.wq2t);
+    a.wq3 = at(p.wq3); a.wq3t = at(p.wq3t);
+    a.bq1 = (float*)at(p.bq1); a.bq2 = (float*)at(p.bq2);
     a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2; a.ki = p.g.ki; a.k1 = p.g.k1; a.k2 = p.g.k2;
     a.lr = lr; a.mu = mu; a.do_step = do_step ? 1 : 0;
     a.part3 = (const float*)(ws + p.grad3);
     a.blocks3 = p.blocks3; a.slot3 = conv3_bwd_slot_floats(p.g); a.C = p.g.C;
-    const bool params = do_step || p.bf16 || a.ext_in;
-    const bool l3 = params && p.mfma && do_step;
     // four parameters per thread when every block below W3, and every row under one tap, starts at a
     // multiple of four
     a.vec = (p.g.c_in % 4 == 0 && p.g.c1 % 4 == 0 && p.g.c2 % 4 == 0) ? 1 : 0;
-    if (a.vec) {
-        a.nb_main = params ? cdiv(p.po.W3 / 4, 256) : 0;
-        a.nb_tail = (params && !l3) ? cdiv(p.po.total - p.po.W3, 256) : 0;
-    } else {
-        a.nb_main = params ? cdiv(l3 ? p.po.W3 : p.po.total, 256) : 0;
-        a.nb_tail = 0;
-    }
-    a.nb_l3 = l3 ? cdiv(p.g.C * p.g.c2 + p.g.C, 16) : 0;
+    a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
+    a.nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
+    a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, 16) : 0;
     a.nb_finish = finish ? f.fph + 1 : 0;
     head_strides(a, p);
     return a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish;
@@ -443,24 +438,25 @@ void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamSte
     UpdateArgs a;
     const FinishArgs f = finish_args(p, ws, loss_out, miou_out, conf_out);
     const int blocks = step_end_args(p, ws, lr, mu, adam, do_step, finish, ext_in, w1t, f, a, save_old);
-    if (blocks == 0) return;
-    const bool params = do_step || p.bf16 || a.ext_in;
-    const char* name = a.ext_in ? "params_in+weights_to_bf16" : do_step ? (adam ? (finish ? "adam_update+finish_pass" : "adam_update") : (finish ? "sgd_update+finish_pass" : "sgd_update")) : (params ? "weights_to_bf16" : "finish_pass");
-    if (a.save_old) ST_LAUNCH(c, name, k_step_end<true>, dim3(blocks, p.g.heads()), dim3(256), 0, a, f);
-    else ST_LAUNCH(c, name, k_step_end<false>, dim3(blocks, p.g.heads()), dim3(256), 0, a, f);
+    const char* name = !do_step ? "params_in+operand_copies"
+                                : adam ? (finish ? "adam_update+finish_pass" : "adam_update") : (finish ? "sgd_update+finish_pass" : "sgd_update");
+    auto go = [&](auto kernel) { ST_LAUNCH(c, name, kernel, dim3(blocks, p.g.heads()), dim3(256), 0, a, f); };
+    if (p.bf16) { if (a.save_old) go(k_step_end<true, false>); else go(k_step_end<false, false>); }
+    else { if (a.save_old) go(k_step_end<true, true>); else go(k_step_end<false, true>); }
 }
 
 // Whether the packing role of the call-opening launch writes the whole padded grid of both feature
-// buffers (then only their guards need clearing): matrix-core path, bfloat16 features whose rows
-// are multiples of 16 bytes from a 16-byte aligned start, in the [n, c_in, h, w] order.
+// buffers (then only their guards need clearing): always on the float32 path; bfloat16 features whose
+// rows are multiples of 16 bytes from a 16-byte aligned start, in the [n, c_in, h, w] order.
 bool pack_covers_borders(const Plan& p, const void* features, int feat_dtype)
 {
-    return p.mfma && !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && p.g.c_in % 64 == 0 && !p.g.padded() &&
+    if (!p.bf16) return true;
+    return !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && p.g.c_in % 64 == 0 && !p.g.padded() &&
            ((uintptr_t)features & 15) == 0;
 }
 
 // Opens a call in one launch: packs the features, takes the caller's parameters (OIHW order)
-// into theta and the bfloat16 copies and, with labels, computes T = U^T (one-hot valid labels)
+// into theta and the operand copies and, with labels, computes T = U^T (one-hot valid labels)
 // and the pixel counts (n_valid must be clear).  The workspace must have been cleared before.
 void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_dtype, const float* head_params,
                 bool w1t, const int32_t* labels, const uint8_t* wmap)
@@ -469,11 +465,14 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
     BeginArgs q;
     memset(&q, 0, sizeof(q));
     q.features = features; q.feat = ws + p.feat;
-    q.featT = (p.bf16 && p.featT) ? ws + p.featT : nullptr;
-    q.in_bf16 = feat_dtype == ST_BF16; q.out_bf16 = p.bf16 ? 1 : 0;
+    q.featT = p.featT ? ws + p.featT : nullptr;
+    q.in_bf16 = feat_dtype == ST_BF16;
     q.PPT = p.PPT; q.guard = p.guard;
     q.pack_vec = pack_covers_borders(p, features, feat_dtype) ? 1 : 0;
-    if (q.pack_vec) {
+    if (!p.bf16) {
+        q.pack_x = cdiv(g.padded_positions(), 256); q.pack_y = g.ki / 8;
+        q.nb_pack = q.pack_x * q.pack_y;
+    } else if (q.pack_vec) {
         q.pack_x = cdiv(g.Wp, 64); q.pack_y = g.c_in / 64;
         q.nb_pack = q.pack_x * q.pack_y * g.n * g.Hp;
     } else {
@@ -493,8 +492,11 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
     q.nb_update_all = q.nb_update * g.heads();
     const size_t lds = std::max(std::max((size_t)32 * 33 * sizeof(float), (size_t)64 * PACKV_PITCH * sizeof(bf16)),
                                 (size_t)(q.CP * (LABEL_NCOL + 1) + 4) * sizeof(float));
-    ST_LAUNCH(c, labels ? "pack+label_adjoint+params_in" : "pack+params_in", k_call_begin,
-              dim3(q.nb_pack + q.nb_label + q.nb_update * g.heads()), dim3(256), lds, q, a, f);
+    auto go = [&](auto kernel) {
+        ST_LAUNCH(c, labels ? "pack+label_adjoint+params_in" : "pack+params_in", kernel,
+                  dim3(q.nb_pack + q.nb_label + q.nb_update * g.heads()), dim3(256), lds, q, a, f);
+    };
+    if (p.bf16) go(k_call_begin<false>); else go(k_call_begin<true>);
 }
 
 // bookkeeping of a pass without an update; with ext_out the same launch hands theta back to the
@@ -514,10 +516,10 @@ void finish_pass(Ctx& c, const Plan& p, char* ws, float* loss_out, double* miou_
         a.nb_out = cdiv(p.po.total, 256);
     }
     if (miou_host)
-        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", k_step_end<true>,
+        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", (k_step_end<true, false>),
                   dim3(a.nb_finish + a.nb_out, p.g.heads()), dim3(256), 0, a, f);
     else
-        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", k_step_end<false>,
+        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", (k_step_end<false, false>),
                   dim3(a.nb_finish + a.nb_out, p.g.heads()), dim3(256), 0, a, f);
 }
 

@@ -26,6 +26,7 @@
 
 #include "st_kernels.hpp"
 #include "st_mfma.hpp"
+#include "st_wgrad.hpp"
 
 namespace st {
 
@@ -269,53 +270,12 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
 #undef WG_UNIT_TAIL
 #undef WG_LOOPS
 
-    // ---- every wavefront leaves its block in LDS as [tap][o][i]; then all 256 threads add the
-    //      four copies in the order ((w0 + w1) + w2) + w3 and write the result with 16-byte stores.
-    //      The X fragment is the MFMA's A operand, so a lane holds four consecutive input channels
-    //      i of one output channel o per register group: one 16-byte LDS write.  Rows are 128
-    //      bytes; the 16-byte chunk c of row o is stored at chunk c ^ ((o >> 1) & 7), which spreads
-    //      the 16 lanes of a write (and of a read) over all banks.
-    float* red = (float*)smem_raw;                 // [4][9 * 32 rows][32]
+    // ---- the wavefronts' blocks are added through LDS; every row of acc[9] holds the sums over the
+    //      positions: row 0 lives in lanes 0 .. 31
+    float* red = (float*)smem_raw;
     float* redb = red + 4 * 9 * 32 * 32;           // [4][32] sums of dY over the positions
-    {
-        const int sw = (l32 >> 1) & 7;
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const f32x4 v = {acc[t][gq * 4], acc[t][gq * 4 + 1], acc[t][gq * 4 + 2], acc[t][gq * 4 + 3]};
-                *(f32x4*)(red + ((wave * 9 + t) * 32 + l32) * 32 + (((gq * 2 + lhi) ^ sw) << 2)) = v;
-            }
-    }
-    // every row of acc[9] holds the sums over the positions: row 0 lives in lanes 0 .. 31
     if (want_bias && lhi == 0) redb[wave * 32 + l32] = acc[9][0];
-    __syncthreads();
-    float* dW = a.dW + head * a.head_out_stride + (size_t)split * a.split_stride;
-    auto sum_of = [&](int q) {
-        const int row = q >> 3, part = q & 7;
-        const int chunk = (part ^ (((row & 31) >> 1) & 7)) << 2;
-        const f32x4 v0 = *(const f32x4*)(red + ((0 * 9 * 32 + row) * 32 + chunk));
-        const f32x4 v1 = *(const f32x4*)(red + ((1 * 9 * 32 + row) * 32 + chunk));
-        const f32x4 v2 = *(const f32x4*)(red + ((2 * 9 * 32 + row) * 32 + chunk));
-        const f32x4 v3 = *(const f32x4*)(red + ((3 * 9 * 32 + row) * 32 + chunk));
-        return ((v0 + v1) + v2) + v3;
-    };
-    auto place_of = [&](int q) {
-        const int t = q >> 8, ol = (q >> 3) & 31, part = q & 7;
-        return dW + ((size_t)(o0 + ol) * 9 + t) * a.cin + i0 + part * 4;
-    };
-    if (o0 + 32 <= a.cout && i0 + 32 <= a.cin && ((a.cin | (int)((uintptr_t)dW >> 2)) & 3) == 0) {
-        for (int q = tid; q < 9 * 32 * 8; q += 256) *(f32x4*)place_of(q) = sum_of(q);
-    } else {
-        // a tile with padded channels of a narrow head: those have no gradient to store
-        for (int q = tid; q < 9 * 32 * 8; q += 256) {
-            const f32x4 sum = sum_of(q);
-            float* dst = place_of(q);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (o0 + ((q >> 3) & 31) < a.cout && i0 + (q & 7) * 4 + e < a.cin) dst[e] = sum[e];
-        }
-    }
+    wgrad_reduce_store(acc, red, a.dW + head * a.head_out_stride + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
     if (want_bias && tid < 32 && o0 + tid < a.cout) {
         float* db = a.db + head * a.head_out_stride + (size_t)split * a.split_stride;
         db[o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
@@ -323,15 +283,19 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
 }
 
 // Position splits of the two layers for the shared launch.  Every block pays a fixed cost (ring
-// fill, the reduction through LDS, the partial-result store: about 22 units' worth) on top of its
-// units, blocks start in launch order on whichever compute unit is free, and every partial copy
-// is read once more by the optimiser kernel.  The search simulates exactly that for every pair of
-// split counts and keeps the shortest; among equals, fewer partial copies.
-void wgrad_splits_for(const Geo& g, int* s1_out, int* s2_out)
+// fill, the reduction through LDS, the partial-result store) on top of its units, blocks start in
+// launch order on whichever compute unit is free, and every partial copy is read once more by the
+// optimiser kernel.  The search simulates exactly that for every pair of split counts and keeps the
+// shortest; among equals, fewer partial copies.
+// bfloat16: units of 16 positions (9 MFMAs of 32 cycles), the fixed cost is about 22 of them.
+// float32: units of 8 positions (36 MFMAs of 64 cycles, eight times the time).
+void wgrad_splits_for(const Geo& g, bool bf16_path, int* s1_out, int* s2_out)
 {
-    constexpr int n_cu = 256, fixed_units = 22, reread_units_per_chip = 13;
+    constexpr int n_cu = 256;
+    const int fixed_units = bf16_path ? 22 : 3, reread_units_per_chip = bf16_path ? 13 : 2;
+    const int min_units = bf16_path ? 8 : 2;       // units per wavefront where a layer is split at all
     const int tiles1 = g.heads() * cdiv(g.c1, 32) * cdiv(g.c_in, 32), tiles2 = g.heads() * cdiv(g.c2, 32) * cdiv(g.c1, 32);
-    const int n_units = cdiv(g.padded_positions() / g.heads(), 16);
+    const int n_units = cdiv(g.padded_positions() / g.heads(), bf16_path ? 16 : 8);
     int best1 = 1, best2 = 1;
     long best_cost = -1;
     // compute units with the same free time form a group: (time, how many)
@@ -356,10 +320,9 @@ void wgrad_splits_for(const Geo& g, int* s1_out, int* s2_out)
     };
     std::vector<Group> gs;
     for (int s1 = 1; s1 <= 16; ++s1) {
-        // keep at least 8 units (128 positions) per wavefront
-        if (s1 > 1 && cdiv(n_units, s1 * 4) < 8) break;
+        if (s1 > 1 && cdiv(n_units, s1 * 4) < min_units) break;
         for (int s2 = 1; s2 <= 16; ++s2) {
-            if (s2 > 1 && cdiv(n_units, s2 * 4) < 8) break;
+            if (s2 > 1 && cdiv(n_units, s2 * 4) < min_units) break;
             const long d1 = cdiv(n_units, s1 * 4) + fixed_units, d2 = cdiv(n_units, s2 * 4) + fixed_units;
             const long n1 = (long)tiles1 * s1, n2 = (long)tiles2 * s2;
             // list scheduling on n_cu units, layer 1 first
@@ -399,7 +362,7 @@ void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, c
     const WgradArgs a1 = wgrad_args(p, da1T, featT, grad + p.po.W1, grad + p.po.b1, g.c_in, g.c1, p.splits1);
     const WgradArgs a2 = wgrad_args(p, da2T, a1T, grad + p.po.W2, grad + p.po.b2, g.c1, g.c2, p.splits2);
     const int blocks1 = a1.items_per_xcd * 8, blocks2 = a2.items_per_xcd * 8;
-    const size_t smem = (size_t)(4 * 9 * 32 * 32 + 4 * 32) * sizeof(float);
+    const size_t smem = WGRAD_SMEM_BYTES;
     ensure_dynamic_lds((const void*)k_wgrad3x3_mfma, smem);
     ST_LAUNCH(c, "conv12_wgrad_mfma", k_wgrad3x3_mfma, dim3(blocks1 + blocks2), dim3(256), smem, a1, a2, blocks1);
 }

@@ -124,24 +124,20 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.bf16 = d.compute == ST_COMPUTE_BF16;
     p.esz = p.bf16 ? 2 : 4;
     const Geo& g = p.g;
-    p.mfma = p.bf16;
-    p.splits1 = p.splits2 = p.splits3 = 1;
-    if (p.mfma) wgrad_splits_for(g, &p.splits1, &p.splits2);
-    else generic_wgrad_splits(g, &p.splits1, &p.splits2, &p.splits3);
-    p.blocks3 = p.mfma ? conv3_bwd_blocks(g) : 0;
-    p.grad_copies = std::max(std::max(p.splits1, p.splits2), p.splits3);
+    wgrad_splits_for(g, p.bf16, &p.splits1, &p.splits2);
+    p.blocks3 = conv3_bwd_blocks(g);
+    p.grad_copies = std::max(p.splits1, p.splits2);
     // guard: a 3x3 tap reaches Wp + 1 rows back/ahead of a tile that may overrun the grid by
     // up to 255 positions
     p.guard = (g.Wp + 2 + 256 + 7) / 8 * 8;
     const size_t PP = (size_t)g.padded_positions();
     p.PPT = (int)(p.guard + (PP + 15) / 16 * 16 + p.guard);
     size_t off = 256;   // offset 0 is kept unused so that "0" can mean "absent"
-    // position-major activations [guard + PP + guard][C]; the offsets point at position 0.
-    // Everything from zero_begin to zero_end is cleared at the start of a call (borders, guards).
-    p.zero_begin = off;
-    auto act = [&](int C) {
-        const size_t base = take(off, (PP + 2 * (size_t)p.guard) * C * p.esz);
-        return base + (size_t)p.guard * C * p.esz;
+    // bfloat16: position-major activations [guard + PP + guard][k], the offsets point at position 0;
+    // float32: [k / 8][PPT][8], the offsets point at the first guard column.
+    auto act = [&](int k) {
+        if (!p.bf16) return take(off, (size_t)k * p.PPT * 4);
+        return take(off, (PP + 2 * (size_t)p.guard) * k * 2) + (size_t)p.guard * k * 2;
     };
     // a buffer that only training needs
     auto train = [&](auto&& taker) -> size_t {
@@ -153,24 +149,23 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     auto train_take = [&](size_t bytes) { return train([&] { return take(off, bytes); }); };
     p.feat = act(g.ki);
     p.a1 = act(g.k1);
-    p.a2 = p.mfma ? train_act(g.k2) : act(g.k2);     // (the classifier-fused convolution keeps it to itself)
+    p.a2 = train_act(g.k2);      // (the classifier-fused convolution of a forward pass keeps it to itself)
     p.da1 = train_act(g.k1);
     p.da2 = train_act(g.k2);
-    if (p.mfma) {
+    if (p.bf16) {
         p.featT = train_take((size_t)g.ki * p.PPT * 2);
         p.a1T = train_take((size_t)g.k1 * p.PPT * 2);
         p.da1T = train_take((size_t)g.k1 * p.PPT * 2);
         p.da2T = train_take((size_t)g.k2 * p.PPT * 2);
     }
-    p.zero_end = off;
     const size_t hw = (size_t)g.h * g.w;
     const size_t heads = (size_t)g.heads();
     p.z = take(off, (size_t)g.n * g.C * hw * 4);
     p.gz = train_take((size_t)g.n * g.C * hw * 4);
     p.tadj = train_take((size_t)g.n * g.C * hw * 4);
     p.lab8 = train_take((size_t)g.pixels());
-    p.z_parts = p.mfma ? g.k2 / 64 : 0;
-    if (p.mfma) p.zpart = take(off, (size_t)p.z_parts * PP * ((g.C + 3) / 4 * 4) * 4);
+    p.z_parts = p.bf16 ? g.k2 / 64 : cdiv(g.c2, 32);
+    p.zpart = take(off, (size_t)p.z_parts * PP * ((g.C + 3) / 4 * 4) * 4);
     p.g_slots = train_take(loss_slot_floats(g) * 4);
     p.grad_stride = (p.po.total + 3) / 4 * 4;
     p.head_stride = p.grad_stride;
@@ -180,16 +175,21 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.grad = train_take(heads * p.grad_stride * 4 * p.grad_copies);
     p.grad3 = train_take(heads * std::max(p.blocks3, 1) * conv3_bwd_slot_floats(g) * 4);
     p.best = train_take(heads * p.head_stride * 4);
-    if (p.bf16) {
-        const size_t w1 = (size_t)g.k1 * 9 * g.ki, w2 = (size_t)g.k2 * 9 * g.k1;
-        p.wq1 = take(off, heads * w1 * 2);
-        p.wq1t = train_take(heads * w1 * 2);
-        p.wq2 = take(off, heads * w2 * 2);
-        p.wq2t = train_take(heads * w2 * 2);
-        p.wq3 = take(off, heads * (size_t)g.C * g.k2 * 2);
-        p.wq3t = train_take(heads * (size_t)g.k2 * 32 * 2);
-        if (g.padded()) { p.bq1 = take(off, (size_t)g.k1 * 4); p.bq2 = take(off, (size_t)g.k2 * 4); }
-    }
+    // (float32 operand copies: rows rounded up to 32)
+    const auto rows = [&](int k) { return (size_t)(p.bf16 ? k : cdiv(k, 32) * 32); };
+    p.bytes_w1 = heads * rows(g.k1) * 9 * g.ki * p.esz;
+    p.bytes_w1t = heads * rows(g.ki) * 9 * g.k1 * p.esz;
+    p.bytes_w2 = heads * rows(g.k2) * 9 * g.k1 * p.esz;
+    p.bytes_w2t = heads * rows(g.k1) * 9 * g.k2 * p.esz;
+    p.bytes_w3 = heads * (p.bf16 ? g.C : 32) * rows(g.k2) * p.esz;
+    p.bytes_w3t = heads * rows(g.k2) * 32 * p.esz;
+    p.wq1 = take(off, p.bytes_w1);
+    p.wq1t = train_take(p.bytes_w1t);
+    p.wq2 = take(off, p.bytes_w2);
+    p.wq2t = train_take(p.bytes_w2t);
+    p.wq3 = take(off, p.bytes_w3);
+    p.wq3t = train_take(p.bytes_w3t);
+    if (!p.bf16 || g.padded()) { p.bq1 = take(off, rows(g.k1) * 4); p.bq2 = take(off, rows(g.k2) * 4); }
     p.loss_part = train_take((size_t)loss_blocks(g) * 4);
     p.counters = take(off, std::max((size_t)256, heads * 8));   // valid pixels (their weights), one count per head
     p.conf = take(off, (size_t)g.n * g.C * g.C * 8);
@@ -314,22 +314,27 @@ static int scratch_of_current_device(char** out)
     return ST_OK;
 }
 
-// Clears everything a call relies on being zero, in one launch: the counters, and of the
-// activation buffers
-//  * plain kernels: all of them (they write interior cells only and rely on zero borders);
-//  * matrix-core kernels: every position of a1, a2, da1, da2 and of their channel-major copies is
+// Clears everything a call relies on being zero, in one launch: the counters, the padding of the
+// operand copies, and of the activation buffers
+//  * bfloat16: every position of a1, a2, da1, da2 and of their channel-major copies is
 //    rewritten (zeros on the border) by its producer in every pass, so only the guards in front
 //    of and behind the positions need clearing -- plus the features, unless their packing role
-//    covers the padded grid as well (feat_covered).
+//    covers the padded grid as well (feat_covered);
+//  * float32: the guards of the two buffers that the weight-gradient kernel multiplies at shifted
+//    positions (with gradients that are zero there).
 static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered)
 {
     ZeroList z;
     const Geo& g = p.g;
-    const int n_regions = 2 + 8 + 2 * 2 * (g.k1 / 32 + g.k2 / 32) + 2 * (g.ki / 32) + 3 + 7;
-    if (!p.mfma || n_regions > ZeroList::MAX) {
-        z.add(ws + p.zero_begin, p.zero_end - p.zero_begin);
+    const size_t PP = (size_t)g.padded_positions(), G = (size_t)p.guard;
+    if (!p.bf16) {
+        const size_t buf[2] = {p.feat, p.a1}, run = (size_t)p.PPT * 32;
+        const int runs[2] = {g.ki / 8, g.k1 / 8};
+        for (int i = 0; i < 2; ++i) {
+            z.add(ws + buf[i], G * 32, runs[i], run);
+            z.add(ws + buf[i] + (G + PP) * 32, run - (G + PP) * 32, runs[i], run);
+        }
     } else {
-        const size_t PP = (size_t)g.padded_positions(), G = (size_t)p.guard;
         if (!feat_covered) {
             z.add(ws + p.feat - G * g.ki * 2, (PP + 2 * G) * g.ki * 2);
             if (p.featT) z.add(ws + p.featT, (size_t)g.ki * p.PPT * 2);
@@ -349,32 +354,33 @@ static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered
         const size_t blk = (size_t)p.PPT * 32 * 2;                 // bytes of one channel block
         const size_t head = G * 32 * 2;                            // guard columns (a multiple of 8)
         const size_t tail_at = (G + PP / 8 * 8) * 32 * 2;
-        for (int i = 0; i < nbuf - 1; ++i)
-            for (int b = 0; tm[i] && b < tc[i] / 32; ++b) {
-                z.add(ws + tm[i] + b * blk, head);
-                z.add(ws + tm[i] + b * blk + tail_at, blk - tail_at);
-            }
+        for (int i = 0; i < nbuf - 1; ++i) {
+            if (!tm[i]) continue;
+            z.add(ws + tm[i], head, tc[i] / 32, blk);
+            z.add(ws + tm[i] + tail_at, blk - tail_at, tc[i] / 32, blk);
+        }
     }
-    if (p.wq3t) z.add(ws + p.wq3t, (size_t)g.heads() * g.k2 * 32 * 2);      // rows of the classes beyond C stay zero
-    if (p.mfma && g.padded()) {     // ... and so do the weights and biases of the channels beyond the caller's
-        const size_t w1 = (size_t)g.k1 * 9 * g.ki * 2, w2 = (size_t)g.k2 * 9 * g.k1 * 2;
-        z.add(ws + p.wq1, w1); z.add(ws + p.wq2, w2);
-        if (p.wq1t) { z.add(ws + p.wq1t, w1); z.add(ws + p.wq2t, w2); }
-        z.add(ws + p.wq3, (size_t)g.C * g.k2 * 2);
-        z.add(ws + p.bq1, (size_t)g.k1 * 4); z.add(ws + p.bq2, (size_t)g.k2 * 4);
+    // classes beyond C in the transposed classifier weights
+    if (p.wq3t) z.add(ws + p.wq3t, p.bytes_w3t);
+    if (!p.bf16) z.add(ws + p.wq3, p.bytes_w3);
+    if (g.padded() || (!p.bf16 && (g.c_in % 32 || g.c1 % 32 || g.c2 % 32))) {
+        // ... and the weights and biases of the channels beyond the caller's
+        z.add(ws + p.wq1, p.bytes_w1); z.add(ws + p.wq2, p.bytes_w2);
+        if (p.wq1t) { z.add(ws + p.wq1t, p.bytes_w1t); z.add(ws + p.wq2t, p.bytes_w2t); }
+        if (p.bf16) z.add(ws + p.wq3, p.bytes_w3);
+        z.add(ws + p.bq1, (size_t)cdiv(g.k1, 32) * 128); z.add(ws + p.bq2, (size_t)cdiv(g.k2, 32) * 128);
     }
     z.add(ws + p.counters, std::max((size_t)256, (size_t)g.heads() * 8));
     z.add(ws + p.conf, (size_t)g.n * g.C * g.C * 8);
     zero_regions(c, z);
 }
 
-// one forward pass of the head: features (already packed) -> low-resolution logits.  The plain
-// path leaves the planar tensor z; the matrix-core path leaves per-channel-tile shares of the
-// logits (the classifier rides along with layer 2), which the loss kernel adds up -- and writes
-// to z on the way.
-static void forward(Ctx& c, const Plan& p, char* ws, float* z)
+// one forward pass of the head: features (already packed) -> shares of the low-resolution logits, one
+// per channel tile (the classifier rides along with layer 2), which the loss kernel adds up -- and
+// writes to the planar tensor on the way.
+static void forward(Ctx& c, const Plan& p, char* ws)
 {
-    if (!p.mfma) { generic_forward(c, p, ws, z); return; }
+    if (!p.bf16) { forward_f32(c, p, ws); return; }
     const Geo& g = p.g;
     const float* theta = (const float*)(ws + p.theta);
     const float* b1 = p.bq1 ? (const float*)(ws + p.bq1) : theta + p.po.b1;
@@ -389,27 +395,19 @@ static void forward(Ctx& c, const Plan& p, char* ws, float* z)
 static ZSrc z_source(const Plan& p, char* ws, float* z)
 {
     ZSrc zs;
-    zs.planar = z; zs.parts = nullptr; zs.n_parts = 0; zs.b3 = nullptr; zs.z_out = nullptr;
-    zs.b3_stride = p.head_stride;
-    if (p.mfma) {
-        zs.planar = nullptr;
-        zs.parts = (const float*)(ws + p.zpart); zs.n_parts = p.z_parts;
-        zs.b3 = (const float*)(ws + p.theta) + p.po.b3; zs.z_out = z;
-    }
+    zs.parts = (const float*)(ws + p.zpart); zs.n_parts = p.z_parts;
+    zs.b3 = (const float*)(ws + p.theta) + p.po.b3; zs.b3_stride = p.head_stride;
+    zs.z_out = z;
     return zs;
 }
 
 // partial backward: gradients of the head's parameters only; nothing flows into the features
 // (with dfeat, the caller's float32 [n, c_in, h, w] tensor, the chain rule is continued one
 // more layer: what an unfrozen front part would need, and what partial distillation saves)
-// finish (matrix-core path only): the bookkeeping of the pass before rides on the first launch
+// finish (bfloat16 path only): the bookkeeping of the pass before rides on the first launch
 static void backward(Ctx& c, const Plan& p, char* ws, float* dfeat, const FinishArgs* finish = nullptr)
 {
-    if (!p.mfma) {
-        generic_backward(c, p, ws);
-        if (dfeat) generic_feature_grad(c, p, ws, dfeat);
-        return;
-    }
+    if (!p.bf16) { backward_f32(c, p, ws, dfeat); return; }
     const Geo& g = p.g;
     float* grad = (float*)(ws + p.grad);
     conv3_bwd_mfma(c, p, (const float*)(ws + p.g_slots), (const float*)(ws + p.tadj),
@@ -477,7 +475,7 @@ int st_get_workspace_layout(const st_head_desc* desc, st_workspace_layout* out)
     out->z = p.z; out->g = p.gz; out->theta = p.theta; out->grad = p.grad;
     out->elem_size = p.esz; out->total = p.total; out->row_pitch = (size_t)p.g.Wp;
     out->grad_copies = (size_t)p.grad_copies; out->grad_stride = p.grad_stride;
-    out->splits[0] = (size_t)p.splits1; out->splits[1] = (size_t)p.splits2; out->splits[2] = (size_t)p.splits3;
+    out->splits[0] = (size_t)p.splits1; out->splits[1] = (size_t)p.splits2; out->splits[2] = 1;
     return ST_OK;
 }
 
@@ -490,10 +488,8 @@ static int head_forward_launches(const st_head_desc* desc, const Plan& p, const 
     prepare_workspace(c, p, ws, pack_covers_borders(p, features, desc->feat_dtype));
     call_begin(c, p, ws, features, desc->feat_dtype, head_params, false, nullptr, nullptr);
     float* z = logits_lowres ? logits_lowres : (float*)(ws + p.z);
-    forward(c, p, ws, z);
-    if (pred || p.mfma)
-        loss_pass(c, p.g, z_source(p, ws, z), nullptr, nullptr, nullptr, pred, nullptr, nullptr, nullptr, nullptr, nullptr,
-                  false, false);
+    forward(c, p, ws);
+    loss_pass(c, p.g, z_source(p, ws, z), nullptr, nullptr, nullptr, pred, nullptr, nullptr, nullptr, false);
     return c.status;
 }
 
@@ -660,7 +656,6 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
 
     float* theta = (float*)(ws + p.theta);
     float* z = (float*)(ws + p.z);
-    unsigned long long* n_valid = (unsigned long long*)(ws + p.counters);
     unsigned long long* conf = (unsigned long long*)(ws + p.conf);
     double* metric_dev = (double*)(ws + p.scal);
 
@@ -684,7 +679,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
     bool params_out_done = false;
     for (int it = 0; it <= steps; ++it) {
         const bool last = it == steps;
-        forward(c, p, ws, z);
+        forward(c, p, ws);
         // The first pass of the early-exit form only scores the head (loss, class map, counts):
         // most frames are not key frames and end right there.  A key frame runs the same kernel
         // once more for the gradient half, below, once the host has seen the metric.
@@ -693,8 +688,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         const bool score_only = early_exit && it == 0 && !key_hint;
         loss_pass(c, g, z_source(p, ws, z), (const uint8_t*)(ws + p.lab8), pixel_weights, (const float*)(ws + p.tadj),
                   (out && (last || early_exit)) ? out->pred : nullptr,
-                  (float*)(ws + p.g_slots),
-                  (float*)(ws + p.gz), (float*)(ws + p.loss_part), conf, n_valid, !last && !score_only, !p.mfma);
+                  (float*)(ws + p.g_slots), (float*)(ws + p.loss_part), conf, !last && !score_only);
         float* loss_out = (out && out->losses) ? out->losses + (size_t)it * g.heads() : nullptr;
         double* miou_out = (out && out->mious) ? out->mious + (size_t)it * g.n : nullptr;
         long long* conf_out = (out && out->confusion && (last || early_exit)) ? (long long*)out->confusion : nullptr;
@@ -713,11 +707,11 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         const bool device_writes = mb && mb->host && mb->dev;
         const unsigned long long token = device_writes ? mb->next_token++ : 0;
         // From the second pass on the backward kernels are queued before the host looks at the
-        // metric (below); on the matrix-core path the bookkeeping then rides on the first of them
+        // metric (below); on the bfloat16 path the bookkeeping then rides on the first of them
         // instead of taking a launch of its own.
         const bool speculate = early_exit && !last && !feature_grad && (it > 0 || key_hint);
         const bool polled = device_writes && mb->poll && g_metric_polling.load(std::memory_order_relaxed);
-        const bool finish_rides = speculate && polled && p.mfma;
+        const bool finish_rides = speculate && polled && p.bf16;
         if (finish_now && !finish_rides)
             finish_pass(c, p, ws, loss_out, miou_out, conf_out, out_now ? head_params : nullptr,
                         device_writes ? mb->dev : nullptr, device_writes ? mb->dev_tok : nullptr, token);
@@ -782,7 +776,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         if (stop) break;
         if (score_only)   // the gradient half of the pass just scored: no counts, no loss, no class map again
             loss_pass(c, g, z_source(p, ws, z), (const uint8_t*)(ws + p.lab8), pixel_weights, (const float*)(ws + p.tadj), nullptr,
-                      (float*)(ws + p.g_slots), (float*)(ws + p.gz), nullptr, nullptr, n_valid, true, !p.mfma);
+                      (float*)(ws + p.g_slots), nullptr, nullptr, true);
         if (!backward_queued) backward(c, p, ws, feature_grad);
         AdamStep ad;
         if (use_adam) {

@@ -7,16 +7,36 @@
 
 namespace st {
 
-// features [n, c_in, h, w] (or [n, h, w, c_in]: Geo::nhwc) (Tin) -> padded position-major
-// [n, Hp, Wp, c_in] (E) and, when
+// Float32 path: features [n, c_in, h, w] (or [n, h, w, c_in]: Geo::nhwc) -> runs of eight channels
+// (pos8_index), the whole padded grid (zeros on the border and in padded channels).  One thread per
+// padded position and run: position tile bx (256 positions), run by.
+template <class Tin>
+__device__ __forceinline__ void pack_features_f32_block(const Tin* __restrict__ f, float* __restrict__ out, const Geo& g, int PPT,
+                                                        int guard, int bx, int by)
+{
+    const int mp = bx * 256 + threadIdx.x, frame = g.Hp * g.Wp, c0 = by * 8;
+    if (mp >= g.padded_positions()) return;
+    const int img = mp / frame, rr = mp - img * frame, y = rr / g.Wp - 1, x = rr % g.Wp - 1;
+    const bool inside = y >= 0 && y < g.h && x >= 0 && x < g.w;
+    const size_t at = !inside ? 0 : g.nhwc ? (((size_t)img * g.h + y) * g.w + x) * g.c_in : (size_t)img * g.c_in * g.h * g.w + y * g.w + x;
+    const size_t step = g.nhwc ? 1 : (size_t)g.h * g.w;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = inside && c0 + e < g.c_in ? to_f32(f[at + (c0 + e) * step]) : 0.f;
+    float4* dst = (float4*)(out + pos8_index(c0, guard + mp, PPT));
+    dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+    dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+}
+
+// bfloat16 path: features (Tin) -> padded position-major [n, Hp, Wp, ki] and, when
 // outT != nullptr, a channel-major copy in the blocked layout of xt_index() for the
 // weight-gradient kernel.
 // One block (256 threads) transposes a 32-channel x 32-column tile of one row through LDS so that
 // both the read (along x) and the write (along c) are contiguous.  Block coordinates: column
 // tile bx, channel tile by, row bz = img * h + y.  `tile` is 32 x 33 floats of LDS.
-template <class Tin, class E>
-__device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E* __restrict__ out,
-                                                    E* __restrict__ outT, const Geo& g, int PPT, int guard,
+template <class Tin>
+__device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, bf16* __restrict__ out,
+                                                    bf16* __restrict__ outT, const Geo& g, int PPT, int guard,
                                                     int bx, int by, int bz, float (*tile)[33])
 {
     const int x0 = bx * 32, c0 = by * 32;
@@ -30,7 +50,7 @@ __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E
             float v = 0.f;
             if (c < g.c_in && x < g.w) {
                 v = to_f32(f[(((size_t)img * g.h + y) * g.w + x) * g.c_in + c]);
-                out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<E>(v);
+                out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<bf16>(v);
             }
             tile[tx][k] = v;
         }
@@ -39,7 +59,7 @@ __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E
         for (int k = ty; k < 32; k += 8) {
             const int c = c0 + k, x = x0 + tx;
             if (c < g.c_in && x < g.w)
-                outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<E>(tile[k][tx]);
+                outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<bf16>(tile[k][tx]);
         }
         return;
     }
@@ -49,13 +69,13 @@ __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, E
         if (c < g.c_in && x < g.w) v = to_f32(f[(((size_t)img * g.c_in + c) * g.h + y) * g.w + x]);
         tile[k][tx] = v;
         if (outT && c < g.c_in && x < g.w)
-            outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<E>(v);
+            outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<bf16>(v);
     }
     __syncthreads();
     for (int k = ty; k < 32; k += 8) {
         const int x = x0 + k, c = c0 + tx;
         if (c < g.c_in && x < g.w)
-            out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<E>(tile[tx][k]);
+            out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<bf16>(tile[tx][k]);
     }
 }
 

@@ -51,7 +51,8 @@ inline Geo make_geo(const st_head_desc& d)
     // matrix-core kernels: whole 64-channel stages.  (A narrow head costs up to the work of a 64-channel
     // one, but that is matrix-core work on a chip such a head cannot fill anyway: 96 -> 48 -> 48 on
     // 60 x 107 cells went from 3.12 ms per 4-step call on plain kernels to the time of the launches.)
-    const int q = d.compute == ST_COMPUTE_BF16 ? 64 : 1;
+    // float32 kernels: runs of eight channels.
+    const int q = d.compute == ST_COMPUTE_BF16 ? 64 : 8;
     g.ki = (d.c_in + q - 1) / q * q; g.k1 = (d.c1 + q - 1) / q * q; g.k2 = (d.c2 + q - 1) / q * q;
     g.ignore_index = d.ignore_index;
     g.grouped = d.grouped ? 1 : 0;
@@ -114,35 +115,31 @@ struct Plan {
     LossTiling lt;
     bool bf16;          // compute path
     size_t esz;         // bytes per activation element
-    bool mfma;          // bf16 path: matrix-core kernels (else the plain tiled kernels)
     // With several heads (Geo::grouped) every per-head buffer holds heads() consecutive blocks:
     // theta, vel, vel2, best (head_stride floats apart), grad (grad_copies * grad_stride floats
     // apart), grad3 (blocks3 slots apart), the bfloat16 weight copies (their own size apart),
     // the pixel counters (one each).
     int splits1, splits2;   // position splits (per head) of the layer-1 / layer-2 weight-gradient kernels
-    int splits3;            // the same for the classifier layer on the plain kernels (the matrix-core
-                            // path leaves per-block slots instead: blocks3)
     int blocks3;            // per-block partial slots (per head) of the layer-3 backward kernel
     int grad_copies;        // max of the splits: partial gradient copies the update sums
     size_t grad_stride;     // floats between two copies (total rounded up to 16 bytes)
     size_t head_stride;     // floats between two heads' parameters (total rounded up to 16 bytes)
     int guard;          // guard rows before and after every position-major activation buffer;
                         // also the number of guard columns in front of a channel-major row
-    int PPT;            // row pitch (elements) of the channel-major copies
-    // byte offsets
+    int PPT;            // row pitch (elements) of the channel-major copies; columns per run of channels (float32)
+    // byte offsets (activations: of position 0; float32: of the first guard column of the first run)
     size_t feat, a1, a2, da1, da2;
     size_t featT, a1T, da1T, da2T;        // channel-major copies [C][PPT] for the weight-gradient kernels
     size_t grad3;                         // per-block partials of dW3 / db3
-    size_t zero_begin, zero_end;          // region cleared at the start of every call
     size_t z, g_slots, gz, tadj;   // tadj: U^T of the one-hot labels, [n, C, h, w] float32
     size_t lab8;                   // the labels as bytes, [n, 8h, 8w]: the class, or 255 for a pixel that does not count
-    size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution
+    size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution, one per channel tile
     size_t theta, vel, vel2, grad, best;   // vel: velocity or Adam's m; vel2: Adam's v
-    size_t wq1, wq1t, wq2, wq2t, wq3;      // bfloat16 operand copies of the weights
-    size_t bq1, bq2;                       // biases followed by zeros up to k1 / k2, where the pitches exceed the counts
+    size_t wq1, wq1t, wq2, wq2t, wq3;      // operand copies of the weights: bfloat16, or float32 in its kernels' order
+    size_t bq1, bq2;                       // biases followed by zeros, where the kernels read beyond the counts
     size_t wq3t;                           // W3 transposed, [k2][32 classes] (zero beyond C): MFMA A fragments of its backward
     size_t loss_part, counters, conf, scal;
-    size_t losses, mious;            // staging when the caller passes no result arrays
+    size_t bytes_w1, bytes_w1t, bytes_w2, bytes_w2t, bytes_w3, bytes_w3t;   // sizes of the operand copies
     size_t total;
 };
 

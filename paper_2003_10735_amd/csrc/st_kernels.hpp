@@ -7,28 +7,27 @@ namespace st {
 struct FinishArgs;   // st_finish.hpp: arguments of the bookkeeping role
 
 // k_layout.hip
-// regions to clear, each 16-byte aligned and padded to 16 bytes; one launch clears them all
+// regions to clear, each 16-byte aligned and padded to 16 bytes (`count` of them, `stride` bytes apart);
+// one launch clears them all
 struct ZeroList {
-    static constexpr int MAX = 96;
-    void* ptr[MAX]; size_t n16[MAX]; int first[MAX + 1]; int n = 0; bool overflow = false;
+    static constexpr int MAX = 40;
+    char* ptr[MAX]; size_t stride[MAX]; unsigned n16[MAX]; int first[MAX + 1], per[MAX]; int n = 0; bool overflow = false;
     ZeroList() { first[0] = 0; }
-    void add(void* p, size_t bytes);
+    void add(void* p, size_t bytes, int count = 1, size_t stride_bytes = 0);
 };
 void zero_regions(Ctx& c, const ZeroList& z);
 void zero_u64(Ctx& c, unsigned long long* p, size_t n);
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
 
-// k_conv_generic.hip -- plain tiled kernels of the float32 path
-void generic_forward(Ctx& c, const Plan& p, char* ws, float* z);
-void generic_backward(Ctx& c, const Plan& p, char* ws);
-void generic_feature_grad(Ctx& c, const Plan& p, char* ws, float* dfeat);
+// k_conv_f32.hip -- the float32 path's kernels
+void forward_f32(Ctx& c, const Plan& p, char* ws);
+void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 
 // k_conv_mfma.hip, k_wgrad_mfma.hip, k_conv3_mfma.hip -- matrix-core kernels of the bfloat16 path
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
                   const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, int layer,
                   const bf16* W3q = nullptr, float* zpart = nullptr, float* dense = nullptr);
-void wgrad_splits_for(const Geo& g, int* splits1, int* splits2);
-void generic_wgrad_splits(const Geo& g, int* splits1, int* splits2, int* splits3);
+void wgrad_splits_for(const Geo& g, bool bf16_path, int* splits1, int* splits2);
 void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, const bf16* da2T,
                    const bf16* a1T, float* grad);
 int conv3_bwd_blocks(const Geo& g);
@@ -42,20 +41,17 @@ void conv3_bwd_mfma(Ctx& c, const Plan& p, const float* slots, const float* T,
 // k_loss.hip
 size_t loss_slot_floats(const Geo& g);
 int loss_blocks(const Geo& g);
-// Where the loss kernel finds the low-resolution logits: either the planar tensor [n, C, h, w], or
-// the shares the classifier-fused convolution left behind, [n_parts][padded position][classes rounded up to a multiple of four],
-// to be added in ascending order together with the bias b3; in that case the kernel also writes
-// the sums to the planar tensor z_out (each tile its own cells), if given.
+// The low-resolution logits as the classifier-fused convolution left them: shares
+// [n_parts][padded position][classes rounded up to a multiple of four], added in ascending order
+// together with the bias b3; the kernel also writes the sums to the planar tensor z_out
+// [n, C, h, w] (each tile its own cells).
 struct ZSrc {
-    const float* planar;
     const float* parts; int n_parts; const float* b3; float* z_out;
     size_t b3_stride;     // floats between the biases of two heads (one head per frame)
 };
 // labels8: the labels as bytes (class, or 255 where the pixel does not count), or null: no loss, prediction only
 void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels8, const uint8_t* pixel_weights,
-               const float* T, uint8_t* pred,
-               float* slots, float* gz, float* loss_part, unsigned long long* conf,
-               const unsigned long long* n_valid, bool grad, bool assemble);
+               const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad);
 
 // k_update.hip
 // (every per-head quantity below -- parameters, optimiser state, partial gradients, weight copies,
