@@ -70,9 +70,7 @@ enum { ST_COMPUTE_F32 = 0, ST_COMPUTE_BF16 = 1 }; /* st_head_desc.compute */
  * compute = ST_COMPUTE_BF16: convolution operands (features, weights, activations and the
  *   back-propagated gradients) are rounded to bfloat16, products accumulate in float32 on the
  *   matrix cores; master weights, optimiser arithmetic, logits, loss and weight gradients stay
- *   float32.  Shapes with c_in and c1 multiples of 64 and c2 one of 64, 128, 256 run on the
- *   matrix-core kernels; every other shape runs on plain tiled kernels
- *   with the same rounding points (same results up to the order of float32 additions).
+ *   float32.  (Channel counts that are no multiples of 64 are padded with zeros internally.)
  * Limits: upscale == 8; 2 <= n_classes <= 32; labels outside [0, n_classes) are skipped like
  * ignore_index (they count neither in the loss nor in the metric).
  *
@@ -82,8 +80,8 @@ enum { ST_COMPUTE_F32 = 0, ST_COMPUTE_BF16 = 1 }; /* st_head_desc.compute */
  *   consecutive blocks: head_params, velocity, adam_m, adam_v are [n, st_num_params] and losses is
  *   [steps + 1, n]; the result of head f is what a call with n = 1 on frame f alone gives.  All
  *   heads take the same number of steps with the same learning rate: threshold must be <= 0, and
- *   feature_grad NULL (ST_ERR_ARG otherwise).  Runs on the matrix-core kernels only
- *   (ST_ERR_SHAPE for compute / shapes that do not, see above). */
+ *   feature_grad NULL (ST_ERR_ARG otherwise).  bfloat16 path with c_in and c1 multiples of 64 and
+ *   c2 one of 64, 128, 256 only (ST_ERR_SHAPE otherwise). */
 typedef struct st_head_desc {
     int32_t n, c_in, h, w;     /* feature map [n, c_in, h, w]                         */
     int32_t c1, c2, n_classes; /* conv3x3 c_in->c1, conv3x3 c1->c2, conv1x1 c2->classes */
@@ -134,8 +132,7 @@ typedef struct st_distill_opts {
      * whatever feat_layout says), or NULL.  When
      * given, every backward pass also computes d loss / d features (the data-gradient of the
      * first layer, which partial distillation leaves out); the tensor holds that of the last
-     * backward pass of the call (untouched if no step is taken).  On the matrix-core path this
-     * needs c1 in multiples of 64 (ST_ERR_SHAPE otherwise). */
+     * backward pass of the call (untouched if no step is taken). */
     float* feature_grad;
     /* Launch through a HIP graph.  A step is a handful of short kernels, and in a stream every launch
      * costs more dispatch time than it does inside a graph.  With use_graph = 1 and threshold <= 0

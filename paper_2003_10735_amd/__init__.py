@@ -154,6 +154,18 @@ class HeadDesc:
     feat_layout: int = ST_NCHW
     grouped: int = 0        # 1: n heads, one per frame; per-head arrays are [n, ...]
 
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        self.__dict__.pop("_struct", None)
+
+    def _ref(self):
+        """A reference to this descriptor's C struct for the calls below, which only read it (built once,
+        again after a field has changed: filling thirteen fields costs more than the call)."""
+        struct = self.__dict__.get("_struct")
+        if struct is None:
+            struct = self.__dict__["_struct"] = self.c()
+        return C.byref(struct)
+
     def c(self) -> StHeadDesc:
         return StHeadDesc(self.n, self.c_in, self.h, self.w, self.c1, self.c2, self.n_classes,
                           self.upscale, self.feat_dtype, self.feat_layout, self.compute,
@@ -172,10 +184,23 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+def _addr(t):
+    """Device address of a tensor as the integer that ctypes takes for a pointer argument or field."""
+    return None if t is None else t.data_ptr()
+
+
+_TORCH = None
+
+
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    """The stream's handle as an integer (the current stream if none is given)."""
+    global _TORCH
+    if stream is not None:
+        return stream.cuda_stream
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH.cuda.current_stream().cuda_stream
 
 
 def _check(status: int, where: str):
@@ -213,18 +238,16 @@ def st_head_forward(desc: HeadDesc, features, head_params, logits_lowres=None, p
                     workspace=None, stream=None):
     """features [n,c_in,h,w] (float32 or bfloat16 cuda tensor), head_params float32 [num_params]
     ([n, num_params] for a grouped descriptor).  Fills logits_lowres [n,C,h,w] float32 and/or pred [n,8h,8w] uint8 when given."""
-    d = desc.c()
     ws = workspace if workspace is not None else new_workspace(desc, features.device)
-    _check(lib().st_head_forward(C.byref(d), _ptr(features), _ptr(head_params), _ptr(logits_lowres),
-                                 _ptr(pred), _ptr(ws), _stream(stream)), "st_head_forward")
+    _check(lib().st_head_forward(desc._ref(), features.data_ptr(), head_params.data_ptr(), _addr(logits_lowres), _addr(pred),
+                                 ws.data_ptr(), _stream(stream)), "st_head_forward")
     return logits_lowres, pred
 
 
 def st_head_forward_noalloc(desc: HeadDesc, features, head_params, logits_lowres=None, pred=None, stream=None):
     """st_head_forward on the library's built-in scratch: no workspace argument, no allocation."""
-    d = desc.c()
-    _check(lib().st_head_forward_noalloc(C.byref(d), _ptr(features), _ptr(head_params), _ptr(logits_lowres),
-                                         _ptr(pred), _stream(stream)), "st_head_forward_noalloc")
+    _check(lib().st_head_forward_noalloc(desc._ref(), features.data_ptr(), head_params.data_ptr(), _addr(logits_lowres),
+                                         _addr(pred), _stream(stream)), "st_head_forward_noalloc")
     return logits_lowres, pred
 
 
@@ -245,41 +268,53 @@ def st_partial_distill(desc: HeadDesc, features, teacher_labels, head_params, st
     gradients at once instead of scoring first (st_distill_opts.expect_key_frame).
     Returns (steps_taken, best_metric or None); with a threshold the returned tuple also carries
     `.first_metric`, the metric before any update."""
-    d = desc.c()
     ws = workspace if workspace is not None else new_workspace(desc, features.device)
-    use_opts = (momentum != 0.0 or threshold > 0.0 or velocity is not None or adam is not None
-                or pixel_weights is not None or feature_grad is not None or graph or best_params is not None
-                or expect_key_frame)
-    opts = StDistillOpts(momentum, _ptr(velocity), threshold, 1 if strict_break else 0,
-                         1 if return_best else 0, ST_OPTIM_SGD, 0.0, 0.0, 0.0, None, None, 0,
-                         _ptr(pixel_weights), _ptr(feature_grad), 1 if graph else 0, _ptr(best_params),
-                         1 if expect_key_frame else 0)
-    if adam is not None:
-        opts.optimizer = ST_OPTIM_ADAM
-        opts.beta1, opts.beta2 = adam.get("beta1", 0.9), adam.get("beta2", 0.999)
-        opts.eps = adam.get("eps", 1e-8)
-        opts.adam_m, opts.adam_v = _ptr(adam["m"]), _ptr(adam["v"])
-        opts.adam_t0 = int(adam.get("t0", 0))
-    res = StDistillResult(_ptr(losses), _ptr(mious), _ptr(confusion), _ptr(pred), 0, 0.0)
-    st = lib().st_partial_distill(C.byref(d), _ptr(features), _ptr(teacher_labels), _ptr(head_params),
-                                  steps, lr, C.byref(opts) if use_opts else None, C.byref(res),
-                                  _ptr(ws), _stream(stream))
-    _check(st, "st_partial_distill")
-    ret = DistillReturn((int(res.steps_taken), (float(res.best_metric) if threshold > 0.0 else None)))
-    ret.first_metric = float(res.first_metric) if threshold > 0.0 else None
+    opts = None
+    if (momentum != 0.0 or threshold > 0.0 or velocity is not None or adam is not None or pixel_weights is not None
+            or feature_grad is not None or graph or best_params is not None or expect_key_frame):
+        # (fields start as zeros: only what differs is filled in)
+        o = StDistillOpts()
+        o.momentum, o.threshold, o.strict_break = momentum, threshold, 1 if strict_break else 0
+        if return_best:
+            o.return_best = 1
+        if velocity is not None:
+            o.velocity = velocity.data_ptr()
+        if pixel_weights is not None:
+            o.pixel_weights = pixel_weights.data_ptr()
+        if feature_grad is not None:
+            o.feature_grad = feature_grad.data_ptr()
+        if graph:
+            o.use_graph = 1
+        if best_params is not None:
+            o.best_params = best_params.data_ptr()
+        if expect_key_frame:
+            o.expect_key_frame = 1
+        if adam is not None:
+            o.optimizer = ST_OPTIM_ADAM
+            o.beta1, o.beta2 = adam.get("beta1", 0.9), adam.get("beta2", 0.999)
+            o.eps = adam.get("eps", 1e-8)
+            o.adam_m, o.adam_v = _addr(adam["m"]), _addr(adam["v"])
+            o.adam_t0 = int(adam.get("t0", 0))
+        opts = C.byref(o)
+    res = StDistillResult(_addr(losses), _addr(mious), _addr(confusion), _addr(pred))
+    _check(lib().st_partial_distill(desc._ref(), features.data_ptr(), teacher_labels.data_ptr(), head_params.data_ptr(), steps, lr,
+                                    opts, C.byref(res), ws.data_ptr(), _stream(stream)), "st_partial_distill")
+    ret = DistillReturn((res.steps_taken, res.best_metric if threshold > 0.0 else None))
+    ret.first_metric = res.first_metric if threshold > 0.0 else None
     return ret
 
 
 def st_miou(pred, labels, n_classes: int, ignore_index: int = -1, confusion=None, miou=None,
             stream=None):
     """pred uint8 [..], labels int32 [..] cuda tensors.  Returns (confusion int64 [C,C], miou float64 [1])."""
-    import torch
-    if confusion is None:
-        confusion = torch.empty((n_classes, n_classes), dtype=torch.int64, device=pred.device)
-    if miou is None:
-        miou = torch.empty(1, dtype=torch.float64, device=pred.device)
-    _check(lib().st_miou(_ptr(pred), _ptr(labels), pred.numel(), n_classes, ignore_index,
-                         _ptr(confusion), _ptr(miou), _stream(stream)), "st_miou")
+    if confusion is None or miou is None:
+        import torch
+        if confusion is None:
+            confusion = torch.empty((n_classes, n_classes), dtype=torch.int64, device=pred.device)
+        if miou is None:
+            miou = torch.empty(1, dtype=torch.float64, device=pred.device)
+    _check(lib().st_miou(pred.data_ptr(), labels.data_ptr(), pred.numel(), n_classes, ignore_index,
+                         confusion.data_ptr(), miou.data_ptr(), _stream(stream)), "st_miou")
     return confusion, miou
 
 
@@ -287,12 +322,12 @@ def st_object_weights(labels, n_classes: int, radius: int, factor: int = 5, back
                       ignore_index: int = -1, weights=None, stream=None):
     """labels int32 [n, H, W] cuda tensor -> uint8 [n, H, W] loss weights (`factor` within `radius`
     pixels of an object label, 1 elsewhere): the `pixel_weights` of st_partial_distill."""
-    import torch
     n, H, W = labels.shape
     if weights is None:
+        import torch
         weights = torch.empty((n, H, W), dtype=torch.uint8, device=labels.device)
-    _check(lib().st_object_weights(_ptr(labels), n, H, W, n_classes, background, ignore_index, radius, factor,
-                                   _ptr(weights), _stream(stream)), "st_object_weights")
+    _check(lib().st_object_weights(labels.data_ptr(), n, H, W, n_classes, background, ignore_index, radius, factor,
+                                   weights.data_ptr(), _stream(stream)), "st_object_weights")
     return weights
 
 

@@ -5,24 +5,7 @@
 
 namespace st {
 
-// Clears a list of regions in one launch: region r owns blocks [first[r], first[r + 1]), per[r] of them
-// for each of its repetitions, each block a fixed run of ZERO_PER_BLOCK 16-byte words.
-constexpr int ZERO_PER_BLOCK = 256 * 8;
-
-__global__ void __launch_bounds__(256) k_zero_regions(ZeroList z)
-{
-    int r = 0;
-    while (r + 1 < z.n && (int)blockIdx.x >= z.first[r + 1]) ++r;     // block-uniform, n is small
-    const int local = (int)blockIdx.x - z.first[r], rep = local / z.per[r];
-    uint4* p = (uint4*)(z.ptr[r] + (size_t)rep * z.stride[r]);
-    const unsigned base = (unsigned)(local - rep * z.per[r]) * ZERO_PER_BLOCK;
-    const uint4 zero = make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int k = 0; k < ZERO_PER_BLOCK / 256; ++k) {
-        const unsigned i = base + (unsigned)k * 256 + threadIdx.x;
-        if (i < z.n16[r]) p[i] = zero;
-    }
-}
+__global__ void __launch_bounds__(256) k_zero_regions(ZeroList z) { zero_block(z, blockIdx.x); }
 
 void ZeroList::add(void* p, size_t bytes, int count, size_t stride_bytes)
 {

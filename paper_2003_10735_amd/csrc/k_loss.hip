@@ -63,7 +63,7 @@ template <int CP, int CA, bool GRAD>
 __global__ void __launch_bounds__(LOSS_THREADS, (CP <= 24 ? 4 : 2))
 k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ wmap, const float* __restrict__ T,
        uint8_t* __restrict__ pred, float* __restrict__ slots, float* __restrict__ loss_part,
-       unsigned long long* __restrict__ conf, Geo g, LossTiling lt, int n_tiles)
+       unsigned long long* __restrict__ conf, Geo g, LossTiling lt, int n_tiles, CountSum count)
 {
     static_assert(LOSS_TY == 1, "one row group per tile: the two halves of a block split its 8 pixel rows");
     constexpr int CW = LOSS_CW, CH = LOSS_CH, CWP = CW + 1, NT = LOSS_THREADS;
@@ -75,6 +75,24 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
     __shared__ float wsum[NT / 64];
 
     const int tid = threadIdx.x;
+    const int tile_blocks = (n_tiles + 7) & ~7;
+    if ((int)blockIdx.x >= tile_blocks) {
+        // (a block behind the tiles: the pixel count of one head, a whole number)
+        const int head = blockIdx.x - tile_blocks;
+        unsigned int* part = conf_l;
+        unsigned long long total = 0;
+        for (int i = tid; i < count.per_head; i += NT) total += count.counts[(size_t)head * count.per_head + i];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) total += __shfl_down(total, off, 64);
+        if ((tid & 63) == 0) { part[tid >> 6] = (unsigned int)total; part[16 + (tid >> 6)] = (unsigned int)(total >> 32); }
+        __syncthreads();
+        if (tid == 0) {
+            total = 0;
+            for (int w = 0; w < NT / 64; ++w) total += part[w] | ((unsigned long long)part[16 + w] << 32);
+            count.n_valid[head] = total;
+        }
+        return;
+    }
     // XCD-aware tile order: consecutive blocks go to different XCDs, each with an L2 of its own.
     // Every XCD gets a contiguous run of tiles (a band of rows), so the three tiles that stage the
     // same row of cells run on one XCD and two of them find the row in its L2.
@@ -390,17 +408,18 @@ int loss_blocks(const Geo& g) { return g.n * loss_tiling(g).tiles(); }
 
 template <int CP, int CA>
 static void loss_launch(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels, const uint8_t* wmap,
-                        const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad)
+                        const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad, const CountSum* count)
 {
     const LossTiling lt = loss_tiling(g);
     const int n_tiles = g.n * lt.tiles();
-    const int blocks = (n_tiles + 7) / 8 * 8;      // whole rounds over the eight XCDs
+    const int blocks = (n_tiles + 7) / 8 * 8 + (count ? g.heads() : 0);      // whole rounds over the eight XCDs
+    const CountSum cs = count ? *count : CountSum{nullptr, 0, nullptr};
     if (grad) {
         ST_LAUNCH(c, "upsample_ce_grad", (k_loss<CP, CA, true>), dim3(blocks), dim3(LOSS_THREADS), 0, zs, labels, wmap, T, pred,
-                  slots, loss_part, conf, g, lt, n_tiles);
+                  slots, loss_part, conf, g, lt, n_tiles, cs);
     } else {
         ST_LAUNCH(c, "upsample_ce", (k_loss<CP, CA, false>), dim3(blocks), dim3(LOSS_THREADS), 0, zs, labels, wmap, T, pred, slots,
-                  loss_part, conf, g, lt, n_tiles);
+                  loss_part, conf, g, lt, n_tiles, cs);
     }
 }
 
@@ -418,9 +437,9 @@ static void loss_launch(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* lab
     }
 
 void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels, const uint8_t* wmap, const float* T,
-               uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad)
+               uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad, const CountSum* count)
 {
-#define ST_ARGS c, g, zs, labels, wmap, T, pred, slots, loss_part, conf, grad
+#define ST_ARGS c, g, zs, labels, wmap, T, pred, slots, loss_part, conf, grad, count
 #define ST_CALL(CP)                                                                           \
     switch (CP - g.C) {                                                                       \
     case 0: loss_launch<CP, CP>(ST_ARGS); break;                                              \

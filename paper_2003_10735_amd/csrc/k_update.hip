@@ -147,6 +147,13 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
     } else if (j < a.po.b3) {
         const unsigned r = j - (unsigned)a.po.W3;
         const unsigned cl = r / (unsigned)a.c2, o = r - cl * a.c2;
+        if (!a.do_step && a.wq3t && (int)cl == a.C - 1) {
+            // the call opens: the classes beyond the last are zeros (nothing writes them later)
+            for (unsigned k = cl + 1; k < 32; ++k) {
+                if (F32) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, k, 32)] = 0.f;
+                else ((bf16*)a.wq3t)[o * 32 + k] = (bf16)0.f;
+            }
+        }
         if (F32) {
             ((float*)a.wq3)[cl * ((a.c2 + 31) & ~31) + o] = w;
             if (a.wq3t) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, cl, 32)] = w;
@@ -202,7 +209,9 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f
     else if (a.bq2) *(f32x4*)(a.bq2 + (j - a.po.b2)) = w;
 }
 
-template <bool EE, bool F32>
+// (OPEN: as a role of the launch that opens a call: parameters in, operand copies; no other roles, so that the
+//  launch carries none of their LDS)
+template <bool EE, bool F32, bool OPEN>
 __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f, int b, int head)
 {
     if (head) {
@@ -256,7 +265,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         // [W3, total) one by one (no step: only the copies)
         const unsigned j = (unsigned)a.po.W3 + (unsigned)(b - a.nb_main) * 256 + threadIdx.x;
         if (j < a.po.total) apply_update<EE, F32>(a, j, 0.f);
-    } else if (b < a.nb_main + a.nb_tail + a.nb_l3) {
+    } else if constexpr (!OPEN) { if (b < a.nb_main + a.nb_tail + a.nb_l3) {
         // role (2): slot layout [32 classes][k2] weights, then [32] biases.  The slots were
         // written by other compute units, so every load is a round trip to memory: the role is
         // laid out for few of them.  A block takes 16 consecutive values; its 256 threads split
@@ -305,34 +314,35 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         // parameters back to the caller's order
         const unsigned j = (unsigned)(b - a.nb_main - a.nb_tail - a.nb_l3 - a.nb_finish) * 256 + threadIdx.x;
         if (j < a.po.total) a.ext_out[external_index(a, j)] = a.theta[j];
-    }
+    } }
 }
 
 template <bool EE, bool F32>
 __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 {
-    step_end_block<EE, F32>(a, f, blockIdx.x, blockIdx.y);
+    step_end_block<EE, F32, false>(a, f, blockIdx.x, blockIdx.y);
 }
 
-// The launch that opens a call: three kinds of blocks that do not depend on each other,
+// The launch that opens a call: kinds of blocks that do not depend on each other,
 //   first   U^T of the label map and the pixel counts (label_adjoint_block),
 //   then    the caller's parameters into theta and the operand copies: the blocks of
 //           k_step_end, head by head,
-//   last    feature packing (pack_features_block).
-// Run one after the other they are three short launches, each of which leaves most of the chip
+//   then    feature packing (pack_features_block),
+//   last    clearing what later kernels expect to be zero (ZeroList).
+// Run one after the other they are four short launches, each of which leaves most of the chip
 // idle for most of its time.
 struct BeginArgs {
     const void* features; void* feat; void* featT; int in_bf16, PPT, guard;
-    int pack_vec;                          // the 16-byte packing role over the padded grid
-    int pack_x, pack_y, nb_pack;           // pack grid: pack_x column tiles x pack_y channel tiles x rows
-    const int32_t* labels; const uint8_t* wmap; float* T; unsigned long long* n_valid; int CP, nb_label;
+    int pack_vec;                          // the 16-byte packing role
+    int pack_x, pack_y, nb_pack;           // pack grid: pack_x position (16-byte role: column) tiles x pack_y channel tiles (x rows)
+    const int32_t* labels; const uint8_t* wmap; float* T; unsigned int* counts; int CP, nb_label;
     uint8_t* lab8;                         // the labels as bytes for the loss kernel (written by the label role)
     int nb_update, nb_update_all;          // blocks of the parameter role per head, and of all heads
     Geo g;
 };
 
 template <bool F32>
-__global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, FinishArgs f)
+__global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, ZeroList z)
 {
     extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
     int b = blockIdx.x;
@@ -341,12 +351,13 @@ __global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, F
     if (b < q.nb_label) {
         float* colsum = dyn_lds;
         unsigned int* cnt_part = (unsigned int*)(dyn_lds + q.CP * (LABEL_NCOL + 1));
-        label_adjoint_block(q.labels, q.wmap, q.T, q.n_valid, q.g, b, colsum, cnt_part, q.CP, q.lab8);
+        label_adjoint_block(q.labels, q.wmap, q.T, q.counts + b, q.g, b, colsum, cnt_part, q.CP, q.lab8);
         return;
     }
     b -= q.nb_label;
     if (b >= q.nb_update_all) {
         b -= q.nb_update_all;
+        if (b >= q.nb_pack) { zero_block(z, b - q.nb_pack); return; }
         const int bx = b % q.pack_x, by = (b / q.pack_x) % q.pack_y, bz = b / (q.pack_x * q.pack_y);
         if (F32) {
             if (q.in_bf16) pack_features_f32_block((const bf16*)q.features, (float*)q.feat, q.g, q.PPT, q.guard, bx, by);
@@ -357,12 +368,11 @@ __global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, F
             pack_features_vec_block((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, (bf16*)dyn_lds);
             return;
         }
-        float (*tile)[33] = (float (*)[33])dyn_lds;
-        if (q.in_bf16) pack_features_block((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
-        else pack_features_block((const float*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, bz, tile);
+        if (q.in_bf16) pack_features_block((const bf16*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, (bf16*)dyn_lds);
+        else pack_features_block((const float*)q.features, (bf16*)q.feat, (bf16*)q.featT, q.g, q.PPT, q.guard, bx, by, (bf16*)dyn_lds);
         return;
     }
-    step_end_block<false, F32>(a, f, b % q.nb_update, b / q.nb_update);
+    step_end_block<false, F32, true>(a, FinishArgs{}, b % q.nb_update, b / q.nb_update);
 }
 
 FinishArgs finish_args(const Plan& p, char* ws, float* loss_out, double* miou_out, long long* conf_out,
@@ -445,21 +455,18 @@ void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamSte
     else { if (a.save_old) go(k_step_end<true, true>); else go(k_step_end<false, true>); }
 }
 
-// Whether the packing role of the call-opening launch writes the whole padded grid of both feature
-// buffers (then only their guards need clearing): always on the float32 path; bfloat16 features whose
-// rows are multiples of 16 bytes from a 16-byte aligned start, in the [n, c_in, h, w] order.
-bool pack_covers_borders(const Plan& p, const void* features, int feat_dtype)
+// Whether the packing role can move 16 bytes at a time: bfloat16 path, bfloat16 features whose rows are
+// multiples of 16 bytes from a 16-byte aligned start, in the [n, c_in, h, w] order, no padded channels.
+static bool pack_vectors(const Plan& p, const void* features, int feat_dtype)
 {
-    if (!p.bf16) return true;
-    return !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && p.g.c_in % 64 == 0 && !p.g.padded() &&
-           ((uintptr_t)features & 15) == 0;
+    return p.bf16 && !p.g.nhwc && feat_dtype == ST_BF16 && p.g.w % 8 == 0 && !p.g.padded() && ((uintptr_t)features & 15) == 0;
 }
 
 // Opens a call in one launch: packs the features, takes the caller's parameters (OIHW order)
-// into theta and the operand copies and, with labels, computes T = U^T (one-hot valid labels)
-// and the pixel counts (n_valid must be clear).  The workspace must have been cleared before.
+// into theta and the operand copies, clears `zero` and, with labels, computes T = U^T (one-hot valid
+// labels) and every label block's pixel count (the first loss pass adds them up).
 void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_dtype, const float* head_params,
-                bool w1t, const int32_t* labels, const uint8_t* wmap)
+                bool w1t, const int32_t* labels, const uint8_t* wmap, const ZeroList& zero)
 {
     const Geo& g = p.g;
     BeginArgs q;
@@ -468,7 +475,7 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
     q.featT = p.featT ? ws + p.featT : nullptr;
     q.in_bf16 = feat_dtype == ST_BF16;
     q.PPT = p.PPT; q.guard = p.guard;
-    q.pack_vec = pack_covers_borders(p, features, feat_dtype) ? 1 : 0;
+    q.pack_vec = pack_vectors(p, features, feat_dtype) ? 1 : 0;
     if (!p.bf16) {
         q.pack_x = cdiv(g.padded_positions(), 256); q.pack_y = g.ki / 8;
         q.nb_pack = q.pack_x * q.pack_y;
@@ -476,28 +483,32 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
         q.pack_x = cdiv(g.Wp, 64); q.pack_y = g.c_in / 64;
         q.nb_pack = q.pack_x * q.pack_y * g.n * g.Hp;
     } else {
-        q.pack_x = cdiv(g.w, 32); q.pack_y = cdiv(g.c_in, 32);
-        q.nb_pack = q.pack_x * q.pack_y * g.n * g.h;
+        q.pack_x = cdiv(g.padded_positions(), 64); q.pack_y = g.ki / 64;
+        q.nb_pack = q.pack_x * q.pack_y;
     }
     q.g = g;
     q.CP = (g.C + 3) / 4 * 4;
     if (labels) {
         q.labels = labels; q.wmap = wmap; q.T = (float*)(ws + p.tadj); q.lab8 = (uint8_t*)(ws + p.lab8);
-        q.n_valid = (unsigned long long*)(ws + p.counters);
-        q.nb_label = g.n * g.h * cdiv(g.w, LABEL_TX);
+        q.counts = (unsigned int*)(ws + p.label_counts);
+        q.nb_label = label_blocks(g);
     }
     UpdateArgs a;
     const FinishArgs f = finish_args(p, ws, nullptr, nullptr, nullptr);
     q.nb_update = step_end_args(p, ws, 0.f, 0.f, nullptr, false, false, head_params, w1t, f, a);
     q.nb_update_all = q.nb_update * g.heads();
-    const size_t lds = std::max(std::max((size_t)32 * 33 * sizeof(float), (size_t)64 * PACKV_PITCH * sizeof(bf16)),
-                                (size_t)(q.CP * (LABEL_NCOL + 1) + 4) * sizeof(float));
+    if (zero.overflow) { c.status = ST_ERR_SHAPE; return; }
+    size_t lds = p.bf16 ? (size_t)64 * PACKV_PITCH * sizeof(bf16) : 0;
+    if (labels) lds = std::max(lds, (size_t)(q.CP * (LABEL_NCOL + 1) + 4) * sizeof(float));
+    const int nb_zero = zero.n ? zero.first[zero.n] : 0;
     auto go = [&](auto kernel) {
         ST_LAUNCH(c, labels ? "pack+label_adjoint+params_in" : "pack+params_in", kernel,
-                  dim3(q.nb_pack + q.nb_label + q.nb_update * g.heads()), dim3(256), lds, q, a, f);
+                  dim3(q.nb_pack + q.nb_label + q.nb_update_all + nb_zero), dim3(256), lds, q, a, zero);
     };
     if (p.bf16) go(k_call_begin<false>); else go(k_call_begin<true>);
 }
+
+int label_blocks(const Geo& g) { return g.n * g.h * cdiv(g.w, LABEL_TX); }
 
 // bookkeeping of a pass without an update; with ext_out the same launch hands theta back to the
 // caller's vector (OIHW order)

@@ -190,12 +190,29 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.wq3 = take(off, p.bytes_w3);
     p.wq3t = train_take(p.bytes_w3t);
     if (!p.bf16 || g.padded()) { p.bq1 = take(off, rows(g.k1) * 4); p.bq2 = take(off, rows(g.k2) * 4); }
+    p.label_counts = train_take((size_t)label_blocks(g) * 4);
     p.loss_part = train_take((size_t)loss_blocks(g) * 4);
     p.counters = take(off, std::max((size_t)256, heads * 8));   // valid pixels (their weights), one count per head
     p.conf = take(off, (size_t)g.n * g.C * g.C * 8);
     p.scal = take(off, (size_t)g.n * 8);               // per-frame mean IoU of the last pass (double)
     p.total = off;
     return p;
+}
+
+// The plan is a pure function of the descriptor, and its search for position splits (up to 256
+// simulated launches) takes longer than enqueueing a kernel: every calling thread keeps its last few.
+static const Plan& plan_of(const st_head_desc& d, PlanKind kind = PLAN_FULL)
+{
+    struct Entry { st_head_desc desc; PlanKind kind; bool used = false; Plan plan; };
+    static thread_local Entry cache[4];
+    static thread_local int next = 0;
+    for (const Entry& e : cache)
+        if (e.used && e.kind == kind && memcmp(&e.desc, &d, sizeof(d)) == 0) return e.plan;     // (all int32: no padding)
+    Entry& e = cache[next];
+    next = (next + 1) % 4;
+    e.plan = make_plan(d, kind);
+    e.desc = d; e.kind = kind; e.used = true;
+    return e.plan;
 }
 
 static hipStream_t as_stream(void* s) { return (hipStream_t)s; }
@@ -314,15 +331,15 @@ static int scratch_of_current_device(char** out)
     return ST_OK;
 }
 
-// Clears everything a call relies on being zero, in one launch: the counters, the padding of the
-// operand copies, and of the activation buffers
-//  * bfloat16: every position of a1, a2, da1, da2 and of their channel-major copies is
+// What a call relies on being zero, for the launch that opens it: the confusion counts and, of the
+// activation buffers,
+//  * bfloat16: every position of the buffers and of their channel-major copies is
 //    rewritten (zeros on the border) by its producer in every pass, so only the guards in front
-//    of and behind the positions need clearing -- plus the features, unless their packing role
-//    covers the padded grid as well (feat_covered);
+//    of and behind the positions need clearing;
 //  * float32: the guards of the two buffers that the weight-gradient kernel multiplies at shifted
 //    positions (with gradients that are zero there).
-static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered)
+// The padding of the operand copies is cleared by a launch of its own in front of it, where there is any.
+static ZeroList regions_to_clear(Ctx& c, const Plan& p, char* ws)
 {
     ZeroList z;
     const Geo& g = p.g;
@@ -335,14 +352,9 @@ static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered
             z.add(ws + buf[i] + (G + PP) * 32, run - (G + PP) * 32, runs[i], run);
         }
     } else {
-        if (!feat_covered) {
-            z.add(ws + p.feat - G * g.ki * 2, (PP + 2 * G) * g.ki * 2);
-            if (p.featT) z.add(ws + p.featT, (size_t)g.ki * p.PPT * 2);
-        }
         const size_t pm[5] = {p.a1, p.a2, p.da1, p.da2, p.feat};
         const int pc[5] = {g.k1, g.k2, g.k1, g.k2, g.ki};
-        const int nbuf = feat_covered ? 5 : 4;
-        for (int i = 0; i < nbuf; ++i) {
+        for (int i = 0; i < 5; ++i) {
             if (!pm[i]) continue;
             z.add(ws + pm[i] - G * pc[i] * 2, G * pc[i] * 2);
             z.add(ws + pm[i] + PP * pc[i] * 2, G * pc[i] * 2);
@@ -354,25 +366,26 @@ static void prepare_workspace(Ctx& c, const Plan& p, char* ws, bool feat_covered
         const size_t blk = (size_t)p.PPT * 32 * 2;                 // bytes of one channel block
         const size_t head = G * 32 * 2;                            // guard columns (a multiple of 8)
         const size_t tail_at = (G + PP / 8 * 8) * 32 * 2;
-        for (int i = 0; i < nbuf - 1; ++i) {
+        for (int i = 0; i < 4; ++i) {
             if (!tm[i]) continue;
             z.add(ws + tm[i], head, tc[i] / 32, blk);
             z.add(ws + tm[i] + tail_at, blk - tail_at, tc[i] / 32, blk);
         }
     }
-    // classes beyond C in the transposed classifier weights
-    if (p.wq3t) z.add(ws + p.wq3t, p.bytes_w3t);
-    if (!p.bf16) z.add(ws + p.wq3, p.bytes_w3);
-    if (g.padded() || (!p.bf16 && (g.c_in % 32 || g.c1 % 32 || g.c2 % 32))) {
-        // ... and the weights and biases of the channels beyond the caller's
-        z.add(ws + p.wq1, p.bytes_w1); z.add(ws + p.wq2, p.bytes_w2);
-        if (p.wq1t) { z.add(ws + p.wq1t, p.bytes_w1t); z.add(ws + p.wq2t, p.bytes_w2t); }
-        if (p.bf16) z.add(ws + p.wq3, p.bytes_w3);
-        z.add(ws + p.bq1, (size_t)cdiv(g.k1, 32) * 128); z.add(ws + p.bq2, (size_t)cdiv(g.k2, 32) * 128);
+    if (!p.bf16) {      // classes beyond C
+        const size_t row = (size_t)cdiv(g.c2, 32) * 32 * 4;
+        z.add(ws + p.wq3 + g.C * row, (32 - g.C) * row);
     }
-    z.add(ws + p.counters, std::max((size_t)256, (size_t)g.heads() * 8));
     z.add(ws + p.conf, (size_t)g.n * g.C * g.C * 8);
-    zero_regions(c, z);
+    if (g.padded() || (!p.bf16 && (g.c_in % 32 || g.c1 % 32 || g.c2 % 32))) {
+        // the weights and biases of the channels beyond the caller's (the opening launch writes the others)
+        ZeroList w;
+        w.add(ws + p.wq1, p.bytes_w1); w.add(ws + p.wq2, p.bytes_w2); w.add(ws + p.wq3, p.bytes_w3);
+        if (p.wq1t) { w.add(ws + p.wq1t, p.bytes_w1t); w.add(ws + p.wq2t, p.bytes_w2t); w.add(ws + p.wq3t, p.bytes_w3t); }
+        w.add(ws + p.bq1, (size_t)cdiv(g.k1, 32) * 128); w.add(ws + p.bq2, (size_t)cdiv(g.k2, 32) * 128);
+        zero_regions(c, w);
+    }
+    return z;
 }
 
 // one forward pass of the head: features (already packed) -> shares of the low-resolution logits, one
@@ -485,8 +498,8 @@ static int head_forward_launches(const st_head_desc* desc, const Plan& p, const 
                                  float* logits_lowres, uint8_t* pred, char* ws, void* stream, bool no_profile)
 {
     Ctx c{as_stream(stream), ST_OK, no_profile};
-    prepare_workspace(c, p, ws, pack_covers_borders(p, features, desc->feat_dtype));
-    call_begin(c, p, ws, features, desc->feat_dtype, head_params, false, nullptr, nullptr);
+    const ZeroList zero = regions_to_clear(c, p, ws);
+    call_begin(c, p, ws, features, desc->feat_dtype, head_params, false, nullptr, nullptr, zero);
     float* z = logits_lowres ? logits_lowres : (float*)(ws + p.z);
     forward(c, p, ws);
     loss_pass(c, p.g, z_source(p, ws, z), nullptr, nullptr, nullptr, pred, nullptr, nullptr, nullptr, false);
@@ -500,7 +513,7 @@ int st_head_forward(const st_head_desc* desc, const void* features, const float*
     if (v != ST_OK) return v;
     if (!features || !head_params) return ST_ERR_NULL;
     if (!workspace || !aligned(workspace, 256)) return ST_ERR_WORKSPACE;
-    const Plan p = make_plan(*desc, PLAN_FORWARD);
+    const Plan& p = plan_of(*desc, PLAN_FORWARD);
     return head_forward_launches(desc, p, features, head_params, logits_lowres, pred, (char*)workspace, stream, false);
 }
 
@@ -510,10 +523,10 @@ int st_head_forward_noalloc(const st_head_desc* desc, const void* features, cons
     const int v = validate(desc);
     if (v != ST_OK) return v;
     if (!features || !head_params) return ST_ERR_NULL;
-    Plan p = make_plan(*desc, PLAN_FORWARD);
+    Plan p = plan_of(*desc, PLAN_FORWARD);
     // (heads whose internal buffers hold padded channels, and float32 ones: what the forward pass
     //  itself needs is what counts)
-    if (p.total > NOALLOC_SCRATCH_BYTES && (!p.bf16 || p.g.padded())) p = make_plan(*desc, PLAN_COMPACT);
+    if (p.total > NOALLOC_SCRATCH_BYTES && (!p.bf16 || p.g.padded())) p = plan_of(*desc, PLAN_COMPACT);
     if (p.total > NOALLOC_SCRATCH_BYTES) return ST_ERR_TOO_LARGE;
     char* ws = nullptr;
     const int sr = scratch_of_current_device(&ws);
@@ -649,7 +662,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         }
     }
 
-    const Plan p = make_plan(*desc);
+    const Plan& p = plan_of(*desc);
     const Geo& g = p.g;
     char* ws = (char*)workspace;
     Ctx c{as_stream(stream), ST_OK};
@@ -658,16 +671,17 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
     float* z = (float*)(ws + p.z);
     unsigned long long* conf = (unsigned long long*)(ws + p.conf);
     double* metric_dev = (double*)(ws + p.scal);
+    const CountSum count{(const unsigned int*)(ws + p.label_counts), label_blocks(g) / g.heads(), (unsigned long long*)(ws + p.counters)};
 
-    prepare_workspace(c, p, ws, pack_covers_borders(p, features, desc->feat_dtype));
+    const ZeroList zero = regions_to_clear(c, p, ws);
     if (mu != 0.f) permute_params(c, p, velocity, (float*)(ws + p.vel), 0);
     if (use_adam) {
         permute_params(c, p, adam_m, (float*)(ws + p.vel), 0);
         permute_params(c, p, adam_v, (float*)(ws + p.vel2), 0);
     }
-    // features packed, theta in internal order + bfloat16 copies, U^T of the labels and the sums
-    // of the weights of the valid labels: one launch
-    call_begin(c, p, ws, features, desc->feat_dtype, head_params, feature_grad != nullptr, teacher_labels, pixel_weights);
+    // features packed, theta in internal order + operand copies, U^T of the labels, the sums
+    // of the weights of the valid labels, and what has to be zero: one launch
+    call_begin(c, p, ws, features, desc->feat_dtype, head_params, feature_grad != nullptr, teacher_labels, pixel_weights, zero);
 
     double best_metric = -1.0, first_metric = -1.0;
     std::vector<double> frame_metric;
@@ -688,7 +702,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         const bool score_only = early_exit && it == 0 && !key_hint;
         loss_pass(c, g, z_source(p, ws, z), (const uint8_t*)(ws + p.lab8), pixel_weights, (const float*)(ws + p.tadj),
                   (out && (last || early_exit)) ? out->pred : nullptr,
-                  (float*)(ws + p.g_slots), (float*)(ws + p.loss_part), conf, !last && !score_only);
+                  (float*)(ws + p.g_slots), (float*)(ws + p.loss_part), conf, !last && !score_only, it == 0 ? &count : nullptr);
         float* loss_out = (out && out->losses) ? out->losses + (size_t)it * g.heads() : nullptr;
         double* miou_out = (out && out->mious) ? out->mious + (size_t)it * g.n : nullptr;
         long long* conf_out = (out && out->confusion && (last || early_exit)) ? (long long*)out->confusion : nullptr;

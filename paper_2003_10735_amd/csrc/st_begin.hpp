@@ -30,61 +30,90 @@ __device__ __forceinline__ void pack_features_f32_block(const Tin* __restrict__ 
 
 // bfloat16 path: features (Tin) -> padded position-major [n, Hp, Wp, ki] and, when
 // outT != nullptr, a channel-major copy in the blocked layout of xt_index() for the
-// weight-gradient kernel.
-// One block (256 threads) transposes a 32-channel x 32-column tile of one row through LDS so that
-// both the read (along x) and the write (along c) are contiguous.  Block coordinates: column
-// tile bx, channel tile by, row bz = img * h + y.  `tile` is 32 x 33 floats of LDS.
+// weight-gradient kernel; the whole padded grid (zeros on the border and in padded channels).
+// One block (256 threads) takes 64 padded positions (position tile bx) x 64 channels (by) through LDS, so that
+// the reads (along x, or along c for Geo::nhwc) are contiguous and the writes are 16 bytes each.
+// `tile` is 64 rows of PACKV_PITCH bfloat16 in LDS.
+constexpr int PACKV_PITCH = 64 + 8;
 template <class Tin>
 __device__ __forceinline__ void pack_features_block(const Tin* __restrict__ f, bf16* __restrict__ out,
                                                     bf16* __restrict__ outT, const Geo& g, int PPT, int guard,
-                                                    int bx, int by, int bz, float (*tile)[33])
+                                                    int bx, int by, bf16* tile)
 {
-    const int x0 = bx * 32, c0 = by * 32;
-    const int img = bz / g.h, y = bz % g.h;
-    const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;  // 32 x 8
+    const int tid = threadIdx.x, mp0 = bx * 64, c0 = by * 64;
+    const int frame = g.Hp * g.Wp, hw = g.h * g.w, PP = g.padded_positions();
+    // cell (row-major over all frames) of padded position mp, or -1 on the border and behind the grid
+    auto cell_of = [&](int mp) {
+        const int img = mp / frame, rr = mp - img * frame, yp = rr / g.Wp, x = rr - yp * g.Wp - 1, y = yp - 1;
+        return mp < PP && y >= 0 && y < g.h && x >= 0 && x < g.w ? img * hw + y * g.w + x : -1;
+    };
     if (g.nhwc) {
-        // channels are already the fast index: the position-major copy is a straight (padded)
-        // copy, and only the channel-major one goes through the tile
-        for (int k = ty; k < 32; k += 8) {
-            const int x = x0 + k, c = c0 + tx;
-            float v = 0.f;
-            if (c < g.c_in && x < g.w) {
-                v = to_f32(f[(((size_t)img * g.h + y) * g.w + x) * g.c_in + c]);
-                out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<bf16>(v);
+        // eight channels of a position per thread: they go straight to the position-major copy
+        const bool vec = g.c_in % 8 == 0 && ((uintptr_t)f & 15) == 0;
+        bf16x8 o[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int i = tid + r * 256, pl = i >> 3, c = c0 + (i & 7) * 8;
+            const int cell = cell_of(mp0 + pl);
+            const Tin* src = f + (size_t)max(cell, 0) * g.c_in + c;
+            if (vec) {
+                typedef Tin tin8 __attribute__((ext_vector_type(8)));
+                tin8 v = {};
+                if (cell >= 0 && c < g.c_in) v = *(const tin8*)src;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[r][e] = from_f32<bf16>(to_f32(v[e]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[r][e] = cell >= 0 && c + e < g.c_in ? from_f32<bf16>(to_f32(src[e])) : (bf16)0.f;
             }
-            tile[tx][k] = v;
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int i = tid + r * 256, pl = i >> 3, cl = (i & 7) * 8;
+            if (mp0 + pl < PP) *(bf16x8*)(out + (size_t)(mp0 + pl) * g.ki + c0 + cl) = o[r];
+            if (outT)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) tile[(cl + e) * PACKV_PITCH + pl] = o[r][e];
         }
         if (!outT) return;
         __syncthreads();
-        for (int k = ty; k < 32; k += 8) {
-            const int c = c0 + k, x = x0 + tx;
-            if (c < g.c_in && x < g.w)
-                outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<bf16>(tile[k][tx]);
+    } else {
+        const int pl = tid & 63, cell = cell_of(mp0 + pl);
+        const int img = max(cell, 0) / hw;
+        const Tin* src = f + ((size_t)img * g.c_in + c0) * hw + (max(cell, 0) - img * hw);
+        Tin v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int q = (tid >> 6) + 4 * k;
+            v[k] = cell >= 0 && c0 + q < g.c_in ? src[(size_t)q * hw] : (Tin)0.f;
         }
-        return;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) tile[((tid >> 6) + 4 * k) * PACKV_PITCH + pl] = from_f32<bf16>(to_f32(v[k]));
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            // position-major: 8 channels of one position
+            const int i = tid + r * 256, p = i >> 3, cq = i & 7;
+            if (mp0 + p < PP) {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = tile[(cq * 8 + e) * PACKV_PITCH + p];
+                *(bf16x8*)(out + (size_t)(mp0 + p) * g.ki + c0 + cq * 8) = o;
+            }
+        }
+        if (!outT) return;
     }
-    for (int k = ty; k < 32; k += 8) {
-        const int c = c0 + k, x = x0 + tx;
-        float v = 0.f;
-        if (c < g.c_in && x < g.w) v = to_f32(f[(((size_t)img * g.c_in + c) * g.h + y) * g.w + x]);
-        tile[k][tx] = v;
-        if (outT && c < g.c_in && x < g.w)
-            outT[xt_index(c, guard + (img * g.Hp + y + 1) * g.Wp + x + 1, PPT / 8)] = from_f32<bf16>(v);
-    }
-    __syncthreads();
-    for (int k = ty; k < 32; k += 8) {
-        const int x = x0 + k, c = c0 + tx;
-        if (c < g.c_in && x < g.w)
-            out[(((size_t)img * g.Hp + y + 1) * g.Wp + x + 1) * g.ki + c] = from_f32<bf16>(tile[tx][k]);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        // channel-major: 8 positions of one channel (PP is a multiple of eight)
+        const int i = tid + r * 256, ch = i >> 3, g8 = i & 7;
+        if (mp0 + 8 * g8 < PP)
+            *(bf16x8*)(outT + xt_index(c0 + ch, guard + mp0 + 8 * g8, PPT / 8)) = *(const bf16x8*)(tile + ch * PACKV_PITCH + 8 * g8);
     }
 }
 
-// The same for bfloat16 in and out on the matrix-core path, with 16-byte accesses and covering the
-// whole padded grid (zeros on the border), so that nothing of the two feature buffers but their
-// guards needs clearing beforehand.  One block (256 threads): one padded row yp (bz = img * Hp + yp),
-// 64 channels (by), 64 padded columns xp0 .. xp0 + 63 (bx).  Needs w % 8 == 0, c_in % 64 == 0 and a
-// 16-byte aligned source.  `tile` is 64 rows of PACKV_PITCH bfloat16 in LDS.
-constexpr int PACKV_PITCH = 64 + 8;
+// The same for bfloat16 features with 16-byte reads (pack_vectors): one padded row yp (bz = img * Hp + yp),
+// 64 channels (by), 64 padded columns xp0 .. xp0 + 63 (bx) per block.
 __device__ __forceinline__ void pack_features_vec_block(const bf16* __restrict__ f, bf16* __restrict__ out,
                                                         bf16* __restrict__ outT, const Geo& g, int PPT, int guard,
                                                         int bx, int by, int bz, bf16* tile)
@@ -164,7 +193,7 @@ constexpr int LABEL_TX = 32;                 // 8-pixel column groups per block 
 constexpr int LABEL_NCOL = LABEL_TX * 8 + 8;
 __device__ __forceinline__ void label_adjoint_block(const int32_t* __restrict__ labels,
                                                     const uint8_t* __restrict__ wmap, float* __restrict__ T,
-                                                    unsigned long long* __restrict__ n_valid, const Geo& g,
+                                                    unsigned int* __restrict__ count, const Geo& g,
                                                     int block, float* colsum, unsigned int* cnt_part, int CP,
                                                     uint8_t* __restrict__ lab8)
 {
@@ -175,8 +204,6 @@ __device__ __forceinline__ void label_adjoint_block(const int32_t* __restrict__ 
     const int hw = g.h * g.w;
     const int32_t* lab = labels + (size_t)img * g.H * g.W;
     const uint8_t* wm = wmap ? wmap + (size_t)img * g.H * g.W : nullptr;
-    for (int i = tid; i < CP * PITCH; i += 256) colsum[i] = 0.f;
-    __syncthreads();
     const int X0 = tx * LABEL_TX * 8 - 4;                  // frame column of table column 0
     const int Yt = 8 * cy - 4;                             // frame row of tent position 0
     unsigned int cnt = 0;     // valid labels (their weights) of this block's own 8 x 256 pixels
@@ -199,6 +226,9 @@ __device__ __forceinline__ void label_adjoint_block(const int32_t* __restrict__ 
             ws[k][r] = wm ? wm[at] : 1u;
         }
     }
+    // (the table is cleared while the labels are on their way)
+    for (int i = tid; i < CP * PITCH; i += 256) colsum[i] = 0.f;
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         if (k == 1 && !second) break;
@@ -232,23 +262,24 @@ __device__ __forceinline__ void label_adjoint_block(const int32_t* __restrict__ 
         }
         if (run_y >= 0) colsum[run_y * PITCH + col] += run;
     }
-    if (n_valid) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
-        if ((tid & 63) == 0) cnt_part[tid >> 6] = cnt;
-    }
+    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
+    if ((tid & 63) == 0) cnt_part[tid >> 6] = cnt;
     __syncthreads();
-    if (n_valid && tid == 0)
-        atomicAdd(n_valid + g.head_of(img), (unsigned long long)(cnt_part[0] + cnt_part[1] + cnt_part[2] + cnt_part[3]));
+    if (tid == 0) *count = cnt_part[0] + cnt_part[1] + cnt_part[2] + cnt_part[3];
     for (int i = tid; i < g.C * LABEL_TX; i += 256) {
         const int lc = i % LABEL_TX, c = i / LABEL_TX;
         const int cx = tx * LABEL_TX + lc;
         if (cx >= g.w) continue;
+        // (the tent's weights, for the first and last cell folded back by the edge replication: see tap_weight;
+        //  columns off the frame hold zero sums)
+        const bool first = cx == 0, last = cx == g.w - 1;
         float acc = 0.f;
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
-            const int X = 8 * cx - 4 + t;                  // table column 8 * lc + t
-            if (X >= 0 && X < g.W) acc += tap_weight(X, cx, g.w) * colsum[c * PITCH + 8 * lc + t];
+            const float tent = (t < 8 ? 2 * t + 1 : 31 - 2 * t) * 0.0625f;
+            const float wgt = (t < 8 ? first : last) ? 1.f : tent;
+            acc += wgt * colsum[c * PITCH + 8 * lc + t];   // table column 8 * lc + t: X = 8 * cx - 4 + t
         }
         T[((size_t)img * g.C + c) * hw + cy * g.w + cx] = acc;
     }

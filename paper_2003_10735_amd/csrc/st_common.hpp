@@ -138,7 +138,7 @@ struct Plan {
     size_t wq1, wq1t, wq2, wq2t, wq3;      // operand copies of the weights: bfloat16, or float32 in its kernels' order
     size_t bq1, bq2;                       // biases followed by zeros, where the kernels read beyond the counts
     size_t wq3t;                           // W3 transposed, [k2][32 classes] (zero beyond C): MFMA A fragments of its backward
-    size_t loss_part, counters, conf, scal;
+    size_t loss_part, counters, label_counts, conf, scal;   // label_counts: per label block of the opening launch
     size_t bytes_w1, bytes_w1t, bytes_w2, bytes_w2t, bytes_w3, bytes_w3t;   // sizes of the operand copies
     size_t total;
 };

@@ -10,11 +10,27 @@ struct FinishArgs;   // st_finish.hpp: arguments of the bookkeeping role
 // regions to clear, each 16-byte aligned and padded to 16 bytes (`count` of them, `stride` bytes apart);
 // one launch clears them all
 struct ZeroList {
-    static constexpr int MAX = 40;
+    static constexpr int MAX = 24;
     char* ptr[MAX]; size_t stride[MAX]; unsigned n16[MAX]; int first[MAX + 1], per[MAX]; int n = 0; bool overflow = false;
     ZeroList() { first[0] = 0; }
     void add(void* p, size_t bytes, int count = 1, size_t stride_bytes = 0);
 };
+// Region r owns blocks [first[r], first[r + 1]), per[r] of them for each of its repetitions, each block
+// (256 threads) a fixed run of ZERO_PER_BLOCK 16-byte words.
+constexpr int ZERO_PER_BLOCK = 256 * 8;
+__device__ __forceinline__ void zero_block(const ZeroList& z, int block)
+{
+    int r = 0;
+    while (r + 1 < z.n && block >= z.first[r + 1]) ++r;     // block-uniform, n is small
+    const int local = block - z.first[r], rep = local / z.per[r];
+    uint4* p = (uint4*)(z.ptr[r] + (size_t)rep * z.stride[r]);
+    const unsigned base = (unsigned)(local - rep * z.per[r]) * ZERO_PER_BLOCK;
+#pragma unroll
+    for (int k = 0; k < ZERO_PER_BLOCK / 256; ++k) {
+        const unsigned i = base + (unsigned)k * 256 + threadIdx.x;
+        if (i < z.n16[r]) p[i] = make_uint4(0, 0, 0, 0);
+    }
+}
 void zero_regions(Ctx& c, const ZeroList& z);
 void zero_u64(Ctx& c, unsigned long long* p, size_t n);
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
@@ -49,9 +65,13 @@ struct ZSrc {
     const float* parts; int n_parts; const float* b3; float* z_out;
     size_t b3_stride;     // floats between the biases of two heads (one head per frame)
 };
+// One more block per head adds up the label blocks' pixel counts (the first pass of a call: the kernels that divide
+// by the number of valid pixels come behind it).
+struct CountSum { const unsigned int* counts; int per_head; unsigned long long* n_valid; };
 // labels8: the labels as bytes (class, or 255 where the pixel does not count), or null: no loss, prediction only
 void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels8, const uint8_t* pixel_weights,
-               const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad);
+               const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad,
+               const CountSum* count = nullptr);
 
 // k_update.hip
 // (every per-head quantity below -- parameters, optimiser state, partial gradients, weight copies,
@@ -60,9 +80,10 @@ void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels8, con
 //   theta <- theta - step_scale * m / (sqrt(v) * inv_sqrt_bc2 + eps),
 //   step_scale = lr / (1 - beta1^t),  inv_sqrt_bc2 = 1 / sqrt(1 - beta2^t).
 struct AdamStep { float beta1, beta2, one_minus_beta1, one_minus_beta2, eps, step_scale, inv_sqrt_bc2; };
-bool pack_covers_borders(const Plan& p, const void* features, int feat_dtype);
 void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_dtype, const float* head_params,
-                bool w1t, const int32_t* labels, const uint8_t* pixel_weights);
+                bool w1t, const int32_t* labels, const uint8_t* pixel_weights, const ZeroList& zero);
+// blocks of the label role of that launch, in the order of the frames; each leaves its pixel count (weight sum)
+int label_blocks(const Geo& g);
 void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool do_step, bool finish, float* loss_out,
               double* miou_out, long long* conf_out, const float* ext_in = nullptr,
               bool w1t = false, float* save_old = nullptr);
