@@ -27,21 +27,6 @@ void zero_regions(Ctx& c, const ZeroList& z)
     ST_LAUNCH(c, "zero_fill", k_zero_regions, dim3(z.first[z.n]), dim3(256), 0, z);
 }
 
-__global__ void __launch_bounds__(256) k_zero8(unsigned long long* p, size_t n)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = 0ull;
-}
-
-void zero_u64(Ctx& c, unsigned long long* p, size_t n)
-{
-    if (n == 0) return;
-    int blocks = (int)((n + 255) / 256);
-    if (blocks > 1024) blocks = 1024;
-    ST_LAUNCH(c, "zero_fill", k_zero8, dim3(blocks), dim3(256), 0, p, n);
-}
-
 // Parameter permutation.  dir = 0: external (OIHW) -> internal; dir = 1: internal -> external.
 // Thread j walks the internal index; inside a 3x3 weight block
 //   internal (o*9 + tap)*ci + i   <->   external (o*ci + i)*9 + tap.

@@ -534,24 +534,56 @@ void finish_pass(Ctx& c, const Plan& p, char* ws, float* loss_out, double* miou_
                   dim3(a.nb_finish + a.nb_out, p.g.heads()), dim3(256), 0, a, f);
 }
 
-// Mean IoU (Eq. 1) of a C x C table of counts, any C up to 256: one wavefront per class adds
+// ------------------------------------------------------------------ stand-alone metric
+// Confusion counts of a class map against labels.  Each block keeps its own C x C table in
+// LDS and adds it to the result at the end; integer counts, so the order of additions does
+// not matter.  Few, large blocks: the final additions of every block land on the same few
+// cache lines.  Per trip a wavefront takes 1024 consecutive pixels as four label loads of 16
+// bytes and four prediction loads of 4 bytes per lane, each instruction reading one contiguous
+// stretch, all issued before the first is used.  Label maps are piecewise constant, so most
+// wavefronts hold a single (label, prediction) pair: that case is detected with one ballot and
+// costs one LDS addition.  Otherwise every lane merges equal neighbours among its 16 pixels
+// and adds each run to the table itself; LDS resolves lanes that hit the same counter.  (Counting the
+// pairs of the stretch's two ends with ballots and adding only other pixels one by one: 12.7 us at 1920 x 1080
+// with 2 % of the pixels off, against 7.6 -- most pixel slots of a wavefront then hold one of those.)
+// Tables too large for LDS (more than 128 classes) go to the result directly, one addition
+// per distinct pair of a wavefront and pixel slot.
+// (Blocks of 512 threads, one per compute unit at 1920 x 1080 instead of half as many: 8.2 against 7.6 us, the
+// merge has twice the additions.  The last block in computing the mean IoU instead of a launch of its own:
+// 18.2 us for this kernel -- additions that must complete before a block counts itself in, and a table
+// read back past the caches -- against 7.6 + 3.7.)
+constexpr int CONF_THREADS = 1024;
+constexpr int CONF_PER_T = 16;                       // pixels of one thread per trip
+constexpr int CONF_MAX_BLOCKS = 256;
+constexpr int MIOU_THREADS = 1024;
+
+// Mean IoU (Eq. 1) of a C x C table of counts, any C up to 256: 16 lanes per class add
 // that class's row and column (exact integer sums), then a single thread adds the per-class
 // ratios of the classes that occur as a label in ascending order in float64 and divides by
-// their number; 0 when there is none.
-constexpr int MIOU_THREADS = 1024;
+// their number; 0 when there is none.  A table of up to 64 classes is fetched once, by all threads, into LDS.
 __global__ void __launch_bounds__(MIOU_THREADS)
 k_miou_from_counts(const unsigned long long* __restrict__ conf, int C, double* __restrict__ out)
 {
+    __shared__ unsigned long long tab[64 * 64];
     __shared__ double iou[256];
     __shared__ int present[256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int c = wave; c < C; c += MIOU_THREADS / 64) {
+    const bool staged = C <= 64;
+    if (staged) {
+        for (int i = threadIdx.x; i < C * C; i += MIOU_THREADS) tab[i] = conf[i];
+        __syncthreads();
+    }
+    const int sub = threadIdx.x & 15;
+    for (int c = threadIdx.x >> 4; c < (C + 3) / 4 * 4; c += MIOU_THREADS / 16) {      // (whole wavefronts)
         unsigned long long row = 0, col = 0;
-        for (int k = lane; k < C; k += 64) { row += conf[(size_t)c * C + k]; col += conf[(size_t)k * C + c]; }
+        if (c < C)
+            for (int k = sub; k < C; k += 16) {
+                row += staged ? tab[c * C + k] : conf[c * C + k];
+                col += staged ? tab[k * C + c] : conf[k * C + c];
+            }
 #pragma unroll
-        for (int d = 32; d; d >>= 1) { row += __shfl_xor(row, d, 64); col += __shfl_xor(col, d, 64); }
-        if (lane == 0) {
-            const unsigned long long inter = conf[(size_t)c * C + c];
+        for (int d = 8; d; d >>= 1) { row += __shfl_xor(row, d, 64); col += __shfl_xor(col, d, 64); }
+        if (sub == 0 && c < C) {
+            const unsigned long long inter = staged ? tab[c * C + c] : conf[c * C + c];
             present[c] = row != 0;
             iou[c] = row ? (double)inter / (double)(row + col - inter) : 0.0;
         }
@@ -566,21 +598,6 @@ k_miou_from_counts(const unsigned long long* __restrict__ conf, int C, double* _
     }
 }
 
-// ------------------------------------------------------------------ stand-alone metric
-// Confusion counts of a class map against labels.  Each block keeps its own C x C table in
-// LDS and adds it to the result at the end; integer counts, so the order of additions does
-// not matter.  Few, large blocks: the final additions of every block land on the same few
-// cache lines.  Per trip a wavefront takes 1024 consecutive pixels as four label loads of 16
-// bytes and four prediction loads of 4 bytes per lane, each instruction reading one contiguous
-// stretch, all issued before the first is used.  Label maps are piecewise constant, so most
-// wavefronts hold a single (label, prediction) pair: that case is detected with one ballot and
-// costs one LDS addition.  Otherwise every lane merges equal neighbours among its 16 pixels
-// and adds each run to the table itself; LDS resolves lanes that hit the same counter.
-// Tables too large for LDS (more than 128 classes) go to the result directly, one addition
-// per distinct pair of a wavefront and pixel slot.
-constexpr int CONF_THREADS = 1024;
-constexpr int CONF_PER_T = 16;                       // pixels of one thread per trip
-constexpr int CONF_MAX_BLOCKS = 256;
 template <bool LDS_TABLE>
 __global__ void __launch_bounds__(CONF_THREADS)
 k_confusion(const uint8_t* __restrict__ pred, const int32_t* __restrict__ labels, long long P, int C,
@@ -610,7 +627,12 @@ k_confusion(const uint8_t* __restrict__ pred, const int32_t* __restrict__ labels
             for (int i = 0; i < CONF_PER_T; ++i) {
                 const int y = (int)lv[i >> 2][i & 3];
                 const int q = (int)((pv[i >> 2] >> (8 * (i & 3))) & 0xFFu);
-                bins[i] = (y != ignore && y >= 0 && y < C && q < C) ? y * C + q : -1;
+                bins[i] = ((unsigned)y < (unsigned)C && q < C) ? y * C + q : -1;
+            }
+            if ((unsigned)ignore < (unsigned)C) {        // (an ignored label that is also a class index)
+#pragma unroll
+                for (int i = 0; i < CONF_PER_T; ++i)
+                    if ((int)lv[i >> 2][i & 3] == ignore) bins[i] = -1;
             }
         } else {
 #pragma unroll
@@ -663,10 +685,16 @@ k_confusion(const uint8_t* __restrict__ pred, const int32_t* __restrict__ labels
     }
 }
 
+__global__ void __launch_bounds__(256) k_clear_counts(unsigned long long* conf, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) conf[i] = 0ull;
+}
+
 void confusion_and_miou(Ctx& c, const uint8_t* pred, const int32_t* labels, long long P, int C, int ignore,
                         long long* conf, double* miou)
 {
-    zero_u64(c, (unsigned long long*)conf, (size_t)C * C);
+    ST_LAUNCH(c, "zero_fill", k_clear_counts, dim3(cdiv(C * C, 256)), dim3(256), 0, (unsigned long long*)conf, C * C);
     const int blocks = std::min(std::max(cdiv(P, CONF_THREADS * CONF_PER_T), 1), CONF_MAX_BLOCKS);
     const size_t lds = (size_t)C * C * 4;
     if (lds <= 64 * 1024)

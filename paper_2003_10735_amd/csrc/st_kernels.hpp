@@ -32,7 +32,6 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
     }
 }
 void zero_regions(Ctx& c, const ZeroList& z);
-void zero_u64(Ctx& c, unsigned long long* p, size_t n);
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
 
 // k_conv_f32.hip -- the float32 path's kernels
