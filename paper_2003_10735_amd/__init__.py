@@ -239,14 +239,14 @@ def st_head_forward(desc: HeadDesc, features, head_params, logits_lowres=None, p
     """features [n,c_in,h,w] (float32 or bfloat16 cuda tensor), head_params float32 [num_params]
     ([n, num_params] for a grouped descriptor).  Fills logits_lowres [n,C,h,w] float32 and/or pred [n,8h,8w] uint8 when given."""
     ws = workspace if workspace is not None else new_workspace(desc, features.device)
-    _check(lib().st_head_forward(desc._ref(), features.data_ptr(), head_params.data_ptr(), _addr(logits_lowres), _addr(pred),
-                                 ws.data_ptr(), _stream(stream)), "st_head_forward")
+    _check(lib().st_head_forward(desc._ref(), _addr(features), _addr(head_params), _addr(logits_lowres), _addr(pred),
+                                 _addr(ws), _stream(stream)), "st_head_forward")
     return logits_lowres, pred
 
 
 def st_head_forward_noalloc(desc: HeadDesc, features, head_params, logits_lowres=None, pred=None, stream=None):
     """st_head_forward on the library's built-in scratch: no workspace argument, no allocation."""
-    _check(lib().st_head_forward_noalloc(desc._ref(), features.data_ptr(), head_params.data_ptr(), _addr(logits_lowres),
+    _check(lib().st_head_forward_noalloc(desc._ref(), _addr(features), _addr(head_params), _addr(logits_lowres),
                                          _addr(pred), _stream(stream)), "st_head_forward_noalloc")
     return logits_lowres, pred
 
@@ -297,8 +297,8 @@ def st_partial_distill(desc: HeadDesc, features, teacher_labels, head_params, st
             o.adam_t0 = int(adam.get("t0", 0))
         opts = C.byref(o)
     res = StDistillResult(_addr(losses), _addr(mious), _addr(confusion), _addr(pred))
-    _check(lib().st_partial_distill(desc._ref(), features.data_ptr(), teacher_labels.data_ptr(), head_params.data_ptr(), steps, lr,
-                                    opts, C.byref(res), ws.data_ptr(), _stream(stream)), "st_partial_distill")
+    _check(lib().st_partial_distill(desc._ref(), _addr(features), _addr(teacher_labels), _addr(head_params), steps, lr,
+                                    opts, C.byref(res), _addr(ws), _stream(stream)), "st_partial_distill")
     ret = DistillReturn((res.steps_taken, res.best_metric if threshold > 0.0 else None))
     ret.first_metric = res.first_metric if threshold > 0.0 else None
     return ret
@@ -313,7 +313,7 @@ def st_miou(pred, labels, n_classes: int, ignore_index: int = -1, confusion=None
             confusion = torch.empty((n_classes, n_classes), dtype=torch.int64, device=pred.device)
         if miou is None:
             miou = torch.empty(1, dtype=torch.float64, device=pred.device)
-    _check(lib().st_miou(pred.data_ptr(), labels.data_ptr(), pred.numel(), n_classes, ignore_index,
+    _check(lib().st_miou(_addr(pred), _addr(labels), pred.numel(), n_classes, ignore_index,
                          confusion.data_ptr(), miou.data_ptr(), _stream(stream)), "st_miou")
     return confusion, miou
 

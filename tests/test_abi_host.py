@@ -146,3 +146,20 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_missing_tensors_are_the_librarys_error():
+    """A tensor that is not there is refused by the library (status of a null pointer), through every binding."""
+    import types
+    import torch
+    d, stream = good(), types.SimpleNamespace(cuda_stream=0)
+    t = torch.zeros(256)
+    for call in (lambda: st.st_head_forward(d, None, t, workspace=t, stream=stream),
+                 lambda: st.st_head_forward(d, t, None, workspace=t, stream=stream),
+                 lambda: st.st_head_forward_noalloc(d, None, t, stream=stream),
+                 lambda: st.st_partial_distill(d, None, t, t, 1, 0.1, workspace=t, stream=stream),
+                 lambda: st.st_partial_distill(d, t, None, t, 1, 0.1, workspace=t, stream=stream),
+                 lambda: st.st_miou(t, None, 9, confusion=t, miou=t, stream=stream)):
+        with pytest.raises(st.StError) as e:
+            call()
+        assert e.value.status == st.ST_ERR_NULL
