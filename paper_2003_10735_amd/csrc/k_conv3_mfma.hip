@@ -26,10 +26,10 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // and padded to 32 classes from the optimiser kernel ([channel][32]), so its MFMA A fragments are
 // 16-byte loads straight from memory.
 // Then
-//   wavefront w computes da2 for positions 32 (w % 2) .. +31 and half of the channel tiles
-//   (K = classes),
-//   wavefront w computes dW3 for channel tiles w, w+4, ..  over all positions (K = positions),
-// so no sum crosses wavefronts.  Partial dW3 / db3 go to one slot per block; the optimiser
+//   wavefront w < 4 computes da2 for positions 32 (w % 2) .. +31 and half of the channel tiles
+//   (K = classes), and db3 for eight classes,
+//   wavefront 4 + w computes dW3 for channel tiles w, w+4, ..  over all positions (K = positions),
+// so no sum of theirs crosses wavefronts and the two products run side by side.  Partial dW3 / db3 go to one slot per block; the optimiser
 // kernel adds the slots in order (only the rows of real classes are stored).  The block's a2
 // tile is loaded once, position-major, before the first barrier (its latency overlaps the
 // staging of g) and kept in LDS: the ReLU mask is read from it directly, the dW3 operand
@@ -37,8 +37,12 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // A block takes C2 channels of the layer: all of them, or (RUNS, heads with more than 256) the run of
 // channels that blockIdx.y names, each run forming g for itself.
 // The work per position is small and every phase is a chain of dependent memory round trips, so
-// the block is kept small: the grid then covers the whole chip and each chain is short.
-constexpr int C3B_BP = 64;
+// the block is kept small: the grid then covers the whole chip and each chain is short.  512 threads
+// halve a thread's share of the gather and let the two products (and db3, once a serial loop over the
+// positions in one wavefront) run side by side.  Against 256 threads that did one after the other, 8-step
+// key frame at 90 x 160 cells, C2 = 128: 715 -> 704 us; with loop exits 797 -> 783; on larger grids, where
+// other blocks fill the gaps, 0.1 to 0.6 % of a call.
+constexpr int C3B_BP = 64, C3B_NT = 512;
 
 // (one or two wavefronts per SIMD are all this kernel asks for: said explicitly, because the
 //  compiler otherwise keeps to 128 registers and then issues the slot loads one at a time)
@@ -48,7 +52,7 @@ constexpr int C3B_BP = 64;
 // metric for the host) instead -- it touches nothing this kernel reads or writes, and riding
 // along saves that pass a launch of its own.
 template <int C2, bool RUNS, bool FIN>
-__global__ void __launch_bounds__(256, 1)
+__global__ void __launch_bounds__(C3B_NT, 1)
 k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
                  const unsigned long long* __restrict__ n_valid, int CP, LossTiling lt,
                  const bf16* __restrict__ a2,
@@ -56,10 +60,10 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
                  float* __restrict__ part, Geo g, int PPT, int guard, int grp_blocks, int main_blocks, FinishArgs fin)
 {
     if (FIN && (int)blockIdx.x >= main_blocks) {
-        if (!RUNS || blockIdx.y == 0) finish_block<true>(fin, (int)blockIdx.x - main_blocks, 0);
+        if (!RUNS || blockIdx.y == 0) finish_block<true, C3B_NT>(fin, (int)blockIdx.x - main_blocks, 0);
         return;
     }
-    constexpr int BP = C3B_BP;
+    constexpr int BP = C3B_BP, NT = C3B_NT;
     constexpr int OT = C2 / 32;            // channel tiles
     constexpr int OH = OT / 2;             // da2 channel tiles per wavefront
     constexpr int DW = (OT + 3) / 4;       // dW3 channel tiles per wavefront
@@ -73,7 +77,8 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     __shared__ __attribute__((aligned(16))) bf16 Os[BP * OLD];      // da2 tile [position][channel]
     __shared__ __attribute__((aligned(16))) bf16 A2s[BP * OLD];     // a2 tile [position][channel]
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave & 3;   // half: place among the four of its role
     const int l32 = lane & 31, lhi = lane >> 5;
     const int PP = g.padded_positions(), frame = g.Hp * g.Wp;
     // several heads: blocks are counted per frame (grp_blocks each), so that no block mixes the
@@ -89,17 +94,18 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     //      reduction runs over the positions and therefore wants 8 consecutive positions of one
     //      channel per lane -- the transposing LDS read hands out exactly that, so the layer-2
     //      convolution need not leave a channel-major copy of a2 behind.
-    const int pm = (wave & 1) * 32 + l32;          // position (inside the block) for the da2 part
-    const int t0 = (wave >> 1) * OH;               // first channel tile of the da2 part
-    constexpr int A2_CHUNKS = BP * (C2 / 8) / 256; // 16-byte chunks of the tile per thread
+    const int pm = (half & 1) * 32 + l32;          // position (inside the block) for the da2 part
+    const int t0 = (half >> 1) * OH;               // first channel tile of the da2 part
+    constexpr int A2_CHUNKS = BP * (C2 / 8) / NT;  // 16-byte chunks of the tile per thread
     u32x4 a2v[A2_CHUNKS];
 #pragma unroll
     for (int k = 0; k < A2_CHUNKS; ++k) {
-        const int q = tid + 256 * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
+        const int q = tid + NT * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
         // (rows past the last position repeat it: d loss / d z is zero there)
         a2v[k] = *(const u32x4*)(a2 + (size_t)min(m0 + p, PP - 1) * k2 + ch0 + part8 * 8);
     }
     // W3^T fragments of this wavefront's da2 tiles: rows = channels, k = 16 classes per step
+    // (the dW3 wavefronts load them too: a load under a branch would be waited for at the join)
     bf16x8 wfr[OH][2];
 #pragma unroll
     for (int t = 0; t < OH; ++t)
@@ -107,8 +113,8 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
         for (int ks = 0; ks < 2; ++ks) wfr[t][ks] = *(const bf16x8*)(W3T + ((size_t)(t0 + t) * 32 + l32) * 32 + ks * 16 + lhi * 8);
     // ---- stage g (both orientations) and W3^T
     {
-        const int p = tid & (BP - 1), cq = tid / BP;     // this thread: one position, every fourth class
-        constexpr int NQ = 256 / BP;
+        const int p = tid & (BP - 1), cq = tid / BP;     // this thread: one position, every eighth class
+        constexpr int NQ = NT / BP;
         float v[32 / NQ];
         gather_g<32 / NQ, NQ>(slots, T, n_valid[head], CP, lt, g, m0 + p, m_end, cq, v);
 #pragma unroll
@@ -121,87 +127,94 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     }
 #pragma unroll
     for (int k = 0; k < A2_CHUNKS; ++k) {
-        const int q = tid + 256 * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
+        const int q = tid + NT * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
         *(u32x4*)(A2s + p * OLD + part8 * 8) = a2v[k];
     }
     __syncthreads();
 
-    // ReLU mask of this lane's position
-    bf16x4 mk[OH][4];
-#pragma unroll
-    for (int t = 0; t < OH; ++t)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) mk[t][rg] = *(const bf16x4*)(A2s + pm * OLD + (t0 + t) * 32 + rg * 8 + lhi * 4);
-
-    // ---- da2: D[o][pos] = sum_c W3T[o][c] * g[c][pos], two K steps cover 32 classes
-    {
-        f32x16 acc[OH];
-#pragma unroll
-        for (int t = 0; t < OH; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 gf = *(const bf16x8*)(g_pc + pm * GC + ks * 16 + lhi * 8);
-#pragma unroll
-            for (int t = 0; t < OH; ++t) {
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr[t][ks], gf, acc[t], 0, 0, 0);
-            }
-        }
-        // (a2 is zero on the border, and g is zero there too: border rows of da2 come out zero)
-#pragma unroll
-        for (int t = 0; t < OH; ++t)
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                bf16x4 ov;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ov[e] = (bf16)((float)mk[t][rg][e] > 0.f ? acc[t][rg * 4 + e] : 0.f);
-                *(bf16x4*)(Os + pm * OLD + (t0 + t) * 32 + rg * 8 + lhi * 4) = ov;
-            }
-    }
-
-    // ---- dW3: D[c][o] = sum_pos g[c][pos] * a2[pos][o] over this block's positions
     float* slot = part + (size_t)blockIdx.x * (32 * k2 + 32);
+    if (wave < 4) {
+        // ReLU mask of this lane's position
+        bf16x4 mk[OH][4];
 #pragma unroll
-    for (int d = 0; d < DW; ++d) {
-        const int t = wave + 4 * d;
-        if (t < OT) {
-            f32x16 acc;
+        for (int t = 0; t < OH; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            for (int rg = 0; rg < 4; ++rg) mk[t][rg] = *(const bf16x4*)(A2s + pm * OLD + (t0 + t) * 32 + rg * 8 + lhi * 4);
+
+        // ---- da2: D[o][pos] = sum_c W3T[o][c] * g[c][pos], two K steps cover 32 classes
+        {
+            f32x16 acc[OH];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 gf = *(const bf16x8*)(g_cp + l32 * GP + ks * 16 + lhi * 8);
-                // B fragment: lane = channel l32 of tile t, positions 16 ks + 8 lhi .. + 7.  In a
-                // group of 16 lanes, lane r names the row (position r / 4, channels 4 (r % 4) .. + 3)
-                // and lane i receives channel i of positions 0 .. 3 of the group's rows: two reads.
-                const bf16* row = A2s + (ks * 16 + lhi * 8 + ((lane & 15) >> 2)) * OLD + t * 32 + (lane & 16) + 4 * (lane & 3);
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * OLD));
-                const s16x8 xs = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf, __builtin_bit_cast(bf16x8, xs), acc, 0, 0, 0);
+            for (int t = 0; t < OH; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const bf16x8 gf = *(const bf16x8*)(g_pc + pm * GC + ks * 16 + lhi * 8);
+#pragma unroll
+                for (int t = 0; t < OH; ++t) {
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr[t][ks], gf, acc[t], 0, 0, 0);
+                }
             }
+            // (a2 is zero on the border, and g is zero there too: border rows of da2 come out zero)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
-                if (c < g.C) slot[c * k2 + ch0 + t * 32 + l32] = acc[r];    // (rows beyond the classes are never read)
+            for (int t = 0; t < OH; ++t)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    bf16x4 ov;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ov[e] = (bf16)((float)mk[t][rg][e] > 0.f ? acc[t][rg * 4 + e] : 0.f);
+                    *(bf16x4*)(Os + pm * OLD + (t0 + t) * 32 + rg * 8 + lhi * 4) = ov;
+                }
+        }
+        // ---- db3: eight threads per class, eight positions each
+        if (ch0 == 0) {
+            const int c = tid >> 3, q = tid & 7;
+            const bf16x8 gv = *(const bf16x8*)(g_cp + c * GP + q * 8);
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += (float)gv[e];
+            s += __shfl_xor(s, 1, 64); s += __shfl_xor(s, 2, 64); s += __shfl_xor(s, 4, 64);
+            if (q == 0 && c < g.C) slot[32 * k2 + c] = s;
+        }
+    } else {
+        // ---- dW3: D[c][o] = sum_pos g[c][pos] * a2[pos][o] over this block's positions
+#pragma unroll
+        for (int d = 0; d < DW; ++d) {
+            const int t = half + 4 * d;
+            if (t < OT) {
+                f32x16 acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 gf = *(const bf16x8*)(g_cp + l32 * GP + ks * 16 + lhi * 8);
+                    // B fragment: lane = channel l32 of tile t, positions 16 ks + 8 lhi .. + 7.  In a
+                    // group of 16 lanes, lane r names the row (position r / 4, channels 4 (r % 4) .. + 3)
+                    // and lane i receives channel i of positions 0 .. 3 of the group's rows: two reads.
+                    const bf16* row = A2s + (ks * 16 + lhi * 8 + ((lane & 15) >> 2)) * OLD + t * 32 + (lane & 16) + 4 * (lane & 3);
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * OLD));
+                    const s16x8 xs = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf, __builtin_bit_cast(bf16x8, xs), acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
+                    if (c < g.C) slot[c * k2 + ch0 + t * 32 + l32] = acc[r];    // (rows beyond the classes are never read)
+                }
             }
         }
-    }
-    if (tid < 32 && ch0 == 0) {
-        float s = 0.f;
-        for (int p = 0; p < BP; ++p) s += (float)g_cp[tid * GP + p];
-        if (tid < g.C) slot[32 * k2 + tid] = s;
     }
     __syncthreads();
 
     // ---- write the da2 tile: position-major rows and channel-major 8-position groups
-    for (int q = tid; q < BP * (C2 / 8); q += 256) {
+    for (int q = tid; q < BP * (C2 / 8); q += NT) {
         const int p = q / (C2 / 8), part8 = q % (C2 / 8);
         if (m0 + p < m_end)
             *(uint4*)(da2 + (size_t)(m0 + p) * k2 + ch0 + part8 * 8) = *(const uint4*)(Os + p * OLD + part8 * 8);
     }
-    for (int q = tid; q < (BP / 8) * C2; q += 256) {
+    for (int q = tid; q < (BP / 8) * C2; q += NT) {
         const int o = q % C2, pg = q / C2;
         if (m0 + pg * 8 >= m_end) continue;
         bf16x8 ov;
@@ -235,10 +248,10 @@ void conv3_bwd_mfma(Ctx& c, const Plan& p, const float* slots, const float* T,
 #define ST_C3B(C2, RUNS)                                                                                       \
     do {                                                                                                       \
         if (finish)                                                                                            \
-            ST_LAUNCH(c, "conv3_bwd_mfma+finish_pass", (k_conv3_bwd_mfma<C2, RUNS, true>), grid, dim3(256), 0, slots, T, \
+            ST_LAUNCH(c, "conv3_bwd_mfma+finish_pass", (k_conv3_bwd_mfma<C2, RUNS, true>), grid, dim3(C3B_NT), 0, slots, T, \
                       n_valid, CP, p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin); \
         else                                                                                                   \
-            ST_LAUNCH(c, "conv3_bwd_mfma", (k_conv3_bwd_mfma<C2, RUNS, false>), grid, dim3(256), 0, slots, T, n_valid, CP, \
+            ST_LAUNCH(c, "conv3_bwd_mfma", (k_conv3_bwd_mfma<C2, RUNS, false>), grid, dim3(C3B_NT), 0, slots, T, n_valid, CP, \
                       p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin);    \
     } while (0)
     if (run == g.k2) {

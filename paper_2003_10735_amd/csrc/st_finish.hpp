@@ -16,8 +16,9 @@ struct FinishArgs {
     double* miou_c; unsigned long long* token_c; unsigned long long token;
 };
 
-// (EE: the early-exit form's extra -- the host copy of the metric -- is compiled in)
-template <bool EE>
+// (EE: the early-exit form's extra -- the host copy of the metric -- is compiled in; NT: threads of the
+// block, 256 of which add the tile losses whatever NT is, so that the order of the sum is one)
+template <bool EE, int NT = 256>
 __device__ void finish_block(const FinishArgs& f, int block, int head)
 {
     __shared__ double part[256];
@@ -26,11 +27,13 @@ __device__ void finish_block(const FinishArgs& f, int block, int head)
     __shared__ int present[32];
     const int tid = threadIdx.x;
     if (block == f.fph) {
-        double acc = 0.0;
-        const int per = (f.pph + 255) / 256;
-        const float* lp = f.loss_part + (size_t)head * f.pph;
-        for (int i = tid * per; i < min(f.pph, (tid + 1) * per); ++i) acc += (double)lp[i];
-        part[tid] = acc;
+        if (tid < 256) {
+            double acc = 0.0;
+            const int per = (f.pph + 255) / 256;
+            const float* lp = f.loss_part + (size_t)head * f.pph;
+            for (int i = tid * per; i < min(f.pph, (tid + 1) * per); ++i) acc += (double)lp[i];
+            part[tid] = acc;
+        }
         __syncthreads();
         for (int s = 128; s > 0; s >>= 1) {
             if (tid < s) part[tid] += part[tid + s];
@@ -45,7 +48,7 @@ __device__ void finish_block(const FinishArgs& f, int block, int head)
     block += head * f.fph;      // the frame
     const int C = f.C;
     unsigned long long* cf = f.conf + (size_t)block * C * C;
-    for (int i = tid; i < C * C; i += 256) {
+    for (int i = tid; i < C * C; i += NT) {
         const unsigned long long v = cf[i];
         cl[i] = v;
         if (f.conf_out) f.conf_out[(size_t)block * C * C + i] = (long long)v;
