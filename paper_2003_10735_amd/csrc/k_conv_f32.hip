@@ -11,6 +11,8 @@
 //   * weights lie in the matching fragment order (wfrag32_index), one contiguous kilobyte per
 //     32 rows x 8 channels of a tap.
 // So eight channels of one tap cost two coalesced 16-byte loads per lane and four MFMAs.
+// Against a plain LDS-tiled GEMM on the vector units: 68 x 120 cells, 256 -> 128 -> 128, a 4-step call
+// 4.62 -> 0.90 ms; 16 x 16 cells, 64 -> 64 -> 64, 1.52 -> 0.20 ms.
 #include <algorithm>
 
 #include "st_gather.hpp"
@@ -22,7 +24,7 @@ namespace st {
 
 // ------------------------------------------------------------------ 3x3 convolution
 //   out[p][n] = epi( sum_{tap, c} X[p + shift(tap)][c] * W[n][tap][c] )        p: padded positions
-// A block owns 32 J positions x 32 output channels; its KG wavefronts split the reduction (taps x
+// A block owns 32 positions x 32 output channels; its KG wavefronts split the reduction (taps x
 // groups of eight channels) into contiguous runs and are added through LDS in ascending order.  Small
 // tiles, because a frame has few of them: 68 x 120 cells and 128 channels make 1120, 4.4 per compute
 // unit, where 64 x 64 tiles would make 280 and leave half the chip idle in the second round.  KG grows
@@ -42,23 +44,21 @@ struct Conv32Args {
 
 constexpr int C32_DEPTH = 4;    // operand sets on their way per wavefront: 3 x 256 cycles of MFMAs ahead
 
-template <int EPI, int KG, int J>
+template <int EPI, int KG>
 __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
 {
-    extern __shared__ __attribute__((aligned(16))) float red[];    // [KG][J][4 register groups][64 lanes][4]
+    extern __shared__ __attribute__((aligned(16))) float red[];    // [KG][4 register groups][64 lanes][4]
     // (consecutive blocks go to different XCDs: every XCD gets a contiguous run of position tiles)
     const int tile = (blockIdx.x % 8) * a.tiles_per_xcd + blockIdx.x / 8;
     if ((int)(blockIdx.x / 8) >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
     const int mt = tile / a.n_tiles, nt = tile % a.n_tiles;
-    const int m0 = mt * 32 * J;
+    const int m0 = mt * 32;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
 
-    f32x16 acc[J];
+    f32x16 acc;
 #pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
     const int total = 9 * a.G, per = (total + KG - 1) / KG;
     const int i0 = wave * per, i1 = min(total, i0 + per);
@@ -68,12 +68,12 @@ __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
         const unsigned wlane = lane * 4, xlane = l32 * 8 + lhi * 4;
         int tap = i0 / a.G, g = i0 - tap * a.G, li = i0;
         const float* xp = xb + ((ptrdiff_t)g * a.PPT + (tap / 3 - 1) * a.Wp + (tap % 3 - 1)) * 8;
-        f32x4 ra[C32_DEPTH], rb[C32_DEPTH][J];
+        f32x4 ra[C32_DEPTH], rb[C32_DEPTH];
         // (past the end of the run the last item is loaded again and not used)
 #define C32_LOAD(S)                                                                                \
         {                                                                                          \
             ra[S] = *(const f32x4*)(wp + wlane);                                                   \
-            _Pragma("unroll") for (int j = 0; j < J; ++j) rb[S][j] = *(const f32x4*)(xp + xlane + j * 256); \
+            rb[S] = *(const f32x4*)(xp + xlane);                                                   \
             if (++li < i1) {                                                                       \
                 wp += 256;                                                                         \
                 if (++g == a.G) {                                                                  \
@@ -85,8 +85,7 @@ __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
 #define C32_MMA(S)                                                                                 \
         {                                                                                          \
             _Pragma("unroll") for (int e = 0; e < 4; ++e)                                          \
-            _Pragma("unroll") for (int j = 0; j < J; ++j)                                          \
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[S][e], rb[S][j][e], acc[j], 0, 0, 0); \
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[S][e], rb[S][e], acc, 0, 0, 0);      \
         }
 #pragma unroll
         for (int d = 0; d < C32_DEPTH; ++d) C32_LOAD(d)
@@ -102,71 +101,65 @@ __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
 #undef C32_MMA
     }
 #pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-        for (int rq = 0; rq < 4; ++rq)
-            *(f32x4*)(red + (((wave * J + j) * 4 + rq) * 64 + lane) * 4) =
-                f32x4{acc[j][rq * 4], acc[j][rq * 4 + 1], acc[j][rq * 4 + 2], acc[j][rq * 4 + 3]};
+    for (int rq = 0; rq < 4; ++rq)
+        *(f32x4*)(red + ((wave * 4 + rq) * 64 + lane) * 4) = f32x4{acc[rq * 4], acc[rq * 4 + 1], acc[rq * 4 + 2], acc[rq * 4 + 3]};
     __syncthreads();
 
     // wavefront rq < 4 finishes channels 8 rq .. + 7 of the tile: a lane holds 4 channels of one position
     const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;
     const int frame = a.Hp * a.Wp;
+    const int mp = m0 + l32;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (rq < 4) {
+        const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
+        const bool inside = mp < a.PP && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int mp = m0 + j * 32 + l32;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (rq < 4) {
-            const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
-            const bool inside = mp < a.PP && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
+        for (int k = 0; k < KG; ++k) v += *(const f32x4*)(red + ((k * 4 + rq) * 64 + lane) * 4);
+        const size_t at = ((size_t)(nt * 4 + rq) * a.PPT + a.guard + mp) * 8 + lhi * 4;
+        const bool stored = nt * 4 + rq < a.GY && mp < a.PP;
+        if (EPI == 0 || EPI == 2) {
+            const f32x4 b = *(const f32x4*)(a.bias + ch);
 #pragma unroll
-            for (int k = 0; k < KG; ++k) v += *(const f32x4*)(red + (((k * J + j) * 4 + rq) * 64 + lane) * 4);
-            const size_t at = ((size_t)(nt * 4 + rq) * a.PPT + a.guard + mp) * 8 + lhi * 4;
-            const bool stored = nt * 4 + rq < a.GY && mp < a.PP;
-            if (EPI == 0 || EPI == 2) {
-                const f32x4 b = *(const f32x4*)(a.bias + ch);
+            for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + b[e], 0.f) : 0.f;
+        } else if (EPI == 1) {
+            f32x4 m = {0.f, 0.f, 0.f, 0.f};
+            if (stored) m = *(const f32x4*)(a.mask + at);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + b[e], 0.f) : 0.f;
-            } else if (EPI == 1) {
-                f32x4 m = {0.f, 0.f, 0.f, 0.f};
-                if (stored) m = *(const f32x4*)(a.mask + at);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = inside && m[e] > 0.f ? v[e] : 0.f;
-            }
-            if (EPI == 3) {
-                if (inside) {
-                    float* dst = a.dense + (((size_t)img * a.dense_c + ch) * a.h + (y - 1)) * a.w + (x - 1);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (ch + e < a.dense_c) dst[(size_t)e * a.h * a.w] = v[e];
-                }
-            } else if (stored && a.Y) *(f32x4*)(a.Y + at) = v;
+            for (int e = 0; e < 4; ++e) v[e] = inside && m[e] > 0.f ? v[e] : 0.f;
         }
-        if (EPI == 2) {
-            // the classifier rides along: what this lane holds is the B operand of four MFMAs against
-            // W3 (rows = classes, k = the 8 channels of this wavefront); the four wavefronts' sums
-            // meet in LDS.  (All shares of the logits: one per 32 channels.)
-            __syncthreads();       // the partial sums are read
-            if (rq < 4) {
-                f32x16 z;
+        if (EPI == 3) {
+            if (inside) {
+                float* dst = a.dense + (((size_t)img * a.dense_c + ch) * a.h + (y - 1)) * a.w + (x - 1);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) z[r] = 0.f;
-                const f32x4 w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], v[e], z, 0, 0, 0);
-                float* zr = red + (size_t)(J > 1 ? KG * J * 1024 : 0);       // (J > 1: behind the partial sums still needed)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *(f32x4*)(zr + ((rq * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
+                for (int e = 0; e < 4; ++e)
+                    if (ch + e < a.dense_c) dst[(size_t)e * a.h * a.w] = v[e];
             }
-            __syncthreads();
-            if (rq < 4 && mp < a.PP && rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
-                const float* zr = red + (size_t)(J > 1 ? KG * J * 1024 : 0);
-                f32x4 s = *(const f32x4*)(zr + (rq * 64 + lane) * 4);
+        } else if (stored && a.Y) *(f32x4*)(a.Y + at) = v;
+    }
+    if (EPI == 2) {
+        // the classifier rides along: what this lane holds is the B operand of four MFMAs against
+        // W3 (rows = classes, k = the 8 channels of this wavefront); the four wavefronts' sums
+        // meet in LDS.  (All shares of the logits: one per 32 channels.)
+        __syncthreads();       // the partial sums are read
+        if (rq < 4) {
+            f32x16 z;
 #pragma unroll
-                for (int k = 1; k < 4; ++k) s += *(const f32x4*)(zr + ((k * 4 + rq) * 64 + lane) * 4);
-                *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = s;
-            }
+            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+            const f32x4 w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], v[e], z, 0, 0, 0);
+            float* zr = red;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4*)(zr + ((rq * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
+        }
+        __syncthreads();
+        if (rq < 4 && mp < a.PP && rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
+            const float* zr = red;
+            f32x4 s = *(const f32x4*)(zr + (rq * 64 + lane) * 4);
+#pragma unroll
+            for (int k = 1; k < 4; ++k) s += *(const f32x4*)(zr + ((k * 4 + rq) * 64 + lane) * 4);
+            *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = s;
         }
     }
 }
@@ -174,10 +167,9 @@ __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
 template <int EPI, int KG>
 static void conv_f32_launch(Ctx& c, const char* name, const Conv32Args& a, int blocks)
 {
-    constexpr int J = 1;
-    const size_t smem = (size_t)KG * J * 1024 * sizeof(float);
-    ensure_dynamic_lds((const void*)k_conv3x3_f32<EPI, KG, J>, smem);
-    ST_LAUNCH(c, name, (k_conv3x3_f32<EPI, KG, J>), dim3(blocks), dim3(64 * KG), smem, a);
+    const size_t smem = (size_t)KG * 1024 * sizeof(float);
+    ensure_dynamic_lds((const void*)k_conv3x3_f32<EPI, KG>, smem);
+    ST_LAUNCH(c, name, (k_conv3x3_f32<EPI, KG>), dim3(blocks), dim3(64 * KG), smem, a);
 }
 
 // cin, cout: channels of the layer as run here (exchanged for a data gradient)
@@ -307,6 +299,9 @@ static Wgrad32Args wgrad_f32_args(const Plan& p, const float* dY, const float* X
 //   da2[p][o] = [a2[p][o] > 0] * sum_c g[c][p] * W3[c][o];   dW3, db3: one slot per block (the optimiser kernel adds them)
 // A block of 256 threads takes 64 padded positions.  Bound by its chain of dependent memory round
 // trips, like the bfloat16 kernel of the same layer.
+// (Four wavefronts for da2 and four for dW3 side by side, as there: without prefetching what a role reads,
+// 16 x 16 cells 203 -> 208 us and 68 x 120 cells 901 -> 911 us a call; with it 203 -> 197 and 900 -> 893, but at
+// 204 registers, one block per compute unit.)
 constexpr int B32_BP = 64;
 
 __global__ void __launch_bounds__(256)
