@@ -72,7 +72,10 @@ enum { ST_COMPUTE_F32 = 0, ST_COMPUTE_BF16 = 1 }; /* st_head_desc.compute */
  *   matrix cores; master weights, optimiser arithmetic, logits, loss and weight gradients stay
  *   float32.  (Channel counts that are no multiples of 64 are padded with zeros internally.)
  * Limits: upscale == 8; 2 <= n_classes <= 32; labels outside [0, n_classes) are skipped like
- * ignore_index (they count neither in the loss nor in the metric).
+ * ignore_index (they count neither in the loss nor in the metric).  What the kernels' 32-bit
+ * indices cannot reach is refused (ST_ERR_SHAPE): 2^31 pixels, 2^31 activations or 2^28 weights of
+ * a layer; bfloat16 path: also 2^30 weights counted with the padding, and a frame wider than about
+ * 1.6 * 10^7 cells.
  *
  * grouped = 0: one head, trained on a mini-batch of n frames (one loss over all of them).
  * grouped = 1: n clients in one call (the server of Algorithm 3 serves one student per client):

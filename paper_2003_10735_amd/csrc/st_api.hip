@@ -98,6 +98,17 @@ static int validate(const st_head_desc* d)
     if ((long long)d->n * d->h * d->w * UP * UP >= (1ll << 31)) return ST_ERR_SHAPE;
     if ((long long)d->c1 * d->c_in * 9 >= (1ll << 28) || (long long)d->c2 * d->c1 * 9 >= (1ll << 28))
         return ST_ERR_SHAPE;
+    if (d->compute == ST_COMPUTE_BF16) {
+        // the matrix-core kernels address the padded weights and a wavefront's share of the positions with
+        // 32-bit byte offsets
+        const Geo g = make_geo(*d);
+        if ((long long)g.k1 * g.ki * 9 >= (1ll << 30) || (long long)g.k2 * g.k1 * 9 >= (1ll << 30)) return ST_ERR_SHAPE;
+        if (wgrad_offset_bytes(g, 1) >= (1ll << 31)) {
+            int s1, s2;
+            wgrad_splits_for(g, true, &s1, &s2);
+            if (wgrad_offset_bytes(g, std::min(s1, s2)) >= (1ll << 31)) return ST_ERR_SHAPE;
+        }
+    }
     if (d->grouped) {
         // one head per frame: matrix-core kernels without padded channels only, and all heads' parameters in 32-bit reach
         if (d->compute != ST_COMPUTE_BF16 || make_geo(*d).padded() || (d->c2 != 64 && d->c2 != 128 && d->c2 != 256)) return ST_ERR_SHAPE;

@@ -72,6 +72,27 @@ def test_grouped_descriptor_sizes_and_limits():
     assert st.st_workspace_bytes(st.HeadDesc(2, 64, 16, 16, 64, 64, 9, grouped=2)) == 0
 
 
+@pytest.mark.parametrize("kw,fits,too_large", [
+    # 64 rows x 9 taps x channels of padded weights, at two bytes: below 2^31 bytes
+    (dict(c_in=1, h=1, w=1, c1=1, c2=1), dict(c_in=1864128), dict(c_in=1864129)),
+    (dict(c_in=1, h=1, w=1, c1=1, c2=1), dict(c1=1864128), dict(c1=1864129)),
+    (dict(c_in=1, h=1, w=1, c1=1, c2=1), dict(c2=1864128), dict(c2=1864129)),
+    # two kernel rows of a frame, 64 bytes a cell, in the weight-gradient kernel
+    (dict(c_in=1, h=1, w=1, c1=1, c2=1), dict(w=16 * 10**6), dict(w=17 * 10**6)),
+])
+def test_sizes_beyond_the_32_bit_offsets_of_the_padded_buffers(kw, fits, too_large):
+    """bfloat16 heads are padded to 64 channels inside: what the kernels' 32-bit byte offsets cannot reach is
+    refused, the last size before that is not, and the float32 path (padded to eight) takes both."""
+    def desc(extra, compute):
+        return st.HeadDesc(**{**dict(n=1, n_classes=2, compute=compute, feat_dtype=compute), **kw, **extra})
+    assert st.st_workspace_bytes(desc(fits, st.ST_COMPUTE_BF16)) > 0
+    d = desc(too_large, st.ST_COMPUTE_BF16)
+    assert st.st_workspace_bytes(d) == 0
+    dummy, cd = C.c_void_p(256), d.c()
+    assert st.lib().st_partial_distill(C.byref(cd), dummy, dummy, dummy, 1, 0.1, None, None, dummy, None) == st.ST_ERR_SHAPE
+    assert st.st_workspace_bytes(desc(too_large, st.ST_COMPUTE_F32)) > 0
+
+
 def test_null_and_argument_errors():
     L = st.lib()
     cd = good().c()
