@@ -336,14 +336,6 @@ void wgrad_splits_for(const Geo& g, bool bf16_path, int* s1_out, int* s2_out)
     *s1_out = best1; *s2_out = best2;
 }
 
-// Bytes that a wavefront's 32-bit offsets span at `splits` position splits: its units, one more on either side,
-// and two kernel rows.
-long long wgrad_offset_bytes(const Geo& g, int splits)
-{
-    const long long units = cdiv(cdiv(g.padded_positions() / g.heads(), 16), splits * 4);
-    return (units + 2) * 1024 + 2ll * (g.Wp / 8) * 512;
-}
-
 static WgradArgs wgrad_args(const Plan& p, const bf16* dYT, const bf16* XT, float* dW, float* db, int cin,
                             int cout, int splits)
 {

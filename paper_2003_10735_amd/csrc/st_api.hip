@@ -80,6 +80,14 @@ void ensure_dynamic_lds(const void* kernel, size_t bytes)
 }
 
 // ------------------------------------------------------------------ validation and plan
+// Bytes that the 32-bit offsets of a wavefront of the bfloat16 weight-gradient kernel span at `splits`
+// position splits: its units, one more on either side, and two kernel rows.
+static long long wgrad_offset_bytes(const Geo& g, int splits)
+{
+    const long long units = cdiv(cdiv(g.padded_positions() / g.heads(), 16), splits * 4);
+    return (units + 2) * 1024 + 2ll * (g.Wp / 8) * 512;
+}
+
 static int validate(const st_head_desc* d)
 {
     if (!d) return ST_ERR_NULL;

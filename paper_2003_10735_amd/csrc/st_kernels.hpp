@@ -42,7 +42,6 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
                   const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, int layer,
                   const bf16* W3q = nullptr, float* zpart = nullptr, float* dense = nullptr);
-long long wgrad_offset_bytes(const Geo& g, int splits);
 void wgrad_splits_for(const Geo& g, bool bf16_path, int* splits1, int* splits2);
 void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, const bf16* da2T,
                    const bf16* a1T, float* grad);
