@@ -200,10 +200,15 @@ int st_head_forward(const st_head_desc* desc, const void* features, const float*
  * results as st_head_forward, but the workspace is a device array built into the library:
  * ST_NOALLOC_MAX_WORKSPACE_MIB MiB per GPU the library runs on, held from the first call on that
  * GPU until the process ends (enough for the 1280x720 head 256 -> 128 -> 128 -> 19, which needs
- * 75 MiB).  The call allocates nothing, on the device or through any library; shapes with
- * st_workspace_bytes(desc) above the limit are refused with ST_ERR_TOO_LARGE before any GPU work
- * (float32 heads, and those with channel counts that are no multiples of 64: only where the
- * buffers of the forward pass alone exceed it).
+ * 75 MiB).  The call allocates nothing, on the device or through any library; shapes that need more are
+ * refused with ST_ERR_TOO_LARGE before any GPU work.  What counts is
+ *   bfloat16 heads with c_in and c1 multiples of 64 and c2 one of 64, 128, 256: st_workspace_bytes(desc),
+ *     but for 4 bytes per cell row and 32 columns of every frame;
+ *   any other head: the buffers of the forward pass on the padded channels and, where those exceed the
+ *     limit too, the activations and logits at the head's own sizes,
+ *     n*h*w*(c1 + c2) elements and n*(h+2)*(w+9)*(n_classes+3) floats at most: such calls run on
+ *     kernels without padding, with the same rounding points (same results up to the order of
+ *     float32 additions; the other calls' results are those of st_head_forward bit for bit).
  * The first call on a device looks the array's address up (hipGetSymbolAddress); make that call
  * outside a capture.  Every call on a GPU uses that GPU's one array: calls that overlap on one
  * GPU (two streams, two threads) race -- serialise them.  The event profile (st_profile_enable)

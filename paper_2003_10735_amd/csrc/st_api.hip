@@ -209,11 +209,12 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.wq3 = take(off, p.bytes_w3);
     p.wq3t = train_take(p.bytes_w3t);
     if (!p.bf16 || g.padded()) { p.bq1 = take(off, rows(g.k1) * 4); p.bq2 = take(off, rows(g.k2) * 4); }
-    p.label_counts = train_take((size_t)label_blocks(g) * 4);
     p.loss_part = train_take((size_t)loss_blocks(g) * 4);
     p.counters = take(off, std::max((size_t)256, heads * 8));   // valid pixels (their weights), one count per head
     p.conf = take(off, (size_t)g.n * g.C * g.C * 8);
     p.scal = take(off, (size_t)g.n * 8);               // per-frame mean IoU of the last pass (double)
+    // (last, and no part of a forward plan: the built-in scratch takes every frame that fits without it)
+    if (kind == PLAN_FULL) p.label_counts = take(off, (size_t)label_blocks(g) * 4);
     p.total = off;
     return p;
 }
@@ -543,14 +544,26 @@ int st_head_forward_noalloc(const st_head_desc* desc, const void* features, cons
     if (v != ST_OK) return v;
     if (!features || !head_params) return ST_ERR_NULL;
     Plan p = plan_of(*desc, PLAN_FORWARD);
-    // (heads whose internal buffers hold padded channels, and float32 ones: what the forward pass
-    //  itself needs is what counts)
-    if (p.total > NOALLOC_SCRATCH_BYTES && (!p.bf16 || p.g.padded())) p = plan_of(*desc, PLAN_COMPACT);
-    if (p.total > NOALLOC_SCRATCH_BYTES) return ST_ERR_TOO_LARGE;
+    // Heads that the matrix-core kernels take without padding and in one run of channels: the whole workspace
+    // counts.  Others, whose buffers are larger than the head itself: what the forward pass needs, on padded
+    // buffers or, where those do not fit, on buffers of the head's own sizes.
+    const bool whole = p.bf16 && !p.g.padded() && (p.g.c2 == 64 || p.g.c2 == 128 || p.g.c2 == 256);
+    bool direct = false;
+    if (p.total > NOALLOC_SCRATCH_BYTES && !whole) {
+        p = plan_of(*desc, PLAN_COMPACT);
+        direct = p.total > NOALLOC_SCRATCH_BYTES && direct_forward_bytes(p.g, p.bf16) <= NOALLOC_SCRATCH_BYTES;
+    }
+    if (p.total > NOALLOC_SCRATCH_BYTES && !direct) return ST_ERR_TOO_LARGE;
     char* ws = nullptr;
     const int sr = scratch_of_current_device(&ws);
     if (sr != ST_OK) return sr;
     // (no event profile here: handing out event pairs may create events)
+    if (direct) {
+        Ctx c{as_stream(stream), ST_OK, true};
+        const ZSrc z = forward_direct(c, p.g, p.bf16, features, desc->feat_dtype, head_params, ws, logits_lowres);
+        loss_pass(c, p.g, z, nullptr, nullptr, nullptr, pred, nullptr, nullptr, nullptr, false);
+        return c.status;
+    }
     return head_forward_launches(desc, p, features, head_params, logits_lowres, pred, ws, stream, true);
 }
 

@@ -67,6 +67,12 @@ struct ZSrc {
 // One more block per head adds up the label blocks' pixel counts (the first pass of a call: the kernels that divide
 // by the number of valid pixels come behind it).
 struct CountSum { const unsigned int* counts; int per_head; unsigned long long* n_valid; };
+
+// k_head_direct.hip -- forward pass on buffers of the head's own sizes (one head only): the logits for
+// loss_pass.  `ws` holds direct_forward_bytes; z: the planar tensor to leave, or null
+size_t direct_forward_bytes(const Geo& g, bool bf16_path);
+ZSrc forward_direct(Ctx& c, const Geo& g, bool bf16_path, const void* features, int feat_dtype, const float* params, char* ws, float* z);
+
 // labels8: the labels as bytes (class, or 255 where the pixel does not count), or null: no loss, prediction only
 void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels8, const uint8_t* pixel_weights,
                const float* T, uint8_t* pred, float* slots, float* loss_part, unsigned long long* conf, bool grad,
