@@ -310,14 +310,17 @@ const char* st_version(void);
 
 /* Byte offsets of the library's internal buffers inside `workspace`, so that a test can look
  * at intermediate tensors after a call.  Offsets are 0 for buffers this shape does not use.  On
- * the bfloat16 path the channels of feat .. da2 are padded with zeros to a multiple of 64; on the
- * float32 path these buffers hold runs of eight channels, [c / 8][position][8]. */
+ * the bfloat16 path the channels of feat .. da2 are padded with zeros to a multiple of 64.  On the
+ * float32 path these buffers hold runs of eight channels, channel c of position p at element
+ * ((c / 8) * pitch + p) * 8 + c % 8 of the given offset, where a run's pitch is n*(h+2)*row_pitch rounded
+ * up to a multiple of 16, plus twice the row_pitch + 258 rounded up to a multiple of 8. */
 typedef struct st_workspace_layout {
     size_t feat;      /* features, position-major [n, h+2, row_pitch, c_in], zero border    */
     size_t a1, a2;    /* activations after ReLU, same layout, c1 / c2 channels              */
     size_t da1, da2;  /* back-propagated gradients (after the ReLU mask), same layout       */
     size_t z;         /* low-resolution logits [n, C, h, w] float32                         */
-    size_t g;         /* d loss / d z        [n, C, h, w] float32                           */
+    size_t g;         /* d loss / d z        [n, C, h, w] float32; float32 path (0 otherwise: the    */
+                      /* bfloat16 path never assembles it)                                   */
     size_t theta;     /* master parameters, internal order (3x3 weights as [o][kh][kw][i])  */
     size_t grad;      /* parameter gradient, internal order, as partial sums: grad_copies   */
                       /* copies grad_stride floats apart (the weight-gradient kernels split  */

@@ -504,8 +504,11 @@ int st_get_workspace_layout(const st_head_desc* desc, st_workspace_layout* out)
     const int v = validate(desc);
     if (v != ST_OK) return v;
     const Plan p = make_plan(*desc);
-    out->feat = p.feat; out->a1 = p.a1; out->a2 = p.a2; out->da1 = p.da1; out->da2 = p.da2;
-    out->z = p.z; out->g = p.gz; out->theta = p.theta; out->grad = p.grad;
+    // (of position 0; float32: the plan's offsets are those of the first guard column)
+    const size_t first = p.bf16 ? 0 : (size_t)p.guard * 32;
+    out->feat = p.feat + first; out->a1 = p.a1 + first; out->a2 = p.a2 + first;
+    out->da1 = p.da1 + first; out->da2 = p.da2 + first;
+    out->z = p.z; out->g = p.bf16 ? 0 : p.gz; out->theta = p.theta; out->grad = p.grad;
     out->elem_size = p.esz; out->total = p.total; out->row_pitch = (size_t)p.g.Wp;
     out->grad_copies = (size_t)p.grad_copies; out->grad_stride = p.grad_stride;
     out->splits[0] = (size_t)p.splits1; out->splits[1] = (size_t)p.splits2; out->splits[2] = 1;

@@ -131,7 +131,7 @@ struct Plan {
     size_t feat, a1, a2, da1, da2;
     size_t featT, a1T, da1T, da2T;        // channel-major copies [C][PPT] for the weight-gradient kernels
     size_t grad3;                         // per-block partials of dW3 / db3
-    size_t z, g_slots, gz, tadj;   // tadj: U^T of the one-hot labels, [n, C, h, w] float32
+    size_t z, g_slots, gz, tadj;   // gz: float32 path (elsewhere room that nothing uses); tadj: U^T of the one-hot labels, [n, C, h, w] float32
     size_t lab8;                   // the labels as bytes, [n, 8h, 8w]: the class, or 255 for a pixel that does not count
     size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution, one per channel tile
     size_t theta, vel, vel2, grad, best;   // vel: velocity or Adam's m; vel2: Adam's v

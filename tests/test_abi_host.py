@@ -207,3 +207,11 @@ def test_what_the_built_in_scratch_takes(shape, fits):
     d = st.HeadDesc(n, c_in, h, w, c1, c2, classes, compute=code, feat_dtype=code).c()
     dummy = C.c_void_p(256)
     assert st.lib().st_head_forward_noalloc(C.byref(d), dummy, dummy, None, None, None) == (st.ST_ERR_NO_DEVICE if fits else st.ST_ERR_TOO_LARGE)
+
+
+def test_layout_names_no_buffer_that_nothing_writes():
+    """d loss / d z is assembled on the float32 path only."""
+    for compute in (st.ST_COMPUTE_F32, st.ST_COMPUTE_BF16):
+        for c in (24, 64):
+            lay = st.st_get_workspace_layout(st.HeadDesc(1, c, 12, 20, c, c, 9, compute=compute, feat_dtype=compute))
+            assert (lay["g"] == 0) == (compute == st.ST_COMPUTE_BF16) and min(lay[k] for k in ("feat", "a1", "a2", "da1", "da2", "z")) > 0

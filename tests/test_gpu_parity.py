@@ -183,6 +183,42 @@ def test_intermediate_tensors_of_the_bf16_path_element_by_element():
     assert zd1.sum() <= z1.sum() + 0.002 * da1.size
 
 
+def test_intermediate_tensors_of_the_f32_path():
+    """The float32 path's activations and back-propagated gradients after one step with a zero learning rate, read back
+    where the header says they lie: runs of eight channels, padded channels and the border zero.  Sums of at
+    most 9 * 33 float32 products: 1e-5 of the largest value."""
+    wl = WL.small_variant(WL.WORKLOADS["tiny"], n=2, c_in=20, h=9, w=21, c1=33, c2=24, n_classes=7, steps=1, lr=0.0, n_sites=9)
+    f, lab, p = inputs(wl)
+    gpu = run_gpu(wl, f, lab, p)
+    lay, ws = gpu["layout"], gpu["workspace"]
+    Hp, Wp = wl.h + 2, lay["row_pitch"]
+    PP = wl.n * Hp * Wp
+    pitch = (PP + 15) // 16 * 16 + 2 * ((Wp + 258 + 7) // 8 * 8)
+
+    def grid(off, C):
+        runs = []
+        for r in range((C + 7) // 8):
+            at = off + 4 * 8 * r * pitch
+            runs.append(ws[at:at + 4 * 8 * PP].view(torch.float32).reshape(wl.n, Hp, Wp, 8).cpu().numpy().astype(np.float64))
+        t = np.concatenate(runs, axis=3)
+        inner = t[:, 1:wl.h + 1, 1:wl.w + 1, :C].transpose(0, 3, 1, 2).copy()
+        t[:, 1:wl.h + 1, 1:wl.w + 1, :C] = 0
+        assert np.abs(t).max() == 0.0
+        return inner
+
+    sl, p64, x = WL.param_slices(wl), p.astype(np.float64), WL.features_as_f64(wl, f)
+    W1, W2, W3 = (p64[sl[k]].reshape(s) for k, s in (("W1", (wl.c1, wl.c_in, 3, 3)), ("W2", (wl.c2, wl.c1, 3, 3)),
+                                                     ("W3", (wl.n_classes, wl.c2, 1, 1))))
+    np.testing.assert_array_equal(grid(lay["feat"], wl.c_in), x)
+    a1 = np.maximum(O.conv_fwd(x, W1, p64[sl["b1"]]), 0.0)
+    a2 = np.maximum(O.conv_fwd(a1, W2, p64[sl["b2"]]), 0.0)
+    _, G, _ = O.softmax_ce(O.upsample8(O.conv_fwd(a2, W3, p64[sl["b3"]])), lab)
+    da2 = O.conv_dgrad(O.upsample8_adjoint(G), W3) * (a2 > 0)
+    da1 = O.conv_dgrad(da2, W2) * (a1 > 0)
+    for name, C, want in (("a1", wl.c1, a1), ("a2", wl.c2, a2), ("da2", wl.c2, da2), ("da1", wl.c1, da1)):
+        assert rel_err(grid(lay[name], C), want) < 1e-5, name
+
+
 @pytest.mark.parametrize("compute", ["f32", "bf16"])
 def test_equal_logits_go_to_the_lowest_class(compute):
     """With a zero classifier every pixel's logits are the biases, exactly: the predicted class
