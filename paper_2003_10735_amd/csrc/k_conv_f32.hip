@@ -1,7 +1,7 @@
 // Float32 path: the head's contractions on the matrix cores at full float32 precision
 // (v_mfma_f32_32x32x2_f32: float32 operands, float32 accumulation, each product and sum rounded once).
 //
-// One such instruction takes 64 cycles for 4096 multiply-adds' worth of flops/2 and needs only 256 bytes of
+// One such instruction takes 64 cycles for 2048 multiply-adds and needs only 256 bytes of
 // either operand, so these kernels are bound by the matrix cores as soon as every SIMD has work and
 // the operands arrive in whole cache lines; LDS staging would buy nothing.  Hence:
 //   * activations lie in runs of eight channels, [c / 8][position][8] (pos8_index): the B operand of a

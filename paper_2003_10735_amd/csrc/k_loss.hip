@@ -119,7 +119,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             const int lc = cell % CW, r = cell / CW;
             const int cx = min(max(cx0 + lc, 0), g.w - 1), cy = min(max(cy0 + r, 0), g.h - 1);
             const size_t mp = ((size_t)img * g.Hp + cy + 1) * g.Wp + cx + 1;
-            // up to four shares (one per 64 channels); within a group of two an absent
+            // up to four shares (one per 64 channels, float32 path 32); within a group of two an absent
             // share re-reads the last one (it is then not added), so that the loads of a group are
             // issued together.  Only loaded here: the sums wait until every load of the prologue
             // is on its way.
@@ -220,7 +220,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
                     acc[e] = __builtin_fmaf(1.f, zr[k][2][e], acc[e]);
                     if (zs.n_parts > 3) acc[e] = __builtin_fmaf(1.f, zr[k][3][e], acc[e]);
                 }
-                // (heads with more than 256 channels in the second layer)
+                // (more than 256 channels in the second layer, float32 path 128)
                 for (int s = 4; s < zs.n_parts; ++s) {
                     const int ii = min(i, CH * CW * QC - 1), cl = ii / QC, ch = ii - cl * QC;
                     const int cx = min(max(cx0 + cl % CW, 0), g.w - 1), cy = min(max(cy0 + cl / CW, 0), g.h - 1);
