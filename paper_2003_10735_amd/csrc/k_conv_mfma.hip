@@ -56,7 +56,7 @@ static_assert((size_t)CV_NBUF * CV_XS_ROWS * CV_BK * sizeof(bf16) <= CV_SMEM_BYT
 struct ConvArgs {
     const bf16* X;      // [PP][cin] position-major, guards before/after
     const bf16* Wq;     // fragment order, see wfrag_index(): rows = cout, K = cin
-    const float* bias;  // EPI 0
+    const float* bias;  // EPI 0, 2
     const bf16* mask;   // EPI 1: activation whose sign gates the gradient, [PP][cout]
     bf16* Y;            // [PP][cout] or nullptr
     bf16* YT;           // channel-major copy, blocked layout of xt_index(), or nullptr
@@ -112,9 +112,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     const int c_chunks = a.cin / CV_BK;
     const int n_stages = 3 * c_chunks;
     const int kfr = a.cin >> 4;                                   // 16-channel fragments per tap
-    // this wavefront's block of 32 output channels (clamped: a half tile beyond cout computes
-    // a copy of the last block and drops it in the epilogue)
-    const int nb = min((n0 >> 5) + wn, (a.cout >> 5) - 1);
+    const int nb = (n0 >> 5) + wn;                                // this wavefront's block of 32 output channels
 
     u32x4 wr[3][3];          // weight fragments of the three taps of a stage: in use, and two stages ahead
 
@@ -323,17 +321,16 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
             const int c = wn * 32 + rg * 8 + lhi * 4;   // channel inside the tile
-            const int cg = min(n0 + c, a.cout - 4);
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = mine[rg * 4 + e];
             if (EPI == 0 || EPI == 2) {
-                const float4 b = *(const float4*)(bias + cg);
+                const float4 b = *(const float4*)(bias + n0 + c);
                 v[0] = fmaxf(v[0] + b.x, 0.f); v[1] = fmaxf(v[1] + b.y, 0.f);
                 v[2] = fmaxf(v[2] + b.z, 0.f); v[3] = fmaxf(v[3] + b.w, 0.f);
             } else {
                 bf16x4 mk = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
-                if (inside) mk = *(const bf16x4*)(a.mask + (size_t)mp * a.cout + cg);
+                if (inside) mk = *(const bf16x4*)(a.mask + (size_t)mp * a.cout + n0 + c);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = (float)mk[e] > 0.f ? v[e] : 0.f;
             }
@@ -364,12 +361,11 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
                     *(f32x4*)(zrow + gq * 8) = f32x4{zacc[gq * 4], zacc[gq * 4 + 1], zacc[gq * 4 + 2], zacc[gq * 4 + 3]};
         }
     }
-    const int n_valid = min(CV_BN, a.cout - n0);
     if (a.Y) {
         // position-major: 16 bytes = 8 channels of one position
         for (int q = tid; q < CV_BM * (CV_BN / 8); q += NT) {
             const int p = q / (CV_BN / 8), part = q % (CV_BN / 8);
-            if (m0 + p < m_end && part * 8 < n_valid)
+            if (m0 + p < m_end)
                 *(uint4*)(a.Y + (size_t)(m0 + p) * a.cout + n0 + part * 8) = *(const uint4*)(Os + p * CV_OLD + part * 8);
         }
     }
@@ -377,7 +373,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         // channel-major: 16 bytes = 8 consecutive positions of one channel
         for (int q = tid; q < (CV_BM / 8) * CV_BN; q += NT) {
             const int c = q % CV_BN, pg = q / CV_BN;
-            if (c < n_valid && m0 + pg * 8 < m_end) {
+            if (m0 + pg * 8 < m_end) {
                 bf16x8 o;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = Os[(pg * 8 + e) * CV_OLD + c];
@@ -388,11 +384,11 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 }
 
 // (cin and cout are multiples of 64 here: Geo::ki, k1, k2)
-// epi 0: Y = relu(conv + bias); epi 1: Y = conv * [mask > 0]; with W3q / zpart (epi 0, cout a
-// multiple of 64) the block also leaves its share of the classifier's logits; epi 3: the plain
+// epi 0: Y = relu(conv + bias) (layer 1); epi 2: the same, and with W3q / zpart the block also leaves its share
+// of the classifier's logits (layer 2); epi 1: Y = conv * [mask > 0]; epi 3: the plain
 // sums as float32 to the dense tensor `dense` [n][cout][h][w]
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
-                  const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, int layer, const bf16* W3q,
+                  const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, const bf16* W3q,
                   float* zpart, float* dense)
 {
     const Geo& g = p.g;
@@ -410,21 +406,20 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.bias_stride = p.head_stride;
     a.w3_stride = (size_t)g.C * cout;
     a.m_tiles = g.heads() * a.grp_tiles;
-    a.n_tiles = cdiv(cout, CV_BN);
+    a.n_tiles = cout / CV_BN;
     const int tiles = a.m_tiles * a.n_tiles;
     a.tiles_per_xcd = cdiv(tiles, 8);
     const dim3 grid(a.tiles_per_xcd * 8);
     const size_t smem = CV_SMEM_BYTES;
-    // tag 1: layer-1 forward, 2: layer-2 forward, 3: layer-2 data-gradient
+    // tag 1: layer-1 forward, 2: layer-2 forward, 3: layer-2 data-gradient, 4: layer-1 data-gradient
     auto go = [&](auto kernel) {
         ensure_dynamic_lds((const void*)kernel, smem);
         ST_LAUNCH(c, name, kernel, grid, dim3(512), smem, a);
     };
     if (epi == 3) go(k_conv3x3_mfma<3, 4>);
     else if (epi == 1) go(k_conv3x3_mfma<1, 3>);
-    else if (zpart) go(k_conv3x3_mfma<2, 2>);
-    else if (layer == 1) go(k_conv3x3_mfma<0, 1>);
-    else go(k_conv3x3_mfma<0, 2>);
+    else if (epi == 2) go(k_conv3x3_mfma<2, 2>);
+    else go(k_conv3x3_mfma<0, 1>);
 }
 
 }  // namespace st

@@ -406,7 +406,7 @@ static void head_strides(UpdateArgs& a, const Plan& p)
     a.hs_part3 = (size_t)p.blocks3 * conv3_bwd_slot_floats(p.g);
 }
 
-// do_step: optimiser step (else only the operand copies are refreshed);
+// do_step: optimiser step (else, when a call opens: theta from ext_in and the operand copies);
 // finish: also close the forward pass that preceded it (loss, per-frame mIoU, counts)
 static int step_end_args(const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool do_step, bool finish,
                          const float* ext_in, bool w1t, const FinishArgs& f, UpdateArgs& a, float* save_old = nullptr)
@@ -442,14 +442,13 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     return a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish;
 }
 
-void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool do_step, bool finish, float* loss_out,
-              double* miou_out, long long* conf_out, const float* ext_in, bool w1t, float* save_old)
+void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool finish, float* loss_out,
+              double* miou_out, long long* conf_out, bool w1t, float* save_old)
 {
     UpdateArgs a;
     const FinishArgs f = finish_args(p, ws, loss_out, miou_out, conf_out);
-    const int blocks = step_end_args(p, ws, lr, mu, adam, do_step, finish, ext_in, w1t, f, a, save_old);
-    const char* name = !do_step ? "params_in+operand_copies"
-                                : adam ? (finish ? "adam_update+finish_pass" : "adam_update") : (finish ? "sgd_update+finish_pass" : "sgd_update");
+    const int blocks = step_end_args(p, ws, lr, mu, adam, true, finish, nullptr, w1t, f, a, save_old);
+    const char* name = adam ? (finish ? "adam_update+finish_pass" : "adam_update") : (finish ? "sgd_update+finish_pass" : "sgd_update");
     auto go = [&](auto kernel) { ST_LAUNCH(c, name, kernel, dim3(blocks, p.g.heads()), dim3(256), 0, a, f); };
     if (p.bf16) { if (a.save_old) go(k_step_end<true, false>); else go(k_step_end<false, false>); }
     else { if (a.save_old) go(k_step_end<true, true>); else go(k_step_end<false, true>); }

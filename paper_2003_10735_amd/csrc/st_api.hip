@@ -419,9 +419,9 @@ static void forward(Ctx& c, const Plan& p, char* ws)
     const float* b1 = p.bq1 ? (const float*)(ws + p.bq1) : theta + p.po.b1;
     const float* b2 = p.bq2 ? (const float*)(ws + p.bq2) : theta + p.po.b2;
     conv3x3_mfma(c, "conv1_fwd_mfma", p, (const bf16*)(ws + p.feat), (const bf16*)(ws + p.wq1), b1,
-                 nullptr, (bf16*)(ws + p.a1), p.a1T ? (bf16*)(ws + p.a1T) : nullptr, g.ki, g.k1, 0, 1);
+                 nullptr, (bf16*)(ws + p.a1), p.a1T ? (bf16*)(ws + p.a1T) : nullptr, g.ki, g.k1, 0);
     conv3x3_mfma(c, "conv2_fwd_logits_mfma", p, (const bf16*)(ws + p.a1), (const bf16*)(ws + p.wq2),
-                 b2, nullptr, p.a2 ? (bf16*)(ws + p.a2) : nullptr, nullptr, g.k1, g.k2, 0, 2,
+                 b2, nullptr, p.a2 ? (bf16*)(ws + p.a2) : nullptr, nullptr, g.k1, g.k2, 2,
                  (const bf16*)(ws + p.wq3), (float*)(ws + p.zpart));
 }
 
@@ -447,10 +447,10 @@ static void backward(Ctx& c, const Plan& p, char* ws, float* dfeat, const Finish
                    (const unsigned long long*)(ws + p.counters), (const bf16*)(ws + p.a2),
                    (const bf16*)(ws + p.wq3t), (bf16*)(ws + p.da2), (bf16*)(ws + p.da2T), (float*)(ws + p.grad3), finish);
     conv3x3_mfma(c, "conv2_dgrad_mfma", p, (const bf16*)(ws + p.da2), (const bf16*)(ws + p.wq2t), nullptr,
-                 (const bf16*)(ws + p.a1), dfeat ? (bf16*)(ws + p.da1) : nullptr, (bf16*)(ws + p.da1T), g.k2, g.k1, 1, 2);
+                 (const bf16*)(ws + p.a1), dfeat ? (bf16*)(ws + p.da1) : nullptr, (bf16*)(ws + p.da1T), g.k2, g.k1, 1);
     if (dfeat)
         conv3x3_mfma(c, "conv1_dgrad_mfma", p, (const bf16*)(ws + p.da1), (const bf16*)(ws + p.wq1t), nullptr, nullptr,
-                     nullptr, nullptr, g.k1, g.ki, 3, 1, nullptr, nullptr, dfeat);
+                     nullptr, nullptr, g.k1, g.ki, 3, nullptr, nullptr, dfeat);
     wgrad3x3_mfma(c, p, (const bf16*)(ws + p.da1T), (const bf16*)(ws + p.featT), (const bf16*)(ws + p.da2T),
                   (const bf16*)(ws + p.a1T), grad);
 }
@@ -837,7 +837,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
             ad.step_scale = (float)((double)lr / (1.0 - pow(beta1, t)));
             ad.inv_sqrt_bc2 = (float)(1.0 / sqrt(1.0 - pow(beta2, t)));
         }
-        step_end(c, p, ws, lr, mu, use_adam ? &ad : nullptr, true, !finish_now, loss_out, miou_out, conf_out, nullptr,
+        step_end(c, p, ws, lr, mu, use_adam ? &ad : nullptr, !finish_now, loss_out, miou_out, conf_out,
                  feature_grad != nullptr, best_is_theta ? (float*)(ws + p.best) : nullptr);
         best_is_theta = false;
         ++taken;

@@ -40,7 +40,7 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 
 // k_conv_mfma.hip, k_wgrad_mfma.hip, k_conv3_mfma.hip -- matrix-core kernels of the bfloat16 path
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
-                  const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi, int layer,
+                  const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi,
                   const bf16* W3q = nullptr, float* zpart = nullptr, float* dense = nullptr);
 void wgrad_splits_for(const Geo& g, bool bf16_path, int* splits1, int* splits2);
 void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, const bf16* da2T,
@@ -89,9 +89,8 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
                 bool w1t, const int32_t* labels, const uint8_t* pixel_weights, const ZeroList& zero);
 // blocks of the label role of that launch, in the order of the frames; each leaves its pixel count (weight sum)
 int label_blocks(const Geo& g);
-void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool do_step, bool finish, float* loss_out,
-              double* miou_out, long long* conf_out, const float* ext_in = nullptr,
-              bool w1t = false, float* save_old = nullptr);
+void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool finish, float* loss_out,
+              double* miou_out, long long* conf_out, bool w1t = false, float* save_old = nullptr);
 // arguments of the bookkeeping role; miou_host / token_host / token as for finish_pass
 FinishArgs finish_args(const Plan& p, char* ws, float* loss_out, double* miou_out, long long* conf_out,
                        double* miou_host = nullptr, unsigned long long* token_host = nullptr,
