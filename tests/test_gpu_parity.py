@@ -40,9 +40,10 @@ RAGGED = [
     dict(n=2, c_in=20, h=9, w=37, c1=24, c2=16, n_classes=5, ignore_index=255, ignore_fraction=0.1),
     dict(n=1, c_in=16, h=3, w=70, c1=16, c2=40, n_classes=21, momentum=0.9),
     dict(n=3, c_in=4, h=1, w=1, c1=4, c2=4, n_classes=2),
-    # enough positions (2 x 33 x 37 = 2442) for the plain path's largest number of partial gradient
-    # copies (16), with a ragged last share
+    # several partial gradient copies (float32 15, bfloat16 6), with a ragged last share
     dict(n=2, c_in=12, h=33, w=37, c1=16, c2=12, n_classes=4, momentum=0.5),
+    # enough positions for the largest number of copies (16) on both paths, the last shares ragged
+    dict(n=2, c_in=12, h=61, w=70, c1=16, c2=12, n_classes=4, momentum=0.5),
 ]
 
 
@@ -53,6 +54,8 @@ def test_ragged_shapes(case, compute):
                           feat_dtype="bf16" if compute == "bf16" else "f32", n_sites=7, **RAGGED[case])
     f, lab, p = inputs(wl)
     gpu = run_gpu(wl, f, lab, p)
+    if case == len(RAGGED) - 1:
+        assert gpu["layout"]["splits"][:2] == [16, 16]
     check_staged_bit_exact(wl, gpu, lab)
     if compute == "f32":
         ora = run_oracle(wl, f, lab, p)
