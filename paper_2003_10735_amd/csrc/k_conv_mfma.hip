@@ -36,8 +36,8 @@
 // (operand of the weight-gradient kernel).  For the layer that feeds the 1x1 classifier the
 // staged tile is also multiplied with the classifier's weights (16 more MFMAs per block), which
 // saves the classifier a launch and a pass over the activations.
+#include "st_conv.hpp"
 #include "st_kernels.hpp"
-#include "st_mfma.hpp"
 
 namespace st {
 
@@ -52,31 +52,6 @@ constexpr int CV_OLD = CV_BN + 8;   // pitch of the staged output tile
 constexpr size_t CV_RED_BYTES = (size_t)8 * 3 * 16 * 64 * sizeof(float);
 constexpr size_t CV_SMEM_BYTES = CV_RED_BYTES + (size_t)CV_BM * CV_OLD * sizeof(bf16);
 static_assert((size_t)CV_NBUF * CV_XS_ROWS * CV_BK * sizeof(bf16) <= CV_SMEM_BYTES, "K-loop buffers fit");
-
-struct ConvArgs {
-    const bf16* X;      // [PP][cin] position-major, guards before/after
-    const bf16* Wq;     // fragment order, see wfrag_index(): rows = cout, K = cin
-    const float* bias;  // EPI 0, 2
-    const bf16* mask;   // EPI 1: activation whose sign gates the gradient, [PP][cout]
-    bf16* Y;            // [PP][cout] or nullptr
-    bf16* YT;           // channel-major copy, blocked layout of xt_index(), or nullptr
-    // EPI 2: the 1x1 classifier rides along.  Every block adds its 64 channels' share of the
-    // logits of its 128 positions: zpart[n-tile][padded position][zpitch classes] float32 (zpitch =
-    // the class count rounded up to a multiple of four); the consumer adds the n_tiles shares and
-    // the bias.
-    const bf16* W3q;    // [n_cls][cout] bfloat16
-    float* zpart;
-    int n_cls, zpitch;
-    // EPI 3: the plain sums go, as float32, straight to a dense [n][cout][h][w] tensor
-    float* dense; int dense_c;   // (channels of that tensor: cout without the padding)
-    int PP, Hp, Wp, h, w, cin, cout, PPT, guard;
-    int m_tiles, n_tiles, tiles_per_xcd;
-    // Several heads: positions [k * grp_pp, (k + 1) * grp_pp) use weight set k (Wq, bias and W3q
-    // advance by wq_stride, bias_stride, w3_stride elements per set); position tiles are counted
-    // per set (grp_tiles each) so that no tile mixes two sets.  One head: grp_pp = PP.
-    int grp_pp, grp_tiles;
-    size_t wq_stride, bias_stride, w3_stride;
-};
 
 // TAG only gives every call site (layer 1 forward, layer 2 forward, layer 2 data-gradient) a
 // kernel symbol of its own, so that profiles list them separately.
@@ -401,10 +376,12 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     // several heads: one weight set per frame (Wq holds them back to back, the biases sit
     // head_stride floats apart inside the parameter vectors, W3q back to back)
     a.grp_pp = g.grouped ? g.Hp * g.Wp : a.PP;
-    a.grp_tiles = cdiv(a.grp_pp, CV_BM);
     a.wq_stride = (size_t)cin * cout * 9;
     a.bias_stride = p.head_stride;
     a.w3_stride = (size_t)g.C * cout;
+    const ConvTile t = conv_tile(g, cin, cout);
+    if (t.bn != CV_BN) { conv3x3_wide(c, name, a, epi, g.heads(), t); return; }
+    a.grp_tiles = cdiv(a.grp_pp, CV_BM);
     a.m_tiles = g.heads() * a.grp_tiles;
     a.n_tiles = cout / CV_BN;
     const int tiles = a.m_tiles * a.n_tiles;

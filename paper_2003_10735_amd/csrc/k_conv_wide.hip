@@ -1,0 +1,389 @@
+// 3x3 convolution (forward, and data-gradient as a forward with mirrored taps) on the matrix cores with a tile
+// twice as wide as that of k_conv_mfma.hip: for grids that give a compute unit more than one block.
+//
+// What binds those grids in the small-tile kernel (128 positions x 64 channels per block, 8 wavefronts that each
+// hold four 32 x 32 accumulator tiles) is not its K loop but what surrounds it: one block owns the compute unit, so
+// the matrix cores idle while it fills its pipeline, exchanges its partial sums and stores (about 5 of 14 us per
+// round), and its 0.25 weight kilobytes and one activation kilobyte per MFMA cost energy that the clock then lacks
+// (a long launch of dense MFMAs runs at 1.3 - 1.7 GHz here).  Hence:
+//   * a block is 256 threads = 4 wavefronts, 32 P positions x 128 channels; two blocks share a compute unit (at most
+//     256 registers and 64 KB of LDS each), so one block's K loop covers the other's prologue, exchange and stores;
+//   * a wavefront holds 64 channels x 32 P positions (2 P accumulator tiles), so each activation fragment read from
+//     LDS feeds two MFMAs and each weight fragment P; the four are 2 channel halves x 2 K groups.
+// Operands take the same routes as in k_conv_mfma.hip (weights in fragment order straight to registers, activations
+// from memory into swizzled LDS slabs, three of which rotate), with the loads of one stage ahead in a ring of six
+// weight fragments pairs and the next step's activation fragments read while this step's MFMAs run.
+// Measured, us per launch, small tiles -> this kernel (probe with random data, one box each):
+//   4 x 90 x 160 cells, 320 -> 256 111 -> 86, data gradient 256 -> 256 89 -> 71, layer 2 with classifier 106 -> 68;
+//   135 x 240, 256 -> 128 31.3 -> 24.4, 128 -> 128 22.5 -> 16.1;  four heads of 90 x 160, 256 -> 128 47 -> 37.
+// Wider tiles still (256 x 256 and 256 x 128 with one block per compute unit: 86 and 96 us where this one takes
+// 86; 160 x 128 98; 192 x 128, one block, 50 us at 180 x 320 cells, 256 -> 128, where this one takes 34) do not pay.
+#include <algorithm>
+
+#include "st_conv.hpp"
+#include "st_kernels.hpp"
+
+namespace st {
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int CW_BN = 128;                 // channels per block
+constexpr int CW_OLD = CW_BN + 8;          // pitch of the staged output tile
+constexpr int CW_STEPS = 6;                // steps of a stage per wavefront: three taps x two fragments of 16 channels
+#define CW_F __builtin_amdgcn_sched_barrier(0);
+
+// dynamic LDS: the three slabs, later the exchanged sums (P accumulator tiles per wavefront), then the output tile
+template <int P>
+constexpr size_t cw_lds()
+{
+    return std::max(std::max((size_t)3 * (32 * P + 2) * 128, (size_t)4 * P * 4096), (size_t)32 * P * CW_OLD * 2);
+}
+
+// EPI as for k_conv3x3_mfma: 0 bias + ReLU, 1 ReLU mask of a data gradient, 2 as 0 with the classifier, 3 plain
+// float32 sums to a dense tensor.
+template <int P, int EPI>
+__global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
+{
+    constexpr int BM = 32 * P, BN = CW_BN, SLAB = (BM + 2) * 128, STEPS = CW_STEPS, OLD = CW_OLD;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+
+    // XCD-aware tile order, several heads: as in k_conv3x3_mfma
+    const int tile = (blockIdx.x % 8) * a.tiles_per_xcd + blockIdx.x / 8;
+    if ((int)(blockIdx.x / 8) >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
+    const int mt = tile / a.n_tiles, nt = tile % a.n_tiles;
+    const int grp = mt / a.grp_tiles;
+    const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * BM, n0 = nt * BN;
+    const int m_end = (grp + 1) * a.grp_pp;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, kgrp = wave >> 1;
+    const int l32 = lane & 31, lhi = lane >> 5;
+
+    f32x16 acc[2][P];
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
+
+    const int c_chunks = a.cin / 64, n_stages = 3 * c_chunks, kfr = a.cin >> 4;
+
+    // Activations: slab rows are positions m0 - 1 .. m0 + BM (shifted by the kernel row), 64 channels each, 16-byte
+    // chunk c of row r at c ^ ((r >> 1) & 7).  A load of a wavefront fills eight rows; wavefront w takes the groups
+    // w, w + 4, .. and wavefront 0 the two rows behind them.  (Rows behind the grid lie in the guard, whose
+    // length counts on tiles of at most 256 positions.)
+    static_assert(BM <= 256, "guard rows");
+    const int lrow = lane >> 3, lpc = lane & 7;
+    const int xo = ((8 * wave + lrow) * a.cin + ((lpc ^ ((4 * wave + (lrow >> 1)) & 7)) << 3)) * 2;
+    const int xo_rest = ((BM + lrow) * a.cin + ((lpc ^ (lrow >> 1)) << 3)) * 2;
+    const int x32 = 32 * a.cin * 2;
+    const char* xsp = (const char*)(a.X + ((long long)m0 - 1 - a.Wp) * a.cin);
+    const long long x_row = ((long long)a.Wp * a.cin - (c_chunks - 1) * 64) * 2;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
+    int rd[3];
+#pragma unroll
+    for (int kw = 0; kw < 3; ++kw) rd[kw] = (l32 + kw) * 128 + (((kgrp * 4 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4);
+
+    // Weights.  Slot n of K group k is channel block n ^ k of the wavefront's half, so that after the K loop every
+    // wavefront keeps its slot 0 and hands slot 1 to the wavefront of the other K group.  (Channel blocks behind the
+    // last one read zeros or another block's weights; their sums are dropped.)
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.Wq + grp * a.wq_stride), 0, (int)(a.wq_stride * 2), 0x00020000);
+    unsigned wv[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) wv[n] = (unsigned)((((n0 >> 5) + 2 * wn + (n ^ kgrp)) * 9 * kfr + kgrp * 2) * 1024 + lane * 16);
+    int w_soff = 0;
+    const int w_row = (2 * kfr + 4) * 1024;
+    int w_cc = 0, x_cc = 0;
+
+    u32x4 wr[STEPS][2];       // weight fragments of a stage's steps; a slot is refilled for the next stage once used
+    bf16x8 xb[P];             // activation fragments of the step in work, each replaced by the next step's once used
+
+    // step t: tap column t / 2, channel fragment t % 2
+    auto load_w = [&](int soff, int t) __attribute__((always_inline)) {
+        const int s = soff + ((t >> 1) * kfr + (t & 1)) * 1024;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) wr[t][n] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv[n], s, 0);
+    };
+    // (assembly, and M0: see k_conv3x3_mfma)
+    auto dma = [&](int slab, int i) __attribute__((always_inline)) {
+        const char* src = xsp + (long long)i * x32;
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(xo), "s"(src),
+                     "s"(lds0 + slab * SLAB + (i * 4 + wave) * 1024) : "memory");
+    };
+    auto dma_rest = [&](int slab) __attribute__((always_inline)) {
+        if (wave == 0 && lane < 16)
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(xo_rest), "s"(xsp),
+                         "s"(lds0 + slab * SLAB + BM * 128) : "memory");
+    };
+    auto read_x = [&](int slab, int t, int j) __attribute__((always_inline)) {
+        return *(const bf16x8*)(smem_raw + slab * SLAB + (rd[t >> 1] ^ ((t & 1) << 5)) + j * 4096);
+    };
+    auto x_next = [&]() __attribute__((always_inline)) { if (++x_cc == c_chunks) { x_cc = 0; xsp += x_row; } else xsp += 128; };
+    auto w_next = [&]() __attribute__((always_inline)) { if (++w_cc == c_chunks) { w_cc = 0; w_soff += w_row; } else w_soff += 4096; };
+    // s_waitcnt vmcnt(N) alone
+#define CW_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | 0x0F70)
+
+    // One stage out of slab B.  FX: the activations of the stage two ahead start their way into slab (B + 2) % 3,
+    // which every wavefront has left behind the barrier of the stage before.  NEXT: another stage follows; its
+    // slab is waited for in front of the last step (everything but the loads this stage has issued by then must
+    // have landed), because that step already reads the next stage's first fragments.
+    auto stage = [&](auto B_, auto FX_, auto NEXT_) __attribute__((always_inline)) {
+        constexpr int B = decltype(B_)::value;
+        constexpr bool FX = decltype(FX_)::value, NEXT = decltype(NEXT_)::value;
+        if (NEXT) w_next();
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            const bool last = t == STEPS - 1;
+            if (last && NEXT) {
+                constexpr int issued = 2 * (STEPS - 1) + (FX ? P : 0);
+                CW_VMCNT(issued);
+                __syncthreads();
+                CW_F
+            }
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+                    acc[n][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[t][n]), xb[j], acc[n][j], 0, 0, 0);
+                CW_F
+                if (!last) xb[j] = read_x(B, t + 1, j);
+                else if (NEXT) xb[j] = read_x((B + 1) % 3, 0, j);
+                if (FX && !last) {
+                    // the stage's P activation loads, spread over the steps in front of the barrier
+                    constexpr int GAPS = (STEPS - 1) * P;
+                    const int at = t * P + j;
+                    if (at * P / GAPS != (at + 1) * P / GAPS) dma((B + 2) % 3, at * P / GAPS);
+                    if (at == 0) dma_rest((B + 2) % 3);
+                }
+                CW_F
+            }
+            if (NEXT) load_w(w_soff, t);
+            CW_F
+        }
+        if (FX) x_next();
+    };
+    typedef std::integral_constant<int, 0> I0; typedef std::integral_constant<int, 1> I1; typedef std::integral_constant<int, 2> I2;
+    const std::true_type yes; const std::false_type no;
+
+#pragma unroll
+    for (int i = 0; i < P; ++i) dma(0, i);
+    dma_rest(0);
+    x_next();
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) load_w(0, t);
+    CW_F
+#pragma unroll
+    for (int i = 0; i < P; ++i) dma(1, i);
+    dma_rest(1);
+    x_next();
+    CW_VMCNT(2 * STEPS + P);
+    __syncthreads();
+    CW_F
+#pragma unroll
+    for (int j = 0; j < P; ++j) xb[j] = read_x(0, 0, j);
+    CW_F
+    // (the number of stages is a multiple of three; the last three are written out)
+    for (int s = 0; s + 3 < n_stages; s += 3) {
+        stage(I0{}, yes, yes);
+        stage(I1{}, yes, yes);
+        stage(I2{}, yes, yes);
+    }
+    stage(I0{}, yes, yes);
+    stage(I1{}, no, yes);
+    stage(I2{}, no, no);
+#undef CW_VMCNT
+#undef CW_F
+
+    // ---- what the epilogue needs from memory, on its way while the partial sums are exchanged
+    constexpr int CHUNKS = BM * (BN / 8) / 256;      // 16-byte chunks of the output tile per thread
+    const int frame = a.Hp * a.Wp;
+    const int cw = wn * 64 + kgrp * 32;              // this wavefront's 32 channels inside the tile
+    u32x4 mk[EPI == 1 ? CHUNKS : 1];
+    if (EPI == 1) {
+#pragma unroll
+        for (int k = 0; k < CHUNKS; ++k) {
+            const int q = tid + 256 * k, p = q / (BN / 8), c = n0 + q % (BN / 8) * 8;
+            mk[k] = *(const u32x4*)(a.mask + (size_t)min(m0 + p, m_end - 1) * a.cout + min(c, a.cout - 8));
+        }
+    }
+    f32x4 bias[EPI == 0 || EPI == 2 ? 4 : 1];
+    unsigned inside = 0;      // bit j: position 32 j + l32 of the tile lies on the grid
+    if (EPI == 0 || EPI == 2) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            bias[k] = *(const f32x4*)(a.bias + grp * a.bias_stride + min(n0 + cw + k * 8 + lhi * 4, a.cout - 4));
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const int mp = m0 + j * 32 + l32;
+            const int rr = mp % frame, y = rr / a.Wp, x = rr - y * a.Wp;
+            if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) inside |= 1u << j;
+        }
+    }
+    __syncthreads();
+    {
+        float* red = (float*)smem_raw;     // [receiving wavefront][P][4 register groups][64 lanes][4]
+        float* dst = red + (size_t)(wave ^ 2) * P * 1024 + lane * 4;
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq)
+                *(f32x4*)(dst + (j * 4 + rq) * 256) = f32x4{acc[1][j][rq * 4], acc[1][j][rq * 4 + 1], acc[1][j][rq * 4 + 2], acc[1][j][rq * 4 + 3]};
+        __syncthreads();
+        const float* src = red + (size_t)wave * P * 1024 + lane * 4;
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                const f32x4 v = *(const f32x4*)(src + (j * 4 + rq) * 256);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[0][j][rq * 4 + e] += v[e];
+            }
+        __syncthreads();
+    }
+    if (EPI == 3) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const int mp = m0 + j * 32 + l32;
+            const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
+            if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) {
+                float* dst = a.dense + ((size_t)img * a.dense_c * a.h + (y - 1)) * a.w + (x - 1);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int ch = n0 + cw + (r >> 2) * 8 + lhi * 4 + (r & 3);
+                    if (ch < a.dense_c) dst[(size_t)ch * a.h * a.w] = acc[0][j][r];
+                }
+            }
+        }
+        return;
+    }
+
+    // classifier fragments (A operand: rows = classes, k = this tile's channels)
+    u32x4 w3f[EPI == 2 ? BN / 16 : 1];
+    if (EPI == 2) {
+        const bf16* w3row = a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + lhi * 8;
+#pragma unroll
+        for (int ks = 0; ks < BN / 16; ++ks) {
+            const u32x4 v = *(const u32x4*)(w3row + min(n0 + ks * 16, a.cout - 16));
+            w3f[ks] = l32 < a.n_cls && n0 + ks * 16 < a.cout ? v : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    bf16* Os = (bf16*)smem_raw;      // [BM][OLD]
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = acc[0][j][rg * 4 + e];
+                if (EPI != 1) v = inside & (1u << j) ? fmaxf(v + bias[rg][e], 0.f) : 0.f;
+                o[e] = (bf16)v;
+            }
+            *(bf16x4*)(Os + (j * 32 + l32) * OLD + cw + rg * 8 + lhi * 4) = o;
+        }
+    }
+    __syncthreads();
+    if (EPI == 2) {
+        // D[class][position], 32 positions per wavefront and turn, over the tile's channels
+        for (int j = wave; j < P; j += 4) {
+            f32x16 z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < BN / 16; ++ks) {
+                const bf16x8 xf = *(const bf16x8*)(Os + (j * 32 + l32) * OLD + ks * 16 + lhi * 8);
+                z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w3f[ks]), xf, z, 0, 0, 0);
+            }
+            const int mp = m0 + j * 32 + l32;
+            if (mp < m_end) {
+                float* zrow = a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + lhi * 4;
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq)
+                    if (gq * 8 + lhi * 4 < a.zpitch)
+                        *(f32x4*)(zrow + gq * 8) = f32x4{z[gq * 4], z[gq * 4 + 1], z[gq * 4 + 2], z[gq * 4 + 3]};
+            }
+        }
+    }
+    // position-major: 16 bytes = 8 channels of one position; a data gradient is masked on the way (the mask is zero
+    // on the border of the grid)
+    if (EPI == 1 || a.Y) {
+#pragma unroll
+        for (int k = 0; k < CHUNKS; ++k) {
+            const int q = tid + 256 * k, p = q / (BN / 8), c = q % (BN / 8) * 8;
+            bf16x8 o = *(const bf16x8*)(Os + p * OLD + c);
+            if (EPI == 1) {
+                const bf16x8 m = __builtin_bit_cast(bf16x8, mk[k]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (float)m[e] > 0.f ? o[e] : (bf16)0.f;
+                *(bf16x8*)(Os + p * OLD + c) = o;
+            }
+            if (a.Y && m0 + p < m_end && n0 + c < a.cout) *(bf16x8*)(a.Y + (size_t)(m0 + p) * a.cout + n0 + c) = o;
+        }
+        if (EPI == 1) __syncthreads();
+    }
+    if (a.YT) {
+        // channel-major: 16 bytes = 8 consecutive positions of one channel, a wavefront two such groups of 32
+        // channels, through the transposing LDS read: in a group of 16 lanes, lane r names (position r / 4,
+        // channels 4 (r % 4) .. + 3) and lane i receives channel i of four consecutive positions
+        for (int u = wave; u < 2 * P * (BN / 32); u += 4) {
+            const int pg = u / (BN / 32) * 2 + lhi, c = u % (BN / 32) * 32;
+            const bf16* row = Os + (pg * 8 + ((lane & 15) >> 2)) * OLD + c + (lane & 16) + 4 * (lane & 3);
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * OLD));
+            const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            if (m0 + pg * 8 < m_end && n0 + c < a.cout)
+                *(s16x8*)(a.YT + xt_index(n0 + c + l32, a.guard + m0 + pg * 8, a.PPT / 8)) = v;
+        }
+    }
+}
+
+// Which tile a layer runs with.  A launch takes about (blocks on the busiest compute unit) x (time of a block) + a
+// constant, the time of a block being linear in the input channels.  Fitted, in microseconds, to sweeps over 7 000 to 74 000
+// positions, 64, 128 and 256 input and 128 and 256 output channels, where it is off by up to a tenth; at the sizes where the
+// choice changes it names the faster kernel (one head, 256 -> 128: 90 x 160 cells small tiles 12.6 / 96 positions
+// 14.7 / 128 positions 17.6 us, 100 x 178 cells 21.0 / 15.4 / 18.3, 120 x 213 cells 21.5 / 23.8 / 19.6).
+ConvTile conv_tile(const Geo& g, int cin, int cout)
+{
+    struct Shape { ConvTile t; float block, per64, launch; };
+    static const Shape shapes[3] = {{{128, 64}, 4.3f, 1.53f, 1.0f}, {{96, CW_BN}, 2.4f, 2.03f, 4.3f}, {{128, CW_BN}, 2.5f, 2.83f, 4.8f}};
+    ConvTile best = shapes[0].t;
+    float best_t = 0.f;
+    for (const Shape& s : shapes) {
+        const int blocks = g.heads() * cdiv(g.padded_positions() / g.heads(), s.t.bm) * cdiv(cout, s.t.bn);
+        const float t = cdiv(blocks, 256) * (s.block + s.per64 * (cin / 64)) + s.launch;
+        if (&s == shapes || t < best_t) { best = s.t; best_t = t; }
+    }
+    return best;
+}
+
+// (a: everything but the tiling)
+void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads, ConvTile t)
+{
+    a.grp_tiles = cdiv(a.grp_pp, t.bm);
+    a.m_tiles = heads * a.grp_tiles;
+    a.n_tiles = cdiv(a.cout, CW_BN);
+    a.tiles_per_xcd = cdiv(a.m_tiles * a.n_tiles, 8);
+    const dim3 grid(a.tiles_per_xcd * 8);
+    auto go = [&](auto p_, auto epi_) {
+        constexpr int P = decltype(p_)::value, EPI = decltype(epi_)::value;
+        const auto kernel = k_conv3x3_wide<P, EPI>;
+        ensure_dynamic_lds((const void*)kernel, cw_lds<P>());
+        ST_LAUNCH(c, name, kernel, grid, dim3(256), cw_lds<P>(), a);
+    };
+    auto with_epi = [&](auto p_) {
+        switch (epi) {
+        case 0: go(p_, std::integral_constant<int, 0>{}); break;
+        case 1: go(p_, std::integral_constant<int, 1>{}); break;
+        case 2: go(p_, std::integral_constant<int, 2>{}); break;
+        default: go(p_, std::integral_constant<int, 3>{}); break;
+        }
+    };
+    if (t.bm == 96) with_epi(std::integral_constant<int, 3>{});
+    else with_epi(std::integral_constant<int, 4>{});
+}
+
+}  // namespace st

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "st_kernels.hpp"
+#include "st_conv.hpp"
 #include "st_finish.hpp"
 
 namespace st {
@@ -183,8 +184,8 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.gz = train_take((size_t)g.n * g.C * hw * 4);
     p.tadj = train_take((size_t)g.n * g.C * hw * 4);
     p.lab8 = train_take((size_t)g.pixels());
-    p.z_parts = p.bf16 ? g.k2 / 64 : cdiv(g.c2, 32);
-    p.zpart = take(off, (size_t)p.z_parts * PP * ((g.C + 3) / 4 * 4) * 4);
+    p.z_parts = cdiv(g.k2, p.bf16 ? conv_tile(g, g.k1, g.k2).bn : 32);     // (float32: the same for c2 and k2)
+    p.zpart = take(off, (size_t)cdiv(g.k2, p.bf16 ? 64 : 32) * PP * ((g.C + 3) / 4 * 4) * 4);
     p.g_slots = train_take(loss_slot_floats(g) * 4);
     p.grad_stride = (p.po.total + 3) / 4 * 4;
     p.head_stride = p.grad_stride;
