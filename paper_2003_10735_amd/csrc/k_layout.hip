@@ -1,12 +1,11 @@
-// Layout kernels: zero fill and the permutation between the caller's parameter order (OIHW) and
+// The list of regions to clear, and the permutation between the caller's parameter order (OIHW) and
 // the internal one ([o][kh][kw][i]).
 #include "st_kernels.hpp"
 #include "st_mfma.hpp"
 
 namespace st {
 
-__global__ void __launch_bounds__(256) k_zero_regions(ZeroList z) { zero_block(z, blockIdx.x); }
-
+// (all workspace regions are 16-byte aligned and padded to 16 bytes)
 void ZeroList::add(void* p, size_t bytes, int count, size_t stride_bytes)
 {
     if (bytes == 0 || count == 0) return;
@@ -17,14 +16,6 @@ void ZeroList::add(void* p, size_t bytes, int count, size_t stride_bytes)
     per[n] = (int)((n16[n] + ZERO_PER_BLOCK - 1) / ZERO_PER_BLOCK);
     first[n + 1] = first[n] + per[n] * count;
     ++n;
-}
-
-// all workspace regions are 16-byte aligned and padded to 16 bytes
-void zero_regions(Ctx& c, const ZeroList& z)
-{
-    if (z.overflow) { c.status = ST_ERR_SHAPE; return; }
-    if (z.n == 0) return;
-    ST_LAUNCH(c, "zero_fill", k_zero_regions, dim3(z.first[z.n]), dim3(256), 0, z);
 }
 
 // Parameter permutation.  dir = 0: external (OIHW) -> internal; dir = 1: internal -> external.

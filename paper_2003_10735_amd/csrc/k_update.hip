@@ -34,7 +34,7 @@ namespace st {
 // bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
 // zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in the order of wfrag32_index,
 // wq3t likewise with one tap, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
-// classes are cleared when the call opens and never written.
+// classes are cleared by the launch that opens the call and never written later.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
     void *wq1, *wq1t, *wq2, *wq2t, *wq3, *wq3t; float* bq1; float* bq2;   // (bf16 or float elements)
@@ -67,6 +67,8 @@ __device__ __forceinline__ Weight3x3 weight3x3(unsigned r, unsigned cin)
     const unsigned row = r / cin, o = row / 9u;
     return Weight3x3{o, row - o * 9u, r - row * cin};
 }
+
+constexpr int PAD_PER_THREAD = 4;     // 16-byte runs of the padding role per thread
 
 // index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
 __device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned j)
@@ -323,10 +325,78 @@ __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
     step_end_block<EE, F32, false>(a, f, blockIdx.x, blockIdx.y);
 }
 
+// Zeros for the padding of the operand copies: channels beyond the caller's counts, of which the parameter role writes
+// nothing (so the two roles share a launch: 64-channel stages of 48 channels in front of 60 x 107 cells once had a clearing
+// launch of their own, 4 us of a 270 us call).  A thread takes 16-byte runs of the four 3x3 copies, in the order they are
+// stored -- a run is one row's and tap's next eight (bfloat16) or four (float32) k -- and then the small ones' rests.
+template <bool F32>
+__device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, unsigned n_runs)
+{
+    constexpr int W = F32 ? 4 : 8, R32 = 32;
+    const int c[3] = {a.c_in, a.c1, a.c2}, k[3] = {a.ki, a.k1, a.k2};
+    auto rows = [&](int m) { return F32 ? (k[m] + R32 - 1) / R32 * R32 : k[m]; };
+    void* const copy[4] = {a.wq1, a.wq2, a.wq1t, a.wq2t};
+    const int row_of[4] = {1, 2, 0, 1}, k_of[4] = {0, 1, 1, 2};
+#pragma unroll 1
+    for (int u = 0; u < PAD_PER_THREAD; ++u) {
+        unsigned i = (block * PAD_PER_THREAD + u) * 256 + threadIdx.x;
+        if (i < n_runs) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                if (!copy[m]) continue;
+                const int K = k[k_of[m]], rv = c[row_of[m]], kv = c[k_of[m]];
+                const unsigned runs = (unsigned)rows(row_of[m]) * 9u * (unsigned)(K / W);
+                if (i >= runs) { i -= runs; continue; }
+                const unsigned t = i >> 6, per = (unsigned)K / (2 * W);
+                const int row = (int)(t / per / 9u * 32u + (i & 31)), k0 = (int)(t % per) * 2 * W + (int)((i >> 5) & 1) * W;
+                char* dst = (char*)copy[m] + (size_t)i * 16;
+                if (row >= rv || k0 >= kv) *(u32x4*)dst = u32x4{0u, 0u, 0u, 0u};
+                else if (k0 + W > kv)
+                    for (int e = kv - k0; e < W; ++e) { if (F32) ((float*)dst)[e] = 0.f; else ((bf16*)dst)[e] = (bf16)0.f; }
+                break;
+            }
+        } else {
+            // per channel of the second layer behind its last one: its column of wq3, its row of wq3t; biases
+            i -= n_runs;
+            const unsigned rest2 = (unsigned)(rows(2) - a.c2), kr1 = (unsigned)((a.k1 + R32 - 1) / R32 * R32), kr2 = (unsigned)((a.k2 + R32 - 1) / R32 * R32);
+            if (i < rest2 * 32) {
+                const int o = a.c2 + (int)(i >> 5), cl = (int)(i & 31);
+                if (F32) {
+                    if (cl < a.C) ((float*)a.wq3)[cl * rows(2) + o] = 0.f;
+                    if (a.wq3t) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, cl, 32)] = 0.f;
+                } else {
+                    if (cl < a.C) ((bf16*)a.wq3)[cl * a.k2 + o] = (bf16)0.f;
+                    if (a.wq3t) ((bf16*)a.wq3t)[o * 32 + cl] = (bf16)0.f;
+                }
+                continue;
+            }
+            i -= rest2 * 32;
+            if (i < kr1 - a.c1) { a.bq1[a.c1 + i] = 0.f; continue; }
+            i -= kr1 - a.c1;
+            if (i < kr2 - a.c2) a.bq2[a.c2 + i] = 0.f;
+        }
+    }
+}
+
+// the runs of 16 bytes of a head's 3x3 operand copies, and the blocks of pad_block (none without padding)
+static unsigned pad_runs(const Plan& p, const UpdateArgs& a)
+{
+    return (unsigned)(((a.wq1 ? p.bytes_w1 : 0) + (a.wq2 ? p.bytes_w2 : 0) + (a.wq1t ? p.bytes_w1t : 0) + (a.wq2t ? p.bytes_w2t : 0)) / 16);
+}
+static int pad_blocks(const Plan& p, const UpdateArgs& a)
+{
+    const Geo& g = p.g;
+    if (!g.padded() && (p.bf16 || (g.c_in % 32 == 0 && g.c1 % 32 == 0 && g.c2 % 32 == 0))) return 0;
+    const auto r32 = [](int k) { return (k + 31) / 32 * 32; };
+    const long long rest = 32ll * ((p.bf16 ? g.k2 : r32(g.k2)) - g.c2) + (r32(g.k1) - g.c1) + (r32(g.k2) - g.c2);
+    return cdiv(pad_runs(p, a) + rest, 256 * PAD_PER_THREAD);
+}
+
 // The launch that opens a call: kinds of blocks that do not depend on each other,
 //   first   U^T of the label map and the pixel counts (label_adjoint_block),
 //   then    the caller's parameters into theta and the operand copies: the blocks of
 //           k_step_end, head by head,
+//   then    zeros for the padding of the operand copies (pad_block), where channels are padded,
 //   then    feature packing (pack_features_block),
 //   last    clearing what later kernels expect to be zero (ZeroList).
 // Run one after the other they are four short launches, each of which leaves most of the chip
@@ -338,6 +408,7 @@ struct BeginArgs {
     const int32_t* labels; const uint8_t* wmap; float* T; unsigned int* counts; int CP, nb_label;
     uint8_t* lab8;                         // the labels as bytes for the loss kernel (written by the label role)
     int nb_update, nb_update_all;          // blocks of the parameter role per head, and of all heads
+    int nb_pad; unsigned pad_runs;         // blocks and 16-byte runs of the padding role (one head: heads of their own are not padded)
     Geo g;
 };
 
@@ -350,13 +421,15 @@ __global__ void __launch_bounds__(256) k_call_begin(BeginArgs q, UpdateArgs a, Z
     //  first, the short packing blocks last)
     if (b < q.nb_label) {
         float* colsum = dyn_lds;
-        unsigned int* cnt_part = (unsigned int*)(dyn_lds + q.CP * (LABEL_NCOL + 1));
+        unsigned int* cnt_part = (unsigned int*)(dyn_lds + q.CP * LABEL_PITCH);
         label_adjoint_block(q.labels, q.wmap, q.T, q.counts + b, q.g, b, colsum, cnt_part, q.CP, q.lab8);
         return;
     }
     b -= q.nb_label;
     if (b >= q.nb_update_all) {
         b -= q.nb_update_all;
+        if (b < q.nb_pad) { pad_block<F32>(a, (unsigned)b, q.pad_runs); return; }
+        b -= q.nb_pad;
         if (b >= q.nb_pack) { zero_block(z, b - q.nb_pack); return; }
         const int bx = b % q.pack_x, by = (b / q.pack_x) % q.pack_y, bz = b / (q.pack_x * q.pack_y);
         if (F32) {
@@ -496,13 +569,14 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
     const FinishArgs f = finish_args(p, ws, nullptr, nullptr, nullptr);
     q.nb_update = step_end_args(p, ws, 0.f, 0.f, nullptr, false, false, head_params, w1t, f, a);
     q.nb_update_all = q.nb_update * g.heads();
+    q.nb_pad = pad_blocks(p, a); q.pad_runs = pad_runs(p, a);
     if (zero.overflow) { c.status = ST_ERR_SHAPE; return; }
     size_t lds = p.bf16 ? (size_t)64 * PACKV_PITCH * sizeof(bf16) : 0;
-    if (labels) lds = std::max(lds, (size_t)(q.CP * (LABEL_NCOL + 1) + 4) * sizeof(float));
+    if (labels) lds = std::max(lds, (size_t)(q.CP * LABEL_PITCH + 4) * sizeof(float));
     const int nb_zero = zero.n ? zero.first[zero.n] : 0;
     auto go = [&](auto kernel) {
         ST_LAUNCH(c, labels ? "pack+label_adjoint+params_in" : "pack+params_in", kernel,
-                  dim3(q.nb_pack + q.nb_label + q.nb_update_all + nb_zero), dim3(256), lds, q, a, zero);
+                  dim3(q.nb_label + q.nb_update_all + q.nb_pad + q.nb_pack + nb_zero), dim3(256), lds, q, a, zero);
     };
     if (p.bf16) go(k_call_begin<false>); else go(k_call_begin<true>);
 }

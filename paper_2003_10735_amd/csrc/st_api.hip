@@ -359,8 +359,8 @@ static int scratch_of_current_device(char** out)
 //    of and behind the positions need clearing;
 //  * float32: the guards of the two buffers that the weight-gradient kernel multiplies at shifted
 //    positions (with gradients that are zero there).
-// The padding of the operand copies is cleared by a launch of its own in front of it, where there is any.
-static ZeroList regions_to_clear(Ctx& c, const Plan& p, char* ws)
+// The padding of the operand copies is another role of that launch (pad_block).
+static ZeroList regions_to_clear(const Plan& p, char* ws)
 {
     ZeroList z;
     const Geo& g = p.g;
@@ -398,14 +398,6 @@ static ZeroList regions_to_clear(Ctx& c, const Plan& p, char* ws)
         z.add(ws + p.wq3 + g.C * row, (32 - g.C) * row);
     }
     z.add(ws + p.conf, (size_t)g.n * g.C * g.C * 8);
-    if (g.padded() || (!p.bf16 && (g.c_in % 32 || g.c1 % 32 || g.c2 % 32))) {
-        // the weights and biases of the channels beyond the caller's (the opening launch writes the others)
-        ZeroList w;
-        w.add(ws + p.wq1, p.bytes_w1); w.add(ws + p.wq2, p.bytes_w2); w.add(ws + p.wq3, p.bytes_w3);
-        if (p.wq1t) { w.add(ws + p.wq1t, p.bytes_w1t); w.add(ws + p.wq2t, p.bytes_w2t); w.add(ws + p.wq3t, p.bytes_w3t); }
-        w.add(ws + p.bq1, (size_t)cdiv(g.k1, 32) * 128); w.add(ws + p.bq2, (size_t)cdiv(g.k2, 32) * 128);
-        zero_regions(c, w);
-    }
     return z;
 }
 
@@ -522,7 +514,7 @@ static int head_forward_launches(const st_head_desc* desc, const Plan& p, const 
                                  float* logits_lowres, uint8_t* pred, char* ws, void* stream, bool no_profile)
 {
     Ctx c{as_stream(stream), ST_OK, no_profile};
-    const ZeroList zero = regions_to_clear(c, p, ws);
+    const ZeroList zero = regions_to_clear(p, ws);
     call_begin(c, p, ws, features, desc->feat_dtype, head_params, false, nullptr, nullptr, zero);
     float* z = logits_lowres ? logits_lowres : (float*)(ws + p.z);
     forward(c, p, ws);
@@ -709,7 +701,7 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
     double* metric_dev = (double*)(ws + p.scal);
     const CountSum count{(const unsigned int*)(ws + p.label_counts), label_blocks(g) / g.heads(), (unsigned long long*)(ws + p.counters)};
 
-    const ZeroList zero = regions_to_clear(c, p, ws);
+    const ZeroList zero = regions_to_clear(p, ws);
     if (mu != 0.f) permute_params(c, p, velocity, (float*)(ws + p.vel), 0);
     if (use_adam) {
         permute_params(c, p, adam_m, (float*)(ws + p.vel), 0);

@@ -8,7 +8,7 @@ struct FinishArgs;   // st_finish.hpp: arguments of the bookkeeping role
 
 // k_layout.hip
 // regions to clear, each 16-byte aligned and padded to 16 bytes (`count` of them, `stride` bytes apart);
-// one launch clears them all
+// a role of the launch that opens a call clears them all
 struct ZeroList {
     static constexpr int MAX = 24;
     char* ptr[MAX]; size_t stride[MAX]; unsigned n16[MAX]; int first[MAX + 1], per[MAX]; int n = 0; bool overflow = false;
@@ -31,7 +31,6 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
         if (i < z.n16[r]) p[i] = make_uint4(0, 0, 0, 0);
     }
 }
-void zero_regions(Ctx& c, const ZeroList& z);
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
 
 // k_conv_f32.hip -- the float32 path's kernels
