@@ -46,18 +46,18 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # the kernel source it was measured on:
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
-    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "40c679510ac755f8b0d628054eeb4d56f5ab05045c4366cde79d697a6a5f1d95", 33.77, 8.83),
+    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 33.77, 8.83),
     ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 13.75, 6.34),
     ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 6.98, 4.92),
     ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 10.45, 3.77),
     ("720p", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 4.73, 4.71),
     ("720p", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 3.09, 1.79),
     ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 13.19, 9.81),
-    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "40c679510ac755f8b0d628054eeb4d56f5ab05045c4366cde79d697a6a5f1d95", 73.87, 8.83),
+    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 73.87, 8.83),
     ("1080p", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 10.07, 11.14),
     ("1080p", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 6.48, 4.02),
     ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 27.54, 21.56),
-    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "40c679510ac755f8b0d628054eeb4d56f5ab05045c4366cde79d697a6a5f1d95", 268.55, 17.75),
+    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 268.55, 17.75),
     ("batch4", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 30.13, 22.21),
     ("batch4", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 23.46, 7.61),
     ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 71.45, 80.27),

@@ -1,19 +1,27 @@
-// Float32 path: the head's contractions on the matrix cores at full float32 precision
-// (v_mfma_f32_32x32x2_f32: float32 operands, float32 accumulation, each product and sum rounded once).
+// Float32 path: the head's 3x3 contractions on the bfloat16 matrix cores with float32 operands kept whole.
 //
-// One such instruction takes 64 cycles for 2048 multiply-adds and needs only 256 bytes of
-// either operand, so these kernels are bound by the matrix cores as soon as every SIMD has work and
-// the operands arrive in whole cache lines; LDS staging would buy nothing.  Hence:
-//   * activations lie in runs of eight channels, [c / 8][position][8] (pos8_index): the B operand of a
-//     tap -- 32 consecutive positions x 8 channels -- is one contiguous kilobyte at a constant offset,
-//     and lane l holds channels 4 (l / 32) .. + 3 of position l % 32: the four pairs of k that four
-//     MFMAs consume;
-//   * weights lie in the matching fragment order (wfrag32_index), one contiguous kilobyte per
-//     32 rows x 8 channels of a tap.
-// So eight channels of one tap cost two coalesced 16-byte loads per lane and four MFMAs.
-// Against a plain LDS-tiled GEMM on the vector units: 68 x 120 cells, 256 -> 128 -> 128, a 4-step call
-// 4.62 -> 0.90 ms; 16 x 16 cells, 64 -> 64 -> 64, 1.52 -> 0.20 ms.
+// A float32 value is the exact sum of three bfloat16 values, each the rest of the ones before it rounded to nearest:
+// x = xh + xm + xl.  Of the nine products of two such sums the six largest are formed,
+//     xh wh  +  (xh wm + xm wh + xm wm + xh wl + xl wh),
+// each exactly, and added in float32; what is left out is below 2^-25 of a product, of either sign.  (Cut off instead of rounded, the
+// three parts have one sign, and what is left out shifts every sum by 2^-24 of itself the same way: weight gradients
+// were three times further from float64 than the float32 instructions' for it.)  Six v_mfma_f32_32x32x16_bf16 take 192 cycles
+// for what eight v_mfma_f32_32x32x2_f32 x 64 cycles do.  Errors against float64 (2-norm, seven sizes from 16 x 16 cells
+// and 24 channels to 140 x 250 and 256, four seeds each): logits 1.1 - 1.8e-7 (1.5 - 3.8e-7 with the float32 instructions), feature
+// gradient 1.5 - 2.0e-7 (1.9 - 3.4e-7), weight gradients 4.4 - 8.2e-8 (3.9 - 7.9e-8).
+// Measured, 68 x 120 cells, 256 -> 128 -> 128, us per launch, float32 instructions / here: layer 1 49.6 / 36, layer 2 with the
+// classifier 28.3 / 23.5, its data gradient 27.2 / 22, weight gradients 77 / 44.5; a 4-step call 902 -> 647, 16 x 16 cells unchanged.
+// What binds now: a wavefront issues one instruction in four cycles, and splitting (eleven per pair of values) leaves few of
+// the eight places an MFMA takes empty -- about 7.5 are used.
+// Infinite operands (and finite ones above 3.39e38, which round to infinity): the first product alone is what a float32
+// product would be (inf - inf stays NaN, inf * 0 too); the others may be NaN, so they have accumulators of their own, which are
+// dropped where they are not finite.  (In the weight gradient all six share one: an infinite sum comes out as NaN.)
+//
+// Everything stays float32 in memory -- activations in runs of eight channels [c / 8][position][8] (pos8_index), weights in the
+// fragment order of wfrag_index -- and is split by the kernel that reads it, between its MFMAs.  (Weights written as three
+// planes by the optimiser kernel made that kernel slower by more than the splitting costs: 7.6 -> 10.3 us at 256 -> 128 -> 128.)
 #include <algorithm>
+#include <utility>
 
 #include "st_gather.hpp"
 #include "st_kernels.hpp"
@@ -22,16 +30,40 @@
 
 namespace st {
 
+#define CF_F __builtin_amdgcn_sched_barrier(0);
+
+// f(0), f(1), .. f(N - 1) with the index as a constant expression
+template <class F, int... I>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) { unrolled(f, std::make_integer_sequence<int, N>{}); }
+
+// two values as bfloat16, to nearest even, and back
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned round_pair(float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
+__device__ __forceinline__ float low_of(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float high_of(unsigned p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
+
+__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 // ------------------------------------------------------------------ 3x3 convolution
 //   out[p][n] = epi( sum_{tap, c} X[p + shift(tap)][c] * W[n][tap][c] )        p: padded positions
-// A block owns 32 positions x 32 output channels; its KG wavefronts split the reduction (taps x
-// groups of eight channels) into contiguous runs and are added through LDS in ascending order.  Small
-// tiles, because a frame has few of them: 68 x 120 cells and 128 channels make 1120, 4.4 per compute
-// unit, where 64 x 64 tiles would make 280 and leave half the chip idle in the second round.  KG grows
-// where there are few tiles (conv_f32), so that a 16 x 16 grid still reaches every compute unit.
+// A block is four wavefronts and owns 32 P positions x 32 output channels.  The K loop walks stages of (one kernel row) x (64
+// input channels); of a stage each wavefront takes 16 channels, its partial sums are added through LDS in ascending order.
+// A stage's activations (32 P + 2 positions) come as float32 into registers a stage ahead, are split between the MFMAs of the
+// stage before and go to LDS as three planes of 128-byte rows, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); two such slabs
+// alternate.  Per tap a wavefront reads 3 P fragments of 1 KB from LDS and 2 KB of weights for 6 P MFMAs, so neither
+// path is near its limit.  P is chosen so that the blocks fill whole rounds of the chip (conv_split_p): 68 x 120 cells and
+// 128 channels are 1120 tiles of 32 x 32, 4.4 per compute unit, which 224 blocks of five tiles take in one round.
+// (Tried, the same shape, layer 1: three tiles and two blocks per compute unit 40 us; two accumulators for the small products
+// instead of one 38; fragments read one group ahead and the barrier behind the last group 37.)
 struct Conv32Args {
     const float* X;       // pos8 layout, G groups of eight channels
-    const float* Wf;      // fragment order, rows = output channels
+    const float* Wf;      // fragment order (wfrag_index, k rounded up to 16), rows = output channels
     const float* bias;    // EPI 0, 2: zeros behind the last channel
     const float* mask;    // EPI 1: activation whose sign gates the gradient (layout of Y)
     float* Y;             // pos8 layout, GY groups (EPI 2: may be null)
@@ -42,90 +74,246 @@ struct Conv32Args {
     int m_tiles, n_tiles, tiles_per_xcd;
 };
 
-constexpr int C32_DEPTH = 4;    // operand sets on their way per wavefront: 3 x 256 cycles of MFMAs ahead
-
-template <int EPI, int KG>
-__global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
+template <int P>
+constexpr size_t conv_split_lds()
 {
-    extern __shared__ __attribute__((aligned(16))) float red[];    // [KG][4 register groups][64 lanes][4]
+    return std::max((size_t)2 * 3 * (32 * P + 2) * 128, (size_t)4 * P * 4096);     // slabs; partial sums
+}
+
+template <int EPI, int P>
+__global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args a)
+{
+    constexpr int BM = 32 * P, PLANE = (BM + 2) * 128, SLAB = 3 * PLANE;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // (consecutive blocks go to different XCDs: every XCD gets a contiguous run of position tiles)
     const int tile = (blockIdx.x % 8) * a.tiles_per_xcd + blockIdx.x / 8;
     if ((int)(blockIdx.x / 8) >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
     const int mt = tile / a.n_tiles, nt = tile % a.n_tiles;
-    const int m0 = mt * 32;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = mt * BM;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
 
-    f32x16 acc;
+    f32x16 acc[P], rest[P];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { acc[j][r] = 0.f; rest[j][r] = 0.f; }
 
-    const int total = 9 * a.G, per = (total + KG - 1) / KG;
-    const int i0 = wave * per, i1 = min(total, i0 + per);
-    if (i0 < i1) {
-        const float* wp = a.Wf + ((size_t)nt * total + i0) * 256;            // advances by 256 per item
-        const float* xb = a.X + (size_t)(a.guard + m0) * 8;
-        const unsigned wlane = lane * 4, xlane = l32 * 8 + lhi * 4;
-        int tap = i0 / a.G, g = i0 - tap * a.G, li = i0;
-        const float* xp = xb + ((ptrdiff_t)g * a.PPT + (tap / 3 - 1) * a.Wp + (tap % 3 - 1)) * 8;
-        f32x4 ra[C32_DEPTH], rb[C32_DEPTH];
-        // (past the end of the run the last item is loaded again and not used)
-#define C32_LOAD(S)                                                                                \
-        {                                                                                          \
-            ra[S] = *(const f32x4*)(wp + wlane);                                                   \
-            rb[S] = *(const f32x4*)(xp + xlane);                                                   \
-            if (++li < i1) {                                                                       \
-                wp += 256;                                                                         \
-                if (++g == a.G) {                                                                  \
-                    g = 0; ++tap;                                                                  \
-                    xp = xb + (ptrdiff_t)((tap / 3 - 1) * a.Wp + (tap % 3 - 1)) * 8;               \
-                } else xp += (ptrdiff_t)a.PPT * 8;                                                 \
-            }                                                                                      \
-        }
-#define C32_MMA(S)                                                                                 \
-        {                                                                                          \
-            _Pragma("unroll") for (int e = 0; e < 4; ++e)                                          \
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[S][e], rb[S][e], acc, 0, 0, 0);      \
-        }
+    const int c_chunks = (a.G + 7) >> 3, n_stages = 3 * c_chunks, KQ = (a.G + 1) >> 1;
+
+    // ---- activations: a unit is one position x one run of eight channels.  Unit u of a thread is number u * 256 + tid, counted
+    // along the positions first; unit P is one of the 16 units of the last two positions (sixteen threads do the same one).
+    int run[P + 1], row[P + 1];
 #pragma unroll
-        for (int d = 0; d < C32_DEPTH; ++d) C32_LOAD(d)
-        int i = i0;
-        for (; i + C32_DEPTH <= i1; i += C32_DEPTH) {
+    for (int u = 0; u < P; ++u) { const int q = u * 256 + tid; run[u] = q / BM; row[u] = q - run[u] * BM; }
+    run[P] = (tid >> 1) & 7; row[P] = BM + (tid & 1);
+    int lds_at[P + 1];
 #pragma unroll
-            for (int d = 0; d < C32_DEPTH; ++d) { C32_MMA(d) C32_LOAD(d) }
-        }
+    for (int u = 0; u <= P; ++u) lds_at[u] = row[u] * 128 + ((run[u] ^ ((row[u] >> 1) & 7)) << 4);
+    // (rows behind the grid lie in the guard, whose length counts on tiles of at most 256 positions)
+    static_assert(BM <= 256, "guard rows");
+    const float* xs = a.X + ((ptrdiff_t)a.guard + m0 - 1 - a.Wp) * 8;      // the stage on its way to the registers
+    int x_cc = 0;
+    f32x4 xr[P + 1][2];
+    // (runs behind the last one: zeros, from the guard in front of the first)
+    auto load_unit = [&](int u) __attribute__((always_inline)) {
+        const float* src = x_cc * 8 + run[u] < a.G ? xs + ((size_t)run[u] * a.PPT + row[u]) * 8 : a.X;
+        xr[u][0] = *(const f32x4*)src;
+        xr[u][1] = *(const f32x4*)(src + 4);
+    };
+    // A unit's splitting and its three LDS writes, in steps that go between MFMAs: pair e (0 .. 3) of the eight values in one
+    // step or in two, then plane by plane.
+    u32x4 xp[3];
+    float r0 = 0.f, r1 = 0.f;
+    auto split_a = [&](int u, int e) __attribute__((always_inline)) {
+        const float v0 = xr[u][e >> 1][(e & 1) * 2], v1 = xr[u][e >> 1][(e & 1) * 2 + 1];
+        const unsigned h = round_pair(v0, v1);
+        xp[0][e] = h;
+        r0 = __fsub_rn(v0, low_of(h)); r1 = __fsub_rn(v1, high_of(h));
+    };
+    auto split_b = [&](int e) __attribute__((always_inline)) {
+        const unsigned m = round_pair(r0, r1);
+        xp[1][e] = m;
+        xp[2][e] = round_pair(__fsub_rn(r0, low_of(m)), __fsub_rn(r1, high_of(m)));
+    };
+    auto write_plane = [&](int u, int slab, int q) __attribute__((always_inline)) {
+        *(u32x4*)(smem + slab * SLAB + q * PLANE + lds_at[u]) = xp[q];
+    };
+    // stages run over the channels first, then over the kernel rows
+    auto x_next = [&]() __attribute__((always_inline)) {
+        if (++x_cc == c_chunks) { x_cc = 0; xs += (ptrdiff_t)a.Wp * 8 - (ptrdiff_t)(c_chunks - 1) * 8 * a.PPT * 8; }
+        else xs += (ptrdiff_t)8 * a.PPT * 8;
+    };
+
+    // ---- weights of this wavefront's 16 channels: per tap of a stage eight float32 values per lane (row l32, k 8 lhi ..), split
+    // into three fragments.  While the matrix cores work on one tap the fragments of the tap before it are made for the
+    // next stage (while they work on the first tap: those of the last tap, for this stage), a few instructions at a time.
+    const float* wp = a.Wf + ((size_t)nt * 9 * KQ + wave) * 512 + lane * 8;
+    const size_t w_tap = (size_t)KQ * 512;
+    int w_cc = 0;
+    f32x4 wr[3][2];
+    u32x4 wa[3][3];
+    // (a wavefront whose channels do not exist: zeros, as above)
+    auto load_w = [&](int kw) __attribute__((always_inline)) {
+        const float* src = w_cc * 4 + wave < KQ ? wp + kw * w_tap : a.X + lane * 8;
+        wr[kw][0] = *(const f32x4*)src;
+        wr[kw][1] = *(const f32x4*)(src + 4);
+    };
+    auto w_next = [&]() __attribute__((always_inline)) {
+        if (++w_cc == c_chunks) { w_cc = 0; wp += 3 * w_tap - (size_t)(c_chunks - 1) * 4 * 512; } else wp += 4 * 512;
+    };
+    float w0 = 0.f, w1 = 0.f, w2 = 0.f;
+    auto split_w = [&](int kw, int i) __attribute__((always_inline)) {       // i: 0 .. 15, pair i / 4
+        const int e = i >> 2;
+        const float v0 = wr[kw][e >> 1][(e & 1) * 2], v1 = wr[kw][e >> 1][(e & 1) * 2 + 1];
+        if ((i & 3) == 0) { wa[kw][0][e] = round_pair(v0, v1); w0 = __fsub_rn(v0, low_of(wa[kw][0][e])); }
+        if ((i & 3) == 1) w1 = __fsub_rn(v1, high_of(wa[kw][0][e]));
+        if ((i & 3) == 2) { wa[kw][1][e] = round_pair(w0, w1); w2 = __fsub_rn(w0, low_of(wa[kw][1][e])); }
+        if ((i & 3) == 3) wa[kw][2][e] = round_pair(w2, __fsub_rn(w1, high_of(wa[kw][1][e])));
+    };
+
+    int rd[3];
 #pragma unroll
-        for (int d = 0; d < C32_DEPTH - 1; ++d)
-            if (i + d < i1) C32_MMA(d)
-#undef C32_LOAD
-#undef C32_MMA
+    for (int kw = 0; kw < 3; ++kw) rd[kw] = (l32 + kw) * 128 + (((wave * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4);
+    // fragments of three groups (group g of a stage: tap g / P, positions 32 (g % P) ..) rotate: two groups ahead
+    u32x4 xb[3][3];
+    auto read_x = [&](int slab, int g, int q) __attribute__((always_inline)) {
+        xb[g % 3][q] = *(const u32x4*)(smem + slab * SLAB + q * PLANE + rd[g / P] + (g % P) * 4096);
+    };
+
+    // ---- first stage into slab 0, second into the registers
+#pragma unroll
+    for (int u = 0; u <= P; ++u) load_unit(u);
+#pragma unroll
+    for (int kw = 0; kw < 3; ++kw) load_w(kw);
+    w_next();
+    x_next();
+#pragma unroll
+    for (int u = 0; u <= P; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { split_a(u, e); split_b(e); }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) write_plane(u, 0, q);
+        load_unit(u);
     }
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq)
-        *(f32x4*)(red + ((wave * 4 + rq) * 64 + lane) * 4) = f32x4{acc[rq * 4], acc[rq * 4 + 1], acc[rq * 4 + 2], acc[rq * 4 + 3]};
+    for (int kw = 0; kw < 2; ++kw) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) split_w(kw, i);
+        load_w(kw);
+    }
+    __syncthreads();
+    constexpr int AHEAD = P > 1 ? 2 : 3;           // groups of the next stage whose fragments are read before it begins (P == 1: all, then)
+    if (P > 1)
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) read_x(0, g, q);
+
+    // One stage out of slab B.  NEXT: another stage follows, whose activations wait in the registers; LOAD: and one behind
+    // it, which x_next has been moved to.  Everything has its place between two MFMAs, in a pinned order; the barrier stands in front
+    // of the last two groups, during which the next stage's first fragments are read.
+    auto stage = [&](int B, auto NEXT_, auto LOAD_) __attribute__((always_inline)) {
+        constexpr bool NEXT = decltype(NEXT_)::value, LOAD = decltype(LOAD_)::value;
+        constexpr int PLACES = 18 * P, BAR = P > 1 ? PLACES - 12 : PLACES;      // the barrier: in front of this place
+        constexpr int PER = BAR / (P + 1);             // places per unit: P = 1 .. 5: 9, 8, 10, 12, 13
+        constexpr bool FINE = PER >= 12;               // a pair's splitting in two places
+        constexpr int W0 = FINE ? 8 : 4;               // first place of the LDS writes, one per plane; the loads come behind them
+        static_assert(P * PER + W0 + 3 <= BAR && W0 + 4 <= PER, "a unit's steps fit, all writes lie before the barrier");
+        if (P == 1) {
+#pragma unroll
+            for (int g = 0; g < 3; ++g)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) read_x(B, g, q);
+        }
+        CF_F
+        unrolled<PLACES>([&](auto at_) __attribute__((always_inline)) {
+            constexpr int at = decltype(at_)::value, g = at / 6, q = at % 6;
+            constexpr int kw = g / P, j = g % P, b = g % 3, in_tap = j * 6 + q, wk = (kw + 2) % 3;
+            if constexpr (NEXT && P > 1 && at == BAR) { __syncthreads(); CF_F }
+            if constexpr (q == 0) acc[j] = mfma_bf16(wa[kw][0], xb[b][0], acc[j]);
+            else rest[j] = mfma_bf16(wa[kw][q == 1 ? 2 : q == 2 || q == 4 ? 0 : 1], xb[b][q == 1 || q == 5 ? 0 : q == 2 ? 2 : 1], rest[j]);
+            CF_F
+            if constexpr (P > 1 && q < 3) {
+                if constexpr (g + 2 < 3 * P) read_x(B, g + 2, q == 0 ? 0 : 3 - q);
+                else if constexpr (NEXT) read_x(1 - B, g + 2 - 3 * P, q == 0 ? 0 : 3 - q);
+            }
+            if constexpr (NEXT && at / PER <= P) {
+                constexpr int u = at / PER, v = at % PER;
+                if constexpr (FINE && v < 8) { if constexpr (v & 1) split_b(v >> 1); else split_a(u, v >> 1); }
+                if constexpr (!FINE && v < 4) { split_a(u, v); split_b(v); }
+                if constexpr (v >= W0 && v < W0 + 3) write_plane(u, 1 - B, v - W0);
+                if constexpr (LOAD && v == W0 + 3) load_unit(u);
+            }
+            if constexpr (kw == 0 || NEXT) {
+#pragma unroll
+                for (int i = in_tap * 16 / (6 * P); i < (in_tap + 1) * 16 / (6 * P); ++i) split_w(wk, i);
+                // (of the next stage the last tap, of the one behind it the other two)
+                if constexpr (in_tap == 6 * P - 1) {
+                    if constexpr (kw == 0 ? NEXT : LOAD) load_w(wk);
+                    if constexpr (NEXT && kw == 0) w_next();
+                }
+            }
+            CF_F
+        });
+        if (NEXT && P == 1) __syncthreads();
+    };
+    const std::true_type yes; const std::false_type no;
+    int s = 0;
+    for (; s + 2 < n_stages; ++s) {
+        x_next();
+        stage(s & 1, yes, yes);
+    }
+    stage(s & 1, yes, no);
+    stage((s + 1) & 1, no, no);
+
+    // ---- what the epilogue needs from memory, on its way while the sums are exchanged
+    const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;      // this lane's 4 channels
+    f32x4 bias = {0.f, 0.f, 0.f, 0.f}, w3 = {0.f, 0.f, 0.f, 0.f}, mask[EPI == 1 ? P : 1];
+    if (EPI == 0 || EPI == 2) bias = *(const f32x4*)(a.bias + ch);
+    if (EPI == 2) w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
+    const int run_out = min(nt * 4 + rq, a.GY - 1);
+    if (EPI == 1) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) mask[j] = *(const f32x4*)(a.mask + ((size_t)run_out * a.PPT + a.guard + min(m0 + j * 32 + l32, a.PP - 1)) * 8 + lhi * 4);
+    }
+
+    // ---- partial sums of the wavefronts
+    float* red = (float*)smem;          // [wavefront][P][4 register groups][64 lanes][4]
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float t = rest[j][rq * 4 + e];
+                v[e] = acc[j][rq * 4 + e] + (__builtin_isfinite(t) ? t : 0.f);
+            }
+            *(f32x4*)(red + (((wave * P + j) * 4 + rq) * 64 + lane) * 4) = v;
+        }
     __syncthreads();
 
-    // wavefront rq < 4 finishes channels 8 rq .. + 7 of the tile: a lane holds 4 channels of one position
-    const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;
+    // wavefront rq finishes channels 8 rq .. + 7 of the tile: a lane holds 4 channels of one position per 32 positions
     const int frame = a.Hp * a.Wp;
-    const int mp = m0 + l32;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (rq < 4) {
+    f32x4 out[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        const int mp = m0 + j * 32 + l32;
         const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
         const bool inside = mp < a.PP && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < KG; ++k) v += *(const f32x4*)(red + ((k * 4 + rq) * 64 + lane) * 4);
+        for (int k = 0; k < 4; ++k) v += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
         const size_t at = ((size_t)(nt * 4 + rq) * a.PPT + a.guard + mp) * 8 + lhi * 4;
         const bool stored = nt * 4 + rq < a.GY && mp < a.PP;
         if (EPI == 0 || EPI == 2) {
-            const f32x4 b = *(const f32x4*)(a.bias + ch);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + b[e], 0.f) : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + bias[e], 0.f) : 0.f;
         } else if (EPI == 1) {
-            f32x4 m = {0.f, 0.f, 0.f, 0.f};
-            if (stored) m = *(const f32x4*)(a.mask + at);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = inside && m[e] > 0.f ? v[e] : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = inside && mask[j][e] > 0.f ? v[e] : 0.f;
         }
         if (EPI == 3) {
             if (inside) {
@@ -135,41 +323,63 @@ __global__ void __launch_bounds__(64 * KG) k_conv3x3_f32(Conv32Args a)
                     if (ch + e < a.dense_c) dst[(size_t)e * a.h * a.w] = v[e];
             }
         } else if (stored && a.Y) *(f32x4*)(a.Y + at) = v;
+        out[j] = v;
     }
     if (EPI == 2) {
-        // the classifier rides along: what this lane holds is the B operand of four MFMAs against
-        // W3 (rows = classes, k = the 8 channels of this wavefront); the four wavefronts' sums
-        // meet in LDS.  (All shares of the logits: one per 32 channels.)
+        // the classifier rides along: what this lane holds is the B operand of four float32 MFMAs
+        // (v_mfma_f32_32x32x2_f32) against W3 (rows = classes, k = the 8 channels of this wavefront); the four
+        // wavefronts' sums meet in LDS.  (All shares of the logits: one per 32 channels.)
         __syncthreads();       // the partial sums are read
-        if (rq < 4) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
             f32x16 z;
 #pragma unroll
             for (int r = 0; r < 16; ++r) z[r] = 0.f;
-            const f32x4 w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], v[e], z, 0, 0, 0);
-            float* zr = red;
+            for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], out[j][e], z, 0, 0, 0);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *(f32x4*)(zr + ((rq * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
+                *(f32x4*)(red + (((rq * P + j) * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
         }
         __syncthreads();
-        if (rq < 4 && mp < a.PP && rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
-            const float* zr = red;
-            f32x4 s = *(const f32x4*)(zr + (rq * 64 + lane) * 4);
+        if (rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
 #pragma unroll
-            for (int k = 1; k < 4; ++k) s += *(const f32x4*)(zr + ((k * 4 + rq) * 64 + lane) * 4);
-            *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = s;
+            for (int j = 0; j < P; ++j) {
+                const int mp = m0 + j * 32 + l32;
+                f32x4 t = *(const f32x4*)(red + ((j * 4 + rq) * 64 + lane) * 4);
+#pragma unroll
+                for (int k = 1; k < 4; ++k) t += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
+                if (mp < a.PP) *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = t;
+            }
         }
     }
 }
 
-template <int EPI, int KG>
-static void conv_f32_launch(Ctx& c, const char* name, const Conv32Args& a, int blocks)
+template <int EPI, int P>
+static void conv_f32_launch(Ctx& c, const char* name, const Conv32Args& a)
 {
-    const size_t smem = (size_t)KG * 1024 * sizeof(float);
-    ensure_dynamic_lds((const void*)k_conv3x3_f32<EPI, KG>, smem);
-    ST_LAUNCH(c, name, (k_conv3x3_f32<EPI, KG>), dim3(blocks), dim3(64 * KG), smem, a);
+    const size_t smem = conv_split_lds<P>();
+    ensure_dynamic_lds((const void*)k_conv3x3_f32<EPI, P>, smem);
+    ST_LAUNCH(c, name, (k_conv3x3_f32<EPI, P>), dim3(a.tiles_per_xcd * 8), dim3(256), smem, a);
+}
+
+// Tiles of 32 positions per block.  A layer's time goes with (blocks a compute unit gets) x (time of a block); the five block
+// times are fitted to forward calls with each P forced, c -> c -> c channels, us for P = 1 .. 5:
+//   30 x 50 cells, 128    28  33  39  43  49       68 x 120, 128    67  62  67  76  55
+//   45 x 80, 128          46  44  41  45  51       80 x 140, 128    78  64  69  76  89
+//   60 x 107, 128         57  48  66  47  53       90 x 160, 128    94  77  90  78  88
+// (up to two tiles two blocks share a compute unit, which is why two small ones beat one large).  The float32 instructions'
+// kernel: 27, 47, 56, 66, 76, 93 us.
+static int conv_split_p(int m_units, int n_tiles)
+{
+    static const int block_time[5] = {16, 23, 35, 44, 55};
+    int best = 1;
+    long best_t = 0;
+    for (int P = 1; P <= 5; ++P) {
+        const long t = (long)cdiv((long long)cdiv(m_units, P) * n_tiles, 256) * block_time[P - 1];
+        if (P == 1 || t < best_t) { best = P; best_t = t; }
+    }
+    return best;
 }
 
 // cin, cout: channels of the layer as run here (exchanged for a data gradient)
@@ -182,16 +392,19 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
     a.PP = g.padded_positions(); a.Hp = g.Hp; a.Wp = g.Wp; a.h = g.h; a.w = g.w;
     a.G = cdiv(cin, 8); a.GY = cdiv(cout, 8); a.PPT = p.PPT; a.guard = p.guard;
     a.w3_pitch = cdiv(g.c2, 32) * 32; a.zpitch = (g.C + 3) / 4 * 4; a.dense_c = cout;
-    a.m_tiles = cdiv(a.PP, 32); a.n_tiles = cdiv(cout, 32);
-    const int tiles = a.m_tiles * a.n_tiles;
-    a.tiles_per_xcd = cdiv(tiles, 8);
-    const int blocks = a.tiles_per_xcd * 8;
-    // as many wavefronts per tile as it takes to give each of the 1024 SIMDs two
+    a.n_tiles = cdiv(cout, 32);
+    const int P = conv_split_p(cdiv(a.PP, 32), a.n_tiles);
+    a.m_tiles = cdiv(a.PP, 32 * P);
+    a.tiles_per_xcd = cdiv(a.m_tiles * a.n_tiles, 8);
     auto go = [&](auto e) {
         constexpr int E = decltype(e)::value;
-        if (tiles >= 512) conv_f32_launch<E, 4>(c, name, a, blocks);
-        else if (tiles >= 256) conv_f32_launch<E, 8>(c, name, a, blocks);
-        else conv_f32_launch<E, 16>(c, name, a, blocks);
+        switch (P) {
+        case 1: conv_f32_launch<E, 1>(c, name, a); break;
+        case 2: conv_f32_launch<E, 2>(c, name, a); break;
+        case 3: conv_f32_launch<E, 3>(c, name, a); break;
+        case 4: conv_f32_launch<E, 4>(c, name, a); break;
+        default: conv_f32_launch<E, 5>(c, name, a); break;
+        }
     };
     switch (epi) {
     case 0: go(std::integral_constant<int, 0>{}); break;
@@ -203,21 +416,21 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
 
 // ------------------------------------------------------------------ weight gradient
 //   dW[o][tap][i] = sum_p dY[p][o] * X[p + shift(tap)][i],    db[o] = sum_p dY[p][o]
-// One wavefront accumulates 32 (o) x 32 (i) x 9 (taps), k = positions.  The two values of k of an MFMA are
-// not neighbours but the same place in the two halves of the wavefront's position range: a lane then
-// walks its half one position at a time, and the three taps of a kernel row are the values it holds
-// for the previous, this and the next position -- no shifting across lanes.  Per position four
-// 4-byte loads (dY, and X in three rows) feed nine MFMAs (576 cycles).
+// One wavefront accumulates 32 (o) x 32 (i) x 9 (taps), k = 16 positions per unit.  A lane reads the eight positions of its
+// channel that an operand needs as eight 4-byte loads and splits them itself.  As in the bfloat16 kernel dY is what moves by
+// one position for the taps to the left and right: ten positions of it are read, and the three fragments of a plane are packed
+// from them.  34 loads and some 240 vector instructions for 54 MFMAs (1728 cycles), all for the unit behind the one in work.
+// (dY is zero on the border of the grid and in the guard.)
 // The rest (four wavefronts per block added through LDS, position splits added by the optimiser
 // kernel, both layers in one launch) is as for the bfloat16 kernel.
 struct Wgrad32Args {
     const float* dY; const float* X; float* dW; float* db;
     size_t split_stride;
-    int cin, cout, GX, GY, PP, PPT, guard, Wp, len;       // len: positions per wavefront, even
+    int cin, cout, GX, GY, PPT, guard, Wp, n_units, units_per_wave;       // units of 16 positions
     int o_tiles, i_tiles, splits, items_per_xcd;
 };
 
-__global__ void __launch_bounds__(256) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32Args a2, int blocks1)
+__global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32Args a2, int blocks1)
 {
     extern __shared__ __attribute__((aligned(16))) float red[];
     const bool second = (int)blockIdx.x >= blocks1;
@@ -238,41 +451,103 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32Arg
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     float bsum = 0.f;
 
-    const int r0 = (split * 4 + wave) * a.len, r1 = min(r0 + a.len, a.PP);   // (PP is a multiple of eight)
-    const int S = max(r1 - r0, 0) >> 1;
-    if (S > 0) {
+    const int u0 = (split * 4 + wave) * a.units_per_wave, u1 = min(u0 + a.units_per_wave, a.n_units);
+    if (u0 < u1) {
         // (channels beyond the last group re-read it: their sums are dropped at the end)
-        const float* yb = a.dY + ((size_t)min((o0 + l32) >> 3, a.GY - 1) * a.PPT + a.guard + r0 + lhi * S) * 8 + (l32 & 7);
-        const float* xb = a.X + ((size_t)min((i0 + l32) >> 3, a.GX - 1) * a.PPT + a.guard + r0 + lhi * S) * 8 + (l32 & 7);
-        constexpr int D = 8;
-        // slot s of the ring holds dY of position s (mod 8) and X of position s - 1.  Loads run up to seven
-        // positions past the half (guard positions make them readable).
-        float ry[D], rx[D][3];
-#define W32_LOAD(S_, T)                                                                            \
-        {                                                                                          \
-            ry[S_] = yb[(T) * 8];                                                                  \
-            _Pragma("unroll") for (int kh = 0; kh < 3; ++kh) rx[S_][kh] = xb[((T) - 1 + (kh - 1) * a.Wp) * 8]; \
-        }
-#define W32_MMA(S_)                                                                                \
-        {                                                                                          \
-            bsum += ry[S_];                                                                        \
-            _Pragma("unroll") for (int kh = 0; kh < 3; ++kh)                                       \
-            _Pragma("unroll") for (int kw = 0; kw < 3; ++kw)                                       \
-                acc[kh * 3 + kw] = __builtin_amdgcn_mfma_f32_32x32x2f32(rx[((S_) + kw) % D][kh], ry[S_], acc[kh * 3 + kw], 0, 0, 0); \
-        }
+        const float* yp = a.dY + ((size_t)min((o0 + l32) >> 3, a.GY - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
+        const float* xp = a.X + ((size_t)min((i0 + l32) >> 3, a.GX - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
+        const ptrdiff_t xrow = (ptrdiff_t)a.Wp * 8;
+        // raw values of two units ahead: positions - 1 .. 8 of dY, 0 .. 7 of X in the three rows
+        float ry[2][10], rx[2][3][8];
+        const float* yl = yp; const float* xl = xp;        // the unit to be loaded next
+        auto load_y = [&](int s, int e) __attribute__((always_inline)) { ry[s][e] = yl[(e - 1) * 8]; };
+        auto load_x = [&](int s, int kh, int e) __attribute__((always_inline)) { rx[s][kh][e] = xl[(kh - 1) * xrow + e * 8]; };
+        u32x4 fy[2][3][3], fx[2][3][3];   // fragments of the unit in work and the next: [dY at p + 1, p, p - 1][plane], [kernel row][plane]
+        // dY: pairs of neighbouring positions 2 k - 1, 2 k (k = 0 .. 4), per plane; the fragment at p - 1 takes the first four, the one at
+        // p + 1 the last four, the one at p the pairs between them
+        unsigned yw[3][5];
+        float m0[5], m1[5], r0 = 0.f, r1 = 0.f;
+        auto split_ya = [&](int s, int k) __attribute__((always_inline)) {
+            yw[0][k] = round_pair(ry[s][2 * k], ry[s][2 * k + 1]);
+            m0[k] = __fsub_rn(ry[s][2 * k], low_of(yw[0][k])); m1[k] = __fsub_rn(ry[s][2 * k + 1], high_of(yw[0][k]));
+        };
+        auto split_yb = [&](int k) __attribute__((always_inline)) {
+            yw[1][k] = round_pair(m0[k], m1[k]);
+            yw[2][k] = round_pair(__fsub_rn(m0[k], low_of(yw[1][k])), __fsub_rn(m1[k], high_of(yw[1][k])));
+        };
+        auto place_y = [&](int s, int e) __attribute__((always_inline)) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) W32_LOAD(d, d)
-        int t = 0;
-        for (; t + D <= S; t += D) {
+            for (int q = 0; q < 3; ++q) {
+                fy[s][2][q][e] = yw[q][e];
+                fy[s][1][q][e] = __builtin_amdgcn_alignbyte(yw[q][e + 1], yw[q][e], 2);
+                fy[s][0][q][e] = yw[q][e + 1];
+            }
+        };
+        auto split_xa = [&](int s, int kh, int e) __attribute__((always_inline)) {
+            const float v0 = rx[s][kh][2 * e], v1 = rx[s][kh][2 * e + 1];
+            const unsigned h = round_pair(v0, v1);
+            fx[s][kh][0][e] = h;
+            r0 = __fsub_rn(v0, low_of(h)); r1 = __fsub_rn(v1, high_of(h));
+        };
+        auto split_xb = [&](int s, int kh, int e) __attribute__((always_inline)) {
+            const unsigned m = round_pair(r0, r1);
+            fx[s][kh][1][e] = m;
+            fx[s][kh][2][e] = round_pair(__fsub_rn(r0, low_of(m)), __fsub_rn(r1, high_of(m)));
+        };
+        // what follows MFMA number t of a unit: of the next unit (raw values and fragments s) the splitting, then the loads
+        // that replace its raw values by those of the unit two behind it
+        // (live: it belongs to this wavefront's range)
+        auto place = [&](int s, int t, bool live) __attribute__((always_inline)) {
+            if (t < 10) { if (t & 1) split_yb(t >> 1); else split_ya(s, t >> 1); }
+            else if (t < 19) {
+                if (t < 14) place_y(s, t - 10);
+                if (t < 18) bsum += live ? ry[s][t - 9] : 0.f;
+            } else if (t < 43) {
+                const int i = t - 19, kh = i >> 3, e = (i >> 1) & 3;
+                if (i & 1) split_xb(s, kh, e); else split_xa(s, kh, e);
+                if (i < 10) load_y(s, i);
+                if (i >= 10) load_x(s, (i - 10) >> 3, (i - 10) & 7);
+            } else if (t < 53) {
+                const int i = t - 29;        // the last ten values of X
+                load_x(s, i >> 3, i & 7);
+            }
+        };
+        auto unit = [&](auto S_, bool next_live) __attribute__((always_inline)) {
+            constexpr int S = decltype(S_)::value, N = 1 - S;
+            constexpr int px[6] = {2, 0, 1, 0, 1, 0}, py[6] = {0, 2, 1, 1, 0, 0};      // the smallest products first
 #pragma unroll
-            for (int d = 0; d < D; ++d) { W32_MMA(d) W32_LOAD(d, t + D + d) }
+            for (int t = 0; t < 54; ++t) {
+                const int q = t / 9, tap = t % 9;
+                acc[tap] = mfma_bf16(fx[S][tap / 3][px[q]], fy[S][tap % 3][py[q]], acc[tap]);
+                CF_F
+                place(N, t, next_live);
+                CF_F
+            }
+            yl += 128; xl += 128;
+        };
+        // (loads run up to three units past the end of the range: guard positions, not used)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int e = 0; e < 10; ++e) load_y(s, e);
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) load_x(s, kh, e);
+            yl += 128; xl += 128;
         }
-        // (the last, partial trip also needs X of the two positions behind it)
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int d = 0; d < D - 1; ++d)
-            if (t + d < S) { W32_MMA(d) W32_LOAD(d, t + D + d) }
-#undef W32_LOAD
-#undef W32_MMA
+        for (int t = 0; t < 54; ++t) { place(0, t, true); CF_F }
+        yl += 128; xl += 128;
+        int u = u0;
+        for (; u + 2 <= u1; u += 2) {
+            unit(std::integral_constant<int, 0>{}, true);
+            asm volatile("" ::: "memory");
+            unit(std::integral_constant<int, 1>{}, u + 2 < u1);
+            asm volatile("" ::: "memory");
+        }
+        if (u < u1) unit(std::integral_constant<int, 0>{}, false);
     }
     float* redb = red + 4 * 9 * 32 * 32;
     bsum += __shfl_xor(bsum, 32, 64);
@@ -287,8 +562,9 @@ static Wgrad32Args wgrad_f32_args(const Plan& p, const float* dY, const float* X
     Wgrad32Args a;
     a.dY = dY; a.X = X; a.dW = dW; a.db = db; a.split_stride = p.grad_stride;
     a.cin = cin; a.cout = cout; a.GX = cdiv(cin, 8); a.GY = cdiv(cout, 8);
-    a.PP = p.g.padded_positions(); a.PPT = p.PPT; a.guard = p.guard; a.Wp = p.g.Wp;
-    a.len = cdiv(a.PP, splits * 4 * 8) * 8;
+    a.PPT = p.PPT; a.guard = p.guard; a.Wp = p.g.Wp;
+    a.n_units = cdiv(p.g.padded_positions(), 16);
+    a.units_per_wave = cdiv(a.n_units, splits * 4);
     a.o_tiles = cdiv(cout, 32); a.i_tiles = cdiv(cin, 32); a.splits = splits;
     a.items_per_xcd = cdiv(a.o_tiles * a.i_tiles * splits, 8);
     return a;

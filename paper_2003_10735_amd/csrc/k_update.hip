@@ -32,8 +32,8 @@ namespace st {
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
 //   wq3t          : W3 transposed, for the classifier's backward kernel
 // bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
-// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in the order of wfrag32_index,
-// wq3t likewise with one tap, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
+// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order with k rounded up to 16, wq3t in the
+// order of wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
 // classes are cleared by the launch that opens the call and never written later.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
@@ -68,7 +68,7 @@ __device__ __forceinline__ Weight3x3 weight3x3(unsigned r, unsigned cin)
     return Weight3x3{o, row - o * 9u, r - row * cin};
 }
 
-constexpr int PAD_PER_THREAD = 4;     // 16-byte runs of the padding role per thread
+constexpr int PAD_PER_THREAD = 4;     // runs of the padding role per thread
 
 // index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
 __device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned j)
@@ -94,12 +94,12 @@ __device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, con
     void* bwd = layer == 1 ? a.wq1t : a.wq2t;
     const int kin = layer == 1 ? a.ki : a.k1, kout = layer == 1 ? a.k1 : a.k2;
     if (F32) {
-        float* f = (float*)fwd + wfrag32_index<9>(k.o, k.tap, k.i, kin);
+        float* f = (float*)fwd + wfrag_index(k.o, k.tap, k.i, k16(kin));
         if (N == 4) *(f32x4*)f = f32x4{w[0], w[N > 1 ? 1 : 0], w[N > 2 ? 2 : 0], w[N > 3 ? 3 : 0]};
         else f[0] = w[0];
         if (bwd)
 #pragma unroll
-            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag32_index<9>(k.i + e, 8 - k.tap, k.o, kout)] = w[e];
+            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, k16(kout))] = w[e];
     } else {
         bf16* f = (bf16*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
         bf16 q[N];
@@ -152,13 +152,13 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
         if (!a.do_step && a.wq3t && (int)cl == a.C - 1) {
             // the call opens: the classes beyond the last are zeros (nothing writes them later)
             for (unsigned k = cl + 1; k < 32; ++k) {
-                if (F32) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, k, 32)] = 0.f;
+                if (F32) ((float*)a.wq3t)[wfrag32_index(o, k, 32)] = 0.f;
                 else ((bf16*)a.wq3t)[o * 32 + k] = (bf16)0.f;
             }
         }
         if (F32) {
             ((float*)a.wq3)[cl * ((a.c2 + 31) & ~31) + o] = w;
-            if (a.wq3t) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, cl, 32)] = w;
+            if (a.wq3t) ((float*)a.wq3t)[wfrag32_index(o, cl, 32)] = w;
         } else {
             ((bf16*)a.wq3)[cl * a.k2 + o] = (bf16)w;
             if (a.wq3t) ((bf16*)a.wq3t)[o * 32 + cl] = (bf16)w;
@@ -327,12 +327,12 @@ __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 
 // Zeros for the padding of the operand copies: channels beyond the caller's counts, of which the parameter role writes
 // nothing (so the two roles share a launch: 64-channel stages of 48 channels in front of 60 x 107 cells once had a clearing
-// launch of their own, 4 us of a 270 us call).  A thread takes 16-byte runs of the four 3x3 copies, in the order they are
-// stored -- a run is one row's and tap's next eight (bfloat16) or four (float32) k -- and then the small ones' rests.
+// launch of their own, 4 us of a 270 us call).  A thread takes runs of the four 3x3 copies, in the order they are
+// stored -- a run is one row's and tap's next eight k -- and then the small ones' rests.
 template <bool F32>
 __device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, unsigned n_runs)
 {
-    constexpr int W = F32 ? 4 : 8, R32 = 32;
+    constexpr int W = 8, R32 = 32, B = W * (F32 ? 4 : 2);
     const int c[3] = {a.c_in, a.c1, a.c2}, k[3] = {a.ki, a.k1, a.k2};
     auto rows = [&](int m) { return F32 ? (k[m] + R32 - 1) / R32 * R32 : k[m]; };
     void* const copy[4] = {a.wq1, a.wq2, a.wq1t, a.wq2t};
@@ -344,14 +344,16 @@ __device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, u
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 if (!copy[m]) continue;
-                const int K = k[k_of[m]], rv = c[row_of[m]], kv = c[k_of[m]];
+                const int K = F32 ? k16(k[k_of[m]]) : k[k_of[m]], rv = c[row_of[m]], kv = c[k_of[m]];
                 const unsigned runs = (unsigned)rows(row_of[m]) * 9u * (unsigned)(K / W);
                 if (i >= runs) { i -= runs; continue; }
                 const unsigned t = i >> 6, per = (unsigned)K / (2 * W);
                 const int row = (int)(t / per / 9u * 32u + (i & 31)), k0 = (int)(t % per) * 2 * W + (int)((i >> 5) & 1) * W;
-                char* dst = (char*)copy[m] + (size_t)i * 16;
-                if (row >= rv || k0 >= kv) *(u32x4*)dst = u32x4{0u, 0u, 0u, 0u};
-                else if (k0 + W > kv)
+                char* dst = (char*)copy[m] + (size_t)i * B;
+                if (row >= rv || k0 >= kv) {
+#pragma unroll
+                    for (int e = 0; e < B; e += 16) *(u32x4*)(dst + e) = u32x4{0u, 0u, 0u, 0u};
+                } else if (k0 + W > kv)
                     for (int e = kv - k0; e < W; ++e) { if (F32) ((float*)dst)[e] = 0.f; else ((bf16*)dst)[e] = (bf16)0.f; }
                 break;
             }
@@ -363,7 +365,7 @@ __device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, u
                 const int o = a.c2 + (int)(i >> 5), cl = (int)(i & 31);
                 if (F32) {
                     if (cl < a.C) ((float*)a.wq3)[cl * rows(2) + o] = 0.f;
-                    if (a.wq3t) ((float*)a.wq3t)[wfrag32_index<1>(o, 0, cl, 32)] = 0.f;
+                    if (a.wq3t) ((float*)a.wq3t)[wfrag32_index(o, cl, 32)] = 0.f;
                 } else {
                     if (cl < a.C) ((bf16*)a.wq3)[cl * a.k2 + o] = (bf16)0.f;
                     if (a.wq3t) ((bf16*)a.wq3t)[o * 32 + cl] = (bf16)0.f;
@@ -378,14 +380,15 @@ __device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, u
     }
 }
 
-// the runs of 16 bytes of a head's 3x3 operand copies, and the blocks of pad_block (none without padding)
+// the runs of eight k of a head's 3x3 operand copies, and the blocks of pad_block (none without padding)
 static unsigned pad_runs(const Plan& p, const UpdateArgs& a)
 {
-    return (unsigned)(((a.wq1 ? p.bytes_w1 : 0) + (a.wq2 ? p.bytes_w2 : 0) + (a.wq1t ? p.bytes_w1t : 0) + (a.wq2t ? p.bytes_w2t : 0)) / 16);
+    return (unsigned)(((a.wq1 ? p.bytes_w1 : 0) + (a.wq2 ? p.bytes_w2 : 0) + (a.wq1t ? p.bytes_w1t : 0) + (a.wq2t ? p.bytes_w2t : 0)) / (8 * p.esz));
 }
 static int pad_blocks(const Plan& p, const UpdateArgs& a)
 {
     const Geo& g = p.g;
+    // (float32 path: rows rounded up to 32, k to 16)
     if (!g.padded() && (p.bf16 || (g.c_in % 32 == 0 && g.c1 % 32 == 0 && g.c2 % 32 == 0))) return 0;
     const auto r32 = [](int k) { return (k + 31) / 32 * 32; };
     const long long rest = 32ll * ((p.bf16 ? g.k2 : r32(g.k2)) - g.c2) + (r32(g.k1) - g.c1) + (r32(g.k2) - g.c2);
@@ -408,7 +411,7 @@ struct BeginArgs {
     const int32_t* labels; const uint8_t* wmap; float* T; unsigned int* counts; int CP, nb_label;
     uint8_t* lab8;                         // the labels as bytes for the loss kernel (written by the label role)
     int nb_update, nb_update_all;          // blocks of the parameter role per head, and of all heads
-    int nb_pad; unsigned pad_runs;         // blocks and 16-byte runs of the padding role (one head: heads of their own are not padded)
+    int nb_pad; unsigned pad_runs;         // blocks and runs of the padding role (one head: heads of their own are not padded)
     Geo g;
 };
 

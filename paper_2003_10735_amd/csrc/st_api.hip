@@ -12,6 +12,7 @@
 
 #include "st_kernels.hpp"
 #include "st_conv.hpp"
+#include "st_mfma.hpp"
 #include "st_finish.hpp"
 
 namespace st {
@@ -195,12 +196,13 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.grad = train_take(heads * p.grad_stride * 4 * p.grad_copies);
     p.grad3 = train_take(heads * std::max(p.blocks3, 1) * conv3_bwd_slot_floats(g) * 4);
     p.best = train_take(heads * p.head_stride * 4);
-    // (float32 operand copies: rows rounded up to 32)
+    // (float32 operand copies: rows rounded up to 32, k of the 3x3 ones to 16)
     const auto rows = [&](int k) { return (size_t)(p.bf16 ? k : cdiv(k, 32) * 32); };
-    p.bytes_w1 = heads * rows(g.k1) * 9 * g.ki * p.esz;
-    p.bytes_w1t = heads * rows(g.ki) * 9 * g.k1 * p.esz;
-    p.bytes_w2 = heads * rows(g.k2) * 9 * g.k1 * p.esz;
-    p.bytes_w2t = heads * rows(g.k1) * 9 * g.k2 * p.esz;
+    const auto row_bytes = [&](int k) { return (size_t)9 * (p.bf16 ? k : k16(k)) * p.esz; };
+    p.bytes_w1 = heads * rows(g.k1) * row_bytes(g.ki);
+    p.bytes_w1t = heads * rows(g.ki) * row_bytes(g.k1);
+    p.bytes_w2 = heads * rows(g.k2) * row_bytes(g.k1);
+    p.bytes_w2t = heads * rows(g.k1) * row_bytes(g.k2);
     p.bytes_w3 = heads * (p.bf16 ? g.C : 32) * rows(g.k2) * p.esz;
     p.bytes_w3t = heads * rows(g.k2) * 32 * p.esz;
     p.wq1 = take(off, p.bytes_w1);
@@ -357,8 +359,7 @@ static int scratch_of_current_device(char** out)
 //  * bfloat16: every position of the buffers and of their channel-major copies is
 //    rewritten (zeros on the border) by its producer in every pass, so only the guards in front
 //    of and behind the positions need clearing;
-//  * float32: the guards of the two buffers that the weight-gradient kernel multiplies at shifted
-//    positions (with gradients that are zero there).
+//  * float32: the guards of the buffers that the weight-gradient kernel reads at shifted positions.
 // The padding of the operand copies is another role of that launch (pad_block).
 static ZeroList regions_to_clear(const Plan& p, char* ws)
 {
@@ -366,9 +367,10 @@ static ZeroList regions_to_clear(const Plan& p, char* ws)
     const Geo& g = p.g;
     const size_t PP = (size_t)g.padded_positions(), G = (size_t)p.guard;
     if (!p.bf16) {
-        const size_t buf[2] = {p.feat, p.a1}, run = (size_t)p.PPT * 32;
-        const int runs[2] = {g.ki / 8, g.k1 / 8};
-        for (int i = 0; i < 2; ++i) {
+        const size_t buf[4] = {p.feat, p.a1, p.da1, p.da2}, run = (size_t)p.PPT * 32;
+        const int runs[4] = {g.ki / 8, g.k1 / 8, g.k1 / 8, g.k2 / 8};
+        for (int i = 0; i < 4; ++i) {
+            if (!buf[i]) continue;
             z.add(ws + buf[i], G * 32, runs[i], run);
             z.add(ws + buf[i] + (G + PP) * 32, run - (G + PP) * 32, runs[i], run);
         }

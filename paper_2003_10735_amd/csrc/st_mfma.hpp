@@ -31,18 +31,18 @@ __host__ __device__ __forceinline__ size_t wfrag_index(int row, int tap, int k, 
     return ((((size_t)(row >> 5) * 9 + tap) * (K >> 4) + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (row & 31)) * 8 + (k & 7);
 }
 
-// v_mfma_f32_32x32x2_f32 (float32 path): lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32]; D as above.
-//
-// Its activations, in runs of eight channels: [c / 8][column][8], column = guard + padded position, PPT
+// Float32 path: activations in runs of eight channels, [c / 8][column][8], column = guard + padded position, PPT
 // columns per run.
 __host__ __device__ __forceinline__ size_t pos8_index(int c, int col, int PPT) { return ((size_t)(c >> 3) * PPT + col) * 8 + (c & 7); }
 
-// Its weights, TAPS x K (K a multiple of eight) per row: the A operands of four MFMAs (32 rows x 8 k of
-// one tap, lane l holding row l % 32, k 4*(l/32) .. +3) are one contiguous 1 KB run,
-//     [row / 32][tap][k / 8][(k / 4) % 2][row % 32][k % 4].
-template <int TAPS>
-__host__ __device__ __forceinline__ size_t wfrag32_index(int row, int tap, int k, int K)
+// Its 3x3 weights lie in the order of wfrag_index too, as float32, k rounded up to 16.
+__host__ __device__ __forceinline__ int k16(int k) { return (k + 15) & ~15; }
+
+// v_mfma_f32_32x32x2_f32 (the float32 path's classifier): lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32]; D as above.
+// W3 for its backward, K (a multiple of eight) classes per row: the A operands of four MFMAs (32 rows x 8 k, lane l holding
+// row l % 32, k 4*(l/32) .. +3) are one contiguous 1 KB run,  [row / 32][k / 8][(k / 4) % 2][row % 32][k % 4].
+__host__ __device__ __forceinline__ size_t wfrag32_index(int row, int k, int K)
 {
-    return ((((size_t)(row >> 5) * TAPS + tap) * (K >> 3) + (k >> 3)) * 64 + ((k >> 2) & 1) * 32 + (row & 31)) * 4 + (k & 3);
+    return (((size_t)(row >> 5) * (K >> 3) + (k >> 3)) * 64 + ((k >> 2) & 1) * 32 + (row & 31)) * 4 + (k & 3);
 }
 }  // namespace st

@@ -1,0 +1,68 @@
+"""Float32 path, whose operands enter the matrix cores as three bfloat16 parts: every number of position tiles per block, odd runs of
+eight channels (half a fragment of sixteen), and what an infinite feature reaches."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2003_10735_amd as st
+import workloads as WL
+from gpu_util import to_dev_features
+
+pytestmark = pytest.mark.gpu
+
+
+# tiles of 32 positions per block for c1 / c2 output channels: 1, 2, 3, 4, 5 in turn
+@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 8, 40, 24), (60, 107, 24, 64, 40), (45, 80, 72, 128, 128), (60, 107, 16, 128, 104),
+                                            (68, 120, 88, 128, 128)])
+def test_split_products_are_as_good_as_float32(h, w, c_in, c1, c2):
+    """Logits, gradient of every parameter block and feature gradient of one step against the oracle in float64, 2-norm.  Each sum
+    adds up to 9 * 128 products that are right to 2^-25 in float32: 1e-6 for the logits, three times what the float32
+    instructions show.  Backward one activation in a million changes sign with the last bit, which moves a gradient by one
+    position's share (1 / 319 of it at the smallest size) and elements of the feature gradient as a whole."""
+    wl = WL.small_variant(WL.WORKLOADS["tiny"], h=h, w=w, c_in=c_in, c1=c1, c2=c2, n_classes=9, steps=1, lr=1.0, n_sites=20)
+    f, lab, p = WL.make_features(wl), WL.make_labels(wl), WL.make_head_params(wl)
+    d, fd, f64 = st.HeadDesc.of(wl), to_dev_features(wl, f), WL.features_as_f64(wl, f)
+    pt = torch.from_numpy(p).cuda()
+    z = torch.empty((1, 9, h, w), dtype=torch.float32, device="cuda")
+    st.st_head_forward(d, fd, pt, z, None)
+    zo, _ = O.head_forward(O.desc_of(wl), f64, p.astype(np.float64), want_pred=False)
+    assert np.linalg.norm(z.cpu().numpy() - zo) < 1e-6 * np.linalg.norm(zo)
+    df = torch.zeros((1, c_in, h, w), dtype=torch.float32, device="cuda")
+    st.st_partial_distill(d, fd, torch.from_numpy(lab).cuda(), pt, 1, 1.0, feature_grad=df)
+    _, grad, df_o = O.feature_grad(O.desc_of(wl), f64, lab, p.astype(np.float64))
+    step = p.astype(np.float64) - pt.cpu().numpy()               # lr = 1: the gradient, rounded where the new weight is
+    for name, sl in WL.param_slices(wl).items():
+        rounding = 2.0 ** -24 * np.linalg.norm(p[sl])
+        assert np.linalg.norm(step[sl] - grad[sl]) < 1e-4 * np.linalg.norm(grad[sl]) + rounding, name
+    assert np.linalg.norm(df.cpu().numpy() - df_o) < 1e-3 * np.linalg.norm(df_o)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_infinite_features_reach_what_they_reach_in_float32(value):
+    """Two 3x3 layers see two cells in every direction: beyond them the logits are those of the finite frame, bit for bit; within,
+    infinities and NaN lie where float32 arithmetic has them (a ReLU of NaN is 0; the second layer's weights are positive and the
+    classifier's of one sign per class, so that infinities get through).  8 input channels: the other half of a fragment is the
+    zeros in front of the buffer."""
+    wl = WL.small_variant(WL.WORKLOADS["tiny"], h=12, w=40, c_in=8, c1=24, c2=40, n_classes=5, n_sites=9)
+    f, p, sl = WL.make_features(wl), WL.make_head_params(wl), WL.param_slices(wl)
+    p[sl["W2"]] = np.abs(p[sl["W2"]])
+    p[sl["W3"]] = (np.abs(p[sl["W3"]]).reshape(5, 40) * np.array([1, -1, 1, -1, 1])[:, None]).reshape(-1)
+    d, pd, zs = st.HeadDesc.of(wl), torch.from_numpy(p.astype(np.float32)).cuda(), []
+    for bad in (False, True):
+        if bad:
+            f = f.copy()
+            f[0, 3, 5, 17] = value
+        z = torch.empty((1, 5, 12, 40), dtype=torch.float32, device="cuda")
+        st.st_head_forward(d, torch.from_numpy(f).cuda(), pd, z, None)
+        zs.append(z.cpu().numpy())
+    near = np.zeros((12, 40), dtype=bool)
+    near[3:8, 15:20] = True
+    np.testing.assert_array_equal(zs[0][:, :, ~near], zs[1][:, :, ~near])
+    x, shapes = f.astype(np.float64), (("W1", (24, 8, 3, 3)), ("W2", (40, 24, 3, 3)), ("W3", (5, 40, 1, 1)))
+    with np.errstate(invalid="ignore"):
+        for i, (name, shape) in enumerate(shapes):
+            x = O.conv_fwd(x, p[sl[name]].astype(np.float64).reshape(shape), p[sl["b%d" % (i + 1)]].astype(np.float64))
+            x = np.fmax(x, 0.0) if i < 2 else x
+    np.testing.assert_array_equal(np.where(np.isfinite(zs[1]), 0, zs[1]), np.where(np.isfinite(x), 0, x))
+    assert np.isinf(x).any() == (value == float("inf"))
