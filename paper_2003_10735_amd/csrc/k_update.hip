@@ -211,6 +211,26 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f
     else if (a.bq2) *(f32x4*)(a.bq2 + (j - a.po.b2)) = w;
 }
 
+// Classifier's role of k_step_end: values per block, and the runs its threads split the slots into.
+constexpr int L3_VALUES = 32, L3_RUNS = 256 / L3_VALUES;
+
+// acc + src[s * stride] for s0 <= s < s1, in ascending order; N loads in flight.  Loads beyond the end repeat the last
+// slot (`n` slots) and are not added.
+template <int N>
+__device__ __forceinline__ float add_slots(float acc, const float* src, size_t stride, int s0, int s1, int n)
+{
+    float v[N];
+    src += (size_t)s0 * stride;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        v[e] = *src;
+        src += s0 + e + 1 < n ? stride : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) acc += s0 + e < s1 ? v[e] : 0.f;
+    return acc;
+}
+
 // (OPEN: as a role of the launch that opens a call: parameters in, operand copies; no other roles, so that the
 //  launch carries none of their LDS)
 template <bool EE, bool F32, bool OPEN>
@@ -270,43 +290,36 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
     } else if constexpr (!OPEN) { if (b < a.nb_main + a.nb_tail + a.nb_l3) {
         // role (2): slot layout [32 classes][k2] weights, then [32] biases.  The slots were
         // written by other compute units, so every load is a round trip to memory: the role is
-        // laid out for few of them.  A block takes 16 consecutive values; its 256 threads split
-        // the slots into 16 contiguous runs (thread = value + 16 * run), every thread adds its
-        // run in ascending order with eight loads in flight, and the 16 partial sums of a value
-        // are added in the order of the runs.
-        __shared__ float run_sum[16][16];
-        const int kk = threadIdx.x & 15, run = threadIdx.x >> 4;
-        const int k = (b - a.nb_main - a.nb_tail) * 16 + kk;
+        // laid out for few of them, and for whole 128-byte lines.  A block takes 32 consecutive values; its 256 threads
+        // split the slots into 8 contiguous runs (thread = value + 32 * run), every thread adds its
+        // run in ascending order, and the 8 partial sums of a value are added in the order of the runs.  A run of up to 32
+        // slots is one trip; a longer one is added 16 at a time, because then the slots' bytes bind and more loads in
+        // flight only get in the way of the parameters' (966 slots of 256 channels, 21 MB: the launch takes 18.6 us with 16,
+        // 20.9 with 32, 21.4 with 24).  16 values in 16 runs of 8 loads fetched every line twice and made two trips where
+        // this makes one: 242 slots of 128 channels (90 x 160 cells) 7.1 -> 6.3 us, four heads of those 14.9 -> 14.1,
+        // 516 slots (135 x 240 cells) 8.2 -> 8.2, the 966 slots 20.2 -> 18.6.  64 values in 4 runs: 7.2 us at 242 slots, 24.3 at 966.
+        __shared__ float run_sum[L3_RUNS][L3_VALUES];
+        const int kk = threadIdx.x % L3_VALUES, run = threadIdx.x / L3_VALUES;
+        const int k = (b - a.nb_main - a.nb_tail) * L3_VALUES + kk;
         const int n_w = a.C * a.c2;
         const bool live = k < n_w + a.C;
         float acc = 0.f;
         if (a.do_step && live) {
             const float* src = a.part3 + (k < n_w ? (size_t)(k / a.c2) * a.k2 + k % a.c2 : (size_t)32 * a.k2 + (k - n_w));
-            const int per = (a.blocks3 + 15) / 16;
+            const int per = (a.blocks3 + L3_RUNS - 1) / L3_RUNS;
             const int s1 = min((run + 1) * per, a.blocks3);
             int s = run * per;
-            for (; s + 8 <= s1; s += 8) {
-                float v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(s + e) * a.slot3];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc += v[e];
-            }
-            if (s < s1) {
-                // the rest of the run, again loaded together (clamped re-loads count as zero)
-                float v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = src[(size_t)min(s + e, a.blocks3 - 1) * a.slot3];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc += s + e < s1 ? v[e] : 0.f;
-            }
+            for (; s1 - s > 32; s += 16) acc = add_slots<16>(acc, src, a.slot3, s, s1, a.blocks3);
+            if (s1 - s > 16) acc = add_slots<32>(acc, src, a.slot3, s, s1, a.blocks3);
+            else if (s1 - s > 8) acc = add_slots<16>(acc, src, a.slot3, s, s1, a.blocks3);
+            else if (s1 > s) acc = add_slots<8>(acc, src, a.slot3, s, s1, a.blocks3);
         }
         run_sum[run][kk] = acc;
         __syncthreads();
         if (run == 0 && live) {
             float total = run_sum[0][kk];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) total += run_sum[r][kk];
+            for (int r = 1; r < L3_RUNS; ++r) total += run_sum[r][kk];
             if (F32 && a.do_step) a.grad[a.po.W3 + k] = total;      // (the float32 path's gradient can be looked at as a whole)
             apply_update<EE, F32>(a, (unsigned)a.po.W3 + k, total);
         }
@@ -512,7 +525,7 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.vec = (p.g.c_in % 4 == 0 && p.g.c1 % 4 == 0 && p.g.c2 % 4 == 0) ? 1 : 0;
     a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
     a.nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
-    a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, 16) : 0;
+    a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, L3_VALUES) : 0;
     a.nb_finish = finish ? f.fph + 1 : 0;
     head_strides(a, p);
     return a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish;
