@@ -41,20 +41,19 @@ struct UpdateArgs {
     ParamOffsets po; int c_in, c1, c2, ki, k1, k2;   // k: channel pitches of the operand copies
     float lr, mu;
     int adam; AdamStep ad;   // adam != 0: vel = first moment m, vel2 = second moment v
-    int do_step;     // 0: only refresh the operand copies
-    // parameter hand-over riding along: with ext_in (do_step == 0) theta is first taken from the
-    // caller's vector (its OIHW order); with ext_out, nb_out more blocks copy theta out to it
-    const float* ext_in; float* ext_out; int nb_out;
+    // the launch that opens a call: the caller's vectors (its OIHW order) from which theta and, where there are any, the
+    // optimiser's state vectors are taken
+    const float *ext_in, *ext_vel, *ext_vel2;
     // role (2)
     const float* part3; int blocks3; size_t slot3; int C;
-    // block ranges; vec: role (1) handles four parameters per thread over [0, W3); nb_tail blocks handle
-    // [W3, total) one by one unless role (2) does
-    int nb_main, nb_tail, nb_l3, nb_finish, vec;
+    // block ranges; vec: role (1) handles four parameters per thread over [0, W3).  (When a call opens, the blocks behind
+    // nb_main handle [W3, total) one by one.)
+    int nb_main, nb_l3, nb_finish, vec;
     // several heads (blockIdx.y): floats / elements from one head's block to the next in the
     // parameter-like vectors (theta, vel, vel2), the caller's vectors, the partial gradients,
     // the bfloat16 copies and the layer-3 slots
     size_t hs_param, hs_ext, hs_grad, hs_wq1, hs_wq2, hs_wq3, hs_part3;
-    // early-exit form only: with do_step, receives theta as it was before the step (theta's order), or null
+    // early-exit form only: receives theta as it was before the step (theta's order), or null
     float* save_old;
 };
 
@@ -71,7 +70,8 @@ __device__ __forceinline__ Weight3x3 weight3x3(unsigned r, unsigned cin)
 constexpr int PAD_PER_THREAD = 4;     // runs of the padding role per thread
 
 // index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
-__device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned j)
+template <class A>
+__device__ __forceinline__ unsigned external_index(const A& a, unsigned j)
 {
     if (j < (unsigned)a.po.b1) {
         const Weight3x3 k = weight3x3(j, a.c_in);
@@ -115,12 +115,18 @@ __device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, con
 
 // (EE: the early-exit form's extras -- save_old here, the host copy of the metric in finish_block --
 //  are compiled in; the kernels of the fixed-step form never look at those fields)
-template <bool EE, bool F32>
+template <bool EE, bool F32, bool OPEN>
 __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, float g)
 {
-    float w = a.ext_in ? a.ext_in[external_index(a, j)] : a.theta[j];
-    if (a.ext_in) a.theta[j] = w;
-    if (a.do_step) {
+    float w;
+    if (OPEN) {
+        const unsigned x = external_index(a, j);
+        w = a.ext_in[x];
+        if (a.ext_vel) a.vel[j] = a.ext_vel[x];
+        if (a.ext_vel2) a.vel2[j] = a.ext_vel2[x];
+        a.theta[j] = w;
+    } else {
+        w = a.theta[j];
         if (EE && a.save_old) a.save_old[j] = w;
         if (a.adam) {
             const float m = __builtin_fmaf(a.ad.beta1, a.vel[j], a.ad.one_minus_beta1 * g);
@@ -149,7 +155,7 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
     } else if (j < a.po.b3) {
         const unsigned r = j - (unsigned)a.po.W3;
         const unsigned cl = r / (unsigned)a.c2, o = r - cl * a.c2;
-        if (!a.do_step && a.wq3t && (int)cl == a.C - 1) {
+        if (OPEN && a.wq3t && (int)cl == a.C - 1) {
             // the call opens: the classes beyond the last are zeros (nothing writes them later)
             for (unsigned k = cl + 1; k < 32; ++k) {
                 if (F32) ((float*)a.wq3t)[wfrag32_index(o, k, 32)] = 0.f;
@@ -168,16 +174,19 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
 
 // Four consecutive parameters (all block boundaries below W3 are multiples of four here, and so are
 // the channel counts: the four lie in the same block and under the same tap).
-template <bool EE, bool F32>
+template <bool EE, bool F32, bool OPEN>
 __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f32x4 g)
 {
     f32x4 w;
-    if (a.ext_in) {
+    if (OPEN) {
+        unsigned x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = a.ext_in[external_index(a, j + e)];
+        for (int e = 0; e < 4; ++e) { x[e] = external_index(a, j + e); w[e] = a.ext_in[x[e]]; }
+        if (a.ext_vel) *(f32x4*)(a.vel + j) = f32x4{a.ext_vel[x[0]], a.ext_vel[x[1]], a.ext_vel[x[2]], a.ext_vel[x[3]]};
+        if (a.ext_vel2) *(f32x4*)(a.vel2 + j) = f32x4{a.ext_vel2[x[0]], a.ext_vel2[x[1]], a.ext_vel2[x[2]], a.ext_vel2[x[3]]};
         *(f32x4*)(a.theta + j) = w;
-    } else w = *(const f32x4*)(a.theta + j);
-    if (a.do_step) {
+    } else {
+        w = *(const f32x4*)(a.theta + j);
         if (EE && a.save_old) *(f32x4*)(a.save_old + j) = w;
         if (a.adam) {
             const f32x4 mo = *(const f32x4*)(a.vel + j), vo = *(const f32x4*)(a.vel2 + j);
@@ -246,7 +255,8 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         move(a.wq2, head * a.hs_wq2); move(a.wq2t, head * a.hs_wq2);
         move(a.wq3, head * a.hs_wq3); move(a.wq3t, head * (size_t)a.k2 * 32);
         if (a.ext_in) a.ext_in += head * a.hs_ext;
-        if (a.ext_out) a.ext_out += head * a.hs_ext;
+        if (a.ext_vel) a.ext_vel += head * a.hs_ext;
+        if (a.ext_vel2) a.ext_vel2 += head * a.hs_ext;
         if (a.part3) a.part3 += head * a.hs_part3;
     }
     if (b < a.nb_main) {
@@ -256,7 +266,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
             const unsigned j = ((unsigned)b * 256 + threadIdx.x) * 4;
             if (j >= a.po.W3) return;
             f32x4 g = {0.f, 0.f, 0.f, 0.f};
-            if (a.do_step) {
+            if (!OPEN) {
                 const int splits = j < a.po.W2 ? a.splits1 : a.splits2;
                 const float* gp = a.grad + j;
                 g = *(const f32x4*)gp;
@@ -270,24 +280,24 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
                 }
                 for (; s < splits; ++s) g += *(const f32x4*)(gp + (size_t)s * a.stride);
             }
-            apply_update4<EE, F32>(a, j, g);
+            apply_update4<EE, F32, OPEN>(a, j, g);
             return;
         }
         // role (1), one parameter per thread
         const unsigned j = (unsigned)b * 256 + threadIdx.x;
         if (j >= a.po.W3) return;
         float g = 0.f;
-        if (a.do_step) {
+        if (!OPEN) {
             const int splits = j < a.po.W2 ? a.splits1 : a.splits2;
             g = a.grad[j];
             for (int s = 1; s < splits; ++s) g += a.grad[(size_t)s * a.stride + j];
         }
-        apply_update<EE, F32>(a, j, g);
-    } else if (b < a.nb_main + a.nb_tail) {
-        // [W3, total) one by one (no step: only the copies)
+        apply_update<EE, F32, OPEN>(a, j, g);
+    } else if constexpr (OPEN) {
+        // [W3, total) one by one
         const unsigned j = (unsigned)a.po.W3 + (unsigned)(b - a.nb_main) * 256 + threadIdx.x;
-        if (j < a.po.total) apply_update<EE, F32>(a, j, 0.f);
-    } else if constexpr (!OPEN) { if (b < a.nb_main + a.nb_tail + a.nb_l3) {
+        if (j < a.po.total) apply_update<EE, F32, OPEN>(a, j, 0.f);
+    } else if (b < a.nb_main + a.nb_l3) {
         // role (2): slot layout [32 classes][k2] weights, then [32] biases.  The slots were
         // written by other compute units, so every load is a round trip to memory: the role is
         // laid out for few of them, and for whole 128-byte lines.  A block takes 32 consecutive values; its 256 threads
@@ -300,11 +310,11 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         // 516 slots (135 x 240 cells) 8.2 -> 8.2, the 966 slots 20.2 -> 18.6.  64 values in 4 runs: 7.2 us at 242 slots, 24.3 at 966.
         __shared__ float run_sum[L3_RUNS][L3_VALUES];
         const int kk = threadIdx.x % L3_VALUES, run = threadIdx.x / L3_VALUES;
-        const int k = (b - a.nb_main - a.nb_tail) * L3_VALUES + kk;
+        const int k = (b - a.nb_main) * L3_VALUES + kk;
         const int n_w = a.C * a.c2;
         const bool live = k < n_w + a.C;
         float acc = 0.f;
-        if (a.do_step && live) {
+        if (live) {
             const float* src = a.part3 + (k < n_w ? (size_t)(k / a.c2) * a.k2 + k % a.c2 : (size_t)32 * a.k2 + (k - n_w));
             const int per = (a.blocks3 + L3_RUNS - 1) / L3_RUNS;
             const int s1 = min((run + 1) * per, a.blocks3);
@@ -320,22 +330,42 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
             float total = run_sum[0][kk];
 #pragma unroll
             for (int r = 1; r < L3_RUNS; ++r) total += run_sum[r][kk];
-            if (F32 && a.do_step) a.grad[a.po.W3 + k] = total;      // (the float32 path's gradient can be looked at as a whole)
-            apply_update<EE, F32>(a, (unsigned)a.po.W3 + k, total);
+            if (F32) a.grad[a.po.W3 + k] = total;      // (the float32 path's gradient can be looked at as a whole)
+            apply_update<EE, F32, OPEN>(a, (unsigned)a.po.W3 + k, total);
         }
-    } else if (b < a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish) {
-        finish_block<EE>(f, b - a.nb_main - a.nb_tail - a.nb_l3, head);
-    } else {
-        // parameters back to the caller's order
-        const unsigned j = (unsigned)(b - a.nb_main - a.nb_tail - a.nb_l3 - a.nb_finish) * 256 + threadIdx.x;
-        if (j < a.po.total) a.ext_out[external_index(a, j)] = a.theta[j];
-    } }
+    } else finish_block<EE>(f, b - a.nb_main - a.nb_l3, head);
 }
 
 template <bool EE, bool F32>
 __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 {
     step_end_block<EE, F32, false>(a, f, blockIdx.x, blockIdx.y);
+}
+
+// Bookkeeping of a pass without an update and, behind it, what the call hands back: nb_out blocks per vector -- theta,
+// then the optimiser's state -- to the caller's order.
+// (Optimiser state once took a launch per vector and direction: four of 5.2 us in an Adam call at 90 x 160 cells,
+//  256 -> 128 -> 128 channels.  Riding here and on the opening launch they cost 3 us together: such a call 728 -> 710 us, one with momentum at
+//  135 x 240 cells 1268 -> 1251.)
+struct HandBack {
+    int nb_finish, nb_out;
+    const float* src[3]; float* dst[3];
+    ParamOffsets po; int c_in, c1;
+    size_t hs_param, hs_ext;     // several heads: floats from one head's vector to the next
+};
+
+template <bool EE>
+__global__ void __launch_bounds__(256) k_finish_pass(HandBack a, FinishArgs f)
+{
+    if ((int)blockIdx.x < a.nb_finish) {
+        finish_block<EE>(f, blockIdx.x, blockIdx.y);
+        return;
+    }
+    const int b = blockIdx.x - a.nb_finish, v = b / a.nb_out;
+    const unsigned j = (unsigned)(b - v * a.nb_out) * 256 + threadIdx.x;
+    const float* src = (v == 0 ? a.src[0] : v == 1 ? a.src[1] : a.src[2]) + blockIdx.y * a.hs_param;
+    float* dst = (v == 0 ? a.dst[0] : v == 1 ? a.dst[1] : a.dst[2]) + blockIdx.y * a.hs_ext;
+    if (j < a.po.total) dst[external_index(a, j)] = src[j];
 }
 
 // Zeros for the padding of the operand copies: channels beyond the caller's counts, of which the parameter role writes
@@ -504,7 +534,7 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.save_old = do_step ? save_old : nullptr;
     a.vel = (float*)(ws + p.vel);
     a.vel2 = (float*)(ws + p.vel2);
-    a.ext_in = do_step ? nullptr : ext_in; a.ext_out = nullptr; a.nb_out = 0;
+    a.ext_in = do_step ? nullptr : ext_in; a.ext_vel = a.ext_vel2 = nullptr;
     a.adam = adam ? 1 : 0;
     if (adam) a.ad = *adam; else memset(&a.ad, 0, sizeof(a.ad));
     a.grad = (float*)(ws + p.grad);
@@ -517,18 +547,18 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.wq3 = at(p.wq3); a.wq3t = at(p.wq3t);
     a.bq1 = (float*)at(p.bq1); a.bq2 = (float*)at(p.bq2);
     a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2; a.ki = p.g.ki; a.k1 = p.g.k1; a.k2 = p.g.k2;
-    a.lr = lr; a.mu = mu; a.do_step = do_step ? 1 : 0;
+    a.lr = lr; a.mu = mu;
     a.part3 = (const float*)(ws + p.grad3);
     a.blocks3 = p.blocks3; a.slot3 = conv3_bwd_slot_floats(p.g); a.C = p.g.C;
     // four parameters per thread when every block below W3, and every row under one tap, starts at a
     // multiple of four
     a.vec = (p.g.c_in % 4 == 0 && p.g.c1 % 4 == 0 && p.g.c2 % 4 == 0) ? 1 : 0;
     a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
-    a.nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
+    const int nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
     a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, L3_VALUES) : 0;
     a.nb_finish = finish ? f.fph + 1 : 0;
     head_strides(a, p);
-    return a.nb_main + a.nb_tail + a.nb_l3 + a.nb_finish;
+    return a.nb_main + nb_tail + a.nb_l3 + a.nb_finish;
 }
 
 void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool finish, float* loss_out,
@@ -551,10 +581,10 @@ static bool pack_vectors(const Plan& p, const void* features, int feat_dtype)
 }
 
 // Opens a call in one launch: packs the features, takes the caller's parameters (OIHW order)
-// into theta and the operand copies, clears `zero` and, with labels, computes T = U^T (one-hot valid
+// into theta and the operand copies and, where there are any, the optimiser's `state` vectors, clears `zero` and, with labels, computes T = U^T (one-hot valid
 // labels) and every label block's pixel count (the first loss pass adds them up).
 void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_dtype, const float* head_params,
-                bool w1t, const int32_t* labels, const uint8_t* wmap, const ZeroList& zero)
+                bool w1t, const int32_t* labels, const uint8_t* wmap, const ZeroList& zero, const float* vel, const float* vel2)
 {
     const Geo& g = p.g;
     BeginArgs q;
@@ -584,6 +614,7 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
     UpdateArgs a;
     const FinishArgs f = finish_args(p, ws, nullptr, nullptr, nullptr);
     q.nb_update = step_end_args(p, ws, 0.f, 0.f, nullptr, false, false, head_params, w1t, f, a);
+    a.ext_vel = vel; a.ext_vel2 = vel2;
     q.nb_update_all = q.nb_update * g.heads();
     q.nb_pad = pad_blocks(p, a); q.pad_runs = pad_runs(p, a);
     if (zero.overflow) { c.status = ST_ERR_SHAPE; return; }
@@ -599,28 +630,29 @@ void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_
 
 int label_blocks(const Geo& g) { return g.n * g.h * cdiv(g.w, LABEL_TX); }
 
-// bookkeeping of a pass without an update; with ext_out the same launch hands theta back to the
-// caller's vector (OIHW order)
+// bookkeeping of a pass without an update; with ext_out the same launch hands theta (and with out_vel, out_vel2 the
+// optimiser's state) back to the caller's vectors (OIHW order), none of which may overlap
 void finish_pass(Ctx& c, const Plan& p, char* ws, float* loss_out, double* miou_out, long long* conf_out,
-                 float* ext_out, double* miou_host, unsigned long long* token_host, unsigned long long token)
+                 float* ext_out, double* miou_host, unsigned long long* token_host, unsigned long long token,
+                 float* out_vel, float* out_vel2)
 {
-    UpdateArgs a;
-    memset(&a, 0, sizeof(a));
     const FinishArgs f = finish_args(p, ws, loss_out, miou_out, conf_out, miou_host, token_host, token);
+    HandBack a;
+    memset(&a, 0, sizeof(a));
     a.nb_finish = f.fph + 1;
-    head_strides(a, p);
+    int vectors = 0;
     if (ext_out) {
-        a.theta = (float*)(ws + p.theta);
-        a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2;
-        a.ext_out = ext_out;
         a.nb_out = cdiv(p.po.total, 256);
+        a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1;
+        a.hs_param = p.head_stride; a.hs_ext = p.po.total;
+        const size_t from[3] = {p.theta, p.vel, p.vel2};
+        float* const to[3] = {ext_out, out_vel, out_vel2};
+        for (; vectors < 3 && to[vectors]; ++vectors) { a.src[vectors] = (const float*)(ws + from[vectors]); a.dst[vectors] = to[vectors]; }
     }
-    if (miou_host)
-        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", (k_step_end<true, false>),
-                  dim3(a.nb_finish + a.nb_out, p.g.heads()), dim3(256), 0, a, f);
-    else
-        ST_LAUNCH(c, ext_out ? "finish_pass+params_out" : "finish_pass", (k_step_end<false, false>),
-                  dim3(a.nb_finish + a.nb_out, p.g.heads()), dim3(256), 0, a, f);
+    const dim3 grid(a.nb_finish + vectors * a.nb_out, p.g.heads());
+    const char* name = ext_out ? "finish_pass+params_out" : "finish_pass";
+    if (miou_host) ST_LAUNCH(c, name, k_finish_pass<true>, grid, dim3(256), 0, a, f);
+    else ST_LAUNCH(c, name, k_finish_pass<false>, grid, dim3(256), 0, a, f);
 }
 
 // ------------------------------------------------------------------ stand-alone metric

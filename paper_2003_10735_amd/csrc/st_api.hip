@@ -704,14 +704,11 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
     const CountSum count{(const unsigned int*)(ws + p.label_counts), label_blocks(g) / g.heads(), (unsigned long long*)(ws + p.counters)};
 
     const ZeroList zero = regions_to_clear(p, ws);
-    if (mu != 0.f) permute_params(c, p, velocity, (float*)(ws + p.vel), 0);
-    if (use_adam) {
-        permute_params(c, p, adam_m, (float*)(ws + p.vel), 0);
-        permute_params(c, p, adam_v, (float*)(ws + p.vel2), 0);
-    }
-    // features packed, theta in internal order + operand copies, U^T of the labels, the sums
+    // the optimiser's state: momentum's velocity, or Adam's two moments
+    float *const state = use_adam ? adam_m : mu != 0.f ? velocity : nullptr, *const state2 = use_adam ? adam_v : nullptr;
+    // features packed, theta and the state in internal order + operand copies, U^T of the labels, the sums
     // of the weights of the valid labels, and what has to be zero: one launch
-    call_begin(c, p, ws, features, desc->feat_dtype, head_params, feature_grad != nullptr, teacher_labels, pixel_weights, zero);
+    call_begin(c, p, ws, features, desc->feat_dtype, head_params, feature_grad != nullptr, teacher_labels, pixel_weights, zero, state, state2);
 
     double best_metric = -1.0, first_metric = -1.0;
     std::vector<double> frame_metric;
@@ -720,7 +717,12 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
     // copied; the optimiser kernel that overwrites them leaves them in the workspace on its way
     bool have_best = false, best_is_theta = false;
     const bool keep_best = early_exit && (return_best || best_params);
-    bool params_out_done = false;
+    bool params_out_done = false, state_out_done = false;
+    const size_t vector_bytes = p.po.total * 4 * g.heads();
+    auto apart = [&](const float* x, const float* y) {
+        return !x || !y || (uintptr_t)x + vector_bytes <= (uintptr_t)y || (uintptr_t)y + vector_bytes <= (uintptr_t)x;
+    };
+    const bool vectors_apart = apart(head_params, state) && apart(head_params, state2) && apart(state, state2);
     for (int it = 0; it <= steps; ++it) {
         const bool last = it == steps;
         forward(c, p, ws);
@@ -740,8 +742,8 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         // along with the optimiser kernel at the end of the step; it needs a launch of its own
         // only when no update follows or when the host must see the metric first.
         const bool finish_now = last || early_exit;
-        // (the last pass of the fixed-step form also hands the parameters back in the same launch)
-        const bool out_now = last && !early_exit;
+        // (the last pass of the fixed-step form also hands the parameters, and the optimiser's state, back in the same launch)
+        const bool out_now = last && !early_exit, state_out_now = out_now && vectors_apart;
         // In the early-exit form the bookkeeping also writes the per-frame metric, and behind it the
         // pass's token, straight into page-locked host memory; the host polls the token (or, where
         // that is switched off, waits on an event), so no copy sits in the stream between the pass
@@ -758,8 +760,10 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         const bool finish_rides = speculate && polled && p.bf16;
         if (finish_now && !finish_rides)
             finish_pass(c, p, ws, loss_out, miou_out, conf_out, out_now ? head_params : nullptr,
-                        device_writes ? mb->dev : nullptr, device_writes ? mb->dev_tok : nullptr, token);
+                        device_writes ? mb->dev : nullptr, device_writes ? mb->dev_tok : nullptr, token,
+                        state_out_now ? state : nullptr, state_out_now ? state2 : nullptr);
         params_out_done = params_out_done || out_now;
+        state_out_done = state_out_done || state_out_now;
         bool stop = last;
         // In the early-exit form the backward pass of an iteration is put into the stream before
         // the host looks at the metric: it only produces gradients (nothing the results depend on
@@ -838,16 +842,15 @@ int st_partial_distill(const st_head_desc* desc, const void* features, const int
         ++taken;
     }
     const bool best_in_workspace = have_best && !best_is_theta;   // else the current parameters are the best
-    if (early_exit && best_params) permute_params(c, p, best_in_workspace ? (const float*)(ws + p.best) : theta, best_params, 1);
+    if (early_exit && best_params) permute_params(c, p, best_in_workspace ? (const float*)(ws + p.best) : theta, best_params);
     if (early_exit && return_best && best_in_workspace && taken > 0)
         ST_HIP(c, hipMemcpyAsync(theta, ws + p.best, p.po.total * 4, hipMemcpyDeviceToDevice, c.stream));
     // (a call that took no update -- not a key frame -- leaves the caller's vectors as they are)
     const bool untouched = early_exit && taken == 0;
-    if (!params_out_done && !untouched) permute_params(c, p, theta, head_params, 1);
-    if (mu != 0.f && !untouched) permute_params(c, p, (const float*)(ws + p.vel), velocity, 1);
-    if (use_adam && !untouched) {
-        permute_params(c, p, (const float*)(ws + p.vel), adam_m, 1);
-        permute_params(c, p, (const float*)(ws + p.vel2), adam_v, 1);
+    if (!params_out_done && !untouched) permute_params(c, p, theta, head_params);
+    if (!state_out_done && !untouched) {
+        if (state) permute_params(c, p, (const float*)(ws + p.vel), state);
+        if (state2) permute_params(c, p, (const float*)(ws + p.vel2), state2);
     }
     if (early_exit) ST_HIP(c, hipStreamSynchronize(c.stream));
     if (out) {

@@ -31,7 +31,7 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
         if (i < z.n16[r]) p[i] = make_uint4(0, 0, 0, 0);
     }
 }
-void permute_params(Ctx& c, const Plan& p, const float* src, float* dst, int dir);
+void permute_params(Ctx& c, const Plan& p, const float* src, float* dst);
 
 // k_conv_f32.hip -- the float32 path's kernels
 void forward_f32(Ctx& c, const Plan& p, char* ws);
@@ -85,7 +85,8 @@ void loss_pass(Ctx& c, const Geo& g, const ZSrc& zs, const uint8_t* labels8, con
 //   step_scale = lr / (1 - beta1^t),  inv_sqrt_bc2 = 1 / sqrt(1 - beta2^t).
 struct AdamStep { float beta1, beta2, one_minus_beta1, one_minus_beta2, eps, step_scale, inv_sqrt_bc2; };
 void call_begin(Ctx& c, const Plan& p, char* ws, const void* features, int feat_dtype, const float* head_params,
-                bool w1t, const int32_t* labels, const uint8_t* pixel_weights, const ZeroList& zero);
+                bool w1t, const int32_t* labels, const uint8_t* pixel_weights, const ZeroList& zero,
+                const float* vel = nullptr, const float* vel2 = nullptr);
 // blocks of the label role of that launch, in the order of the frames; each leaves its pixel count (weight sum)
 int label_blocks(const Geo& g);
 void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamStep* adam, bool finish, float* loss_out,
@@ -98,7 +99,7 @@ FinishArgs finish_args(const Plan& p, char* ws, float* loss_out, double* miou_ou
 // each value followed by `token` in token_host (a release store at system scope)
 void finish_pass(Ctx& c, const Plan& p, char* ws, float* loss_out, double* miou_out, long long* conf_out,
                  float* ext_out = nullptr, double* miou_host = nullptr, unsigned long long* token_host = nullptr,
-                 unsigned long long token = 0);
+                 unsigned long long token = 0, float* out_vel = nullptr, float* out_vel2 = nullptr);
 void confusion_and_miou(Ctx& c, const uint8_t* pred, const int32_t* labels, long long P, int C, int ignore,
                         long long* conf, double* miou);
 
