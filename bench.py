@@ -46,21 +46,27 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # the kernel source it was measured on:
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
-    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 33.77, 8.83),
+    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 33.79, 8.83),
     ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 13.75, 6.34),
     ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 6.98, 4.92),
     ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 10.45, 3.77),
-    ("720p", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 4.73, 4.71),
-    ("720p", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 3.09, 1.79),
+    ("720p", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 4.73, 4.71),
+    ("720p", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 3.09, 1.79),
     ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 13.19, 9.81),
-    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 73.87, 8.83),
-    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 10.07, 11.14),
-    ("1080p", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 6.48, 4.02),
+    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 73.86, 8.83),
+    ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 23.23, 13.93),
+    ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 11.75, 8.23),
+    ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 19.98, 8.29),
+    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 7.32, 11.14),
+    ("1080p", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 3.73, 4.02),
     ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 27.54, 21.56),
-    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 268.55, 17.75),
-    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 30.13, 22.21),
-    ("batch4", "upsample_ce"): ("k_loss.hip", "d45f2e7301fd55c1eb5a38b4374865b0e0d9c893e7a52f336c85c97a7fe81e30", 23.46, 7.61),
-    ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 71.45, 80.27),
+    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 268.19, 17.77),
+    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 85.05, 54.34),
+    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 50.85, 35.47),
+    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 92.17, 30.19),
+    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 19.27, 22.21),
+    ("batch4", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 12.60, 7.61),
+    ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 71.46, 80.27),
 }
 
 
