@@ -63,7 +63,7 @@ __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
 // instead of one 38; fragments read one group ahead and the barrier behind the last group 37.)
 struct Conv32Args {
     const float* X;       // pos8 layout, G groups of eight channels
-    const float* Wf;      // fragment order (wfrag_index, k rounded up to 16), rows = output channels
+    const float* Wf;      // fragment order (wfrag_index, k = 8 G), rows = output channels
     const float* bias;    // EPI 0, 2: zeros behind the last channel
     const float* mask;    // EPI 1: activation whose sign gates the gradient (layout of Y)
     float* Y;             // pos8 layout, GY groups (EPI 2: may be null)
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
 #pragma unroll
         for (int r = 0; r < 16; ++r) { acc[j][r] = 0.f; rest[j][r] = 0.f; }
 
-    const int c_chunks = (a.G + 7) >> 3, n_stages = 3 * c_chunks, KQ = (a.G + 1) >> 1;
+    const int c_chunks = (a.G + 7) >> 3, n_stages = 3 * c_chunks;
 
     // ---- activations: a unit is one position x one run of eight channels.  Unit u of a thread is number u * 256 + tid, counted
     // along the positions first; unit P is one of the 16 units of the last two positions (sixteen threads do the same one).
@@ -148,14 +148,14 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
     // ---- weights of this wavefront's 16 channels: per tap of a stage eight float32 values per lane (row l32, k 8 lhi ..), split
     // into three fragments.  While the matrix cores work on one tap the fragments of the tap before it are made for the
     // next stage (while they work on the first tap: those of the last tap, for this stage), a few instructions at a time.
-    const float* wp = a.Wf + ((size_t)nt * 9 * KQ + wave) * 512 + lane * 8;
-    const size_t w_tap = (size_t)KQ * 512;
+    const float* wp = a.Wf + ((size_t)nt * 9 * a.G + wave * 2) * 256 + lane * 8;
+    const size_t w_tap = (size_t)a.G * 256;
     int w_cc = 0;
     f32x4 wr[3][2];
     u32x4 wa[3][3];
-    // (a wavefront whose channels do not exist: zeros, as above)
+    // (lanes whose channels do not exist: zeros, as above)
     auto load_w = [&](int kw) __attribute__((always_inline)) {
-        const float* src = w_cc * 4 + wave < KQ ? wp + kw * w_tap : a.X + lane * 8;
+        const float* src = w_cc * 8 + wave * 2 + lhi < a.G ? wp + kw * w_tap : a.X + lane * 8;
         wr[kw][0] = *(const f32x4*)src;
         wr[kw][1] = *(const f32x4*)(src + 4);
     };

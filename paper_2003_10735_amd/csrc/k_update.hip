@@ -32,8 +32,8 @@ namespace st {
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
 //   wq3t          : W3 transposed, for the classifier's backward kernel
 // bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
-// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order with k rounded up to 16, wq3t in the
-// order of wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
+// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order, wq3t in the order of
+// wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
 // classes are cleared by the launch that opens the call and never written later.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
@@ -94,12 +94,12 @@ __device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, con
     void* bwd = layer == 1 ? a.wq1t : a.wq2t;
     const int kin = layer == 1 ? a.ki : a.k1, kout = layer == 1 ? a.k1 : a.k2;
     if (F32) {
-        float* f = (float*)fwd + wfrag_index(k.o, k.tap, k.i, k16(kin));
+        float* f = (float*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
         if (N == 4) *(f32x4*)f = f32x4{w[0], w[N > 1 ? 1 : 0], w[N > 2 ? 2 : 0], w[N > 3 ? 3 : 0]};
         else f[0] = w[0];
         if (bwd)
 #pragma unroll
-            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, k16(kout))] = w[e];
+            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = w[e];
     } else {
         bf16* f = (bf16*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
         bf16 q[N];
@@ -387,11 +387,11 @@ __device__ __forceinline__ void pad_block(const UpdateArgs& a, unsigned block, u
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 if (!copy[m]) continue;
-                const int K = F32 ? k16(k[k_of[m]]) : k[k_of[m]], rv = c[row_of[m]], kv = c[k_of[m]];
+                const int K = k[k_of[m]], rv = c[row_of[m]], kv = c[k_of[m]];
                 const unsigned runs = (unsigned)rows(row_of[m]) * 9u * (unsigned)(K / W);
                 if (i >= runs) { i -= runs; continue; }
-                const unsigned t = i >> 6, per = (unsigned)K / (2 * W);
-                const int row = (int)(t / per / 9u * 32u + (i & 31)), k0 = (int)(t % per) * 2 * W + (int)((i >> 5) & 1) * W;
+                const unsigned t = i >> 5, per = (unsigned)K / W;
+                const int row = (int)(t / per / 9u * 32u + (i & 31)), k0 = (int)(t % per) * W;
                 char* dst = (char*)copy[m] + (size_t)i * B;
                 if (row >= rv || k0 >= kv) {
 #pragma unroll
@@ -431,7 +431,7 @@ static unsigned pad_runs(const Plan& p, const UpdateArgs& a)
 static int pad_blocks(const Plan& p, const UpdateArgs& a)
 {
     const Geo& g = p.g;
-    // (float32 path: rows rounded up to 32, k to 16)
+    // (float32 path: rows rounded up to 32)
     if (!g.padded() && (p.bf16 || (g.c_in % 32 == 0 && g.c1 % 32 == 0 && g.c2 % 32 == 0))) return 0;
     const auto r32 = [](int k) { return (k + 31) / 32 * 32; };
     const long long rest = 32ll * ((p.bf16 ? g.k2 : r32(g.k2)) - g.c2) + (r32(g.k1) - g.c1) + (r32(g.k2) - g.c2);

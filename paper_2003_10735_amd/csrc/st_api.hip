@@ -12,7 +12,6 @@
 
 #include "st_kernels.hpp"
 #include "st_conv.hpp"
-#include "st_mfma.hpp"
 #include "st_finish.hpp"
 
 namespace st {
@@ -196,13 +195,12 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.grad = train_take(heads * p.grad_stride * 4 * p.grad_copies);
     p.grad3 = train_take(heads * std::max(p.blocks3, 1) * conv3_bwd_slot_floats(g) * 4);
     p.best = train_take(heads * p.head_stride * 4);
-    // (float32 operand copies: rows rounded up to 32, k of the 3x3 ones to 16)
+    // (float32 operand copies: rows rounded up to 32)
     const auto rows = [&](int k) { return (size_t)(p.bf16 ? k : cdiv(k, 32) * 32); };
-    const auto row_bytes = [&](int k) { return (size_t)9 * (p.bf16 ? k : k16(k)) * p.esz; };
-    p.bytes_w1 = heads * rows(g.k1) * row_bytes(g.ki);
-    p.bytes_w1t = heads * rows(g.ki) * row_bytes(g.k1);
-    p.bytes_w2 = heads * rows(g.k2) * row_bytes(g.k1);
-    p.bytes_w2t = heads * rows(g.k1) * row_bytes(g.k2);
+    p.bytes_w1 = heads * rows(g.k1) * 9 * g.ki * p.esz;
+    p.bytes_w1t = heads * rows(g.ki) * 9 * g.k1 * p.esz;
+    p.bytes_w2 = heads * rows(g.k2) * 9 * g.k1 * p.esz;
+    p.bytes_w2t = heads * rows(g.k1) * 9 * g.k2 * p.esz;
     p.bytes_w3 = heads * (p.bf16 ? g.C : 32) * rows(g.k2) * p.esz;
     p.bytes_w3t = heads * rows(g.k2) * 32 * p.esz;
     p.wq1 = take(off, p.bytes_w1);

@@ -25,18 +25,18 @@ __host__ __device__ __forceinline__ size_t xt_index(int c, int col, int NG)
 // Weights of the 3x3 matrix-core convolutions, [rows][9 taps][K], are kept in the order in which
 // that kernel's wavefronts consume them: one A fragment (32 rows x 16 k of one tap, lane l holding
 // row l % 32, k 8*(l/32) .. +7) is one contiguous 1 KB run,
-//     [row / 32][tap][k / 16][(k / 8) % 2][row % 32][k % 8].
+//     [row / 32][tap][k / 16][(k / 8) % 2][row % 32][k % 8],
+// in other words [row / 32][tap][k / 8][row % 32][k % 8], which also serves a K that ends with half a fragment.
 __host__ __device__ __forceinline__ size_t wfrag_index(int row, int tap, int k, int K)
 {
-    return ((((size_t)(row >> 5) * 9 + tap) * (K >> 4) + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (row & 31)) * 8 + (k & 7);
+    return ((((size_t)(row >> 5) * 9 + tap) * (K >> 3) + (k >> 3)) * 32 + (row & 31)) * 8 + (k & 7);
 }
 
 // Float32 path: activations in runs of eight channels, [c / 8][column][8], column = guard + padded position, PPT
 // columns per run.
 __host__ __device__ __forceinline__ size_t pos8_index(int c, int col, int PPT) { return ((size_t)(c >> 3) * PPT + col) * 8 + (c & 7); }
 
-// Its 3x3 weights lie in the order of wfrag_index too, as float32, k rounded up to 16.
-__host__ __device__ __forceinline__ int k16(int k) { return (k + 15) & ~15; }
+// Its 3x3 weights lie in the order of wfrag_index too, as float32.
 
 // v_mfma_f32_32x32x2_f32 (the float32 path's classifier): lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32]; D as above.
 // W3 for its backward, K (a multiple of eight) classes per row: the A operands of four MFMAs (32 rows x 8 k, lane l holding

@@ -187,15 +187,18 @@ def test_missing_tensors_are_the_librarys_error():
 
 
 # (n, c_in, h, w, c1, c2, classes, compute): heads whose padded buffers, or all of a training call's, exceed the
-# built-in scratch while the head's own activations do not; the last two: an unpadded head, one column
-# below and above the limit
+# built-in scratch while the head's own activations do not; then an unpadded head, one column below and above the
+# limit; last, float32 heads whose half fragments of input channels take no room, one row below and above it
 @pytest.mark.parametrize("shape,fits", [
     ((1, 64, 160, 200, 64, 192, 21, "bf16"), True), ((1, 64, 200, 100, 64, 512, 21, "bf16"), True),
     ((1, 1, 810, 810, 1, 1, 2, "bf16"), True), ((32, 3, 511, 24, 6, 3, 4, "bf16"), True),
     ((2139, 8, 1, 187, 3, 1, 3, "bf16"), True), ((2, 54004, 4, 1, 2, 32, 28, "bf16"), True),
     ((1, 41037, 1, 2, 1, 2, 32, "f32"), True), ((8, 26386, 2, 4, 1, 5, 30, "f32"), True),
     ((1, 8, 6000, 5000, 8, 8, 2, "bf16"), False), ((1, 8, 6000, 5000, 8, 8, 2, "f32"), False),
-    ((2, 256, 217, 33, 64, 256, 24, "bf16"), True), ((2, 256, 218, 33, 64, 256, 24, "bf16"), False)])
+    ((2, 256, 217, 33, 64, 256, 24, "bf16"), True), ((2, 256, 218, 33, 64, 256, 24, "bf16"), False),
+    ((1, 24, 520, 300, 40, 200, 9, "f32"), True), ((1, 24, 521, 300, 40, 200, 9, "f32"), False),
+    ((1, 40, 357, 300, 88, 128, 19, "f32"), True), ((1, 40, 358, 300, 88, 128, 19, "f32"), False),
+    ((1, 8, 230, 300, 8, 512, 19, "f32"), True), ((1, 8, 231, 300, 8, 512, 19, "f32"), False)])
 def test_what_the_built_in_scratch_takes(shape, fits):
     """st_head_forward_noalloc takes a head by what its forward pass needs at least.  (Without a GPU a call that
     passes the size check ends with ST_ERR_NO_DEVICE: nothing is launched, no pointer is followed.)"""
