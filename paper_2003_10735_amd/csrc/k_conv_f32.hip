@@ -13,9 +13,14 @@
 // classifier 28.3 / 23.5, its data gradient 27.2 / 22, weight gradients 77 / 44.5; a 4-step call 902 -> 647, 16 x 16 cells unchanged.
 // What binds now: a wavefront issues one instruction in four cycles, and splitting (eleven per pair of values) leaves few of
 // the eight places an MFMA takes empty -- about 7.5 are used.
-// Infinite operands (and finite ones above 3.39e38, which round to infinity): the first product alone is what a float32
-// product would be (inf - inf stays NaN, inf * 0 too); the others may be NaN, so they have accumulators of their own, which are
-// dropped where they are not finite.  (In the weight gradient all six share one: an infinite sum comes out as NaN.)
+//
+// The whole range of float32 (convolutions).  A bfloat16 has no bits below 2^-133, so the last parts of a value below 2^-110 would be lost.
+// Operands therefore enter times 2^24 -- weights from the kernel that writes their copies, activations on their way to LDS -- which puts
+// even the last bit of a subnormal, 2^-149, among the normal values, and the sums are taken times 2^-48.  What that makes overflow (an
+// operand from 2^104 or a sum from 2^80 on), infinities and NaN give sums that are not finite: those are formed again, from the
+// operands as they are, by the float32 instruction (conv_f32_plain), and no others.  Factors and test cost 0.5 % of the
+// 68 x 120 call (659 -> 662 us).
+// (In the weight gradient operands are not scaled, and all six products share an accumulator: an infinite sum comes out as NaN.)
 //
 // Everything stays float32 in memory -- activations in runs of eight channels [c / 8][position][8] (pos8_index), weights in the
 // fragment order of wfrag_index -- and is split by the kernel that reads it, between its MFMAs.  (Weights written as three
@@ -63,7 +68,8 @@ __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
 // instead of one 38; fragments read one group ahead and the barrier behind the last group 37.)
 struct Conv32Args {
     const float* X;       // pos8 layout, G groups of eight channels
-    const float* Wf;      // fragment order (wfrag_index, k = 8 G), rows = output channels
+    const float* Wf;      // fragment order (wfrag_index, k = 8 G), rows = output channels, scaled
+    const float* W;       // the same as they are: element (row, tap, k) at row * w_row + tap * w_tap + k * w_k
     const float* bias;    // EPI 0, 2: zeros behind the last channel
     const float* mask;    // EPI 1: activation whose sign gates the gradient (layout of Y)
     float* Y;             // pos8 layout, GY groups (EPI 2: may be null)
@@ -71,6 +77,7 @@ struct Conv32Args {
     float* zpart;         // EPI 2: this channel tile's share of the logits, [n-tile][padded position][zpitch]
     float* dense;         // EPI 3: [n][dense_c][h][w]
     int PP, Hp, Wp, h, w, G, GY, PPT, guard, w3_pitch, zpitch, dense_c;
+    int rows, K, w_row, w_tap, w_k;
     int m_tiles, n_tiles, tiles_per_xcd;
 };
 
@@ -78,6 +85,45 @@ template <int P>
 constexpr size_t conv_split_lds()
 {
     return std::max((size_t)2 * 3 * (32 * P + 2) * 128, (size_t)4 * P * 4096);     // slabs; partial sums
+}
+
+// Of the share of a block's sums that wavefront `wave` has, those that are not finite, formed by the float32 matrix instruction
+// (v_mfma_f32_32x32x2_f32; number e of 16 channels pairs channel e with channel 8 + e).
+template <int P>
+__device__ __forceinline__ void conv_f32_plain(const Conv32Args& a, int m0, int nt, int wave, f32x16 (&acc)[P])
+{
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lhi = lane >> 5, row = nt * 32 + l32;
+    f32x16 sum[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[j][r] = 0.f;
+#pragma unroll 1
+    for (int c0 = wave * 2; c0 < a.G; c0 += 8) {
+        const int run = c0 + lhi;
+#pragma unroll 1
+        for (int tap = 0; tap < 9; ++tap) {
+            float w[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = run * 8 + e;
+                w[e] = row < a.rows && k < a.K ? a.W[row * a.w_row + tap * a.w_tap + k * a.w_k] : 0.f;
+            }
+            // (a run that does not exist: zeros, from the guard in front of the first)
+            const float* xp = run < a.G ? a.X + ((ptrdiff_t)run * a.PPT + a.guard + m0 + l32 + (tap / 3 - 1) * a.Wp + tap % 3 - 1) * 8 : a.X;
+            const int step = run < a.G ? 256 : 0;
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const f32x4 x0 = *(const f32x4*)(xp + j * step), x1 = *(const f32x4*)(xp + j * step + 4);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], e < 4 ? x0[e & 3] : x1[e & 3], sum[j], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = __builtin_isfinite(acc[j][r]) ? acc[j][r] : sum[j][r];
 }
 
 template <int EPI, int P>
@@ -125,6 +171,10 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
     // step or in two, then plane by plane.
     u32x4 xp[3];
     float r0 = 0.f, r1 = 0.f;
+    auto scale = [&](int u, int e) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) xr[u][e >> 1][(e & 1) * 2 + i] *= F32_SPLIT_SCALE;
+    };
     auto split_a = [&](int u, int e) __attribute__((always_inline)) {
         const float v0 = xr[u][e >> 1][(e & 1) * 2], v1 = xr[u][e >> 1][(e & 1) * 2 + 1];
         const unsigned h = round_pair(v0, v1);
@@ -191,7 +241,7 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
 #pragma unroll
     for (int u = 0; u <= P; ++u) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { split_a(u, e); split_b(e); }
+        for (int e = 0; e < 4; ++e) { scale(u, e); split_a(u, e); split_b(e); }
 #pragma unroll
         for (int q = 0; q < 3; ++q) write_plane(u, 0, q);
         load_unit(u);
@@ -240,6 +290,9 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
             }
             if constexpr (NEXT && at / PER <= P) {
                 constexpr int u = at / PER, v = at % PER;
+                // (from three units on each is scaled while the one before it is written, the first, and shorter stages', when split)
+                if constexpr ((u == 0 || P <= 2) && v < W0 && !(FINE && v & 1)) scale(u, FINE ? v >> 1 : v);
+                if constexpr (P > 2 && u < P && v >= W0 && v < W0 + 4) scale(u + 1, v - W0);
                 if constexpr (FINE && v < 8) { if constexpr (v & 1) split_b(v >> 1); else split_a(u, v >> 1); }
                 if constexpr (!FINE && v < 4) { split_a(u, v); split_b(v); }
                 if constexpr (v >= W0 && v < W0 + 3) write_plane(u, 1 - B, v - W0);
@@ -267,6 +320,17 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
     stage(s & 1, yes, no);
     stage((s + 1) & 1, no, no);
 
+    // ---- the wavefront's sums, formed again where they are not finite
+    float finite = 0.f;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            acc[j][r] = (acc[j][r] + rest[j][r]) * F32_SPLIT_BACK;
+            finite = __builtin_fmaf(acc[j][r], 0.f, finite);
+        }
+    if (__builtin_expect(__ballot(finite != 0.f) != 0, 0)) conv_f32_plain<P>(a, m0, nt, wave, acc);
+
     // ---- what the epilogue needs from memory, on its way while the sums are exchanged
     const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;      // this lane's 4 channels
     f32x4 bias = {0.f, 0.f, 0.f, 0.f}, w3 = {0.f, 0.f, 0.f, 0.f}, mask[EPI == 1 ? P : 1];
@@ -285,12 +349,7 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
     for (int j = 0; j < P; ++j)
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float t = rest[j][rq * 4 + e];
-                v[e] = acc[j][rq * 4 + e] + (__builtin_isfinite(t) ? t : 0.f);
-            }
+            const f32x4 v = {acc[j][rq * 4], acc[j][rq * 4 + 1], acc[j][rq * 4 + 2], acc[j][rq * 4 + 3]};
             *(f32x4*)(red + (((wave * P + j) * 4 + rq) * 64 + lane) * 4) = v;
         }
     __syncthreads();
@@ -383,7 +442,8 @@ static int conv_split_p(int m_units, int n_tiles)
 }
 
 // cin, cout: channels of the layer as run here (exchanged for a data gradient)
-static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const float* X, const float* Wf, int cin, int cout,
+// W: that layer's weights, [o][tap][i] as its forward pass has them
+static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const float* X, const float* Wf, const float* W, int cin, int cout,
                      const float* bias, const float* mask, float* Y, const float* W3f, float* zpart, float* dense)
 {
     const Geo& g = p.g;
@@ -392,6 +452,10 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
     a.PP = g.padded_positions(); a.Hp = g.Hp; a.Wp = g.Wp; a.h = g.h; a.w = g.w;
     a.G = cdiv(cin, 8); a.GY = cdiv(cout, 8); a.PPT = p.PPT; a.guard = p.guard;
     a.w3_pitch = cdiv(g.c2, 32) * 32; a.zpitch = (g.C + 3) / 4 * 4; a.dense_c = cout;
+    a.rows = cout; a.K = cin;
+    const bool forward = epi == 0 || epi == 2;
+    a.W = forward ? W : W + 8 * cout;        // (a data gradient has the taps mirrored)
+    a.w_row = forward ? 9 * cin : 1; a.w_tap = forward ? cin : -cout; a.w_k = forward ? 1 : 9 * cout;
     a.n_tiles = cdiv(cout, 32);
     const int P = conv_split_p(cdiv(a.PP, 32), a.n_tiles);
     a.m_tiles = cdiv(a.PP, 32 * P);
@@ -674,8 +738,9 @@ void forward_f32(Ctx& c, const Plan& p, char* ws)
 {
     const Geo& g = p.g;
     auto f = [&](size_t at) { return at ? (float*)(ws + at) : nullptr; };
-    conv_f32(c, "conv1_fwd_f32", p, 0, f(p.feat), f(p.wq1), g.c_in, g.c1, f(p.bq1), nullptr, f(p.a1), nullptr, nullptr, nullptr);
-    conv_f32(c, "conv2_fwd_logits_f32", p, 2, f(p.a1), f(p.wq2), g.c1, g.c2, f(p.bq2), nullptr, f(p.a2), f(p.wq3), f(p.zpart), nullptr);
+    const float* theta = f(p.theta);
+    conv_f32(c, "conv1_fwd_f32", p, 0, f(p.feat), f(p.wq1), theta + p.po.W1, g.c_in, g.c1, f(p.bq1), nullptr, f(p.a1), nullptr, nullptr, nullptr);
+    conv_f32(c, "conv2_fwd_logits_f32", p, 2, f(p.a1), f(p.wq2), theta + p.po.W2, g.c1, g.c2, f(p.bq2), nullptr, f(p.a2), f(p.wq3), f(p.zpart), nullptr);
 }
 
 void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat)
@@ -685,9 +750,9 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat)
     ST_LAUNCH(c, "conv3_bwd_f32", k_conv3_bwd_f32, dim3(p.blocks3), dim3(256), 0, f(p.g_slots), f(p.tadj),
               (const unsigned long long*)(ws + p.counters), (g.C + 3) / 4 * 4, p.lt, f(p.a2), f(p.wq3t), f(p.da2), f(p.gz), f(p.grad3), g,
               p.PPT, p.guard);
-    conv_f32(c, "conv2_dgrad_f32", p, 1, f(p.da2), f(p.wq2t), g.c2, g.c1, nullptr, f(p.a1), f(p.da1), nullptr, nullptr, nullptr);
+    conv_f32(c, "conv2_dgrad_f32", p, 1, f(p.da2), f(p.wq2t), f(p.theta) + p.po.W2, g.c2, g.c1, nullptr, f(p.a1), f(p.da1), nullptr, nullptr, nullptr);
     if (dfeat)
-        conv_f32(c, "conv1_dgrad_f32", p, 3, f(p.da1), f(p.wq1t), g.c1, g.c_in, nullptr, nullptr, nullptr, nullptr, nullptr, dfeat);
+        conv_f32(c, "conv1_dgrad_f32", p, 3, f(p.da1), f(p.wq1t), f(p.theta) + p.po.W1, g.c1, g.c_in, nullptr, nullptr, nullptr, nullptr, nullptr, dfeat);
     float* grad = f(p.grad);
     const Wgrad32Args a1 = wgrad_f32_args(p, f(p.da1), f(p.feat), grad + p.po.W1, grad + p.po.b1, g.c_in, g.c1, p.splits1);
     const Wgrad32Args a2 = wgrad_f32_args(p, f(p.da2), f(p.a1), grad + p.po.W2, grad + p.po.b2, g.c1, g.c2, p.splits2);

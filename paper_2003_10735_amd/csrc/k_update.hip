@@ -32,8 +32,8 @@ namespace st {
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
 //   wq3t          : W3 transposed, for the classifier's backward kernel
 // bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
-// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order, wq3t in the order of
-// wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
+// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order times F32_SPLIT_SCALE, wq3t in
+// the order of wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
 // classes are cleared by the launch that opens the call and never written later.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
@@ -95,11 +95,14 @@ __device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, con
     const int kin = layer == 1 ? a.ki : a.k1, kout = layer == 1 ? a.k1 : a.k2;
     if (F32) {
         float* f = (float*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
-        if (N == 4) *(f32x4*)f = f32x4{w[0], w[N > 1 ? 1 : 0], w[N > 2 ? 2 : 0], w[N > 3 ? 3 : 0]};
-        else f[0] = w[0];
+        float q[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) q[e] = w[e] * F32_SPLIT_SCALE;
+        if (N == 4) *(f32x4*)f = f32x4{q[0], q[N > 1 ? 1 : 0], q[N > 2 ? 2 : 0], q[N > 3 ? 3 : 0]};
+        else f[0] = q[0];
         if (bwd)
 #pragma unroll
-            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = w[e];
+            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = q[e];
     } else {
         bf16* f = (bf16*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
         bf16 q[N];

@@ -1,5 +1,5 @@
 """Float32 path, whose operands enter the matrix cores as three bfloat16 parts: every number of position tiles per block, odd runs of
-eight channels (half a fragment of sixteen), and what an infinite feature reaches."""
+eight channels (half a fragment of sixteen), the ends of the float32 range, and what an infinite feature reaches."""
 import numpy as np
 import pytest
 import torch
@@ -66,3 +66,52 @@ def test_infinite_features_reach_what_they_reach_in_float32(value):
             x = np.fmax(x, 0.0) if i < 2 else x
     np.testing.assert_array_equal(np.where(np.isfinite(zs[1]), 0, zs[1]), np.where(np.isfinite(x), 0, x))
     assert np.isinf(x).any() == (value == float("inf"))
+
+
+# powers of two on the features, W1, W2 and W3; what they are compared with; whether the sums stay finite with their operands scaled,
+# so that the result is the same bit for bit; blocks of the parameters rounded to multiples of 2^-16 (exact as subnormals)
+ENDS = [((-112, 60, 52, 0), (0, 0, 0, 0), "z", ""),           # features whose last bits lie below 2^-133
+        ((0, -100, 50, 50), (0, 0, 0, 0), "z", ""),           # weights of layer 1, activations behind it
+        ((0, 0, 40, -95), (0, 0, 0, -40), "df", ""),          # gradients (the logits are nothing against the zero biases)
+        ((126, -126, 0, 0), (0, 0, 0, 0), "", "W1"),          # features up to 3.4e38, beyond the largest bfloat16
+        ((-110, 110, 0, 0), (0, 0, 0, 0), "", ""),            # weights
+        ((0, 0, -126, 126), (0, 0, 0, 0), "", "W2")]          # gradients
+
+
+@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 8, 40, 24), (45, 80, 72, 128, 104)])
+@pytest.mark.parametrize("powers,plain,same,rounded", ENDS)
+def test_convolutions_at_the_ends_of_the_float32_range(powers, plain, same, rounded, h, w, c_in, c1, c2):
+    """Powers of two on the operands are powers of two on the results, as in float32: bit for bit where no sum of scaled
+    products overflows, else (those sums are formed by the float32 instruction, in another order) as far as float32 sums of
+    9 * 128 terms lie apart, through the softmax for the feature gradient.  Parts cut off below 2^-133, or an operand taken for infinite,
+    cost 2e-6 or everything."""
+    wl = WL.small_variant(WL.WORKLOADS["tiny"], h=h, w=w, c_in=c_in, c1=c1, c2=c2, n_classes=9, steps=1, lr=0.0, n_sites=20)
+    rng, sl = np.random.default_rng(h), WL.param_slices(wl)
+    x = (rng.uniform(0.25, 3.9999, (1, c_in, h, w)) * (rng.random((1, c_in, h, w)) < 0.5)).astype(np.float32)
+    lab, p0 = torch.from_numpy(WL.make_labels(wl)).cuda(), WL.make_head_params(wl).astype(np.float32)
+    for b in ("b1", "b2", "b3"):
+        p0[sl[b]] = 0.0
+    p0[sl["W3"]] = np.clip(p0[sl["W3"]], -1, 1)
+    if rounded:
+        p0[sl[rounded]] = np.round(p0[sl[rounded]] * 2.0 ** 16) * 2.0 ** -16
+    res = []
+    for a, b, c, d in (plain, powers):
+        p = p0.astype(np.float64)
+        for block, e in (("W1", b), ("W2", c), ("W3", d)):
+            p[sl[block]] *= 2.0 ** e
+        fd, pd = torch.from_numpy((x * 2.0 ** float(a)).astype(np.float32)).cuda(), torch.from_numpy(p.astype(np.float32)).cuda()
+        z = torch.empty((1, 9, h, w), dtype=torch.float32, device="cuda")
+        st.st_head_forward(st.HeadDesc.of(wl), fd, pd, z, None)
+        df = torch.zeros((1, c_in, h, w), dtype=torch.float32, device="cuda")
+        st.st_partial_distill(st.HeadDesc.of(wl), fd, lab, pd, 1, 0.0, feature_grad=df)
+        res.append((z.cpu().numpy() * 2.0 ** -(a + b + c + d), df.cpu().numpy() * 2.0 ** -(b + c + d)))
+    (z0, df0), (z1, df1) = res
+    assert np.linalg.norm(z0) > 0 and np.linalg.norm(df0) > 0
+    if same == "z":
+        np.testing.assert_array_equal(z1, z0)
+    elif same == "df":
+        np.testing.assert_array_equal(df1, df0)
+    else:
+        assert np.linalg.norm(z1 - z0) < 1e-6 * np.linalg.norm(z0)
+    if powers[1] >= -100:      # (else the feature gradient is subnormal)
+        assert np.linalg.norm(df1 - df0) < 1e-5 * np.linalg.norm(df0)
