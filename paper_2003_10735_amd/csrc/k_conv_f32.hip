@@ -1,4 +1,5 @@
-// Float32 path: the head's 3x3 contractions on the bfloat16 matrix cores with float32 operands kept whole.
+// Float32 path: the head's 3x3 contractions on the bfloat16 matrix cores with float32 operands kept whole.  (The convolutions of grids
+// with few tiles on the float32 instruction: k_conv3x3_f32_few.)
 //
 // A float32 value is the exact sum of three bfloat16 values, each the rest of the ones before it rounded to nearest:
 // x = xh + xm + xl.  Of the nine products of two such sums the six largest are formed,
@@ -68,8 +69,7 @@ __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
 // instead of one 38; fragments read one group ahead and the barrier behind the last group 37.)
 struct Conv32Args {
     const float* X;       // pos8 layout, G groups of eight channels
-    const float* Wf;      // fragment order (wfrag_index, k = 8 G), rows = output channels, scaled
-    const float* W;       // the same as they are: element (row, tap, k) at row * w_row + tap * w_tap + k * w_k
+    const float* Wf;      // fragment order (wfrag_index, k = 8 G), rows = output channels; scaled for the split kernel
     const float* bias;    // EPI 0, 2: zeros behind the last channel
     const float* mask;    // EPI 1: activation whose sign gates the gradient (layout of Y)
     float* Y;             // pos8 layout, GY groups (EPI 2: may be null)
@@ -77,8 +77,10 @@ struct Conv32Args {
     float* zpart;         // EPI 2: this channel tile's share of the logits, [n-tile][padded position][zpitch]
     float* dense;         // EPI 3: [n][dense_c][h][w]
     int PP, Hp, Wp, h, w, G, GY, PPT, guard, w3_pitch, zpitch, dense_c;
-    int rows, K, w_row, w_tap, w_k;
     int m_tiles, n_tiles, tiles_per_xcd;
+    // the weights as they are: element (row, tap, k) at row * w_row + tap * w_tap + k * w_k.  (Behind what every block reads first.)
+    int rows, K, w_row, w_tap, w_k;
+    const float* W;
 };
 
 template <int P>
@@ -124,6 +126,98 @@ __device__ __forceinline__ void conv_f32_plain(const Conv32Args& a, int m0, int 
     for (int j = 0; j < P; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = __builtin_isfinite(acc[j][r]) ? acc[j][r] : sum[j][r];
+}
+
+// Closes a block's tile of 32 P positions x 32 channels: the sums of its KG wavefronts are added through LDS in ascending order (red:
+// [wavefront][P][4 register groups][64 lanes][4]), and the first four finish a quarter of the channels each.
+template <int EPI, int P, int KG>
+__device__ __forceinline__ void conv_f32_finish(const Conv32Args& a, int m0, int nt, float* red, f32x16 (&acc)[P])
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    // ---- what the epilogue needs from memory, on its way while the sums are exchanged
+    const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;      // this lane's 4 channels
+    const bool ends = KG == 4 || wave < 4;
+    f32x4 bias = {0.f, 0.f, 0.f, 0.f}, w3 = {0.f, 0.f, 0.f, 0.f}, mask[EPI == 1 ? P : 1];
+    if (ends && (EPI == 0 || EPI == 2)) bias = *(const f32x4*)(a.bias + ch);
+    if (ends && EPI == 2) w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
+    const int run_out = min(nt * 4 + rq, a.GY - 1);
+    if (ends && EPI == 1) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) mask[j] = *(const f32x4*)(a.mask + ((size_t)run_out * a.PPT + a.guard + min(m0 + j * 32 + l32, a.PP - 1)) * 8 + lhi * 4);
+    }
+
+    // ---- partial sums of the wavefronts
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            const f32x4 v = {acc[j][rq * 4], acc[j][rq * 4 + 1], acc[j][rq * 4 + 2], acc[j][rq * 4 + 3]};
+            *(f32x4*)(red + (((wave * P + j) * 4 + rq) * 64 + lane) * 4) = v;
+        }
+    __syncthreads();
+
+    // wavefront rq finishes channels 8 rq .. + 7 of the tile: a lane holds 4 channels of one position per 32 positions
+    const int frame = a.Hp * a.Wp;
+    f32x4 out[P];
+    if (ends)
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        const int mp = m0 + j * 32 + l32;
+        const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
+        const bool inside = mp < a.PP && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KG; ++k) v += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
+        const size_t at = ((size_t)(nt * 4 + rq) * a.PPT + a.guard + mp) * 8 + lhi * 4;
+        const bool stored = nt * 4 + rq < a.GY && mp < a.PP;
+        if (EPI == 0 || EPI == 2) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + bias[e], 0.f) : 0.f;
+        } else if (EPI == 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = inside && mask[j][e] > 0.f ? v[e] : 0.f;
+        }
+        if (EPI == 3) {
+            if (inside) {
+                float* dst = a.dense + (((size_t)img * a.dense_c + ch) * a.h + (y - 1)) * a.w + (x - 1);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (ch + e < a.dense_c) dst[(size_t)e * a.h * a.w] = v[e];
+            }
+        } else if (stored && a.Y) *(f32x4*)(a.Y + at) = v;
+        out[j] = v;
+    }
+    if (EPI == 2) {
+        // the classifier rides along: what this lane holds is the B operand of four float32 MFMAs
+        // (v_mfma_f32_32x32x2_f32) against W3 (rows = classes, k = the 8 channels of this wavefront); the four
+        // wavefronts' sums meet in LDS.  (All shares of the logits: one per 32 channels.)
+        __syncthreads();       // the partial sums are read
+        if (ends)
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            f32x16 z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], out[j][e], z, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4*)(red + (((rq * P + j) * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
+        }
+        __syncthreads();
+        if (ends && rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const int mp = m0 + j * 32 + l32;
+                f32x4 t = *(const f32x4*)(red + ((j * 4 + rq) * 64 + lane) * 4);
+#pragma unroll
+                for (int k = 1; k < 4; ++k) t += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
+                if (mp < a.PP) *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = t;
+            }
+        }
+    }
 }
 
 template <int EPI, int P>
@@ -331,87 +425,68 @@ __global__ void __launch_bounds__(256, P <= 2 ? 2 : 1) k_conv3x3_f32(Conv32Args 
         }
     if (__builtin_expect(__ballot(finite != 0.f) != 0, 0)) conv_f32_plain<P>(a, m0, nt, wave, acc);
 
-    // ---- what the epilogue needs from memory, on its way while the sums are exchanged
-    const int rq = wave, ct = rq * 8 + lhi * 4, ch = nt * 32 + ct;      // this lane's 4 channels
-    f32x4 bias = {0.f, 0.f, 0.f, 0.f}, w3 = {0.f, 0.f, 0.f, 0.f}, mask[EPI == 1 ? P : 1];
-    if (EPI == 0 || EPI == 2) bias = *(const f32x4*)(a.bias + ch);
-    if (EPI == 2) w3 = *(const f32x4*)(a.W3f + (size_t)l32 * a.w3_pitch + ch);
-    const int run_out = min(nt * 4 + rq, a.GY - 1);
-    if (EPI == 1) {
-#pragma unroll
-        for (int j = 0; j < P; ++j) mask[j] = *(const f32x4*)(a.mask + ((size_t)run_out * a.PPT + a.guard + min(m0 + j * 32 + l32, a.PP - 1)) * 8 + lhi * 4);
-    }
+    conv_f32_finish<EPI, P, 4>(a, m0, nt, (float*)smem, acc);
+}
 
-    // ---- partial sums of the wavefronts
-    float* red = (float*)smem;          // [wavefront][P][4 register groups][64 lanes][4]
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < P; ++j)
-#pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const f32x4 v = {acc[j][rq * 4], acc[j][rq * 4 + 1], acc[j][rq * 4 + 2], acc[j][rq * 4 + 3]};
-            *(f32x4*)(red + (((wave * P + j) * 4 + rq) * 64 + lane) * 4) = v;
-        }
-    __syncthreads();
+// The same by the float32 instruction, for grids whose tiles of 32 x 32 leave compute units without a block.  There a launch is as long as
+// one block's chain of steps, and sixteen wavefronts that split taps x runs of eight channels, operands straight from memory
+// (lane l: row or position l % 32, channels 4 (l / 32) .. + 3 of a run, the four pairs of k that four MFMAs take), have a shorter one
+// than four that hand split operands through LDS.
+constexpr int CF_KG = 16, CF_DEPTH = 4;    // wavefronts; operand sets on their way per wavefront
 
-    // wavefront rq finishes channels 8 rq .. + 7 of the tile: a lane holds 4 channels of one position per 32 positions
-    const int frame = a.Hp * a.Wp;
-    f32x4 out[P];
+template <int EPI>
+__global__ void __launch_bounds__(64 * CF_KG) k_conv3x3_f32_few(Conv32Args a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // (the arguments in one trip: left to itself the compiler asks for them in four, one behind the other)
+    asm volatile("" ::"s"(a.tiles_per_xcd), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.X), "s"(a.Wf), "s"(a.G), "s"(a.PPT), "s"(a.guard), "s"(a.Wp));
+    const int tile = (blockIdx.x % 8) * a.tiles_per_xcd + blockIdx.x / 8;
+    if ((int)(blockIdx.x / 8) >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
+    const int mt = tile / a.n_tiles, nt = tile % a.n_tiles, m0 = mt * 32;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+
+    f32x16 acc[1];
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-        const int mp = m0 + j * 32 + l32;
-        const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
-        const bool inside = mp < a.PP && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
-        const size_t at = ((size_t)(nt * 4 + rq) * a.PPT + a.guard + mp) * 8 + lhi * 4;
-        const bool stored = nt * 4 + rq < a.GY && mp < a.PP;
-        if (EPI == 0 || EPI == 2) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = inside ? fmaxf(v[e] + bias[e], 0.f) : 0.f;
-        } else if (EPI == 1) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = inside && mask[j][e] > 0.f ? v[e] : 0.f;
-        }
-        if (EPI == 3) {
-            if (inside) {
-                float* dst = a.dense + (((size_t)img * a.dense_c + ch) * a.h + (y - 1)) * a.w + (x - 1);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (ch + e < a.dense_c) dst[(size_t)e * a.h * a.w] = v[e];
+    for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+
+    const int total = 9 * a.G, per = (total + CF_KG - 1) / CF_KG;
+    const int i0 = wave * per, i1 = min(total, i0 + per);
+    if (i0 < i1) {
+        const float* wp = a.Wf + ((size_t)nt * total + i0) * 256;            // advances by 256 per item
+        const float* xb = a.X + (size_t)(a.guard + m0) * 8;
+        const unsigned at = l32 * 8 + lhi * 4;
+        int tap = i0 / a.G, g = i0 - tap * a.G, li = i0;
+        const float* xp = xb + ((ptrdiff_t)g * a.PPT + (tap / 3 - 1) * a.Wp + (tap % 3 - 1)) * 8;
+        f32x4 rw[CF_DEPTH], rx[CF_DEPTH];
+        // (past the end of the run the last item is loaded again and not used)
+        auto load = [&](int s) __attribute__((always_inline)) {
+            rw[s] = *(const f32x4*)(wp + at);
+            rx[s] = *(const f32x4*)(xp + at);
+            if (++li < i1) {
+                wp += 256;
+                if (++g == a.G) {
+                    g = 0; ++tap;
+                    xp = xb + (ptrdiff_t)((tap / 3 - 1) * a.Wp + (tap % 3 - 1)) * 8;
+                } else xp += (ptrdiff_t)a.PPT * 8;
             }
-        } else if (stored && a.Y) *(f32x4*)(a.Y + at) = v;
-        out[j] = v;
-    }
-    if (EPI == 2) {
-        // the classifier rides along: what this lane holds is the B operand of four float32 MFMAs
-        // (v_mfma_f32_32x32x2_f32) against W3 (rows = classes, k = the 8 channels of this wavefront); the four
-        // wavefronts' sums meet in LDS.  (All shares of the logits: one per 32 channels.)
-        __syncthreads();       // the partial sums are read
+        };
+        auto product = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < P; ++j) {
-            f32x16 z;
+            for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(rw[s][e], rx[s][e], acc[0], 0, 0, 0);
+        };
 #pragma unroll
-            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+        for (int d = 0; d < CF_DEPTH; ++d) load(d);
+        int i = i0;
+        for (; i + CF_DEPTH <= i1; i += CF_DEPTH) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w3[e], out[j][e], z, 0, 0, 0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *(f32x4*)(red + (((rq * P + j) * 4 + q) * 64 + lane) * 4) = f32x4{z[q * 4], z[q * 4 + 1], z[q * 4 + 2], z[q * 4 + 3]};
+            for (int d = 0; d < CF_DEPTH; ++d) { product(d); load(d); }
         }
-        __syncthreads();
-        if (rq * 8 + lhi * 4 < a.zpitch) {     // (here rq: classes 8 rq .. + 7)
 #pragma unroll
-            for (int j = 0; j < P; ++j) {
-                const int mp = m0 + j * 32 + l32;
-                f32x4 t = *(const f32x4*)(red + ((j * 4 + rq) * 64 + lane) * 4);
-#pragma unroll
-                for (int k = 1; k < 4; ++k) t += *(const f32x4*)(red + (((k * P + j) * 4 + rq) * 64 + lane) * 4);
-                if (mp < a.PP) *(f32x4*)(a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + rq * 8 + lhi * 4) = t;
-            }
-        }
+        for (int d = 0; d < CF_DEPTH - 1; ++d)
+            if (i + d < i1) product(d);
     }
+    conv_f32_finish<EPI, 1, CF_KG>(a, m0, nt, (float*)smem, acc);
 }
 
 template <int EPI, int P>
@@ -428,7 +503,7 @@ static void conv_f32_launch(Ctx& c, const char* name, const Conv32Args& a)
 //   45 x 80, 128          46  44  41  45  51       80 x 140, 128    78  64  69  76  89
 //   60 x 107, 128         57  48  66  47  53       90 x 160, 128    94  77  90  78  88
 // (up to two tiles two blocks share a compute unit, which is why two small ones beat one large).  The float32 instructions'
-// kernel: 27, 47, 56, 66, 76, 93 us.
+// kernel: 27, 47, 56, 66, 76, 93 us.  One tile per block is for 64 input channels on few tiles (conv_f32_few).
 static int conv_split_p(int m_units, int n_tiles)
 {
     static const int block_time[5] = {16, 23, 35, 44, 55};
@@ -440,6 +515,19 @@ static int conv_split_p(int m_units, int n_tiles)
     }
     return best;
 }
+
+// Whether a layer runs on k_conv3x3_f32_few: at most one tile of 32 x 32 per compute unit, and by the launches' times, which are
+// 3.1 us + 0.44 per item of its wavefronts and, on split operands, 2.5 us + 0.83 per stage.  Only 57 - 64 input channels, whole
+// stages of which a block walks three, are quicker split.  us per launch, few / split: 16 x 16 cells, 24 -> 32 channels 4.5 / 5.4, 64 -> 64
+// 5.8 / 5.0, 128 -> 128 7.4 / 7.6, 256 -> 128 11.4 / 12.6; 30 x 50 cells, 320 -> 64 13.8 / 15.0; 45 x 80 cells, 64 -> 64 (260 tiles) 8.4 / 6.8.
+// Calls of 4 steps, all split / as here: 16 x 16 cells, 24 -> 32 -> 24 202 / 190 us, 24 x 40, 256 -> 128 -> 128 305 / 297.
+static bool conv_f32_few(const Geo& g, int cin, int cout)
+{
+    const int G = cdiv(cin, 8);
+    if ((long long)cdiv(g.padded_positions(), 32) * cdiv(cout, 32) > 256) return false;
+    return 310 + 44 * cdiv(9 * G, CF_KG) < 250 + 83 * 3 * cdiv(G, 8);
+}
+float conv_f32_weight_scale(const Geo& g, int cin, int cout) { return conv_f32_few(g, cin, cout) ? 1.f : F32_SPLIT_SCALE; }
 
 // cin, cout: channels of the layer as run here (exchanged for a data gradient)
 // W: that layer's weights, [o][tap][i] as its forward pass has them
@@ -457,11 +545,18 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
     a.W = forward ? W : W + 8 * cout;        // (a data gradient has the taps mirrored)
     a.w_row = forward ? 9 * cin : 1; a.w_tap = forward ? cin : -cout; a.w_k = forward ? 1 : 9 * cout;
     a.n_tiles = cdiv(cout, 32);
-    const int P = conv_split_p(cdiv(a.PP, 32), a.n_tiles);
+    const bool few = conv_f32_few(g, cin, cout);
+    const int P = few ? 1 : conv_split_p(cdiv(a.PP, 32), a.n_tiles);
     a.m_tiles = cdiv(a.PP, 32 * P);
     a.tiles_per_xcd = cdiv(a.m_tiles * a.n_tiles, 8);
     auto go = [&](auto e) {
         constexpr int E = decltype(e)::value;
+        if (few) {
+            const size_t smem = CF_KG * 4096;
+            ensure_dynamic_lds((const void*)k_conv3x3_f32_few<E>, smem);
+            ST_LAUNCH(c, name, k_conv3x3_f32_few<E>, dim3(a.tiles_per_xcd * 8), dim3(64 * CF_KG), smem, a);
+            return;
+        }
         switch (P) {
         case 1: conv_f32_launch<E, 1>(c, name, a); break;
         case 2: conv_f32_launch<E, 2>(c, name, a); break;

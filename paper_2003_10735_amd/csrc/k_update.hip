@@ -32,13 +32,14 @@ namespace st {
 //   wq1t          : the same for W1, only when the caller wants the gradient of the features
 //   wq3t          : W3 transposed, for the classifier's backward kernel
 // bfloat16 path: wq1, wq2, wq2t in fragment order (wfrag_index), wq3 [class][k2], wq3t [k2][32] with
-// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order times F32_SPLIT_SCALE, wq3t in
-// the order of wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
+// zero columns beyond the classes.  Float32 path (F32): wq1, wq2, wq2t in fragment order, times F32_SPLIT_SCALE where the layer
+// runs on split operands (conv_f32_weight_scale), wq3t in the order of wfrag32_index, wq3 [32][c2 rounded up to 32].  Rows and columns of padded channels and
 // classes are cleared by the launch that opens the call and never written later.
 struct UpdateArgs {
     float* theta; float* vel; float* vel2; float* grad; size_t stride; int splits1, splits2;
     void *wq1, *wq1t, *wq2, *wq2t, *wq3, *wq3t; float* bq1; float* bq2;   // (bf16 or float elements)
     ParamOffsets po; int c_in, c1, c2, ki, k1, k2;   // k: channel pitches of the operand copies
+    float scale1, scale1t, scale2, scale2t;   // float32 path: factors of wq1, wq1t, wq2, wq2t
     float lr, mu;
     int adam; AdamStep ad;   // adam != 0: vel = first moment m, vel2 = second moment v
     // the launch that opens a call: the caller's vectors (its OIHW order) from which theta and, where there are any, the
@@ -94,15 +95,13 @@ __device__ __forceinline__ void copy_weights(const UpdateArgs& a, int layer, con
     void* bwd = layer == 1 ? a.wq1t : a.wq2t;
     const int kin = layer == 1 ? a.ki : a.k1, kout = layer == 1 ? a.k1 : a.k2;
     if (F32) {
+        const float s = layer == 1 ? a.scale1 : a.scale2, st = layer == 1 ? a.scale1t : a.scale2t;
         float* f = (float*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
-        float q[N];
-#pragma unroll
-        for (int e = 0; e < N; ++e) q[e] = w[e] * F32_SPLIT_SCALE;
-        if (N == 4) *(f32x4*)f = f32x4{q[0], q[N > 1 ? 1 : 0], q[N > 2 ? 2 : 0], q[N > 3 ? 3 : 0]};
-        else f[0] = q[0];
+        if (N == 4) *(f32x4*)f = f32x4{w[0] * s, w[N > 1 ? 1 : 0] * s, w[N > 2 ? 2 : 0] * s, w[N > 3 ? 3 : 0] * s};
+        else f[0] = w[0] * s;
         if (bwd)
 #pragma unroll
-            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = q[e];
+            for (int e = 0; e < N; ++e) ((float*)bwd)[wfrag_index(k.i + e, 8 - k.tap, k.o, kout)] = w[e] * st;
     } else {
         bf16* f = (bf16*)fwd + wfrag_index(k.o, k.tap, k.i, kin);
         bf16 q[N];
@@ -550,6 +549,9 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.wq3 = at(p.wq3); a.wq3t = at(p.wq3t);
     a.bq1 = (float*)at(p.bq1); a.bq2 = (float*)at(p.bq2);
     a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1; a.c2 = p.g.c2; a.ki = p.g.ki; a.k1 = p.g.k1; a.k2 = p.g.k2;
+    const Geo& g = p.g;
+    a.scale1 = conv_f32_weight_scale(g, g.c_in, g.c1); a.scale1t = conv_f32_weight_scale(g, g.c1, g.c_in);
+    a.scale2 = conv_f32_weight_scale(g, g.c1, g.c2); a.scale2t = conv_f32_weight_scale(g, g.c2, g.c1);
     a.lr = lr; a.mu = mu;
     a.part3 = (const float*)(ws + p.grad3);
     a.blocks3 = p.blocks3; a.slot3 = conv3_bwd_slot_floats(p.g); a.C = p.g.C;

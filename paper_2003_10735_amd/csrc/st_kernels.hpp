@@ -34,6 +34,8 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst);
 
 // k_conv_f32.hip -- the float32 path's kernels
+// factor of the copy of the weights that a 3x3 layer of cin -> cout channels reads
+float conv_f32_weight_scale(const Geo& g, int cin, int cout);
 void forward_f32(Ctx& c, const Plan& p, char* ws);
 void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 

@@ -36,8 +36,8 @@ __host__ __device__ __forceinline__ size_t wfrag_index(int row, int tap, int k, 
 // columns per run.
 __host__ __device__ __forceinline__ size_t pos8_index(int c, int col, int PPT) { return ((size_t)(c >> 3) * PPT + col) * 8 + (c & 7); }
 
-// Its 3x3 weights lie in the order of wfrag_index too, as float32, times F32_SPLIT_SCALE: the factor that either operand of a split
-// product has (k_conv_f32.hip says why).  F32_SPLIT_BACK takes both back out of a sum.
+// Its 3x3 weights lie in the order of wfrag_index too, as float32, where operands are split times F32_SPLIT_SCALE: the factor that
+// either operand of a split product has (k_conv_f32.hip says why).  F32_SPLIT_BACK takes both back out of a sum.
 constexpr float F32_SPLIT_SCALE = 0x1p24f, F32_SPLIT_BACK = 0x1p-48f;
 
 // v_mfma_f32_32x32x2_f32 (the float32 path's classifier): lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32]; D as above.

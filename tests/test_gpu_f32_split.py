@@ -1,4 +1,4 @@
-"""Float32 path, whose operands enter the matrix cores as three bfloat16 parts: every number of position tiles per block, odd runs of
+"""Float32 path, whose operands enter the matrix cores as three bfloat16 parts except on grids of few tiles: every number of position tiles per block, odd runs of
 eight channels (half a fragment of sixteen), the ends of the float32 range, and what an infinite feature reaches."""
 import numpy as np
 import pytest
@@ -12,9 +12,11 @@ from gpu_util import to_dev_features
 pytestmark = pytest.mark.gpu
 
 
-# tiles of 32 positions per block for c1 / c2 output channels: 1, 2, 3, 4, 5 in turn
-@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 8, 40, 24), (60, 107, 24, 64, 40), (45, 80, 72, 128, 128), (60, 107, 16, 128, 104),
-                                            (68, 120, 88, 128, 128)])
+# tiles of 32 positions per block for c1 / c2 output channels: 1 (64 input channels), 2, 3, 4, 5 in turn; then grids of few tiles, on the
+# float32 instruction: wavefronts without an item, with one to three, and more than are on their way at once; 256 tiles and 260
+@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 64, 64, 24), (60, 107, 24, 64, 40), (45, 80, 72, 128, 128), (60, 107, 16, 128, 104),
+                                            (68, 120, 88, 128, 128),
+                                            (11, 29, 8, 40, 24), (11, 29, 104, 128, 56), (62, 126, 24, 32, 32), (63, 126, 24, 32, 32)])
 def test_split_products_are_as_good_as_float32(h, w, c_in, c1, c2):
     """Logits, gradient of every parameter block and feature gradient of one step against the oracle in float64, 2-norm.  Each sum
     adds up to 9 * 128 products that are right to 2^-25 in float32: 1e-6 for the logits, three times what the float32
@@ -78,7 +80,7 @@ ENDS = [((-112, 60, 52, 0), (0, 0, 0, 0), "z", ""),           # features whose l
         ((0, 0, -126, 126), (0, 0, 0, 0), "", "W2")]          # gradients
 
 
-@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 8, 40, 24), (45, 80, 72, 128, 104)])
+@pytest.mark.parametrize("h,w,c_in,c1,c2", [(11, 29, 8, 40, 24), (11, 29, 64, 64, 24), (45, 80, 72, 128, 104)])
 @pytest.mark.parametrize("powers,plain,same,rounded", ENDS)
 def test_convolutions_at_the_ends_of_the_float32_range(powers, plain, same, rounded, h, w, c_in, c1, c2):
     """Powers of two on the operands are powers of two on the results, as in float32: bit for bit where no sum of scaled
