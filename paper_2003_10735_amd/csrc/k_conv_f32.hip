@@ -1,12 +1,12 @@
 // Float32 path: the head's 3x3 contractions on the bfloat16 matrix cores with float32 operands kept whole.  (The convolutions of grids
 // with few tiles on the float32 instruction: k_conv3x3_f32_few.)
 //
-// A float32 value is the exact sum of three bfloat16 values, each the rest of the ones before it rounded to nearest:
+// A float32 value from 2^-110 to 3.39e38 is the exact sum of three bfloat16 values, each the rest of the ones before it rounded to nearest:
 // x = xh + xm + xl.  Of the nine products of two such sums the six largest are formed,
 //     xh wh  +  (xh wm + xm wh + xm wm + xh wl + xl wh),
-// each exactly, and added in float32; what is left out is below 2^-25 of a product, of either sign.  (Cut off instead of rounded, the
-// three parts have one sign, and what is left out shifts every sum by 2^-24 of itself the same way: weight gradients
-// were three times further from float64 than the float32 instructions' for it.)  Six v_mfma_f32_32x32x16_bf16 take 192 cycles
+// each exactly, and added in float32; what is left out is below 2^-24 of a product (worst 1.98 * 2^-25, at 1.0039 * 1.0039; root mean
+// square over all mantissas 2^-27.5), of either sign.  (Cut off instead of rounded, the three parts have one sign, and what is left out
+// shifts every sum the same way: weight gradients were three times further from float64 than the float32 instructions' for it.)  Six v_mfma_f32_32x32x16_bf16 take 192 cycles
 // for what eight v_mfma_f32_32x32x2_f32 x 64 cycles do.  Errors against float64 (2-norm, seven sizes from 16 x 16 cells
 // and 24 channels to 140 x 250 and 256, four seeds each): logits 1.1 - 1.8e-7 (1.5 - 3.8e-7 with the float32 instructions), feature
 // gradient 1.5 - 2.0e-7 (1.9 - 3.4e-7), weight gradients 4.4 - 8.2e-8 (3.9 - 7.9e-8).

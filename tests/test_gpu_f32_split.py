@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
                                             (11, 29, 8, 40, 24), (11, 29, 104, 128, 56), (62, 126, 24, 32, 32), (63, 126, 24, 32, 32)])
 def test_split_products_are_as_good_as_float32(h, w, c_in, c1, c2):
     """Logits, gradient of every parameter block and feature gradient of one step against the oracle in float64, 2-norm.  Each sum
-    adds up to 9 * 128 products that are right to 2^-25 in float32: 1e-6 for the logits, three times what the float32
+    adds up to 9 * 128 products that are right to 2^-24 (2^-27.5 in the mean) in float32: 1e-6 for the logits, three times what the float32
     instructions show.  Backward one activation in a million changes sign with the last bit, which moves a gradient by one
     position's share (1 / 319 of it at the smallest size) and elements of the feature gradient as a whole."""
     wl = WL.small_variant(WL.WORKLOADS["tiny"], h=h, w=w, c_in=c_in, c1=c1, c2=c2, n_classes=9, steps=1, lr=1.0, n_sites=20)
