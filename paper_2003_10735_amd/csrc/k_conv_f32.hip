@@ -9,19 +9,19 @@
 // shifts every sum the same way: weight gradients were three times further from float64 than the float32 instructions' for it.)  Six v_mfma_f32_32x32x16_bf16 take 192 cycles
 // for what eight v_mfma_f32_32x32x2_f32 x 64 cycles do.  Errors against float64 (2-norm, seven sizes from 16 x 16 cells
 // and 24 channels to 140 x 250 and 256, four seeds each): logits 1.1 - 1.8e-7 (1.5 - 3.8e-7 with the float32 instructions), feature
-// gradient 1.5 - 2.0e-7 (1.9 - 3.4e-7), weight gradients 4.4 - 8.2e-8 (3.9 - 7.9e-8).
+// gradient 1.5 - 2.0e-7 (1.9 - 3.4e-7); weight gradients: see there.
 // Measured, 68 x 120 cells, 256 -> 128 -> 128, us per launch, float32 instructions / here: layer 1 49.6 / 36, layer 2 with the
-// classifier 28.3 / 23.5, its data gradient 27.2 / 22, weight gradients 77 / 44.5; a 4-step call 902 -> 647, 16 x 16 cells unchanged.
+// classifier 28.3 / 23.5, its data gradient 27.2 / 22, weight gradients 77 / 49; a 4-step call 901 -> 686, 16 x 16 cells unchanged.
 // What binds now: a wavefront issues one instruction in four cycles, and splitting (eleven per pair of values) leaves few of
 // the eight places an MFMA takes empty -- about 7.5 are used.
 //
-// The whole range of float32 (convolutions).  A bfloat16 has no bits below 2^-133, so the last parts of a value below 2^-110 would be lost.
-// Operands therefore enter times 2^24 -- weights from the kernel that writes their copies, activations on their way to LDS -- which puts
+// The whole range of float32.  A bfloat16 has no bits below 2^-133, so the last parts of a value below 2^-110 would be lost.
+// Operands therefore enter times 2^24 -- weights from the kernel that writes their copies, activations on their way to LDS, both operands
+// of a weight gradient as they are split -- which puts
 // even the last bit of a subnormal, 2^-149, among the normal values, and the sums are taken times 2^-48.  What that makes overflow (an
 // operand from 2^104 or a sum from 2^80 on), infinities and NaN give sums that are not finite: those are formed again, from the
-// operands as they are, by the float32 instruction (conv_f32_plain), and no others.  Factors and test cost 0.5 % of the
-// 68 x 120 call (659 -> 662 us).
-// (In the weight gradient operands are not scaled, and all six products share an accumulator: an infinite sum comes out as NaN.)
+// operands as they are, by the float32 instruction (conv_f32_plain, wgrad_f32_plain), and no others.  Factors and test cost the
+// convolutions 0.5 % of the 68 x 120 call (659 -> 662 us).
 //
 // Everything stays float32 in memory -- activations in runs of eight channels [c / 8][position][8] (pos8_index), weights in the
 // fragment order of wfrag_index -- and is split by the kernel that reads it, between its MFMAs.  (Weights written as three
@@ -578,8 +578,17 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
 // One wavefront accumulates 32 (o) x 32 (i) x 9 (taps), k = 16 positions per unit.  A lane reads the eight positions of its
 // channel that an operand needs as eight 4-byte loads and splits them itself.  As in the bfloat16 kernel dY is what moves by
 // one position for the taps to the left and right: ten positions of it are read, and the three fragments of a plane are packed
-// from them.  34 loads and some 240 vector instructions for 54 MFMAs (1728 cycles), all for the unit behind the one in work.
+// from them.  34 loads and some 270 vector instructions for 54 MFMAs (1728 cycles), all for units to come.
 // (dY is zero on the border of the grid and in the guard.)
+// The large products have accumulators of their own, as in the convolution.  An MFMA cuts off downwards what lies far below its
+// accumulator, and six of them per unit into one round more often than eight float32 instructions do: error of the sums against
+// float64 (2-norm, same dY and features, ten sizes from 16 x 16 cells and 24 channels to 140 x 250 and 128, six seeds each), float32
+// instructions / six into one accumulator / here: 0.63 - 2.8e-7, mean 1.03 / 0.65 - 3.8e-7, mean 1.25, shifted by - 0.14 - 1.2e-7
+// of the elements' size / 0.55 - 1.6e-7, mean 0.76, no shift.
+// 18 tiles of accumulators leave 224 registers for operands; of X only one unit's fragments are held therefore, a kernel row at a time.
+// Measured, 68 x 120 cells, 256 -> 128 -> 128: 77 us with the float32 instructions, 43.8 into one accumulator and without the factors, 49
+// here; four steps 667 -> 686 us, 24 x 40 cells 311 -> 318, 90 x 160 cells, 128 channels 808 -> 828, 16 x 16 cells the same.  (One unit
+// ahead instead of two, one loop body, cleared by MFMAs, the test behind the sum over the wavefronts: 685 - 692 us.)
 // The rest (four wavefronts per block added through LDS, position splits added by the optimiser
 // kernel, both layers in one launch) is as for the bfloat16 kernel.
 struct Wgrad32Args {
@@ -588,6 +597,30 @@ struct Wgrad32Args {
     int cin, cout, GX, GY, PPT, guard, Wp, n_units, units_per_wave;       // units of 16 positions
     int o_tiles, i_tiles, splits, items_per_xcd;
 };
+
+// Those of a wavefront's sums that are not finite, formed by the float32 matrix instruction (number e of a unit pairs positions e and 8 + e).
+__device__ __forceinline__ void wgrad_f32_plain(const float* yp, const float* xp, ptrdiff_t xrow, int units, f32x16 (&acc)[9])
+{
+    f32x16 sum[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[t][r] = 0.f;
+#pragma unroll 1
+    for (int u = 0; u < units; ++u, yp += 128, xp += 128)
+#pragma unroll 1
+        for (int e = 0; e < 8; ++e) {
+            float y[3], x[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { y[k] = yp[(e + 1 - k) * 8]; x[k] = xp[(k - 1) * xrow + e * 8]; }
+#pragma unroll
+            for (int t = 0; t < 9; ++t) sum[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t / 3], y[t % 3], sum[t], 0, 0, 0);
+        }
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = __builtin_isfinite(acc[t][r]) ? acc[t][r] : sum[t][r];
+}
 
 __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32Args a2, int blocks1)
 {
@@ -603,11 +636,11 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
     const int split = item / tiles, tile = item - split * tiles;
     const int o0 = (tile % a.o_tiles) * 32, i0 = (tile / a.o_tiles) * 32;
 
-    f32x16 acc[9];
+    f32x16 acc[9], rest[9];       // the large products' sums, and those of the other five
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        for (int r = 0; r < 16; ++r) { acc[t][r] = 0.f; rest[t][r] = 0.f; }
     float bsum = 0.f;
 
     const int u0 = (split * 4 + wave) * a.units_per_wave, u1 = min(u0 + a.units_per_wave, a.n_units);
@@ -616,97 +649,117 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
         const float* yp = a.dY + ((size_t)min((o0 + l32) >> 3, a.GY - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
         const float* xp = a.X + ((size_t)min((i0 + l32) >> 3, a.GX - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
         const ptrdiff_t xrow = (ptrdiff_t)a.Wp * 8;
-        // raw values of two units ahead: positions - 1 .. 8 of dY, 0 .. 7 of X in the three rows
+        // raw values of two units: positions - 1 .. 8 of dY, 0 .. 7 of X in the three rows
         float ry[2][10], rx[2][3][8];
-        const float* yl = yp; const float* xl = xp;        // the unit to be loaded next
-        auto load_y = [&](int s, int e) __attribute__((always_inline)) { ry[s][e] = yl[(e - 1) * 8]; };
-        auto load_x = [&](int s, int kh, int e) __attribute__((always_inline)) { rx[s][kh][e] = xl[(kh - 1) * xrow + e * 8]; };
-        u32x4 fy[2][3][3], fx[2][3][3];   // fragments of the unit in work and the next: [dY at p + 1, p, p - 1][plane], [kernel row][plane]
+        const float* yl = yp; const float* xl = xp;        // the unit in work
+        auto load_y = [&](int s, int ahead, int e) __attribute__((always_inline)) { ry[s][e] = yl[ahead * 128 + (e - 1) * 8]; };
+        auto load_x = [&](int s, int ahead, int kh, int e) __attribute__((always_inline)) { rx[s][kh][e] = xl[(kh - 1) * xrow + ahead * 128 + e * 8]; };
+        // Fragments: of dY for the unit in work and the next [dY at p + 1, p, p - 1][plane]; of X [kernel row][plane] for the unit in work,
+        // each row replaced by the next unit's once its three taps are done
+        u32x4 fy[2][3][3], fx[3][3];
+        unsigned y4[3];
+        float r0 = 0.f, r1 = 0.f;
         // dY: pairs of neighbouring positions 2 k - 1, 2 k (k = 0 .. 4), per plane; the fragment at p - 1 takes the first four, the one at
         // p + 1 the last four, the one at p the pairs between them
-        unsigned yw[3][5];
-        float m0[5], m1[5], r0 = 0.f, r1 = 0.f;
+        auto put_y = [&](int s, int q, int k, unsigned v) __attribute__((always_inline)) { if (k < 4) fy[s][2][q][k] = v; else y4[q] = v; };
         auto split_ya = [&](int s, int k) __attribute__((always_inline)) {
-            yw[0][k] = round_pair(ry[s][2 * k], ry[s][2 * k + 1]);
-            m0[k] = __fsub_rn(ry[s][2 * k], low_of(yw[0][k])); m1[k] = __fsub_rn(ry[s][2 * k + 1], high_of(yw[0][k]));
+            const float v0 = ry[s][2 * k] * F32_SPLIT_SCALE, v1 = ry[s][2 * k + 1] * F32_SPLIT_SCALE;
+            const unsigned h = round_pair(v0, v1);
+            put_y(s, 0, k, h);
+            r0 = __fsub_rn(v0, low_of(h)); r1 = __fsub_rn(v1, high_of(h));
         };
-        auto split_yb = [&](int k) __attribute__((always_inline)) {
-            yw[1][k] = round_pair(m0[k], m1[k]);
-            yw[2][k] = round_pair(__fsub_rn(m0[k], low_of(yw[1][k])), __fsub_rn(m1[k], high_of(yw[1][k])));
+        auto split_yb = [&](int s, int k) __attribute__((always_inline)) {
+            const unsigned m = round_pair(r0, r1);
+            put_y(s, 1, k, m);
+            put_y(s, 2, k, round_pair(__fsub_rn(r0, low_of(m)), __fsub_rn(r1, high_of(m))));
         };
         auto place_y = [&](int s, int e) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                fy[s][2][q][e] = yw[q][e];
-                fy[s][1][q][e] = __builtin_amdgcn_alignbyte(yw[q][e + 1], yw[q][e], 2);
-                fy[s][0][q][e] = yw[q][e + 1];
+                const unsigned next = e < 3 ? fy[s][2][q][(e + 1) & 3] : y4[q];
+                fy[s][1][q][e] = __builtin_amdgcn_alignbyte(next, fy[s][2][q][e], 2);
+                fy[s][0][q][e] = next;
             }
         };
         auto split_xa = [&](int s, int kh, int e) __attribute__((always_inline)) {
-            const float v0 = rx[s][kh][2 * e], v1 = rx[s][kh][2 * e + 1];
+            const float v0 = rx[s][kh][2 * e] * F32_SPLIT_SCALE, v1 = rx[s][kh][2 * e + 1] * F32_SPLIT_SCALE;
             const unsigned h = round_pair(v0, v1);
-            fx[s][kh][0][e] = h;
+            fx[kh][0][e] = h;
             r0 = __fsub_rn(v0, low_of(h)); r1 = __fsub_rn(v1, high_of(h));
         };
-        auto split_xb = [&](int s, int kh, int e) __attribute__((always_inline)) {
+        auto split_xb = [&](int kh, int e) __attribute__((always_inline)) {
             const unsigned m = round_pair(r0, r1);
-            fx[s][kh][1][e] = m;
-            fx[s][kh][2][e] = round_pair(__fsub_rn(r0, low_of(m)), __fsub_rn(r1, high_of(m)));
+            fx[kh][1][e] = m;
+            fx[kh][2][e] = round_pair(__fsub_rn(r0, low_of(m)), __fsub_rn(r1, high_of(m)));
         };
-        // what follows MFMA number t of a unit: of the next unit (raw values and fragments s) the splitting, then the loads
-        // that replace its raw values by those of the unit two behind it
-        // (live: it belongs to this wavefront's range)
-        auto place = [&](int s, int t, bool live) __attribute__((always_inline)) {
-            if (t < 10) { if (t & 1) split_yb(t >> 1); else split_ya(s, t >> 1); }
-            else if (t < 19) {
-                if (t < 14) place_y(s, t - 10);
-                if (t < 18) bsum += live ? ry[s][t - 9] : 0.f;
-            } else if (t < 43) {
-                const int i = t - 19, kh = i >> 3, e = (i >> 1) & 3;
-                if (i & 1) split_xb(s, kh, e); else split_xa(s, kh, e);
-                if (i < 10) load_y(s, i);
-                if (i >= 10) load_x(s, (i - 10) >> 3, (i - 10) & 7);
-            } else if (t < 53) {
-                const int i = t - 29;        // the last ten values of X
-                load_x(s, i >> 3, i & 7);
+        // What follows MFMA number t of a unit (18 per kernel row; raw values in slot S, the next unit's in N): the splitting of this unit's
+        // last row, then of the next unit's dY and first two rows, and the loads that replace those raw values by the next but one's in
+        // their slot.  (live: the next unit belongs to this wavefront's range)
+        auto place = [&](auto N_, auto t_, bool live) __attribute__((always_inline)) {
+            constexpr int N = decltype(N_)::value, S = 1 - N, t = decltype(t_)::value;
+            constexpr int i = t < 8 ? t : t < 18 ? t - 8 : t < 26 ? t - 18 : t < 36 ? t - 26 : t < 44 ? t - 36 : t - 44;
+            if constexpr (t < 8) { if constexpr (i & 1) split_xb(2, i >> 1); else split_xa(S, 2, i >> 1); }
+            else if constexpr (t < 18) {
+                if constexpr (i & 1) split_yb(N, i >> 1); else split_ya(N, i >> 1);
+                if constexpr (i < 8) load_x(S, 2, 2, i);
+            } else if constexpr (t < 26) { if constexpr (i & 1) split_xb(0, i >> 1); else split_xa(N, 0, i >> 1); }
+            else if constexpr (t < 36) {
+                if constexpr (i < 8) { bsum += live ? ry[N][i + 1] : 0.f; load_x(N, 3, 0, i); }
+                load_y(N, 3, i);
+            } else if constexpr (t < 44) { if constexpr (i & 1) split_xb(1, i >> 1); else split_xa(N, 1, i >> 1); }
+            else {
+                if constexpr (i < 8) load_x(N, 3, 1, i);
+                if constexpr (i >= 6) place_y(N, i - 6);
             }
         };
+        const std::integral_constant<int, 0> slot0; const std::integral_constant<int, 1> slot1;
         auto unit = [&](auto S_, bool next_live) __attribute__((always_inline)) {
-            constexpr int S = decltype(S_)::value, N = 1 - S;
-            constexpr int px[6] = {2, 0, 1, 0, 1, 0}, py[6] = {0, 2, 1, 1, 0, 0};      // the smallest products first
-#pragma unroll
-            for (int t = 0; t < 54; ++t) {
-                const int q = t / 9, tap = t % 9;
-                acc[tap] = mfma_bf16(fx[S][tap / 3][px[q]], fy[S][tap % 3][py[q]], acc[tap]);
+            constexpr int S = decltype(S_)::value;
+            unrolled<54>([&](auto t_) __attribute__((always_inline)) {
+                constexpr int t = decltype(t_)::value, kh = t / 18, q = t % 18 / 3, kw = t % 3, tap = kh * 3 + kw;
+                constexpr int px[6] = {2, 0, 1, 0, 1, 0}, py[6] = {0, 2, 1, 1, 0, 0};
+                if constexpr (q == 5) acc[tap] = mfma_bf16(fx[kh][0], fy[S][kw][0], acc[tap]);
+                else rest[tap] = mfma_bf16(fx[kh][px[q]], fy[S][kw][py[q]], rest[tap]);
                 CF_F
-                place(N, t, next_live);
+                place(std::integral_constant<int, 1 - S>{}, t_, next_live);
                 CF_F
-            }
+            });
             yl += 128; xl += 128;
         };
         // (loads run up to three units past the end of the range: guard positions, not used)
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
 #pragma unroll
-            for (int e = 0; e < 10; ++e) load_y(s, e);
+            for (int e = 0; e < 10; ++e) load_y(s, s, e);
 #pragma unroll
             for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) load_x(s, kh, e);
-            yl += 128; xl += 128;
+                for (int e = 0; e < 8; ++e) load_x(s, s, kh, e);
         }
         asm volatile("" ::: "memory");
-#pragma unroll
-        for (int t = 0; t < 54; ++t) { place(0, t, true); CF_F }
-        yl += 128; xl += 128;
+        // the first unit's dY and first two rows, as a unit in front of it would do it
+        xl -= 128; yl -= 128;
+        unrolled<46>([&](auto i_) __attribute__((always_inline)) { place(slot0, std::integral_constant<int, decltype(i_)::value + 8>{}, true); CF_F });
+        xl += 128; yl += 128;
         int u = u0;
         for (; u + 2 <= u1; u += 2) {
-            unit(std::integral_constant<int, 0>{}, true);
+            unit(slot0, true);
             asm volatile("" ::: "memory");
-            unit(std::integral_constant<int, 1>{}, u + 2 < u1);
+            unit(slot1, u + 2 < u1);
             asm volatile("" ::: "memory");
         }
-        if (u < u1) unit(std::integral_constant<int, 0>{}, false);
+        if (u < u1) unit(slot0, false);
+
+        // ---- the sums, formed again where they are not finite
+        float finite = 0.f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[t][r] = (acc[t][r] + rest[t][r]) * F32_SPLIT_BACK;
+                finite = __builtin_fmaf(acc[t][r], 0.f, finite);
+            }
+        if (__builtin_expect(__ballot(finite != 0.f) != 0, 0)) wgrad_f32_plain(yp, xp, xrow, u1 - u0, acc);
     }
     float* redb = red + 4 * 9 * 32 * 32;
     bsum += __shfl_xor(bsum, 32, 64);

@@ -1,5 +1,6 @@
 """Float32 path, whose operands enter the matrix cores as three bfloat16 parts except on grids of few tiles: every number of position tiles per block, odd runs of
-eight channels (half a fragment of sixteen), the ends of the float32 range, and what an infinite feature reaches."""
+eight channels (half a fragment of sixteen), the ends of the float32 range, and what an infinite feature reaches; the weight gradients
+by themselves."""
 import numpy as np
 import pytest
 import torch
@@ -117,3 +118,74 @@ def test_convolutions_at_the_ends_of_the_float32_range(powers, plain, same, roun
         assert np.linalg.norm(z1 - z0) < 1e-6 * np.linalg.norm(z0)
     if powers[1] >= -100:      # (else the feature gradient is subnormal)
         assert np.linalg.norm(df1 - df0) < 1e-5 * np.linalg.norm(df0)
+
+
+def _identity_layers(h, w, c, powers=(0, 0, 0, 0), one_sign=False):
+    """One step whose 3x3 layers hand their input through, features and layers times powers of two that cancel in the logits: the feature
+    gradient is then both layers' dY exactly, but for its power.  Returns features, dY and the weight gradients without their powers."""
+    C = 2 if one_sign else 9
+    wl = WL.small_variant(WL.WORKLOADS["tiny"], h=h, w=w, c_in=c, c1=c, c2=c, n_classes=C, steps=1, lr=0.0, n_sites=20)
+    rng, sl = np.random.default_rng(h), WL.param_slices(wl)
+    x = (rng.uniform(0.25, 3.9999, (1, c, h, w)) * (rng.random((1, c, h, w)) < 0.5)).astype(np.float32)
+    lab = np.zeros((1, 8 * h, 8 * w), np.int32) if one_sign else WL.make_labels(wl)
+    a, b1, b2, b3 = (2.0 ** float(e) for e in powers)
+    p = np.zeros(WL.make_head_params(wl).size)
+    eye = np.zeros((c, c, 9))
+    eye[np.arange(c), np.arange(c), 4] = 1.0
+    w3 = rng.normal(0, (2.0 / c) ** 0.5, (C, c)).astype(np.float32).astype(np.float64)
+    if one_sign:
+        w3 = np.abs(w3) * np.array([-1.0, 1.0])[:, None]
+    p[sl["W1"]], p[sl["W2"]], p[sl["W3"]] = (eye * b1).reshape(-1), (eye * b2).reshape(-1), (w3 * b3).reshape(-1)
+    fd, pd = torch.from_numpy((x * a).astype(np.float32)).cuda(), torch.from_numpy(p.astype(np.float32)).cuda()
+    v, df = torch.zeros_like(pd), torch.zeros_like(fd)
+    st.st_partial_distill(st.HeadDesc.of(wl), fd, torch.from_numpy(lab).cuda(), pd, 1, 0.0, momentum=0.9, velocity=v, feature_grad=df)
+    v = v.cpu().numpy().astype(np.float64)
+    return (x[0].astype(np.float64), df.cpu().numpy()[0].astype(np.float64) / (b3 * b2 * b1),
+            v[sl["W1"]].reshape(c, c * 9) / (a * b2 * b3), v[sl["W2"]].reshape(c, c * 9) / (a * b1 * b3))
+
+
+def _weight_gradient(x, dy):
+    c = x.shape[0]
+    return dy.reshape(c, -1) @ torch.nn.functional.unfold(torch.from_numpy(x)[None], 3, padding=1)[0].numpy().T
+
+
+# 5.5, 22.5, 39 and 259 units of 16 positions; channels that leave 8 of a tile's 32, half tiles and whole ones
+@pytest.mark.parametrize("h,w,c", [(9, 6, 8), (13, 21, 40), (24, 20, 72), (45, 80, 104)])
+def test_weight_gradients_alone_are_as_good_as_float32(h, w, c):
+    """Against float64 sums of the same dY and features, 2-norm.  The float32 instructions show 6e-8 to 3e-7, one missing product of
+    parts 1.2e-6 and more (test_split_products.py).  Sums do not shift to one side either: an MFMA that adds a product far below its
+    accumulator cuts it off downwards, which showed as 1.4e-8 to 1.2e-7 of the elements' sum; rounded to nearest, the mean of 9 c^2 errors is
+    two orders below their size."""
+    x, dy, g1, g2 = _identity_layers(h, w, c)
+    ref = _weight_gradient(x, dy)
+    for got in (g1, g2):
+        err = got - ref
+        assert np.linalg.norm(err) < 6e-7 * np.linalg.norm(ref)
+        if c >= 40:
+            assert abs(err.sum()) < 6e-9 * np.abs(ref).sum()
+
+
+# powers of two on the features, W1, W2 and W3, with sum 0; whether all sums stay finite with their operands scaled (bit for bit the same)
+@pytest.mark.parametrize("powers,same", [((-112, 60, 52, 0), True),       # features whose last bits lie below 2^-133
+                                         ((95, 0, 0, -95), True),         # gradients
+                                         ((126, -63, 0, -63), False),     # features up to 3.4e38, beyond the largest bfloat16
+                                         ((-115, 0, 0, 115), False)])     # gradients
+@pytest.mark.parametrize("h,w,c", [(13, 21, 40), (24, 20, 72)])
+def test_weight_gradients_at_the_ends_of_the_float32_range(powers, same, h, w, c):
+    _, _, p1, p2 = _identity_layers(h, w, c)
+    _, _, g1, g2 = _identity_layers(h, w, c, powers)
+    for got, plain in ((g1, p1), (g2, p2)):
+        if same:
+            np.testing.assert_array_equal(got, plain)
+        else:
+            assert np.linalg.norm(got - plain) < 1e-6 * np.linalg.norm(plain)
+
+
+def test_weight_gradients_beyond_the_float32_range_are_infinite():
+    """Finite operands of one sign whose sums exceed the largest float32: infinite, as a float32 sum is, and not NaN."""
+    powers = (100, -140, 20, 20)
+    x, dy, g1, g2 = _identity_layers(13, 21, 40, powers, one_sign=True)
+    ref = _weight_gradient(x, dy)
+    beyond = ref * 2.0 ** 140 > 1.01 * float(np.finfo(np.float32).max)
+    assert beyond.any() and np.all(np.isposinf(g1[beyond])) and not np.isnan(g1).any()
+    assert np.linalg.norm(g2 - ref) < 6e-7 * np.linalg.norm(ref)
