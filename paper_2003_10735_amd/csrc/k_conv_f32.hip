@@ -1,5 +1,5 @@
 // Float32 path: the head's 3x3 contractions on the bfloat16 matrix cores with float32 operands kept whole.  (The convolutions of grids
-// with few tiles on the float32 instruction: k_conv3x3_f32_few.)
+// with few tiles and the weight gradients of small frames on the float32 instruction: k_conv3x3_f32_few, k_wgrad3x3_f32_few.)
 //
 // A float32 value from 2^-110 to 3.39e38 is the exact sum of three bfloat16 values, each the rest of the ones before it rounded to nearest:
 // x = xh + xm + xl.  Of the nine products of two such sums the six largest are formed,
@@ -587,14 +587,14 @@ static void conv_f32(Ctx& c, const char* name, const Plan& p, int epi, const flo
 // of the elements' size / 0.55 - 1.6e-7, mean 0.76, no shift.
 // 18 tiles of accumulators leave 224 registers for operands; of X only one unit's fragments are held therefore, a kernel row at a time.
 // Measured, 68 x 120 cells, 256 -> 128 -> 128: 77 us with the float32 instructions, 43.8 into one accumulator and without the factors, 49
-// here; four steps 667 -> 686 us, 24 x 40 cells 311 -> 318, 90 x 160 cells, 128 channels 808 -> 828, 16 x 16 cells the same.  (One unit
+// here; four steps 667 -> 686 us, 24 x 40 cells 311 -> 318, 90 x 160 cells, 128 channels 808 -> 828.  (One unit
 // ahead instead of two, one loop body, cleared by MFMAs, the test behind the sum over the wavefronts: 685 - 692 us.)
 // The rest (four wavefronts per block added through LDS, position splits added by the optimiser
 // kernel, both layers in one launch) is as for the bfloat16 kernel.
 struct Wgrad32Args {
     const float* dY; const float* X; float* dW; float* db;
     size_t split_stride;
-    int cin, cout, GX, GY, PPT, guard, Wp, n_units, units_per_wave;       // units of 16 positions
+    int cin, cout, GX, GY, PPT, guard, Wp, n_units, units_per_wave;       // units of 16 positions (k_wgrad3x3_f32_few: 8)
     int o_tiles, i_tiles, splits, items_per_xcd;
 };
 
@@ -769,13 +769,91 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
         a.db[(size_t)split * a.split_stride + o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
 }
 
+// The same by the float32 instruction, for frames that leave a wavefront few positions: there a launch is what comes before and behind the
+// products, which is less here (no splitting, half the accumulators).  The two values of k of an MFMA are not neighbours but the
+// same place in the two halves of the wavefront's range: a lane walks its half one position at a time, and the three taps of a kernel row
+// are the values it holds for the previous, this and the next position.  Per position four 4-byte loads feed nine MFMAs.
+__global__ void __launch_bounds__(256) k_wgrad3x3_f32_few(Wgrad32Args a1, Wgrad32Args a2, int blocks1)
+{
+    extern __shared__ __attribute__((aligned(16))) float red[];
+    const bool second = (int)blockIdx.x >= blocks1;
+    const Wgrad32Args& a = second ? a2 : a1;
+    const int bid = second ? blockIdx.x - blocks1 : blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const int tiles = a.o_tiles * a.i_tiles;
+    const int item = (bid % 8) * a.items_per_xcd + bid / 8;
+    if (bid / 8 >= a.items_per_xcd || item >= tiles * a.splits) return;
+    const int split = item / tiles, tile = item - split * tiles;
+    const int o0 = (tile % a.o_tiles) * 32, i0 = (tile / a.o_tiles) * 32;
+
+    f32x16 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    float bsum = 0.f;
+
+    const int u0 = (split * 4 + wave) * a.units_per_wave, u1 = min(u0 + a.units_per_wave, a.n_units);
+    const int half = (u1 - u0) * 4;          // (the positions are a multiple of eight)
+    if (half > 0) {
+        // (channels beyond the last group re-read it: their sums are dropped at the end)
+        const size_t from = (size_t)a.guard + u0 * 8 + lhi * half;
+        const float* yp = a.dY + ((size_t)min((o0 + l32) >> 3, a.GY - 1) * a.PPT + from) * 8 + (l32 & 7);
+        const float* xp = a.X + ((size_t)min((i0 + l32) >> 3, a.GX - 1) * a.PPT + from) * 8 + (l32 & 7);
+        // slot s of the ring holds dY of position s (mod 8) and X of position s - 1.  Loads run up to fifteen positions past the half
+        // (guard positions make them readable).
+        constexpr int D = 8;
+        float ry[D], rx[D][3];
+        auto load = [&](int s, int t) __attribute__((always_inline)) {
+            ry[s] = yp[t * 8];
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh) rx[s][kh] = xp[(t - 1 + (kh - 1) * a.Wp) * 8];
+        };
+        auto products = [&](int s) __attribute__((always_inline)) {
+            bsum += ry[s];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(rx[(s + k % 3) % D][k / 3], ry[s], acc[k], 0, 0, 0);
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+        int t = 0;
+        for (; t + D <= half; t += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) { products(d); load(d, t + D + d); }
+        }
+        // (half a ring is left, or nothing)
+        if (t < half)
+#pragma unroll
+            for (int d = 0; d < D / 2; ++d) products(d);
+    }
+    float* redb = red + 4 * 9 * 32 * 32;
+    bsum += __shfl_xor(bsum, 32, 64);
+    if (lhi == 0) redb[wave * 32 + l32] = bsum;
+    wgrad_reduce_store(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
+    if (i0 == 0 && tid < 32 && o0 + tid < a.cout)
+        a.db[(size_t)split * a.split_stride + o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
+}
+
+// Which form a frame's weight gradients take: the float32 instruction where its shorter ends outweigh its longer units, which is where the
+// split form's wavefronts have at most two.  us per launch, few / split: 16 x 16 cells, 24 -> 32 -> 24 channels 8.3 / 11.7, 64 channels 7.8 /
+// 11.8; 12 x 20, 128 channels 9.8 / 12.4; 16 x 24, 256 -> 128 -> 128 12.2 / 13.5; 24 x 40, 64 channels 10.6 / 12.4 (all two units); 24 x 40, 128
+// channels 14.5 / 14.6, 30 x 50, 128 -> 128 -> 64 16.7 / 15.7 (three); 34 x 54, 128 channels 17.4 / 16.5 (four).
+WgradForm wgrad_f32_form(const Geo& g)
+{
+    int s1, s2;
+    wgrad_splits_for(g, WGRAD_F32, &s1, &s2);
+    const int n_units = cdiv(g.padded_positions(), 16);
+    return cdiv(n_units, std::min(s1, s2) * 4) <= 2 ? WGRAD_F32_FEW : WGRAD_F32;
+}
+
 static Wgrad32Args wgrad_f32_args(const Plan& p, const float* dY, const float* X, float* dW, float* db, int cin, int cout, int splits)
 {
     Wgrad32Args a;
     a.dY = dY; a.X = X; a.dW = dW; a.db = db; a.split_stride = p.grad_stride;
     a.cin = cin; a.cout = cout; a.GX = cdiv(cin, 8); a.GY = cdiv(cout, 8);
     a.PPT = p.PPT; a.guard = p.guard; a.Wp = p.g.Wp;
-    a.n_units = cdiv(p.g.padded_positions(), 16);
+    a.n_units = cdiv(p.g.padded_positions(), p.wgrad_few ? 8 : 16);
     a.units_per_wave = cdiv(a.n_units, splits * 4);
     a.o_tiles = cdiv(cout, 32); a.i_tiles = cdiv(cin, 32); a.splits = splits;
     a.items_per_xcd = cdiv(a.o_tiles * a.i_tiles * splits, 8);
@@ -905,8 +983,9 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat)
     const Wgrad32Args a1 = wgrad_f32_args(p, f(p.da1), f(p.feat), grad + p.po.W1, grad + p.po.b1, g.c_in, g.c1, p.splits1);
     const Wgrad32Args a2 = wgrad_f32_args(p, f(p.da2), f(p.a1), grad + p.po.W2, grad + p.po.b2, g.c1, g.c2, p.splits2);
     const int blocks1 = a1.items_per_xcd * 8, blocks2 = a2.items_per_xcd * 8;
-    ensure_dynamic_lds((const void*)k_wgrad3x3_f32, WGRAD_SMEM_BYTES);
-    ST_LAUNCH(c, "conv12_wgrad_f32", k_wgrad3x3_f32, dim3(blocks1 + blocks2), dim3(256), WGRAD_SMEM_BYTES, a1, a2, blocks1);
+    const auto kernel = p.wgrad_few ? k_wgrad3x3_f32_few : k_wgrad3x3_f32;
+    ensure_dynamic_lds((const void*)kernel, WGRAD_SMEM_BYTES);
+    ST_LAUNCH(c, "conv12_wgrad_f32", kernel, dim3(blocks1 + blocks2), dim3(256), WGRAD_SMEM_BYTES, a1, a2, blocks1);
 }
 
 }  // namespace st

@@ -288,14 +288,16 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
 // optimiser kernel.  The search simulates exactly that for every pair of split counts and keeps the
 // shortest; among equals, fewer partial copies.
 // bfloat16: units of 16 positions (9 MFMAs of 32 cycles), the fixed cost is about 22 of them.
-// float32: the same positions take six times the MFMAs.
-void wgrad_splits_for(const Geo& g, bool bf16_path, int* s1_out, int* s2_out)
+// float32: units of 16 positions (54 MFMAs of 32 cycles); a launch takes some 10 us + 1.4 per unit, of which 4 units count as fixed (2: 120 x 200
+// cells, 256 -> 128 -> 128, 0.7 % slower; 8, 14: within 0.3 % at nine sizes from 16 x 16 cells on).  By the float32 instruction: units of 8
+// positions (36 MFMAs of 64 cycles).
+void wgrad_splits_for(const Geo& g, WgradForm form, int* s1_out, int* s2_out)
 {
     constexpr int n_cu = 256;
-    const int fixed_units = bf16_path ? 22 : 4, reread_units_per_chip = bf16_path ? 13 : 2;
-    const int min_units = bf16_path ? 8 : 2;       // units per wavefront where a layer is split at all
+    const int fixed_units = form == WGRAD_BF16 ? 22 : form == WGRAD_F32 ? 4 : 3, reread_units_per_chip = form == WGRAD_BF16 ? 13 : 2;
+    const int min_units = form == WGRAD_BF16 ? 8 : 2;       // units per wavefront where a layer is split at all
     const int tiles1 = g.heads() * cdiv(g.c1, 32) * cdiv(g.c_in, 32), tiles2 = g.heads() * cdiv(g.c2, 32) * cdiv(g.c1, 32);
-    const int n_units = cdiv(g.padded_positions() / g.heads(), 16);
+    const int n_units = cdiv(g.padded_positions() / g.heads(), form == WGRAD_F32_FEW ? 8 : 16);
     int best1 = 1, best2 = 1;
     long best_cost = -1;
     // compute units with the same free time form a group: (time, how many)

@@ -114,7 +114,7 @@ static int validate(const st_head_desc* d)
         if ((long long)g.k1 * g.ki * 9 >= (1ll << 30) || (long long)g.k2 * g.k1 * 9 >= (1ll << 30)) return ST_ERR_SHAPE;
         if (wgrad_offset_bytes(g, 1) >= (1ll << 31)) {
             int s1, s2;
-            wgrad_splits_for(g, true, &s1, &s2);
+            wgrad_splits_for(g, WGRAD_BF16, &s1, &s2);
             if (wgrad_offset_bytes(g, std::min(s1, s2)) >= (1ll << 31)) return ST_ERR_SHAPE;
         }
     }
@@ -144,7 +144,9 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.bf16 = d.compute == ST_COMPUTE_BF16;
     p.esz = p.bf16 ? 2 : 4;
     const Geo& g = p.g;
-    wgrad_splits_for(g, p.bf16, &p.splits1, &p.splits2);
+    const WgradForm form = p.bf16 ? WGRAD_BF16 : wgrad_f32_form(g);
+    p.wgrad_few = form == WGRAD_F32_FEW;
+    wgrad_splits_for(g, form, &p.splits1, &p.splits2);
     p.blocks3 = conv3_bwd_blocks(g);
     p.grad_copies = std::max(p.splits1, p.splits2);
     // guard: a 3x3 tap reaches Wp + 1 rows back/ahead of a tile that may overrun the grid by

@@ -120,6 +120,7 @@ struct Plan {
     // apart), grad3 (blocks3 slots apart), the bfloat16 weight copies (their own size apart),
     // the pixel counters (one each).
     int splits1, splits2;   // position splits (per head) of the layer-1 / layer-2 weight-gradient kernels
+    bool wgrad_few;         // float32 path: those kernels by the float32 instruction
     int blocks3;            // per-block partial slots (per head) of the layer-3 backward kernel
     int grad_copies;        // max of the splits: partial gradient copies the update sums
     size_t grad_stride;     // floats between two copies (total rounded up to 16 bytes)

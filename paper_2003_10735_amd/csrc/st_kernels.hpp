@@ -33,9 +33,13 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
 }
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst);
 
+// what the weight gradients of the 3x3 layers run on (float32: split operands, or the float32 instruction)
+enum WgradForm { WGRAD_BF16, WGRAD_F32, WGRAD_F32_FEW };
+
 // k_conv_f32.hip -- the float32 path's kernels
 // factor of the copy of the weights that a 3x3 layer of cin -> cout channels reads
 float conv_f32_weight_scale(const Geo& g, int cin, int cout);
+WgradForm wgrad_f32_form(const Geo& g);
 void forward_f32(Ctx& c, const Plan& p, char* ws);
 void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 
@@ -43,7 +47,7 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat);
 void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const bf16* Wq, const float* bias,
                   const bf16* mask, bf16* Y, bf16* YT, int cin, int cout, int epi,
                   const bf16* W3q = nullptr, float* zpart = nullptr, float* dense = nullptr);
-void wgrad_splits_for(const Geo& g, bool bf16_path, int* splits1, int* splits2);
+void wgrad_splits_for(const Geo& g, WgradForm form, int* splits1, int* splits2);
 void wgrad3x3_mfma(Ctx& c, const Plan& p, const bf16* da1T, const bf16* featT, const bf16* da2T,
                    const bf16* a1T, float* grad);
 int conv3_bwd_blocks(const Geo& g);

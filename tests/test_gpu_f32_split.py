@@ -149,8 +149,9 @@ def _weight_gradient(x, dy):
     return dy.reshape(c, -1) @ torch.nn.functional.unfold(torch.from_numpy(x)[None], 3, padding=1)[0].numpy().T
 
 
-# 5.5, 22.5, 39 and 259 units of 16 positions; channels that leave 8 of a tile's 32, half tiles and whole ones
-@pytest.mark.parametrize("h,w,c", [(9, 6, 8), (13, 21, 40), (24, 20, 72), (45, 80, 104)])
+# float32 instruction: 11, 42 and 156 units of 8 positions, an odd number of a wavefront and wavefronts without any; split: 44, 259 and 560
+# units of 16; channels that leave 8 of a tile's 32, half tiles and whole ones
+@pytest.mark.parametrize("h,w,c", [(9, 6, 8), (12, 20, 104), (24, 40, 64), (20, 30, 168), (45, 80, 104), (68, 120, 40)])
 def test_weight_gradients_alone_are_as_good_as_float32(h, w, c):
     """Against float64 sums of the same dY and features, 2-norm.  The float32 instructions show 6e-8 to 3e-7, one missing product of
     parts 1.2e-6 and more (test_split_products.py).  Sums do not shift to one side either: an MFMA that adds a product far below its
@@ -170,7 +171,7 @@ def test_weight_gradients_alone_are_as_good_as_float32(h, w, c):
                                          ((95, 0, 0, -95), True),         # gradients
                                          ((126, -63, 0, -63), False),     # features up to 3.4e38, beyond the largest bfloat16
                                          ((-115, 0, 0, 115), False)])     # gradients
-@pytest.mark.parametrize("h,w,c", [(13, 21, 40), (24, 20, 72)])
+@pytest.mark.parametrize("h,w,c", [(13, 21, 40), (34, 54, 104)])
 def test_weight_gradients_at_the_ends_of_the_float32_range(powers, same, h, w, c):
     _, _, p1, p2 = _identity_layers(h, w, c)
     _, _, g1, g2 = _identity_layers(h, w, c, powers)
@@ -181,10 +182,11 @@ def test_weight_gradients_at_the_ends_of_the_float32_range(powers, same, h, w, c
             assert np.linalg.norm(got - plain) < 1e-6 * np.linalg.norm(plain)
 
 
-def test_weight_gradients_beyond_the_float32_range_are_infinite():
+@pytest.mark.parametrize("h,w,c", [(13, 21, 40), (34, 54, 104)])
+def test_weight_gradients_beyond_the_float32_range_are_infinite(h, w, c):
     """Finite operands of one sign whose sums exceed the largest float32: infinite, as a float32 sum is, and not NaN."""
     powers = (100, -140, 20, 20)
-    x, dy, g1, g2 = _identity_layers(13, 21, 40, powers, one_sign=True)
+    x, dy, g1, g2 = _identity_layers(h, w, c, powers, one_sign=True)
     ref = _weight_gradient(x, dy)
     beyond = ref * 2.0 ** 140 > 1.01 * float(np.finfo(np.float32).max)
     assert beyond.any() and np.all(np.isposinf(g1[beyond])) and not np.isnan(g1).any()
