@@ -46,26 +46,26 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # the kernel source it was measured on:
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
-    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 33.79, 8.83),
-    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 13.75, 6.34),
-    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 6.98, 4.92),
-    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "41c0d75c7ea8d471b6225571b38dc4df81e1a3ea4e7f8ab81bfa81674c44d653", 10.45, 3.77),
-    ("720p", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 4.73, 4.71),
-    ("720p", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 3.09, 1.79),
-    ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 13.19, 9.81),
-    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 73.86, 8.83),
-    ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 23.23, 13.93),
-    ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 11.75, 8.23),
-    ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 19.98, 8.29),
-    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 7.32, 11.14),
-    ("1080p", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 3.73, 4.02),
+    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "11faaab0c139408bd52ca675f2c81690182e26c61aa77d6d40a573bbdbee21d2", 33.79, 8.83),
+    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "d65afa796fd22f4abe9c65cb603049a6afd9e5f7924828763942cdc199ff6ee6", 13.75, 6.34),
+    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "d65afa796fd22f4abe9c65cb603049a6afd9e5f7924828763942cdc199ff6ee6", 6.98, 4.92),
+    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "d65afa796fd22f4abe9c65cb603049a6afd9e5f7924828763942cdc199ff6ee6", 10.45, 3.77),
+    ("720p", "upsample_ce_grad"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 4.73, 4.71),
+    ("720p", "upsample_ce"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 3.09, 1.79),
+    ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 13.20, 9.81),
+    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "11faaab0c139408bd52ca675f2c81690182e26c61aa77d6d40a573bbdbee21d2", 73.86, 8.83),
+    ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 23.25, 13.93),
+    ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 11.78, 10.82),
+    ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 20.01, 8.29),
+    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 10.06, 11.14),
+    ("1080p", "upsample_ce"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 6.48, 4.02),
     ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 27.54, 21.56),
-    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "2cb17f6256dec2e9dc8351f95cfe5f8b8e52d64ed02d90acf3be77236a88422b", 268.19, 17.77),
-    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 85.05, 54.34),
-    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 50.85, 35.47),
-    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "d7b1ee6fd91dc69f9ead750fcb8db122dc7e3fe81cc7687694a786981c7d23c3", 92.17, 30.19),
-    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 19.27, 22.21),
-    ("batch4", "upsample_ce"): ("k_loss.hip", "2d460122b34185cca4bb110ac3dab5a785bd6b27d286773533e56251cbd4c6cc", 12.60, 7.61),
+    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "11faaab0c139408bd52ca675f2c81690182e26c61aa77d6d40a573bbdbee21d2", 268.91, 17.85),
+    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 70.42, 54.34),
+    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 53.05, 46.79),
+    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "aeabc5b9e3fc86bd06a9b58f820dd32dae4213c7c2382fe3a53a58e6d63e5edf", 86.71, 30.19),
+    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 30.13, 22.21),
+    ("batch4", "upsample_ce"): ("k_loss.hip", "c055f2e02c8068b63bfccdcd37f630015bbdc295e043132919cc8817d31082c3", 23.46, 7.61),
     ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "ba8926ad7d9dc9f006e6340c122b7a41983d384251a2b6bfdba3963e6bb31689", 71.46, 80.27),
 }
 

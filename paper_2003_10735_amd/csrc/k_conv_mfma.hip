@@ -379,8 +379,7 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.wq_stride = (size_t)cin * cout * 9;
     a.bias_stride = p.head_stride;
     a.w3_stride = (size_t)g.C * cout;
-    const ConvTile t = conv_tile(g, cin, cout);
-    if (t.bn != CV_BN) { conv3x3_wide(c, name, a, epi, g.heads(), t); return; }
+    if (conv_tile(g, cin, cout).bn != CV_BN) { conv3x3_wide(c, name, a, epi, g.heads()); return; }
     a.grp_tiles = cdiv(a.grp_pp, CV_BM);
     a.m_tiles = g.heads() * a.grp_tiles;
     a.n_tiles = cout / CV_BN;

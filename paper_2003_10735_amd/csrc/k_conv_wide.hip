@@ -6,18 +6,23 @@
 // the matrix cores idle while it fills its pipeline, exchanges its partial sums and stores (about 5 of 14 us per
 // round), and its 0.25 weight kilobytes and one activation kilobyte per MFMA cost energy that the clock then lacks
 // (a long launch of dense MFMAs runs at 1.3 - 1.7 GHz here).  Hence:
-//   * a block is 256 threads = 4 wavefronts, 32 P positions x 128 channels; two blocks share a compute unit (at most
-//     256 registers and 64 KB of LDS each), so one block's K loop covers the other's prologue, exchange and stores;
-//   * a wavefront holds 64 channels x 32 P positions (2 P accumulator tiles), so each activation fragment read from
-//     LDS feeds two MFMAs and each weight fragment P; the four are 2 channel halves x 2 K groups.
+//   * a block is 256 threads = 4 wavefronts, 96 positions x 128 channels; two blocks share a compute unit (at most
+//     256 registers and 80 KB of LDS each), so one block's K loop covers the other's prologue, exchange and stores;
+//   * a wavefront holds 64 channels x 96 positions, so each activation fragment read from LDS feeds two MFMAs and each
+//     weight fragment three; the four are 2 channel halves x 2 K groups.
+// The sums are those of the small tiles, bit for bit: of a stage's four fragments of 16 channels a wavefront takes two,
+// adds each to accumulators of its own (2 x 6 tiles, 192 registers), and the four partial sums of an element meet
+// in the same order.  So a frame's activations and logits do not depend on which tile serves it.  (Two
+// chains of twice the length instead of four cost accuracy, 1.44e-7 against 1.11e-7 of the products' 2-norm at 256 input
+// channels and 1.28e-7 against 0.92e-7 at 192, and made ReLU masks and roundings to bfloat16 those of another sum.)
 // Operands take the same routes as in k_conv_mfma.hip (weights in fragment order straight to registers, activations
-// from memory into swizzled LDS slabs, three of which rotate), with the loads of one stage ahead in a ring of six
-// weight fragments pairs and the next step's activation fragments read while this step's MFMAs run.
-// Measured, us per launch, small tiles -> this kernel (probe with random data, one box each):
-//   4 x 90 x 160 cells, 320 -> 256 111 -> 86, data gradient 256 -> 256 89 -> 71, layer 2 with classifier 106 -> 68;
-//   135 x 240, 256 -> 128 31.3 -> 24.4, 128 -> 128 22.5 -> 16.1;  four heads of 90 x 160, 256 -> 128 47 -> 37.
-// Wider tiles still (256 x 256 and 256 x 128 with one block per compute unit: 86 and 96 us where this one takes
-// 86; 160 x 128 98; 192 x 128, one block, 50 us at 180 x 320 cells, 256 -> 128, where this one takes 34) do not pay.
+// from memory into swizzled LDS slabs, three of which rotate), with the weights of three steps in a ring of fragment
+// pairs and the next step's activation fragments read while this step's MFMAs run.
+// Measured, us per launch, small tiles -> this kernel:
+//   4 x 90 x 160 cells, 320 -> 256 104 -> 95, data gradient 256 -> 256 85 -> 72, layer 2 with classifier 85 -> 74;
+//   135 x 240, 256 -> 128 30.5 -> 26.4, 128 -> 128 22.2 -> 17, its data gradient 22 -> 16.8.
+// 128 positions per block need 256 accumulators a lane, so one block per compute unit: that loses the overlap.  (With the two
+// chains of twice the length they fit, and 4 x 90 x 160 cells took 81, 62 and 63 us.)
 #include <algorithm>
 
 #include "st_conv.hpp"
@@ -28,24 +33,25 @@ namespace st {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
+constexpr int CW_P = 3;                    // blocks of 32 positions per block
+constexpr int CW_BM = 32 * CW_P;
 constexpr int CW_BN = 128;                 // channels per block
 constexpr int CW_OLD = CW_BN + 8;          // pitch of the staged output tile
 constexpr int CW_STEPS = 6;                // steps of a stage per wavefront: three taps x two fragments of 16 channels
+constexpr int CW_RING = 3;                 // steps whose weights are in registers or on their way
 #define CW_F __builtin_amdgcn_sched_barrier(0);
 
-// dynamic LDS: the three slabs, later the exchanged sums (P accumulator tiles per wavefront), then the output tile
-template <int P>
-constexpr size_t cw_lds()
-{
-    return std::max(std::max((size_t)3 * (32 * P + 2) * 128, (size_t)4 * P * 4096), (size_t)32 * P * CW_OLD * 2);
-}
+// dynamic LDS: the three slabs, later the exchanged sums (three sets of P accumulator tiles per channel half), then the
+// output tile
+constexpr size_t CW_LDS = std::max(std::max((size_t)3 * (CW_BM + 2) * 128, (size_t)2 * 3 * CW_P * 4096), (size_t)CW_BM * CW_OLD * 2);
+static_assert(2 * CW_LDS <= 160 * 1024, "two blocks per compute unit");
 
 // EPI as for k_conv3x3_mfma: 0 bias + ReLU, 1 ReLU mask of a data gradient, 2 as 0 with the classifier, 3 plain
 // float32 sums to a dense tensor.
-template <int P, int EPI>
+template <int EPI>
 __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
 {
-    constexpr int BM = 32 * P, BN = CW_BN, SLAB = (BM + 2) * 128, STEPS = CW_STEPS, OLD = CW_OLD;
+    constexpr int P = CW_P, BM = CW_BM, BN = CW_BN, SLAB = (BM + 2) * 128, STEPS = CW_STEPS, RING = CW_RING, OLD = CW_OLD;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
     // XCD-aware tile order, several heads: as in k_conv3x3_mfma
@@ -61,13 +67,13 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     const int wn = wave & 1, kgrp = wave >> 1;
     const int l32 = lane & 31, lhi = lane >> 5;
 
-    f32x16 acc[2][P];
+    f32x16 acc[2][2][P];      // [fragment of the K group][channel block][position block]
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < 4; ++n)
 #pragma unroll
         for (int j = 0; j < P; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[n >> 1][n & 1][j][r] = 0.f;
 
     const int c_chunks = a.cin / 64, n_stages = 3 * c_chunks, kfr = a.cin >> 4;
 
@@ -99,14 +105,14 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     const int w_row = (2 * kfr + 4) * 1024;
     int w_cc = 0, x_cc = 0;
 
-    u32x4 wr[STEPS][2];       // weight fragments of a stage's steps; a slot is refilled for the next stage once used
+    u32x4 wr[RING][2];        // weight fragments of step t in slot t % RING, refilled for the step RING ahead once used
     bf16x8 xb[P];             // activation fragments of the step in work, each replaced by the next step's once used
 
     // step t: tap column t / 2, channel fragment t % 2
     auto load_w = [&](int soff, int t) __attribute__((always_inline)) {
         const int s = soff + ((t >> 1) * kfr + (t & 1)) * 1024;
 #pragma unroll
-        for (int n = 0; n < 2; ++n) wr[t][n] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv[n], s, 0);
+        for (int n = 0; n < 2; ++n) wr[t % RING][n] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv[n], s, 0);
     };
     // (assembly, and M0: see k_conv3x3_mfma)
     auto dma = [&](int slab, int i) __attribute__((always_inline)) {
@@ -134,9 +140,9 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     auto stage = [&](auto B_, auto FX_, auto NEXT_) __attribute__((always_inline)) {
         constexpr int B = decltype(B_)::value;
         constexpr bool FX = decltype(FX_)::value, NEXT = decltype(NEXT_)::value;
-        if (NEXT) w_next();
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
+            if (NEXT && t == STEPS - RING) w_next();
             const bool last = t == STEPS - 1;
             if (last && NEXT) {
                 constexpr int issued = 2 * (STEPS - 1) + (FX ? P : 0);
@@ -148,7 +154,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
             for (int j = 0; j < P; ++j) {
 #pragma unroll
                 for (int n = 0; n < 2; ++n)
-                    acc[n][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[t][n]), xb[j], acc[n][j], 0, 0, 0);
+                    acc[t & 1][n][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[t % RING][n]), xb[j], acc[t & 1][n][j], 0, 0, 0);
                 CW_F
                 if (!last) xb[j] = read_x(B, t + 1, j);
                 else if (NEXT) xb[j] = read_x((B + 1) % 3, 0, j);
@@ -161,7 +167,8 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
                 }
                 CW_F
             }
-            if (NEXT) load_w(w_soff, t);
+            if (t < STEPS - RING) load_w(w_soff, t + RING);
+            else if (NEXT) load_w(w_soff, t - (STEPS - RING));
             CW_F
         }
         if (FX) x_next();
@@ -174,13 +181,13 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     dma_rest(0);
     x_next();
 #pragma unroll
-    for (int t = 0; t < STEPS; ++t) load_w(0, t);
+    for (int t = 0; t < RING; ++t) load_w(0, t);
     CW_F
 #pragma unroll
     for (int i = 0; i < P; ++i) dma(1, i);
     dma_rest(1);
     x_next();
-    CW_VMCNT(2 * STEPS + P);
+    CW_VMCNT(2 * RING + P);
     __syncthreads();
     CW_F
 #pragma unroll
@@ -223,25 +230,38 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
             if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) inside |= 1u << j;
         }
     }
+    f32x16 sum[P];            // this wavefront's 32 channels
     __syncthreads();
     {
-        float* red = (float*)smem_raw;     // [receiving wavefront][P][4 register groups][64 lanes][4]
-        float* dst = red + (size_t)(wave ^ 2) * P * 1024 + lane * 4;
-#pragma unroll
-        for (int j = 0; j < P; ++j)
+        // number q = 2 kgrp + f of an element's four partial sums, added in ascending order.  K group 0 hands the sum of
+        // its two over (set 0), K group 1 each of its own (sets 1 and 2).
+        float* red = (float*)smem_raw + (size_t)wn * 3 * P * 1024 + lane * 4;     // [wn][set][P][4 register groups][64 lanes][4]
+        auto put = [&](int set, int j, const f32x16& v) __attribute__((always_inline)) {
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq)
-                *(f32x4*)(dst + (j * 4 + rq) * 256) = f32x4{acc[1][j][rq * 4], acc[1][j][rq * 4 + 1], acc[1][j][rq * 4 + 2], acc[1][j][rq * 4 + 3]};
-        __syncthreads();
-        const float* src = red + (size_t)wave * P * 1024 + lane * 4;
-#pragma unroll
-        for (int j = 0; j < P; ++j)
+                *(f32x4*)(red + ((set * P + j) * 4 + rq) * 256) = f32x4{v[rq * 4], v[rq * 4 + 1], v[rq * 4 + 2], v[rq * 4 + 3]};
+        };
+        auto get = [&](int set, int j) __attribute__((always_inline)) {
+            f32x16 v;
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
-                const f32x4 v = *(const f32x4*)(src + (j * 4 + rq) * 256);
+                const f32x4 u = *(const f32x4*)(red + ((set * P + j) * 4 + rq) * 256);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[0][j][rq * 4 + e] += v[e];
+                for (int e = 0; e < 4; ++e) v[rq * 4 + e] = u[e];
             }
+            return v;
+        };
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            if (kgrp == 0) put(0, j, acc[0][1][j] + acc[1][1][j]);
+            else { put(1, j, acc[0][1][j]); put(2, j, acc[1][1][j]); }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            if (kgrp == 0) sum[j] = acc[0][0][j] + acc[1][0][j] + get(1, j) + get(2, j);
+            else sum[j] = get(0, j) + acc[0][0][j] + acc[1][0][j];
+        }
         __syncthreads();
     }
     if (EPI == 3) {
@@ -254,21 +274,21 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int ch = n0 + cw + (r >> 2) * 8 + lhi * 4 + (r & 3);
-                    if (ch < a.dense_c) dst[(size_t)ch * a.h * a.w] = acc[0][j][r];
+                    if (ch < a.dense_c) dst[(size_t)ch * a.h * a.w] = sum[j][r];
                 }
             }
         }
         return;
     }
 
-    // classifier fragments (A operand: rows = classes, k = this tile's channels)
-    u32x4 w3f[EPI == 2 ? BN / 16 : 1];
+    // classifier fragments (A operand: rows = classes, k = the half of this tile's channels that this wavefront multiplies)
+    u32x4 w3f[EPI == 2 ? 4 : 1];
     if (EPI == 2) {
         const bf16* w3row = a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + lhi * 8;
 #pragma unroll
-        for (int ks = 0; ks < BN / 16; ++ks) {
-            const u32x4 v = *(const u32x4*)(w3row + min(n0 + ks * 16, a.cout - 16));
-            w3f[ks] = l32 < a.n_cls && n0 + ks * 16 < a.cout ? v : u32x4{0u, 0u, 0u, 0u};
+        for (int ks = 0; ks < 4; ++ks) {
+            const u32x4 v = *(const u32x4*)(w3row + min(n0 + (wave & 1) * 64 + ks * 16, a.cout - 16));
+            w3f[ks] = l32 < a.n_cls ? v : u32x4{0u, 0u, 0u, 0u};
         }
     }
     bf16* Os = (bf16*)smem_raw;      // [BM][OLD]
@@ -279,7 +299,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
             bf16x4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v = acc[0][j][rg * 4 + e];
+                float v = sum[j][rg * 4 + e];
                 if (EPI != 1) v = inside & (1u << j) ? fmaxf(v + bias[rg][e], 0.f) : 0.f;
                 o[e] = (bf16)v;
             }
@@ -288,19 +308,23 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     }
     __syncthreads();
     if (EPI == 2) {
-        // D[class][position], 32 positions per wavefront and turn, over the tile's channels
-        for (int j = wave; j < P; j += 4) {
+        // D[class][position], 32 positions and half of the tile's channels per wavefront and turn: one share of the logits
+        // per 64 channels, as from the small tiles
+#pragma unroll 1
+        for (int u = wave; u < 2 * P; u += 4) {
+            const int j = u >> 1, half = wave & 1;
+            if (n0 + half * 64 >= a.cout) continue;
             f32x16 z;
 #pragma unroll
             for (int r = 0; r < 16; ++r) z[r] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < BN / 16; ++ks) {
-                const bf16x8 xf = *(const bf16x8*)(Os + (j * 32 + l32) * OLD + ks * 16 + lhi * 8);
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 xf = *(const bf16x8*)(Os + (j * 32 + l32) * OLD + half * 64 + ks * 16 + lhi * 8);
                 z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w3f[ks]), xf, z, 0, 0, 0);
             }
             const int mp = m0 + j * 32 + l32;
             if (mp < m_end) {
-                float* zrow = a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + lhi * 4;
+                float* zrow = a.zpart + ((size_t)(2 * nt + half) * a.PP + mp) * a.zpitch + lhi * 4;
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq)
                     if (gq * 8 + lhi * 4 < a.zpitch)
@@ -343,13 +367,14 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
 
 // Which tile a layer runs with.  A launch takes about (blocks on the busiest compute unit) x (time of a block) + a
 // constant, the time of a block being linear in the input channels.  Fitted, in microseconds, to sweeps over 7 000 to 74 000
-// positions, 64, 128 and 256 input and 128 and 256 output channels, where it is off by up to a tenth; at the sizes where the
-// choice changes it names the faster kernel (one head, 256 -> 128: 90 x 160 cells small tiles 12.6 / 96 positions
-// 14.7 / 128 positions 17.6 us, 100 x 178 cells 21.0 / 15.4 / 18.3, 120 x 213 cells 21.5 / 23.8 / 19.6).
+// positions, 64 to 320 input and 128 and 256 output channels.  Where the choice changes it names the faster kernel or one within
+// 2 % (plain forward passes, all small / all wide tiles: 90 x 160 cells, 256 -> 128 -> 128 34.3 / 42.2 us, two of them 57.3 / 58.2, four
+// 106.3 / 101.3; two of them with 64 -> 128 -> 128 43.2 / 40.8; 75 x 110, 256 -> 256 -> 256 58.0 / 51.6; 100 x 178, 256 -> 128 -> 128
+// 54.5 / 48.0; 120 x 213 59.3 / 59.5).
 ConvTile conv_tile(const Geo& g, int cin, int cout)
 {
     struct Shape { ConvTile t; float block, per64, launch; };
-    static const Shape shapes[3] = {{{128, 64}, 4.3f, 1.53f, 1.0f}, {{96, CW_BN}, 2.4f, 2.03f, 4.3f}, {{128, CW_BN}, 2.5f, 2.83f, 4.8f}};
+    static const Shape shapes[2] = {{{128, 64}, 4.3f, 1.53f, 1.0f}, {{CW_BM, CW_BN}, 2.4f, 2.03f, 3.6f}};
     ConvTile best = shapes[0].t;
     float best_t = 0.f;
     for (const Shape& s : shapes) {
@@ -361,29 +386,21 @@ ConvTile conv_tile(const Geo& g, int cin, int cout)
 }
 
 // (a: everything but the tiling)
-void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads, ConvTile t)
+void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads)
 {
-    a.grp_tiles = cdiv(a.grp_pp, t.bm);
+    a.grp_tiles = cdiv(a.grp_pp, CW_BM);
     a.m_tiles = heads * a.grp_tiles;
     a.n_tiles = cdiv(a.cout, CW_BN);
     a.tiles_per_xcd = cdiv(a.m_tiles * a.n_tiles, 8);
     const dim3 grid(a.tiles_per_xcd * 8);
-    auto go = [&](auto p_, auto epi_) {
-        constexpr int P = decltype(p_)::value, EPI = decltype(epi_)::value;
-        const auto kernel = k_conv3x3_wide<P, EPI>;
-        ensure_dynamic_lds((const void*)kernel, cw_lds<P>());
-        ST_LAUNCH(c, name, kernel, grid, dim3(256), cw_lds<P>(), a);
+    auto go = [&](auto kernel) {
+        ensure_dynamic_lds((const void*)kernel, CW_LDS);
+        ST_LAUNCH(c, name, kernel, grid, dim3(256), CW_LDS, a);
     };
-    auto with_epi = [&](auto p_) {
-        switch (epi) {
-        case 0: go(p_, std::integral_constant<int, 0>{}); break;
-        case 1: go(p_, std::integral_constant<int, 1>{}); break;
-        case 2: go(p_, std::integral_constant<int, 2>{}); break;
-        default: go(p_, std::integral_constant<int, 3>{}); break;
-        }
-    };
-    if (t.bm == 96) with_epi(std::integral_constant<int, 3>{});
-    else with_epi(std::integral_constant<int, 4>{});
+    if (epi == 3) go(k_conv3x3_wide<3>);
+    else if (epi == 1) go(k_conv3x3_wide<1>);
+    else if (epi == 2) go(k_conv3x3_wide<2>);
+    else go(k_conv3x3_wide<0>);
 }
 
 }  // namespace st

@@ -119,7 +119,7 @@ k_loss(ZSrc zs, const uint8_t* __restrict__ labels, const uint8_t* __restrict__ 
             const int lc = cell % CW, r = cell / CW;
             const int cx = min(max(cx0 + lc, 0), g.w - 1), cy = min(max(cy0 + r, 0), g.h - 1);
             const size_t mp = ((size_t)img * g.Hp + cy + 1) * g.Wp + cx + 1;
-            // up to four shares (one per 64 channels, wide convolution tiles 128, float32 path 32); within a group of two an absent
+            // up to four shares (one per 64 channels, float32 path 32); within a group of two an absent
             // share re-reads the last one (it is then not added), so that the loads of a group are
             // issued together.  Only loaded here: the sums wait until every load of the prologue
             // is on its way.

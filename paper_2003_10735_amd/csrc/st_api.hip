@@ -186,7 +186,7 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.gz = train_take((size_t)g.n * g.C * hw * 4);
     p.tadj = train_take((size_t)g.n * g.C * hw * 4);
     p.lab8 = train_take((size_t)g.pixels());
-    p.z_parts = cdiv(g.k2, p.bf16 ? conv_tile(g, g.k1, g.k2).bn : 32);     // (float32: the same for c2 and k2)
+    p.z_parts = cdiv(g.k2, p.bf16 ? 64 : 32);     // (float32: the same for c2 and k2)
     p.zpart = take(off, (size_t)cdiv(g.k2, p.bf16 ? 64 : 32) * PP * ((g.C + 3) / 4 * 4) * 4);
     p.g_slots = train_take(loss_slot_floats(g) * 4);
     p.grad_stride = (p.po.total + 3) / 4 * 4;
@@ -404,7 +404,7 @@ static ZeroList regions_to_clear(const Plan& p, char* ws)
 }
 
 // one forward pass of the head: features (already packed) -> shares of the low-resolution logits, one
-// per channel tile (the classifier rides along with layer 2), which the loss kernel adds up -- and
+// per 64 channels (the classifier rides along with layer 2), which the loss kernel adds up -- and
 // writes to the planar tensor on the way.
 static void forward(Ctx& c, const Plan& p, char* ws)
 {

@@ -134,7 +134,7 @@ struct Plan {
     size_t grad3;                         // per-block partials of dW3 / db3
     size_t z, g_slots, gz, tadj;   // gz: float32 path (elsewhere room that nothing uses); tadj: U^T of the one-hot labels, [n, C, h, w] float32
     size_t lab8;                   // the labels as bytes, [n, 8h, 8w]: the class, or 255 for a pixel that does not count
-    size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution, one per channel tile
+    size_t zpart; int z_parts;     // shares of the logits left by the classifier-fused convolution, one per 64 channels (float32: 32)
     size_t theta, vel, vel2, grad, best;   // vel: velocity or Adam's m; vel2: Adam's v
     size_t wq1, wq1t, wq2, wq2t, wq3;      // operand copies of the weights: bfloat16, or float32 in its kernels' order
     size_t bq1, bq2;                       // biases followed by zeros, where the kernels read beyond the counts

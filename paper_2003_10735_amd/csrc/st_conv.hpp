@@ -12,8 +12,8 @@ struct ConvArgs {
     bf16* Y;            // [PP][cout] or nullptr
     bf16* YT;           // channel-major copy, blocked layout of xt_index(), or nullptr
     // EPI 2: the 1x1 classifier rides along.  Every block adds its channels' share of the
-    // logits of its positions: zpart[n-tile][padded position][zpitch classes] float32 (zpitch =
-    // the class count rounded up to a multiple of four); the consumer adds the n_tiles shares and
+    // logits of its positions: zpart[64 channels][padded position][zpitch classes] float32 (zpitch =
+    // the class count rounded up to a multiple of four); the consumer adds the shares and
     // the bias.
     const bf16* W3q;    // [n_cls][cout] bfloat16
     float* zpart;
@@ -32,6 +32,6 @@ struct ConvArgs {
 // Positions x channels of a block's tile: 64 channels name the kernel of k_conv_mfma.hip, 128 that of k_conv_wide.hip.
 struct ConvTile { int bm, bn; };
 ConvTile conv_tile(const Geo& g, int cin, int cout);
-void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads, ConvTile t);
+void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads);
 
 }  // namespace st
