@@ -66,7 +66,9 @@ enum { ST_NCHW = 0, ST_NHWC = 1 };                /* st_head_desc.feat_layout */
 enum { ST_COMPUTE_F32 = 0, ST_COMPUTE_BF16 = 1 }; /* st_head_desc.compute */
 
 /* Shape of one training problem.
- * compute = ST_COMPUTE_F32: every convolution in float32 (reference-precision path).
+ * compute = ST_COMPUTE_F32: every convolution in float32 (reference-precision path).  Over the whole range of float32; where it is
+ *   faster, a product is formed as six of the nine products of its operands' three bfloat16 parts, right to 2^-24 of itself, and added
+ *   in float32.
  * compute = ST_COMPUTE_BF16: convolution operands (features, weights, activations and the
  *   back-propagated gradients) are rounded to bfloat16, products accumulate in float32 on the
  *   matrix cores; master weights, optimiser arithmetic, logits, loss and weight gradients stay

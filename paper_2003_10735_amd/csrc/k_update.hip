@@ -19,7 +19,7 @@ namespace st {
 //      AdamStep).  g is the sum, in ascending order, of the partial gradients the weight-gradient
 //      kernel left behind: `splits1` copies for W1/b1, `splits2` for W2/b2 (its position splits,
 //      `stride` floats apart).
-//  (2) the same for W3/b3, of which the classifier's backward kernel left one slot per block: 16
+//  (2) the same for W3/b3, of which the classifier's backward kernel left one slot per block: L3_RUNS (8)
 //      threads per parameter, each adding a contiguous run of the slots, then the runs in order.
 //  (3) bookkeeping of the forward pass that preceded the step: block f: mean IoU of frame f from
 //      its confusion counts (copied out when asked, then cleared for the next pass); one more
