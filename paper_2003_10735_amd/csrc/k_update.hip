@@ -225,8 +225,9 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f
 // Classifier's role of k_step_end: values per block, and the runs its threads split the slots into.
 constexpr int L3_VALUES = 32, L3_RUNS = 256 / L3_VALUES;
 
-// acc + src[s * stride] for s0 <= s < s1, in ascending order; N loads in flight.  Loads beyond the end repeat the last
-// slot (`n` slots) and are not added.
+// acc + the sum of src[s * stride] over s0 <= s < s1; N loads in flight.  Loads beyond the end repeat the last
+// slot (`n` slots) and are not added.  The N values are added in pairs, pairs of pairs, ..: one after the other, 966 slots in eight
+// runs are 2.05e-7 of their 2-norm off (and in 16 runs 1.6e-7), so 0.95e-7, at the same time.
 template <int N>
 __device__ __forceinline__ float add_slots(float acc, const float* src, size_t stride, int s0, int s1, int n)
 {
@@ -238,8 +239,12 @@ __device__ __forceinline__ float add_slots(float acc, const float* src, size_t s
         src += s0 + e + 1 < n ? stride : 0;
     }
 #pragma unroll
-    for (int e = 0; e < N; ++e) acc += s0 + e < s1 ? v[e] : 0.f;
-    return acc;
+    for (int e = 0; e < N; ++e) v[e] = s0 + e < s1 ? v[e] : 0.f;
+#pragma unroll
+    for (int k = 1; k < N; k *= 2)
+#pragma unroll
+        for (int e = 0; e < N; e += 2 * k) v[e] += v[e + k];
+    return acc + v[0];
 }
 
 // (OPEN: as a role of the launch that opens a call: parameters in, operand copies; no other roles, so that the
@@ -304,7 +309,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         // written by other compute units, so every load is a round trip to memory: the role is
         // laid out for few of them, and for whole 128-byte lines.  A block takes 32 consecutive values; its 256 threads
         // split the slots into 8 contiguous runs (thread = value + 32 * run), every thread adds its
-        // run in ascending order, and the 8 partial sums of a value are added in the order of the runs.  A run of up to 32
+        // run group by group (add_slots), and the 8 partial sums of a value are added in the order of the runs.  A run of up to 32
         // slots is one trip; a longer one is added 16 at a time, because then the slots' bytes bind and more loads in
         // flight only get in the way of the parameters' (966 slots of 256 channels, 21 MB: the launch takes 18.6 us with 16,
         // 20.9 with 32, 21.4 with 24).  16 values in 16 runs of 8 loads fetched every line twice and made two trips where
