@@ -7,14 +7,20 @@
 // lane's 8 reduction elements are 16 contiguous bytes and need no transposition.  dY is zero on
 // the border of the padded grid, so the sum may run over all padded positions.
 //
-// One wavefront accumulates a 32 (o) x 32 (i) x 9 (taps) block (144 accumulator registers): per
-// 16 positions it loads one dY fragment and, per kernel row kh, one 16-byte window of X (the
-// row pitch of the padded grid is a multiple of 8, so all of them are aligned fragments of the
-// blocked channel-major layout and every wavefront load is one contiguous kilobyte); the kw = 0
-// and kw = 2 products use the dY fragment shifted by one position, built in registers
-// (v_alignbyte + a cross-lane permute for the element that enters) instead of loading shifted
-// windows.  9 MFMAs per 4 loads.  A bigger block would need fewer loads per MFMA but leaves too few blocks to fill the
-// chip without multiplying the partial copies.
+// One wavefront accumulates a 32 (o) x 32 (i) x 9 (taps) block (144 accumulator registers).  A unit is eight
+// columns of two grid rows, y (lanes 0 .. 31) and y + 1 (lanes 32 .. 63), 16 positions: one dY fragment and, per kernel row
+// kh, the X fragment kh - 1 rows further down (the row pitch of the padded grid is a multiple of 8, so all of them are aligned runs
+// of the blocked channel-major layout); the kw = 0 and kw = 2 products use the dY fragment shifted by one
+// position, built in registers (v_alignbyte with the element that enters from the unit before or behind, which the same
+// lane holds) instead of loading shifted windows.  9 MFMAs per 4 loads.  A bigger block would need fewer loads per MFMA but leaves
+// too few blocks to fill the chip without multiplying the partial copies.
+// Why two rows: the three X fragments of a unit then are four row pieces of 512 bytes, two of them read twice at the same time
+// and the second time out of the L1 cache.  With a unit of 16 columns of one row they were six different ones,
+// and what came from L2 -- 4 KB a unit and wavefront, 45 bytes per cycle and compute unit -- bound the kernel.  Cycles a unit,
+// before / now (288 are MFMAs): 4 x 90 x 160 cells, 320 -> 256 -> 256 391 / 317, 135 x 240, 256 -> 128 -> 128 347 / 316, 90 x 160 366 / 346 (49 units a
+// wavefront: the first operands' way counts); the first of these launches 133.6 / 121.1 us, at a clock that the power draw
+// lowers from 2.2 to 2.05 GHz.  The element that enters a shifted fragment now lies in the same lane; cross-lane
+// permutes fetched it from the other half of the wavefront.
 //
 // The four wavefronts of a block own the same output block and a quarter each of the block's
 // position range; they are added through LDS in a fixed order, and the grid's position splits
@@ -38,12 +44,12 @@ struct WgradArgs {
     size_t split_stride;
     int cin, cout;        // channels of the gradient itself; the operands' are padded to multiples of 32
     int PPT, guard, Wp;
-    int units_per_wave;   // 16-position units per wavefront
-    int n_units;          // units of one head's positions
+    int units_per_wave;   // units per wavefront
+    int n_units;          // units of one head's positions: pairs of rows x groups of eight columns
     int o_tiles, i_tiles, splits, items_per_xcd;
     // Several heads: head k owns the positions from 8-position group k * head_groups8 on and
-    // writes its partial copies head_out_stride floats after head k - 1.  (A head's last unit may
-    // reach into the next frame's first row: dY is zero there, like on every border.)
+    // writes its partial copies head_out_stride floats after head k - 1.  (With an odd number of rows a head's last
+    // pair reaches into the next frame's first row, or the guard: dY is zero there.)
     int heads, head_groups8;
     size_t head_out_stride;
 };
@@ -89,24 +95,30 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     const int unit0 = (split * 4 + wave) * a.units_per_wave;
     const int unit1 = min(unit0 + a.units_per_wave, a.n_units);
     // blocked layout: one 8-position group of 32 channels is 256 elements; lane (l32, lhi) reads
-    // channel l32 of group 2u + lhi, so a wavefront's fragment load is one contiguous kilobyte.
-    // The operands are read through buffer descriptors: the base (the unit before this
-    // wavefront's first; for X one kernel row further up) sits in scalar registers, the lane
-    // offset is fixed, and every load takes one scalar offset -- no address arithmetic at all
-    // in the vector unit, which the K loop has no issue slots to spare for.
+    // channel l32 of column group t % RG of row 2 (t / RG) + lhi, so each half of a wavefront's load is contiguous.
+    // The operands are read through buffer descriptors, for X one per kernel row: the base (the unit before this
+    // wavefront's first) sits in scalar registers, the lane offset is fixed, and every load takes one
+    // scalar offset, the same for all four -- no address arithmetic at all in the vector unit, which the
+    // K loop has no issue slots to spare for.
     const int NG = a.PPT >> 3;
     const int g0 = (a.guard >> 3) + head * a.head_groups8;     // this head's first 8-position group
-    const int row_groups = a.Wp >> 3;   // one kernel row = this many 8-position groups
-    const int row_bytes = row_groups * 512;
-    const bf16* ybase = a.dYT + (((size_t)(o0 >> 5) * NG + g0) << 8) + (ptrdiff_t)(unit0 - 1) * 512;
-    const bf16* xbase = a.XT + (((size_t)(i0 >> 5) * NG + g0) << 8) + (ptrdiff_t)(unit0 - 1) * 512 -
-                        (ptrdiff_t)row_groups * 256;
-    const int span = (max(unit1 - unit0, 0) + 2) * 1024;       // units unit0 - 1 .. unit1
-    const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc((void*)ybase, 0, span, 0x00020000);
-    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)xbase, 0, span + 2 * row_bytes, 0x00020000);
-    const unsigned lane_off = lhi * 512 + l32 * 16;
+    const int row_groups = a.Wp >> 3;   // one grid row = this many 8-position groups
+    const unsigned row_bytes = (unsigned)row_groups * 512u;
+    const int pair0 = unit0 / row_groups;
+    int col = unit0 - pair0 * row_groups;                      // column group of the next unit to load
+    const int first = pair0 * 2 * row_groups + col, before = first - (col ? 1 : row_groups + 1);    // groups of unit0 and unit0 - 1
+    // (a descriptor ends with its channel block, whose head and tail are zeroed guard columns)
+    auto operand = [&](const bf16* base, int block, int group) __attribute__((always_inline)) {
+        const long long left = ((long long)NG - (g0 + group)) * 512;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(base + (((ptrdiff_t)block * NG + g0 + group) << 8)), 0,
+                                                 (int)(unsigned)(left < 0xFFFFFFFFll ? left : 0xFFFFFFFFll), 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t yrs = operand(a.dYT, o0 >> 5, before);
+    const __amdgpu_buffer_rsrc_t xrs[3] = {operand(a.XT, i0 >> 5, before - row_groups), operand(a.XT, i0 >> 5, before),
+                                           operand(a.XT, i0 >> 5, before + row_groups)};
+    const unsigned lane_off = lhi * row_bytes + l32 * 16;
+    unsigned soff = (unsigned)(first - before) * 512u;         // of the next unit to load
     const bool want_bias = it == 0;
-    const int swap_addr = (lane ^ 32) << 2;   // ds_bpermute address of the lane holding the other half
     const bf16 one = (bf16)1.0f;
     const bf16x8 ones = {one, one, one, one, one, one, one, one};
 
@@ -118,156 +130,100 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
 #endif
     constexpr int DEPTH = ST_WGRAD_DEPTH;
     u32x4 ry[DEPTH], rx[DEPTH][3];
-#define WG_LOAD(SLOT, U)                                                                        \
-    {                                                                                           \
-        const int s_ = ((U) - unit0 + 1) * 1024;                                                \
-        ry[SLOT] = __builtin_amdgcn_raw_buffer_load_b128(yrs, lane_off, s_, 0);                 \
-        _Pragma("unroll") for (int kh = 0; kh < 3; ++kh)                                        \
-            rx[SLOT][kh] = __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_off, s_ + kh * row_bytes, 0); \
-    }
+#define WG_LOAD_Y(SLOT, OFF) ry[SLOT] = __builtin_amdgcn_raw_buffer_load_b128(yrs, lane_off, (int)(OFF), 0);
+#define WG_LOAD_X(SLOT, KH) rx[SLOT][KH] = __builtin_amdgcn_raw_buffer_load_b128(xrs[KH], lane_off, (int)soff, 0);
+    // to the next unit: the next group of columns, behind the last one of a pair of rows the first of the next pair
+#define WG_NEXT_A soff += 512u; ++col;
+#define WG_NEXT_B { const bool end_ = col == row_groups; soff += end_ ? row_bytes : 0u; col = end_ ? 0 : col; }
     // The three taps of a kernel row differ by one position.  Moving the reduction index instead
     // of the window,
     //     dW[o][kh][kw][i] = sum_p dY[o][p - (kw - 1)] * X[i][p + (kh - 1) * Wp],
     // the kw = 0 / kw = 2 products use the same X fragment as kw = 1 and a dY fragment moved by
     // one position, which is built once per unit (not once per kernel row) in registers:
     // v_alignbyte over the lane's four dwords plus the one element that enters from the
-    // neighbouring 8-position group.  That element sits in the *other half* of the wavefront
-    // (lane ^ 32), in this unit's registers or in a neighbouring unit's, and is fetched with a
-    // cross-lane permute, issued a unit before its result is picked up.
-    //   up3_: dword 3 of lane^32 in the unit being prepared; dn0_: dword 0 of lane^32 in the unit
-    //   after it.  For a lane of the lower half (lhi = 0) the element before its group is in the
-    //   upper half of the *previous* unit (carry_prev) and the one after its group in the upper
-    //   half of this unit (carry_next, fetched when the previous unit was prepared).
-    // (dY is zero on the border of the padded grid and in the guard columns, so the terms the
-    //  shift moves across the ends of the position range are zero.)
-    unsigned int carry_prev, carry_next;
-    unsigned int up3_, dn0_;              // permute results in flight
+    // neighbouring 8-position group, which this lane holds as the unit before (its dword 3) or behind (its dword 0).
+    // (At the ends of a row what enters is the element of the next pair's first or the last pair's last column: both are
+    //  border columns, where dY is zero, like in the guard columns.)
     u32x4 ymb[2], ypb[2];                 // dY at p - 1 / p + 1 of the unit in work and of the next one
-#define WG_NEIGHBOURS_ISSUE(SLOT, NEXT)                                                         \
-    {                                                                                           \
-        up3_ = __builtin_amdgcn_ds_bpermute(swap_addr, ry[SLOT][3]);                            \
-        dn0_ = __builtin_amdgcn_ds_bpermute(swap_addr, ry[NEXT][0]);                            \
-    }
-    // picks up the permutes issued for the unit in SLOT and builds its shifted fragments in BUF
-#define WG_SHIFTED(SLOT, BUF)                                                                   \
-    {                                                                                           \
-        const unsigned int prev_ = lhi ? up3_ : carry_prev;                                     \
-        const unsigned int next_ = lhi ? dn0_ : carry_next;                                     \
-        carry_prev = up3_;                                                                      \
-        carry_next = dn0_;                                                                      \
-        const u32x4 w_ = ry[SLOT];                                                              \
-        ymb[BUF][0] = __builtin_amdgcn_alignbyte(w_[0], prev_, 2);                              \
-        ymb[BUF][1] = __builtin_amdgcn_alignbyte(w_[1], w_[0], 2);                              \
-        ymb[BUF][2] = __builtin_amdgcn_alignbyte(w_[2], w_[1], 2);                              \
-        ymb[BUF][3] = __builtin_amdgcn_alignbyte(w_[3], w_[2], 2);                              \
-        ypb[BUF][0] = ymb[BUF][1]; ypb[BUF][1] = ymb[BUF][2]; ypb[BUF][2] = ymb[BUF][3];        \
-        ypb[BUF][3] = __builtin_amdgcn_alignbyte(next_, w_[3], 2);                              \
-    }
-    // the same in two halves (the fragment at p - 1, then the one at p + 1), for the steady state:
-    // five vector instructions each, which fit behind one MFMA; ten in a row do not
-#define WG_SHIFTED_A(SLOT, BUF)                                                                 \
-    {                                                                                           \
-        const unsigned int prev_ = lhi ? up3_ : carry_prev;                                     \
-        carry_prev = up3_;                                                                      \
-        const u32x4 w_ = ry[SLOT];                                                              \
-        ymb[BUF][0] = __builtin_amdgcn_alignbyte(w_[0], prev_, 2);                              \
-        ymb[BUF][1] = __builtin_amdgcn_alignbyte(w_[1], w_[0], 2);                              \
-        ymb[BUF][2] = __builtin_amdgcn_alignbyte(w_[2], w_[1], 2);                              \
-        ymb[BUF][3] = __builtin_amdgcn_alignbyte(w_[3], w_[2], 2);                              \
-    }
-#define WG_SHIFTED_B(SLOT, BUF)                                                                 \
-    {                                                                                           \
-        const unsigned int next_ = lhi ? dn0_ : carry_next;                                     \
-        carry_next = dn0_;                                                                      \
-        ypb[BUF][0] = ymb[BUF][1]; ypb[BUF][1] = ymb[BUF][2]; ypb[BUF][2] = ymb[BUF][3];        \
-        ypb[BUF][3] = __builtin_amdgcn_alignbyte(next_, ry[SLOT][3], 2);                        \
-    }
+    // In three parts, so that no gap between two MFMAs has to take more than three instructions.  (And without a loop:
+    // the compiler would move the MFMAs in front behind it.)
+#define WG_SHIFTED_A(PREV, SLOT, BUF)                                                           \
+    ymb[BUF][0] = __builtin_amdgcn_alignbyte(ry[SLOT][0], ry[PREV][3], 2);                      \
+    ymb[BUF][1] = __builtin_amdgcn_alignbyte(ry[SLOT][1], ry[SLOT][0], 2);                      \
+    ymb[BUF][2] = __builtin_amdgcn_alignbyte(ry[SLOT][2], ry[SLOT][1], 2);
+#define WG_SHIFTED_B(SLOT, NEXT, BUF)                                                           \
+    ymb[BUF][3] = __builtin_amdgcn_alignbyte(ry[SLOT][3], ry[SLOT][2], 2);                      \
+    ypb[BUF][3] = __builtin_amdgcn_alignbyte(ry[NEXT][0], ry[SLOT][3], 2);
+#define WG_SHIFTED_C(BUF) ypb[BUF][0] = ymb[BUF][1]; ypb[BUF][1] = ymb[BUF][2]; ypb[BUF][2] = ymb[BUF][3];
 #define WG_MMA(T, Y, KH, SLOT)                                                                  \
     acc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rx[SLOT][KH]), as_bf16x8(Y), acc[T], 0, 0, 0);
 #define WG_F __builtin_amdgcn_sched_barrier(0);
     // One unit in slot D of the ring.  There is one wavefront per SIMD, so whatever this wavefront
-    // issues between two MFMAs is all that can overlap them: the loads of unit + DEPTH - 1, the
-    // pick-up of the permutes and the shifted fragments of unit + 1, and the permutes of unit + 2
-    // are spread over the gaps between this unit's MFMAs, in a pinned order.
-#define WG_UNIT(D, U, BIAS)                                                                     \
+    // issues between two MFMAs is all that can overlap them, and a lone wavefront issues one instruction in
+    // about 7.7 cycles: an MFMA (33) hides three others of any kind, waits and scalar ones included, and each further one
+    // costs those 7.7.  So no gap between this unit's nine MFMAs takes more: the loads of unit + DEPTH - 1, the
+    // shifted fragments of unit + 1 and the step to the next unit to load, in a pinned order.
+#define WG_UNIT(D, BIAS, LOADS)                                                                 \
     {                                                                                           \
-        const int L_ = ((D) + DEPTH - 1) % DEPTH, N1_ = ((D) + 1) % DEPTH;                      \
-        const int N2_ = ((D) + 2) % DEPTH, N3_ = ((D) + 3) % DEPTH, B_ = (D) & 1;               \
-        const int s_ = (min((U) + DEPTH - 1, unit1) - unit0 + 1) * 1024;                        \
+        const int L_ = ((D) + DEPTH - 1) % DEPTH, N1_ = ((D) + 1) % DEPTH, N2_ = ((D) + 2) % DEPTH, B_ = (D) & 1; \
         if (BIAS) acc[9] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, as_bf16x8(ry[D]), acc[9], 0, 0, 0); \
         WG_MMA(0, ypb[B_], 0, D) WG_F                                                           \
-        ry[L_] = __builtin_amdgcn_raw_buffer_load_b128(yrs, lane_off, s_, 0); WG_F              \
+        if (LOADS) WG_LOAD_Y(L_, soff) WG_F                                                     \
         WG_MMA(1, ry[D], 0, D) WG_F                                                             \
-        rx[L_][0] = __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_off, s_, 0); WG_F           \
+        if (LOADS) WG_LOAD_X(L_, 0) WG_F                                                        \
         WG_MMA(2, ymb[B_], 0, D) WG_F                                                           \
-        rx[L_][1] = __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_off, s_ + row_bytes, 0); WG_F \
+        if (LOADS) WG_LOAD_X(L_, 1) WG_F                                                        \
         WG_MMA(3, ypb[B_], 1, D) WG_F                                                           \
-        rx[L_][2] = __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_off, s_ + 2 * row_bytes, 0); WG_F \
+        if (LOADS) WG_LOAD_X(L_, 2) WG_F                                                        \
         WG_MMA(4, ry[D], 1, D) WG_F                                                             \
-        WG_SHIFTED_A(N1_, 1 - B_) WG_F                                                          \
+        WG_SHIFTED_A(D, N1_, 1 - B_) WG_F                                                       \
         WG_MMA(5, ymb[B_], 1, D) WG_F                                                           \
-        WG_SHIFTED_B(N1_, 1 - B_) WG_F                                                          \
+        WG_SHIFTED_B(N1_, N2_, 1 - B_) WG_F                                                     \
         WG_MMA(6, ypb[B_], 2, D) WG_F                                                           \
-        WG_NEIGHBOURS_ISSUE(N2_, N3_) WG_F                                                      \
-        WG_MMA(7, ry[D], 2, D)                                                                  \
+        WG_SHIFTED_C(1 - B_) WG_F                                                               \
+        WG_MMA(7, ry[D], 2, D) WG_F                                                             \
+        if (LOADS) { WG_NEXT_A } WG_F                                                           \
         WG_MMA(8, ymb[B_], 2, D) WG_F                                                           \
-    }
-    // the same unit when it may lie beyond the end of the range (last, partial trip of the loop):
-    // the bookkeeping runs as above, the MFMAs only for units inside the range
-#define WG_UNIT_TAIL(D, U, BIAS)                                                                \
-    {                                                                                           \
-        const int L_ = ((D) + DEPTH - 1) % DEPTH, N1_ = ((D) + 1) % DEPTH;                      \
-        const int N2_ = ((D) + 2) % DEPTH, N3_ = ((D) + 3) % DEPTH, B_ = (D) & 1;               \
-        if ((U) < unit1) {                                                                      \
-            if (BIAS) acc[9] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, as_bf16x8(ry[D]), acc[9], 0, 0, 0); \
-            _Pragma("unroll") for (int kh = 0; kh < 3; ++kh) {                                  \
-                WG_MMA(kh * 3 + 0, ypb[B_], kh, D)                                              \
-                WG_MMA(kh * 3 + 1, ry[D], kh, D)                                                \
-                WG_MMA(kh * 3 + 2, ymb[B_], kh, D)                                              \
-            }                                                                                   \
-        }                                                                                       \
-        WG_F                                                                                    \
-        WG_LOAD(L_, min((U) + DEPTH - 1, unit1))                                                \
-        WG_SHIFTED(N1_, 1 - B_)                                                                 \
-        WG_NEIGHBOURS_ISSUE(N2_, N3_) WG_F                                                      \
+        if (LOADS) WG_NEXT_B WG_F                                                               \
     }
 #define WG_LOOPS(BIAS)                                                                          \
     {                                                                                           \
         int u = unit0;                                                                          \
         for (; u + DEPTH <= unit1; u += DEPTH) {                                                \
-            _Pragma("unroll") for (int d = 0; d < DEPTH; ++d) WG_UNIT(d, u + d, BIAS)           \
+            _Pragma("unroll") for (int d = 0; d < DEPTH; ++d) WG_UNIT(d, BIAS, true)            \
         }                                                                                       \
-        if (u < unit1) {                                                                        \
-            _Pragma("unroll") for (int d = 0; d < DEPTH; ++d) WG_UNIT_TAIL(d, u + d, BIAS)      \
-        }                                                                                       \
+        /* fewer than DEPTH units are left and in the ring, but for dY of the unit behind the last */ \
+        WG_LOAD_Y(DEPTH - 1, soff)                                                              \
+        _Pragma("unroll") for (int d = 0; d < DEPTH - 1; ++d)                                   \
+            if (u + d < unit1) WG_UNIT(d, BIAS, false)                                          \
     }
 
-    static_assert(DEPTH % 2 == 0 && DEPTH >= 4, "two fragment buffers alternate; permutes look three units ahead");
+    static_assert(DEPTH % 2 == 0 && DEPTH >= 4, "two fragment buffers alternate; shifted fragments look two units ahead");
     if (unit0 < unit1) {
         // unit0 - 1 (guard columns make it readable) supplies the first left neighbours and
-        // unit1 (tail guard) the last right neighbours
-        // (all loads are unconditional, with the unit index clamped to unit1: a load under a
-        //  branch would force the compiler to wait for every outstanding load at the join;
-        //  past the end of the range the slots hold clamped re-loads, finite and unused)
-        WG_LOAD(DEPTH - 1, unit0 - 1)
+        // unit1 the last right neighbours
+        // (all loads are unconditional: a load under a branch would force the compiler to wait for every outstanding load
+        //  at the join; past the end of the range the slots hold what follows there, or zeros behind the channel block:
+        //  finite and unused)
+        WG_LOAD_Y(DEPTH - 1, 0)
 #pragma unroll
-        for (int d = 0; d < DEPTH - 1; ++d) WG_LOAD(d, min(unit0 + d, unit1))
-        carry_prev = __builtin_amdgcn_ds_bpermute(swap_addr, ry[DEPTH - 1][3]);
-        carry_next = __builtin_amdgcn_ds_bpermute(swap_addr, ry[0][0]);
-        WG_NEIGHBOURS_ISSUE(0, 1)
-        WG_SHIFTED(0, 0)
-        WG_NEIGHBOURS_ISSUE(1, 2)
+        for (int d = 0; d < DEPTH - 1; ++d) {
+            WG_LOAD_Y(d, soff) WG_LOAD_X(d, 0) WG_LOAD_X(d, 1) WG_LOAD_X(d, 2)
+            WG_NEXT_A WG_NEXT_B
+        }
+        WG_SHIFTED_A(DEPTH - 1, 0, 0) WG_SHIFTED_B(0, 1, 0) WG_SHIFTED_C(0)
         if (want_bias) WG_LOOPS(true) else WG_LOOPS(false)
     }
-#undef WG_LOAD
-#undef WG_NEIGHBOURS_ISSUE
-#undef WG_SHIFTED
+#undef WG_LOAD_Y
+#undef WG_LOAD_X
+#undef WG_NEXT_A
+#undef WG_NEXT_B
 #undef WG_SHIFTED_A
 #undef WG_SHIFTED_B
+#undef WG_SHIFTED_C
 #undef WG_MMA
 #undef WG_F
 #undef WG_UNIT
-#undef WG_UNIT_TAIL
 #undef WG_LOOPS
 
     // ---- the wavefronts' blocks are added through LDS; every row of acc[9] holds the sums over the
@@ -346,7 +302,8 @@ static WgradArgs wgrad_args(const Plan& p, const bf16* dYT, const bf16* XT, floa
     a.split_stride = p.grad_stride;
     a.cin = cin; a.cout = cout; a.PPT = p.PPT; a.guard = p.guard; a.Wp = p.g.Wp;
     a.heads = p.g.heads();
-    a.n_units = cdiv(p.g.padded_positions() / a.heads, 16);
+    const int rows = p.g.n * p.g.Hp / a.heads;
+    a.n_units = (rows + 1) / 2 * (p.g.Wp / 8);
     a.head_groups8 = p.g.Hp * p.g.Wp / 8;
     a.head_out_stride = p.grad_stride * p.grad_copies;
     a.units_per_wave = cdiv(a.n_units, splits * 4);

@@ -1,0 +1,62 @@
+"""Weight gradients of the bfloat16 path against float64 products of the very operands the kernel reads (activations and
+back-propagated gradients, taken from the workspace), on grids whose units of eight columns x two rows end in every way:
+odd and even rows, one and two groups of columns, fewer units than the operand ring holds, many position splits, several heads."""
+import pytest
+
+import paper_2003_10735_amd as st
+
+pytestmark = pytest.mark.gpu
+
+# n, h, w, c_in, c1, c2, grouped
+SHAPES = [(1, 1, 1, 64, 64, 64, 0), (1, 2, 6, 64, 64, 64, 0), (1, 3, 7, 64, 64, 64, 0), (1, 5, 14, 64, 128, 64, 0), (1, 6, 15, 128, 64, 64, 0),
+          (1, 16, 24, 64, 64, 64, 0), (1, 33, 57, 128, 64, 128, 0), (1, 60, 107, 96, 48, 48, 0), (2, 9, 30, 64, 64, 64, 0),
+          (3, 12, 22, 64, 64, 128, 1), (3, 13, 31, 64, 64, 64, 1), (1, 90, 160, 256, 128, 128, 0), (1, 135, 240, 64, 64, 64, 0)]
+
+
+@pytest.mark.parametrize("n,h,w,c_in,c1,c2,grouped", SHAPES)
+def test_weight_gradients_are_the_sums_of_their_operands(n, h, w, c_in, c1, c2, grouped):
+    import torch
+    C = 7
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(h * 1000 + w)
+    d = st.HeadDesc(n, c_in, h, w, c1, c2, C, feat_dtype=st.ST_BF16, compute=st.ST_COMPUTE_BF16, grouped=grouped)
+    heads = n if grouped else 1
+    ws = torch.zeros(st.st_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    f = torch.randn((n, c_in, h, w), generator=gen, device="cuda").clamp(min=0).bfloat16()
+    lab = torch.randint(0, C, (n, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
+    one = [torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5 if b == 0 else torch.zeros(r, device="cuda")
+           for r, k in ((c1, 9 * c_in), (c2, 9 * c1), (C, c2)) for b in (0, 1)]
+    params = torch.cat(one * heads)
+    # (the gradient of the features is asked for where it may be: the first layer's operand is then kept position-major too)
+    dfeat = None if grouped else torch.zeros((n, c_in, h, w), device="cuda")
+    st.st_partial_distill(d, f, lab, params, 1, 0.0, workspace=ws, feature_grad=dfeat)
+    torch.cuda.synchronize()
+    lay = st.st_get_workspace_layout(d)
+    Wp, Hp = lay["row_pitch"], h + 2
+
+    def act(name, c):
+        k = (c + 63) // 64 * 64
+        return ws[lay[name]:lay[name] + n * Hp * Wp * k * 2].view(torch.bfloat16).reshape(n, Hp, Wp, k)[..., :c].double()
+    copies, stride = lay["grad_copies"], lay["grad_stride"]
+    grad = ws[lay["grad"]:lay["grad"] + heads * copies * stride * 4].view(torch.float32).reshape(heads, copies, stride)
+    layers = [("a1", "da2", c1 * c_in * 9 + c1, c2, c1, lay["splits"][1])]
+    if dfeat is not None:
+        layers.append(("feat", "da1", 0, c1, c_in, lay["splits"][0]))
+    for xn, dn, at, co, ci, splits in layers:
+        X, D = act(xn, ci), act(dn, co)
+        assert D.abs().max() > 0
+        for k in range(heads):
+            xs, ds = (X, D) if heads == 1 else (X[k:k + 1], D[k:k + 1])
+            dd = ds[:, 1:h + 1, 1:w + 1].reshape(-1, co)
+            got = grad[k, :splits].double().sum(0)
+            # a sum's terms meet in a chain of at most this many roundings: the units of a wavefront, 16 products inside
+            # an MFMA, four wavefronts
+            units = -(-((n * Hp // heads + 1) // 2 * (Wp // 8)) // (splits * 4))
+            eps = (units + 16 + 4) * 2.0 ** -24
+            for tap in range(9):
+                win = xs[:, tap // 3:tap // 3 + h, tap % 3:tap % 3 + w].reshape(-1, ci)
+                want, size = dd.t() @ win, dd.abs().t() @ win.abs()
+                g = got[at:at + co * 9 * ci].reshape(co, 9, ci)[:, tap]
+                assert ((g - want).abs() <= eps * size + 1e-30).all(), (xn, k, tap, ((g - want).abs() / (size + 1e-30)).max().item(), eps)
+            b = got[at + co * 9 * ci:at + co * 9 * ci + co]
+            assert ((b - dd.sum(0)).abs() <= eps * dd.abs().sum(0) + 1e-30).all(), (xn, k, "bias")
