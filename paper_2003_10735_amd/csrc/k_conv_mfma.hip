@@ -64,13 +64,17 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     // smem_raw during the K loop: [CV_NBUF][XS_ROWS][128 bytes], chunks swizzled
 
+    // (what the first loads need, in one trip for the arguments: left to itself the compiler asks for some of it only
+    //  behind the question whether the block has a tile)
+    asm volatile("" ::"s"(a.tiles_per_xcd), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.by_n_tiles.m), "s"(a.by_grp_tiles.m), "s"(a.grp_tiles), "s"(a.grp_pp),
+                 "s"(a.X), "s"(a.Wq), "s"(a.wq_stride), "s"(a.cin), "s"(a.Wp));
     // XCD-aware tile order: consecutive blocks go to different XCDs, so give each XCD a
     // contiguous run of position tiles (neighbours share activation rows in that XCD's L2)
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int tile = xcd * a.tiles_per_xcd + slot;
     if (slot >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
-    const int mt = tile / a.n_tiles, nt = tile % a.n_tiles;
-    const int grp = mt / a.grp_tiles;
+    const int mt = fast_quot(tile, a.by_n_tiles), nt = tile - mt * a.n_tiles;
+    const int grp = fast_quot(mt, a.by_grp_tiles);
     const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * CV_BM, n0 = nt * CV_BN;
     const int m_end = (grp + 1) * a.grp_pp;     // results from here on belong to another tile
 
@@ -215,6 +219,24 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 #undef CV_VMCNT
 #undef CV_F
 
+    // ---- what the epilogue needs from memory, on its way while the partial sums are exchanged (asked for behind the
+    //      exchange, it cost every launch a memory latency of its own; with the divisions of block and cell indexes as
+    //      products, 8-step key frame at 90 x 160 cells 656 -> 638 us, forward at 60 x 107 27.4 -> 26.4)
+    const int p = kgrp * 32 + l32, mp = m0 + p;         // this lane's position behind the exchange
+    const ConvCell cell = conv_cell(a, mp, m_end);
+    const bool inside = cell.inside;
+    f32x4 bias[EPI == 0 || EPI == 2 ? 4 : 1];
+    bf16x4 mk[EPI == 1 ? 4 : 1];
+    u32x4 w3f[EPI == 2 ? 4 : 1];
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+        const int c = n0 + wn * 32 + rg * 8 + lhi * 4;
+        if (EPI == 0 || EPI == 2) bias[rg] = *(const f32x4*)(a.bias + grp * a.bias_stride + c);
+        if (EPI == 1) mk[rg] = *(const bf16x4*)(a.mask + (size_t)min(mp, m_end - 1) * a.cout + c);
+        // (classifier fragments: A operand, rows = classes, k = 16 channels of this tile)
+        if (EPI == 2) w3f[rg] = *(const u32x4*)(a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + n0 + lhi * 8 + rg * 16);
+    }
+
     // ---- exchange of the partial sums: accumulator tile j of every wavefront goes to the
     //      wavefront (wn, kgrp = j), which adds the four partials in ascending source order
     float* red = (float*)smem_raw;   // [owner = j * 2 + wn][source slot 0..2][4 register groups][64 lanes][4]
@@ -257,11 +279,8 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     if (EPI == 3) {
         // a lane holds 16 channels of one position; for a fixed channel the 32 lanes of a half
         // wavefront are 32 consecutive positions, i.e. (inside one grid row) consecutive floats
-        const int frame = a.Hp * a.Wp;
-        const int mp = m0 + kgrp * 32 + l32;
-        const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
-        if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) {
-            float* dst = a.dense + ((size_t)img * a.dense_c * a.h + (y - 1)) * a.w + (x - 1);
+        if (inside) {
+            float* dst = a.dense + ((size_t)cell.img * a.dense_c * a.h + (cell.y - 1)) * a.w + (cell.x - 1);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int ch = n0 + wn * 32 + (r >> 2) * 8 + lhi * 4 + (r & 3);
@@ -271,49 +290,21 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         return;
     }
 
-    // classifier fragments (A operand: rows = classes, k = 16 channels of this tile), fetched
-    // now so that they arrive while the tile is being staged
-    u32x4 w3f[4];
-    if (EPI == 2) {
-        const bf16* w3row = a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + n0 + lhi * 8;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const u32x4 v = *(const u32x4*)(w3row + ks * 16);
-            w3f[ks] = l32 < a.n_cls ? v : u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-
     // ---- epilogue: bias + ReLU (forward) or ReLU mask (data-gradient), zero outside the grid,
     //      round to bfloat16, stage the tile in LDS as [position][channel]
     bf16* Os = (bf16*)(smem_raw + CV_RED_BYTES);     // [CV_BM][CV_OLD], behind the partial sums
-    {
-        const int frame = a.Hp * a.Wp;
-        const int p = kgrp * 32 + l32;
-        const int mp = m0 + p;
-        const int rr = mp % frame, y = rr / a.Wp, x = rr - y * a.Wp;
-        const bool inside = mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w;
-        const float* bias = (EPI == 0 || EPI == 2) ? a.bias + grp * a.bias_stride : nullptr;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-            const int c = wn * 32 + rg * 8 + lhi * 4;   // channel inside the tile
-            float v[4];
+    for (int rg = 0; rg < 4; ++rg) {
+        const int c = wn * 32 + rg * 8 + lhi * 4;   // channel inside the tile
+        bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = mine[rg * 4 + e];
-            if (EPI == 0 || EPI == 2) {
-                const float4 b = *(const float4*)(bias + n0 + c);
-                v[0] = fmaxf(v[0] + b.x, 0.f); v[1] = fmaxf(v[1] + b.y, 0.f);
-                v[2] = fmaxf(v[2] + b.z, 0.f); v[3] = fmaxf(v[3] + b.w, 0.f);
-            } else {
-                bf16x4 mk = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
-                if (inside) mk = *(const bf16x4*)(a.mask + (size_t)mp * a.cout + n0 + c);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (float)mk[e] > 0.f ? v[e] : 0.f;
-            }
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(inside ? v[e] : 0.f);
-            *(bf16x4*)(Os + p * CV_OLD + c) = o;
+        for (int e = 0; e < 4; ++e) {
+            float v = mine[rg * 4 + e];
+            if (EPI == 1) v = (float)mk[rg][e] > 0.f ? v : 0.f;
+            else v = fmaxf(v + bias[rg][e], 0.f);
+            o[e] = (bf16)(inside ? v : 0.f);
         }
+        *(bf16x4*)(Os + p * CV_OLD + c) = o;
     }
     __syncthreads();
     if (EPI == 2 && wave < 4) {
@@ -324,12 +315,13 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const bf16x8 xf = *(const bf16x8*)(Os + (wave * 32 + l32) * CV_OLD + ks * 16 + lhi * 8);
-            zacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w3f[ks]), xf, zacc, 0, 0, 0);
+            const u32x4 wf = l32 < a.n_cls ? w3f[ks] : u32x4{0u, 0u, 0u, 0u};
+            zacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf), xf, zacc, 0, 0, 0);
         }
-        const int mp = m0 + wave * 32 + l32;
-        if (mp < m_end) {
+        const int zp = m0 + wave * 32 + l32;
+        if (zp < m_end) {
             // (a lane holds classes 8 gq + 4 lhi .. + 3; the groups beyond the classes are padding)
-            float* zrow = a.zpart + ((size_t)nt * a.PP + mp) * a.zpitch + lhi * 4;
+            float* zrow = a.zpart + ((size_t)nt * a.PP + zp) * a.zpitch + lhi * 4;
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq)
                 if (gq * 8 + lhi * 4 < a.zpitch)
@@ -373,6 +365,7 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.PP = p.g.padded_positions(); a.Hp = p.g.Hp; a.Wp = p.g.Wp; a.h = p.g.h; a.w = p.g.w;
     a.cin = cin; a.cout = cout;
     a.PPT = p.PPT; a.guard = p.guard;
+    a.by_frame = fast_div(g.Hp * g.Wp); a.by_row = fast_div(g.Wp);
     // several heads: one weight set per frame (Wq holds them back to back, the biases sit
     // head_stride floats apart inside the parameter vectors, W3q back to back)
     a.grp_pp = g.grouped ? g.Hp * g.Wp : a.PP;
@@ -383,6 +376,7 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.grp_tiles = cdiv(a.grp_pp, CV_BM);
     a.m_tiles = g.heads() * a.grp_tiles;
     a.n_tiles = cout / CV_BN;
+    a.by_n_tiles = fast_div(a.n_tiles); a.by_grp_tiles = fast_div(a.grp_tiles);
     const int tiles = a.m_tiles * a.n_tiles;
     a.tiles_per_xcd = cdiv(tiles, 8);
     const dim3 grid(a.tiles_per_xcd * 8);

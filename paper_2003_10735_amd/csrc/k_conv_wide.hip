@@ -54,11 +54,13 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     constexpr int P = CW_P, BM = CW_BM, BN = CW_BN, SLAB = (BM + 2) * 128, STEPS = CW_STEPS, RING = CW_RING, OLD = CW_OLD;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
-    // XCD-aware tile order, several heads: as in k_conv3x3_mfma
+    // (the arguments, XCD-aware tile order, several heads: as in k_conv3x3_mfma)
+    asm volatile("" ::"s"(a.tiles_per_xcd), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.by_n_tiles.m), "s"(a.by_grp_tiles.m), "s"(a.grp_tiles), "s"(a.grp_pp),
+                 "s"(a.X), "s"(a.Wq), "s"(a.wq_stride), "s"(a.cin), "s"(a.Wp));
     const int tile = (blockIdx.x % 8) * a.tiles_per_xcd + blockIdx.x / 8;
     if ((int)(blockIdx.x / 8) >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
-    const int mt = tile / a.n_tiles, nt = tile % a.n_tiles;
-    const int grp = mt / a.grp_tiles;
+    const int mt = fast_quot(tile, a.by_n_tiles), nt = tile - mt * a.n_tiles;
+    const int grp = fast_quot(mt, a.by_grp_tiles);
     const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * BM, n0 = nt * BN;
     const int m_end = (grp + 1) * a.grp_pp;
 
@@ -207,7 +209,6 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
 
     // ---- what the epilogue needs from memory, on its way while the partial sums are exchanged
     constexpr int CHUNKS = BM * (BN / 8) / 256;      // 16-byte chunks of the output tile per thread
-    const int frame = a.Hp * a.Wp;
     const int cw = wn * 64 + kgrp * 32;              // this wavefront's 32 channels inside the tile
     u32x4 mk[EPI == 1 ? CHUNKS : 1];
     if (EPI == 1) {
@@ -224,11 +225,8 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
         for (int k = 0; k < 4; ++k)
             bias[k] = *(const f32x4*)(a.bias + grp * a.bias_stride + min(n0 + cw + k * 8 + lhi * 4, a.cout - 4));
 #pragma unroll
-        for (int j = 0; j < P; ++j) {
-            const int mp = m0 + j * 32 + l32;
-            const int rr = mp % frame, y = rr / a.Wp, x = rr - y * a.Wp;
-            if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) inside |= 1u << j;
-        }
+        for (int j = 0; j < P; ++j)
+            if (conv_cell(a, m0 + j * 32 + l32, m_end).inside) inside |= 1u << j;
     }
     f32x16 sum[P];            // this wavefront's 32 channels
     __syncthreads();
@@ -267,10 +265,9 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
     if (EPI == 3) {
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            const int mp = m0 + j * 32 + l32;
-            const int img = mp / frame, rr = mp - img * frame, y = rr / a.Wp, x = rr - y * a.Wp;
-            if (mp < m_end && y >= 1 && y <= a.h && x >= 1 && x <= a.w) {
-                float* dst = a.dense + ((size_t)img * a.dense_c * a.h + (y - 1)) * a.w + (x - 1);
+            const ConvCell cell = conv_cell(a, m0 + j * 32 + l32, m_end);
+            if (cell.inside) {
+                float* dst = a.dense + ((size_t)cell.img * a.dense_c * a.h + (cell.y - 1)) * a.w + (cell.x - 1);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int ch = n0 + cw + (r >> 2) * 8 + lhi * 4 + (r & 3);
@@ -391,6 +388,7 @@ void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads)
     a.grp_tiles = cdiv(a.grp_pp, CW_BM);
     a.m_tiles = heads * a.grp_tiles;
     a.n_tiles = cdiv(a.cout, CW_BN);
+    a.by_n_tiles = fast_div(a.n_tiles); a.by_grp_tiles = fast_div(a.grp_tiles);
     a.tiles_per_xcd = cdiv(a.m_tiles * a.n_tiles, 8);
     const dim3 grid(a.tiles_per_xcd * 8);
     auto go = [&](auto kernel) {

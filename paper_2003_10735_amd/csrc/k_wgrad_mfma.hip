@@ -47,6 +47,7 @@ struct WgradArgs {
     int units_per_wave;   // units per wavefront
     int n_units;          // units of one head's positions: pairs of rows x groups of eight columns
     int o_tiles, i_tiles, splits, items_per_xcd;
+    FastDiv by_tiles, by_splits, by_o_tiles, by_row;      // (o_tiles * i_tiles; splits; o_tiles; Wp / 8)
     // Several heads: head k owns the positions from 8-position group k * head_groups8 on and
     // writes its partial copies head_out_stride floats after head k - 1.  (With an odd number of rows a head's last
     // pair reaches into the next frame's first row, or the guard: dY is zero there.)
@@ -78,11 +79,11 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     const int tiles = a.o_tiles * a.i_tiles;
     const int item = (bid % 8) * a.items_per_xcd + bid / 8;     // blocks1 is a multiple of 8
     if (bid / 8 >= a.items_per_xcd || item >= tiles * a.splits * a.heads) return;
-    const int hsplit = item / tiles, tile = item % tiles;
-    const int head = hsplit / a.splits, split = hsplit - head * a.splits;
+    const int hsplit = fast_quot(item, a.by_tiles), tile = item - hsplit * tiles;
+    const int head = fast_quot(hsplit, a.by_splits), split = hsplit - head * a.splits;
     // output-channel tile fastest: the blocks that stream the same X rows (same split, same
     // input-channel tile) are neighbours in the order, run on one XCD and share them in its L2
-    const int ot = tile % a.o_tiles, it = tile / a.o_tiles;
+    const int it = fast_quot(tile, a.by_o_tiles), ot = tile - it * a.o_tiles;
     const int o0 = ot * 32, i0 = it * 32;
 
     // acc[0..8]: the nine taps; acc[9]: row sums of dY (bias gradient), only in blocks with it == 0
@@ -104,7 +105,7 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     const int g0 = (a.guard >> 3) + head * a.head_groups8;     // this head's first 8-position group
     const int row_groups = a.Wp >> 3;   // one grid row = this many 8-position groups
     const unsigned row_bytes = (unsigned)row_groups * 512u;
-    const int pair0 = unit0 / row_groups;
+    const int pair0 = fast_quot(unit0, a.by_row);
     int col = unit0 - pair0 * row_groups;                      // column group of the next unit to load
     const int first = pair0 * 2 * row_groups + col, before = first - (col ? 1 : row_groups + 1);    // groups of unit0 and unit0 - 1
     // (a descriptor ends with its channel block, whose head and tail are zeroed guard columns)
@@ -310,6 +311,7 @@ static WgradArgs wgrad_args(const Plan& p, const bf16* dYT, const bf16* XT, floa
     a.o_tiles = cdiv(cout, 32); a.i_tiles = cdiv(cin, 32);
     a.splits = splits;
     a.items_per_xcd = cdiv(a.o_tiles * a.i_tiles * splits * a.heads, 8);
+    a.by_tiles = fast_div(a.o_tiles * a.i_tiles); a.by_splits = fast_div(splits); a.by_o_tiles = fast_div(a.o_tiles); a.by_row = fast_div(p.g.Wp / 8);
     return a;
 }
 

@@ -22,12 +22,25 @@ struct ConvArgs {
     float* dense; int dense_c;   // (channels of that tensor: cout without the padding)
     int PP, Hp, Wp, h, w, cin, cout, PPT, guard;
     int m_tiles, n_tiles, tiles_per_xcd;
+    FastDiv by_n_tiles, by_grp_tiles, by_frame, by_row;     // (n_tiles; grp_tiles; Hp * Wp; Wp)
     // Several heads: positions [k * grp_pp, (k + 1) * grp_pp) use weight set k (Wq, bias and W3q
     // advance by wq_stride, bias_stride, w3_stride elements per set); position tiles are counted
     // per set (grp_tiles each) so that no tile mixes two sets.  One head: grp_pp = PP.
     int grp_pp, grp_tiles;
     size_t wq_stride, bias_stride, w3_stride;
 };
+
+// where padded position mp lies: the frame, and whether it is a cell of its grid (row y - 1, column x - 1)
+struct ConvCell { int img, y, x; bool inside; };
+__device__ __forceinline__ ConvCell conv_cell(const ConvArgs& a, int mp, int m_end)
+{
+    ConvCell c;
+    c.img = fast_quot(mp, a.by_frame);
+    const int rr = mp - c.img * (int)a.by_frame.d;
+    c.y = fast_quot(rr, a.by_row); c.x = rr - c.y * (int)a.by_row.d;
+    c.inside = mp < m_end && c.y >= 1 && c.y <= a.h && c.x >= 1 && c.x <= a.w;
+    return c;
+}
 
 // Positions x channels of a block's tile: 64 channels name the kernel of k_conv_mfma.hip, 128 that of k_conv_wide.hip.
 struct ConvTile { int bm, bn; };
