@@ -57,8 +57,11 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
                  const unsigned long long* __restrict__ n_valid, int CP, LossTiling lt,
                  const bf16* __restrict__ a2,
                  const bf16* __restrict__ W3T, bf16* __restrict__ da2, bf16* __restrict__ da2T,
-                 float* __restrict__ part, Geo g, int PPT, int guard, int grp_blocks, int main_blocks, FinishArgs fin)
+                 float* __restrict__ part, Geo g, int PPT, int guard, int grp_blocks, FastDiv by_grp_blocks, int main_blocks, FinishArgs fin)
 {
+    // (what the first loads need, in one trip for the arguments)
+    asm volatile("" ::"s"(slots), "s"(T), "s"(n_valid), "s"(CP), "s"(lt.tiles_x), "s"(lt.tiles_y), "s"(a2), "s"(W3T), "s"(g.n), "s"(g.h), "s"(g.w), "s"(g.Hp), "s"(g.Wp),
+                 "s"(g.C), "s"(g.grouped), "s"(g.by_frame.d), "s"(g.by_frame.m), "s"(g.by_row.d), "s"(g.by_row.m));
     if (FIN && (int)blockIdx.x >= main_blocks) {
         if (!RUNS || blockIdx.y == 0) finish_block<true, C3B_NT>(fin, (int)blockIdx.x - main_blocks, 0);
         return;
@@ -83,7 +86,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     const int PP = g.padded_positions(), frame = g.Hp * g.Wp;
     // several heads: blocks are counted per frame (grp_blocks each), so that no block mixes the
     // positions -- and with them W3 and the partial sums -- of two heads
-    const int head = g.grouped ? blockIdx.x / grp_blocks : 0;
+    const int head = g.grouped ? fast_quot(blockIdx.x, by_grp_blocks) : 0;
     const int m0 = g.grouped ? head * frame + (blockIdx.x - head * grp_blocks) * BP : blockIdx.x * BP;
     const int m_end = g.grouped ? (head + 1) * frame : PP;
     const int k2 = RUNS ? g.k2 : C2, ch0 = RUNS ? blockIdx.y * C2 : 0;     // channel pitch; first channel of this block
@@ -116,7 +119,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
         const int p = tid & (BP - 1), cq = tid / BP;     // this thread: one position, every eighth class
         constexpr int NQ = NT / BP;
         float v[32 / NQ];
-        gather_g<32 / NQ, NQ>(slots, T, n_valid[head], CP, lt, g, m0 + p, m_end, cq, v);
+        gather_g<32 / NQ, NQ>(slots, T, n_valid + head, CP, lt, g, m0 + p, m_end, cq, v);
 #pragma unroll
         for (int k = 0; k < 32 / NQ; ++k) {
             const int cc = cq + NQ * k;
@@ -249,10 +252,10 @@ void conv3_bwd_mfma(Ctx& c, const Plan& p, const float* slots, const float* T,
     do {                                                                                                       \
         if (finish)                                                                                            \
             ST_LAUNCH(c, "conv3_bwd_mfma+finish_pass", (k_conv3_bwd_mfma<C2, RUNS, true>), grid, dim3(C3B_NT), 0, slots, T, \
-                      n_valid, CP, p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin); \
+                      n_valid, CP, p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, fast_div(grp_blocks), main_blocks, fin); \
         else                                                                                                   \
             ST_LAUNCH(c, "conv3_bwd_mfma", (k_conv3_bwd_mfma<C2, RUNS, false>), grid, dim3(C3B_NT), 0, slots, T, n_valid, CP, \
-                      p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, main_blocks, fin);    \
+                      p.lt, a2, W3T, da2, da2T, part, g, p.PPT, p.guard, grp_blocks, fast_div(grp_blocks), main_blocks, fin);    \
     } while (0)
     if (run == g.k2) {
         switch (run) {

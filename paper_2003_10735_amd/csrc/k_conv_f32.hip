@@ -877,6 +877,9 @@ k_conv3_bwd_f32(const float* __restrict__ slots, const float* __restrict__ T, co
 {
     constexpr int BP = B32_BP, GP = BP + 8;     // (pitch: the two halves of a B read 32 banks apart)
     __shared__ __attribute__((aligned(16))) float g_cp[32 * GP];    // [class][position]
+    // (what the first loads need, in one trip for the arguments)
+    asm volatile("" ::"s"(slots), "s"(T), "s"(n_valid), "s"(CP), "s"(lt.tiles_x), "s"(lt.tiles_y), "s"(a2), "s"(W3T), "s"(g.n), "s"(g.h), "s"(g.w), "s"(g.Hp), "s"(g.Wp),
+                 "s"(g.C), "s"(g.k2), "s"(g.by_frame.d), "s"(g.by_frame.m), "s"(g.by_row.d), "s"(g.by_row.m));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
     const int PP = g.padded_positions(), hw = g.h * g.w;
@@ -884,7 +887,7 @@ k_conv3_bwd_f32(const float* __restrict__ slots, const float* __restrict__ T, co
     {
         const int pl = tid & 63, cq = tid >> 6;
         float v[8];
-        const GatherCell cell = gather_g<8, 4>(slots, T, n_valid[0], CP, lt, g, m0 + pl, PP, cq, v);
+        const GatherCell cell = gather_g<8, 4>(slots, T, n_valid, CP, lt, g, m0 + pl, PP, cq, v);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int c = cq + 4 * k;

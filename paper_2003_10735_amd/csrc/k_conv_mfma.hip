@@ -41,17 +41,20 @@
 
 namespace st {
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
 constexpr int CV_BM = 128;
 constexpr int CV_BN = 64;
 constexpr int CV_BK = 64;
 constexpr int CV_NBUF = 3;          // activation slabs in LDS: one in use, two on their way
 constexpr int CV_XS_ROWS = CV_BM + 2;
 constexpr int CV_OLD = CV_BN + 8;   // pitch of the staged output tile
-// dynamic LDS: during the K loop the activation slabs; afterwards the exchanged partial sums
-// (8 owners x 3 sources x 16 registers x 64 lanes, float32) followed by the staged output tile
-constexpr size_t CV_RED_BYTES = (size_t)8 * 3 * 16 * 64 * sizeof(float);
-constexpr size_t CV_SMEM_BYTES = CV_RED_BYTES + (size_t)CV_BM * CV_OLD * sizeof(bf16);
-static_assert((size_t)CV_NBUF * CV_XS_ROWS * CV_BK * sizeof(bf16) <= CV_SMEM_BYTES, "K-loop buffers fit");
+// dynamic LDS: the activation slabs, whose room the staged output tile takes afterwards, and behind them the exchanged partial
+// sums (8 owners x 3 sources x 16 registers x 64 lanes, float32), which are written while the last slab is still read
+constexpr size_t CV_SLABS_BYTES = (size_t)CV_NBUF * CV_XS_ROWS * CV_BK * sizeof(bf16);
+constexpr size_t CV_SMEM_BYTES = CV_SLABS_BYTES + (size_t)8 * 3 * 16 * 64 * sizeof(float);
+static_assert((size_t)CV_BM * CV_OLD * sizeof(bf16) <= CV_SLABS_BYTES && CV_SMEM_BYTES <= 160 * 1024, "LDS buffers fit");
 
 // TAG only gives every call site (layer 1 forward, layer 2 forward, layer 2 data-gradient) a
 // kernel symbol of its own, so that profiles list them separately.
@@ -78,10 +81,11 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * CV_BM, n0 = nt * CV_BN;
     const int m_end = (grp + 1) * a.grp_pp;     // results from here on belong to another tile
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kgrp = wave >> 1;
     const int l32 = lane & 31, lhi = lane >> 5;
 
+    // acc[s]: positions 32 (s ^ kgrp) .. + 31 of the tile, so that slot 0 is the one this wavefront owns in the end
     f32x16 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -120,10 +124,13 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     const bf16* xg = a.X + ((long long)m0 - 1 - a.Wp) * a.cin;               // first row of the kh = 0 slabs
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const unsigned wave_lds = __builtin_amdgcn_readfirstlane(wave * 1024);   // a scalar: it goes to M0
-    // fragment reads: row J*32 + l32 + KW, chunk kgrp*2 + lhi
-    int rd[3];
+    // fragment reads: row 32 (J ^ kgrp) + l32 + KW, chunk kgrp*2 + lhi
+    int rd[3][4];
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) rd[kw] = (l32 + kw) * 128 + (((kgrp * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4);
+    for (int kw = 0; kw < 3; ++kw)
+#pragma unroll
+        for (int J = 0; J < 4; ++J)
+            rd[kw][J] = (l32 + kw) * 128 + (((kgrp * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4) + (J ^ kgrp) * 4096;
 
     // The stage being fetched runs two ahead of the one being multiplied.  Its operands are
     // addressed as (scalar base, advanced once per stage) + (per-lane byte offset, fixed), which
@@ -153,7 +160,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     }
 #define CV_LOAD_W(SET, KW) wr[SET][KW] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv[KW], w_soff, 0);
 #define CV_READ1(DST, J, BUF, KW)                                                                 \
-    DST[J] = *(const bf16x8*)(smem_raw + (BUF) * XS_BYTES + rd[KW] + (J) * 4096);
+    DST[J] = *(const bf16x8*)(smem_raw + (BUF) * XS_BYTES + rd[KW][J]);
 #define CV_MMA1(SRC, J, SET, KW)                                                                  \
     acc[J] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[SET][KW]), SRC[J], acc[J], 0, 0, 0);
     // s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, no wait on the others)
@@ -188,14 +195,16 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 
     bf16x8 xa[4], xb[4];
     {
-        CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2)
+        // (activations first: the barrier waits for those of the first stage alone, everything but the eight or nine
+        //  loads behind them)
         CV_LOAD_X1(0, 0) CV_LOAD_X1(0, 1) CV_LOAD_X1(0, 2)
+        CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2)
         CV_FETCH_NEXT
-        CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2)
         CV_LOAD_X1(1, 0) CV_LOAD_X1(1, 1) CV_LOAD_X1(1, 2)
+        CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2)
         CV_FETCH_NEXT
         CV_F
-        CV_VMCNT(5)
+        CV_VMCNT(8)
         __syncthreads();
     }
     // the number of stages is a multiple of three (three kernel rows): three stages per trip make
@@ -208,7 +217,39 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     }
     CV_STAGE(0, true)
     CV_STAGE(1, false)
-    CV_STAGE(2, false)
+    // The last stage takes one accumulator tile behind the other, the tiles of other owners first, so that a finished tile is on its way
+    // to LDS while the next one's MFMAs run.  (With the order of the first loads and the transposing reads below, launches before -> now: 90 x 160
+    // cells, 256 -> 128 -> 128 13.2 -> 12.6, 9.6 -> 9.0, 9.6 -> 8.6 us; 60 x 107 11.6 -> 10.8, 8.05 -> 7.1.)
+    // (red: [owner j][wn][slot - 1][4 register groups][64 lanes][4], slot = source's K group ^ j)
+    float* red = (float*)(smem_raw + CV_SLABS_BYTES) + wn * 3072 + lane * 4;
+#define CV_HAND(S, RQ0, RQ1)                                                                      \
+    {                                                                                             \
+        float* dst_ = red + ((S) ^ kgrp) * 6144 + ((S) - 1) * 1024;                               \
+        _Pragma("unroll") for (int rq = RQ0; rq < RQ1; ++rq)                                      \
+            *(f32x4*)(dst_ + rq * 256) = f32x4{acc[S][rq * 4], acc[S][rq * 4 + 1], acc[S][rq * 4 + 2], acc[S][rq * 4 + 3]}; \
+    }
+    {
+        bf16x8 xc[4];
+        CV_READ1(xa, 1, 2, 0) CV_READ1(xb, 1, 2, 1) CV_READ1(xc, 1, 2, 2) CV_READ1(xa, 2, 2, 0) CV_READ1(xb, 2, 2, 1) CV_READ1(xc, 2, 2, 2) CV_F
+        CV_MMA1(xa, 1, 2, 0) CV_F CV_READ1(xa, 3, 2, 0) CV_F
+        CV_MMA1(xb, 1, 2, 1) CV_F CV_READ1(xb, 3, 2, 1) CV_F
+        CV_MMA1(xc, 1, 2, 2) CV_F CV_READ1(xc, 3, 2, 2) CV_F
+        CV_MMA1(xa, 2, 2, 0) CV_F CV_READ1(xa, 0, 2, 0) CV_F
+        CV_MMA1(xb, 2, 2, 1) CV_F CV_READ1(xb, 0, 2, 1) CV_F
+        CV_MMA1(xc, 2, 2, 2) CV_F CV_READ1(xc, 0, 2, 2) CV_F
+        CV_MMA1(xa, 3, 2, 0) CV_F
+        CV_HAND(1, 0, 2) CV_F
+        CV_MMA1(xb, 3, 2, 1) CV_F
+        CV_HAND(1, 2, 4) CV_F
+        CV_MMA1(xc, 3, 2, 2) CV_F
+        CV_HAND(2, 0, 2) CV_F
+        CV_MMA1(xa, 0, 2, 0) CV_F
+        CV_HAND(2, 2, 4) CV_F
+        CV_MMA1(xb, 0, 2, 1) CV_F
+        CV_MMA1(xc, 0, 2, 2) CV_F
+        CV_HAND(3, 0, 4)
+    }
+#undef CV_HAND
 #undef CV_STAGE
 #undef CV_FETCH_NEXT
 #undef CV_LOAD_X1
@@ -237,22 +278,10 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         if (EPI == 2) w3f[rg] = *(const u32x4*)(a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + n0 + lhi * 8 + rg * 16);
     }
 
-    // ---- exchange of the partial sums: accumulator tile j of every wavefront goes to the
+    // ---- exchange of the partial sums: accumulator tile j of every wavefront has gone to the
     //      wavefront (wn, kgrp = j), which adds the four partials in ascending source order
-    float* red = (float*)smem_raw;   // [owner = j * 2 + wn][source slot 0..2][4 register groups][64 lanes][4]
-    // (all wavefronts are past the last barrier of the K loop: the slabs are free)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (j != kgrp) {
-            const int src = kgrp - (kgrp > j ? 1 : 0);
-            float* dst = red + ((size_t)((j * 2 + wn) * 3 + src) * 16) * 64 + lane * 4;
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq)
-                *(f32x4*)(dst + rq * 256) = f32x4{acc[j][rq * 4], acc[j][rq * 4 + 1], acc[j][rq * 4 + 2], acc[j][rq * 4 + 3]};
-        }
-    }
-    f32x16 mine = kgrp == 0 ? acc[0] : kgrp == 1 ? acc[1] : kgrp == 2 ? acc[2] : acc[3];
     __syncthreads();
+    f32x16 mine = acc[0];
     {
         f32x16 sum;
 #pragma unroll
@@ -260,7 +289,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
             f32x16 term;
             if (k == kgrp) term = mine;
             else {
-                const float* srcp = red + ((size_t)((kgrp * 2 + wn) * 3 + (k - (k > kgrp ? 1 : 0))) * 16) * 64 + lane * 4;
+                const float* srcp = red + kgrp * 6144 + ((k ^ kgrp) - 1) * 1024;
 #pragma unroll
                 for (int rq = 0; rq < 4; ++rq) {
                     const f32x4 v = *(const f32x4*)(srcp + rq * 256);
@@ -292,7 +321,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 
     // ---- epilogue: bias + ReLU (forward) or ReLU mask (data-gradient), zero outside the grid,
     //      round to bfloat16, stage the tile in LDS as [position][channel]
-    bf16* Os = (bf16*)(smem_raw + CV_RED_BYTES);     // [CV_BM][CV_OLD], behind the partial sums
+    bf16* Os = (bf16*)smem_raw;     // [CV_BM][CV_OLD], where the slabs were
 #pragma unroll
     for (int rg = 0; rg < 4; ++rg) {
         const int c = wn * 32 + rg * 8 + lhi * 4;   // channel inside the tile
@@ -337,15 +366,17 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         }
     }
     if (a.YT) {
-        // channel-major: 16 bytes = 8 consecutive positions of one channel
-        for (int q = tid; q < (CV_BM / 8) * CV_BN; q += NT) {
-            const int c = q % CV_BN, pg = q / CV_BN;
-            if (m0 + pg * 8 < m_end) {
-                bf16x8 o;
+        // channel-major: 16 bytes = 8 consecutive positions of one channel, a wavefront two such groups of 32
+        // channels, through the transposing LDS read: in a group of 16 lanes, lane r names (position r / 4,
+        // channels 4 (r % 4) .. + 3) and lane i receives channel i of four consecutive positions
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = Os[(pg * 8 + e) * CV_OLD + c];
-                *(bf16x8*)(a.YT + xt_index(n0 + c, a.guard + m0 + pg * 8, a.PPT / 8)) = o;
-            }
+        for (int k = 0; k < 2; ++k) {
+            const int u = wave + 8 * k, pg = (u >> 1) * 2 + lhi, c = (u & 1) * 32;
+            const bf16* row = Os + (pg * 8 + ((lane & 15) >> 2)) * CV_OLD + c + (lane & 16) + 4 * (lane & 3);
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * CV_OLD));
+            const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            if (m0 + pg * 8 < m_end) *(s16x8*)(a.YT + xt_index(n0 + c + l32, a.guard + m0 + pg * 8, a.PPT / 8)) = v;
         }
     }
 }
@@ -365,7 +396,7 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.PP = p.g.padded_positions(); a.Hp = p.g.Hp; a.Wp = p.g.Wp; a.h = p.g.h; a.w = p.g.w;
     a.cin = cin; a.cout = cout;
     a.PPT = p.PPT; a.guard = p.guard;
-    a.by_frame = fast_div(g.Hp * g.Wp); a.by_row = fast_div(g.Wp);
+    a.by_frame = g.by_frame; a.by_row = g.by_row;
     // several heads: one weight set per frame (Wq holds them back to back, the biases sit
     // head_stride floats apart inside the parameter vectors, W3q back to back)
     a.grp_pp = g.grouped ? g.Hp * g.Wp : a.PP;

@@ -14,6 +14,17 @@ constexpr int UP = 8;  // up-sampling factor of the head's last stage
 
 typedef __bf16 bf16;
 
+// Division by a number the host knows: one high product and a correction (n < 2^31: the quotient of the
+// product is at most one short), where the compiler's own division by a variable is some twenty instructions, and a lone
+// wavefront issues one in eight cycles or more.
+struct FastDiv { unsigned d, m; };
+inline FastDiv fast_div(int d) { return FastDiv{(unsigned)d, d == 1 ? 0xFFFFFFFFu : (unsigned)((1ull << 32) / (unsigned)d)}; }
+__host__ __device__ __forceinline__ int fast_quot(int n, const FastDiv& f)
+{
+    const unsigned q = (unsigned)((unsigned long long)(unsigned)n * f.m >> 32);
+    return (int)(q + ((unsigned)n - q * f.d >= f.d ? 1u : 0u));
+}
+
 // ------------------------------------------------------------------ geometry
 // Activations live position-major ("NHWC") on a grid padded by one zero cell on every side, so
 // a 3x3 tap is a plain offset and needs no bounds test:
@@ -33,6 +44,7 @@ struct Geo {
     int ignore_index;
     int grouped;     // 1: frame f has a head (parameters, loss, pixel count) of its own
     int nhwc;        // 1: the caller's features are [n, h, w, c_in] instead of [n, c_in, h, w]
+    FastDiv by_frame, by_row;    // Hp * Wp; Wp
     bool padded() const { return ki != c_in || k1 != c1 || k2 != c2; }
     __host__ __device__ int heads() const { return grouped ? n : 1; }
     __host__ __device__ int head_of(int img) const { return grouped ? img : 0; }
@@ -57,6 +69,7 @@ inline Geo make_geo(const st_head_desc& d)
     g.ignore_index = d.ignore_index;
     g.grouped = d.grouped ? 1 : 0;
     g.nhwc = d.feat_layout == ST_NHWC ? 1 : 0;
+    g.by_frame = fast_div(g.Hp * g.Wp); g.by_row = fast_div(g.Wp);
     return g;
 }
 
@@ -188,16 +201,5 @@ template <> __device__ __forceinline__ float from_f32<float>(float v) { return v
 template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf16)v; }  // RNE
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
-
-// Division by a number the host knows: one high product and a correction (n < 2^31: the quotient of the
-// product is at most one short), where the compiler's own division by a variable is some twenty instructions, and a lone
-// wavefront issues one in eight cycles or more.
-struct FastDiv { unsigned d, m; };
-inline FastDiv fast_div(int d) { return FastDiv{(unsigned)d, d == 1 ? 0xFFFFFFFFu : (unsigned)((1ull << 32) / (unsigned)d)}; }
-__device__ __forceinline__ int fast_quot(int n, const FastDiv& f)
-{
-    const unsigned q = __umulhi((unsigned)n, f.m);
-    return (int)(q + ((unsigned)n - q * f.d >= f.d ? 1u : 0u));
-}
 
 }  // namespace st

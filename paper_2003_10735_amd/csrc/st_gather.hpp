@@ -19,43 +19,53 @@ __host__ __device__ __forceinline__ GatherAt gather_at(int CP, const LossTiling&
 {
     GatherAt at;
     const int frame = g.Hp * g.Wp;
-    const int f = mp / frame, img = f < g.n ? f : g.n - 1;
-    const int rr = mp - img * frame, y = rr / g.Wp, x = rr - y * g.Wp;
+    const int f = fast_quot(mp, g.by_frame), img = f < g.n ? f : g.n - 1;
+    const int rr = mp - img * frame, y = fast_quot(rr, g.by_row), x = rr - y * g.Wp;
     const bool inside = mp < m_end && y >= 1 && y <= g.h && x >= 1 && x <= g.w;
     const int cy = inside ? y - 1 : 0, cx = inside ? x - 1 : 0;
     at.cell = GatherCell{img, cy, cx, inside};
-    // the tiles whose cell window contains (cy, cx): up to 3 tile rows x 2 tile columns
-    const int ty_top = (cy + 1) / LOSS_TY, tx_top = (cx + 1) / LOSS_TX;
-    const int ty_hi = ty_top < lt.tiles_y ? ty_top : lt.tiles_y - 1, tx_hi = tx_top < lt.tiles_x ? tx_top : lt.tiles_x - 1;
-    // offset of class 0 and a 0/1 weight: tiles that do not exist or do not touch the
-    // cell read slot element 0 with weight 0, so that every load is unconditional
+    // the tiles whose cell window contains (cy, cx): up to 3 tile rows, and beside the tile column with the cell the one next to
+    // it if the cell is its first or last column.  From one tile row to the next a cell moves up by one row of the window, so the
+    // offsets of a column are equally far apart.
+    static_assert(LOSS_TY == 1, "a cell row is a tile row");
+    const int tx = cx / LOSS_TX, in = cx % LOSS_TX;
+    const int tx1 = in == 0 ? tx - 1 : tx + 1, in1 = in == 0 ? LOSS_TX : -1;
+    const bool beside = (in == 0 || in == LOSS_TX - 1) && tx1 >= 0 && tx1 < lt.tiles_x;
     const unsigned tile_floats = (unsigned)CP * (LOSS_CH * LOSS_CW);
+    // tile row cy, where the cell is row 1 of the window.  (A call has fewer tiles than cells, and those are fewer than 2^25.)
+    const unsigned tile = (unsigned)(img * lt.tiles() + cy * lt.tiles_x + tx);
+    const long long step = (long long)lt.tiles_x * tile_floats - LOSS_CW;
+    const long long col[2] = {(long long)((size_t)tile * tile_floats) + (LOSS_CW + in + 1),
+                              (long long)((size_t)(tile + tx1 - tx) * tile_floats) + (LOSS_CW + in1 + 1)};
+    // a 0/1 weight: tiles that do not exist or do not touch the cell read slot element 0 with weight 0, so that every
+    // load is unconditional
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int ty = ty_hi - 2 + a, tx = tx_hi - 1 + b;
-            const int r = cy - (ty * LOSS_TY - 1), lc = cx - (tx * LOSS_TX - 1);
-            const bool ok = inside && ty >= 0 && tx >= 0 && r >= 0 && r < LOSS_CH && lc >= 0 && lc < LOSS_CW;
-            // (a call has fewer tiles than cells, and those are fewer than 2^25)
-            const unsigned tile = ok ? img * lt.tiles() + ty * lt.tiles_x + tx : 0, in_tile = ok ? r * LOSS_CW + lc : 0;
-            at.off[a][b] = (size_t)tile * tile_floats + in_tile;
+            const bool ok = inside && (a > 0 || cy > 0) && (a < 2 || cy + 1 < lt.tiles_y) && (b == 0 || beside);
+            at.off[a][b] = ok ? (size_t)(col[b] + (a - 1) * step) : 0;
             at.wgt[a][b] = ok ? 1.f : 0.f;
         }
     return at;
 }
 
 // Classes cq + STEP k (k < K) of padded position mp (< m_end: of this head) into v; 0 outside the grid,
-// classes beyond the last hold its value.  All loads are issued before the first sum.
+// classes beyond the last hold its value.  cq: the same for all lanes.  All loads are issued before the first sum -- that of
+// the pixel count among them, by a vector load: a scalar one would be waited for with the kernel's arguments.
 template <int K, int STEP>
-__device__ __forceinline__ GatherCell gather_g(const float* __restrict__ slots, const float* __restrict__ T, unsigned long long nv,
+__device__ __forceinline__ GatherCell gather_g(const float* __restrict__ slots, const float* __restrict__ T, const unsigned long long* __restrict__ n_valid,
                                                int CP, const LossTiling& lt, const Geo& g, int mp, int m_end, int cq, float (&v)[K])
 {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 nv_raw = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+        __builtin_amdgcn_make_buffer_rsrc((void*)n_valid, 0, 8, 0x00020000), 0, 0, 0));
+    cq = __builtin_amdgcn_readfirstlane(cq);
     const int hw = g.h * g.w;
     const GatherAt at = gather_at(CP, lt, g, mp, m_end);
-    const float inv_n = (at.cell.inside && nv) ? 1.0f / (float)nv : 0.f;
     const int cstride = LOSS_CH * LOSS_CW;
-    const size_t tbase = (size_t)at.cell.img * g.C * hw + at.cell.cy * g.w + at.cell.cx;
+    // (logits of a call are fewer than 2^30)
+    const unsigned tbase = (unsigned)(at.cell.img * g.C * hw + at.cell.cy * g.w + at.cell.cx);
     float sv[K][6], tv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -63,10 +73,14 @@ __device__ __forceinline__ GatherCell gather_g(const float* __restrict__ slots, 
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) sv[k][a * 2 + b] = slots[at.off[a][b] + (size_t)c * cstride];
-        tv[k] = T[tbase + (size_t)c * hw];
+            for (int b = 0; b < 2; ++b) sv[k][a * 2 + b] = (slots + c * cstride)[at.off[a][b]];
+        tv[k] = (T + (size_t)c * hw)[tbase];
     }
     __builtin_amdgcn_sched_barrier(0);
+    unsigned nv_lo = nv_raw[0], nv_hi = nv_raw[1];
+    asm volatile("" : "+v"(nv_lo), "+v"(nv_hi));      // (what is made of it stays behind the loads)
+    const unsigned long long nv = nv_lo | (unsigned long long)nv_hi << 32;
+    const float inv_n = (at.cell.inside && nv) ? 1.0f / (float)nv : 0.f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         float s = 0.f;
