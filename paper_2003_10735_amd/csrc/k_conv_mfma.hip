@@ -25,6 +25,8 @@
 // accumulator tiles), and of every 64-channel stage the 16 input channels 16 kgrp .. +15.  The
 // four partial sums per output are exchanged once, through LDS, after the K loop: wavefront
 // (wn, kgrp) ends up owning positions 32 kgrp .. +31 and adds the partials in ascending kgrp.
+// Grids that leave compute units without a block run tiles of 64 or 32 positions (MB = 2, 1; the rule is conv_tile's): the same
+// wavefronts, channels and sums, two or one accumulator tiles each, and an owner of 8 or 4 of a tile's 16 registers.
 // K loop: stages of (one kernel row kh) x (64 input channels): 130 activation rows in LDS (the
 // tile's rows shifted by kh, plus one on each side) of 128 bytes, their 16-byte chunks swizzled
 // by the row number so that the fragment reads of 16 consecutive rows spread over all banks.  Three
@@ -36,6 +38,8 @@
 // (operand of the weight-gradient kernel).  For the layer that feeds the 1x1 classifier the
 // staged tile is also multiplied with the classifier's weights (16 more MFMAs per block), which
 // saves the classifier a launch and a pass over the activations.
+#include <type_traits>
+
 #include "st_conv.hpp"
 #include "st_kernels.hpp"
 
@@ -44,28 +48,30 @@ namespace st {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int CV_BM = 128;
 constexpr int CV_BN = 64;
 constexpr int CV_BK = 64;
 constexpr int CV_NBUF = 3;          // activation slabs in LDS: one in use, two on their way
-constexpr int CV_XS_ROWS = CV_BM + 2;
 constexpr int CV_OLD = CV_BN + 8;   // pitch of the staged output tile
-// dynamic LDS: the activation slabs, whose room the staged output tile takes afterwards, and behind them the exchanged partial
-// sums (8 owners x 3 sources x 16 registers x 64 lanes, float32), which are written while the last slab is still read
-constexpr size_t CV_SLABS_BYTES = (size_t)CV_NBUF * CV_XS_ROWS * CV_BK * sizeof(bf16);
-constexpr size_t CV_SMEM_BYTES = CV_SLABS_BYTES + (size_t)8 * 3 * 16 * 64 * sizeof(float);
-static_assert((size_t)CV_BM * CV_OLD * sizeof(bf16) <= CV_SLABS_BYTES && CV_SMEM_BYTES <= 160 * 1024, "LDS buffers fit");
+// Tiles of 32 MB positions: 128, or 64 or 32 where those find a compute unit each of their own (conv_tile).
+template <int MB>
+struct ConvLds {
+    static constexpr int BM = 32 * MB, ROWS = BM + 2, SLAB = ROWS * CV_BK * 2;       // one slab: BM + 2 rows of 64 channels, unpadded
+    // dynamic LDS: the activation slabs, whose room the staged output tile takes afterwards, and behind them the exchanged partial
+    // sums (8 owners x 3 sources x 4 MB registers x 64 lanes, float32), which are written while the last slab is still read
+    static constexpr size_t SLABS = (size_t)CV_NBUF * SLAB, BYTES = SLABS + (size_t)8 * 3 * 4 * MB * 64 * sizeof(float);
+    static_assert((size_t)BM * CV_OLD * sizeof(bf16) <= SLABS && BYTES <= 160 * 1024, "LDS buffers fit");
+};
 
 // TAG only gives every call site (layer 1 forward, layer 2 forward, layer 2 data-gradient) a
 // kernel symbol of its own, so that profiles list them separately.
-template <int EPI, int TAG>
+template <int EPI, int TAG, int MB>
 __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 {
     constexpr int NT = 512;                // threads per block
-    // 16-byte chunks per stage: XS_FULL per thread and one more for the first XS_REST threads
-    constexpr int XS_BYTES = CV_XS_ROWS * CV_BK * 2;   // one slab: 130 rows of 64 channels, unpadded
+    constexpr int BM = ConvLds<MB>::BM, XS_BYTES = ConvLds<MB>::SLAB;
+    constexpr int NR = 4 * MB;             // registers (of 16 per 32 x 32 sums) of an owner: a wavefront's MB tiles are four parts
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    // smem_raw during the K loop: [CV_NBUF][XS_ROWS][128 bytes], chunks swizzled
+    // smem_raw during the K loop: [CV_NBUF][BM + 2][128 bytes], chunks swizzled
 
     // (what the first loads need, in one trip for the arguments: left to itself the compiler asks for some of it only
     //  behind the question whether the block has a tile)
@@ -78,17 +84,20 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     if (slot >= a.tiles_per_xcd || tile >= a.m_tiles * a.n_tiles) return;
     const int mt = fast_quot(tile, a.by_n_tiles), nt = tile - mt * a.n_tiles;
     const int grp = fast_quot(mt, a.by_grp_tiles);
-    const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * CV_BM, n0 = nt * CV_BN;
+    const int m0 = grp * a.grp_pp + (mt - grp * a.grp_tiles) * BM, n0 = nt * CV_BN;
     const int m_end = (grp + 1) * a.grp_pp;     // results from here on belong to another tile
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kgrp = wave >> 1;
     const int l32 = lane & 31, lhi = lane >> 5;
 
-    // acc[s]: positions 32 (s ^ kgrp) .. + 31 of the tile, so that slot 0 is the one this wavefront owns in the end
-    f32x16 acc[4];
+    // The sums in four parts: part s goes to the wavefront of K group kgrp ^ s, and part 0 is the one this wavefront owns in the
+    // end.  MB = 4: part s is acc[s], 32 channels of positions 32 (s ^ kgrp) .. + 31.  With fewer positions a part is a half or a quarter of
+    // a tile's channels: acc[j] are positions 32 (j ^ kgrp % MB) .. + 31, and row m of the MFMAs is channel m ^ row_x.
+    const int row_x = MB == 4 ? 0 : MB == 2 ? (kgrp >> 1) * 16 : kgrp * 8;
+    f32x16 acc[MB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < MB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
 
@@ -107,7 +116,10 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     // are 8 even rows (banks 0-31) and 8 odd rows (banks 32-63), and within each group the eight
     // values of (r >> 1) & 7 differ, so the reads spread over all banks just as padded rows
     // would.  The lane that fills position pc of row r fetches chunk pc ^ ((r >> 1) & 7).
-    // Wavefront w fills rows 8w .. 8w+7 and 64+8w .. 64+8w+7; wavefront 0 also rows 128, 129.
+    // Wavefront w fills rows 8w .. 8w+7 and, of 130, 64+8w .. 64+8w+7; wavefront 0 also rows 128, 129.  The short stages of small
+    // tiles cannot afford that wavefront 0 so has one load more to wait for than the others: there every wavefront that fills rows (of
+    // 34 the first four) also fills the two behind BM, all with the same bytes.  (With 130 rows the eight loads cost more: key frame at 90 x 160
+    // cells 641 -> 649 us.)
     // The loads are written in assembly: the compiler would order every barrier behind all
     // outstanding loads of this kind, while the pipeline below needs two stages in flight.
     // (M0 is a reserved register for this compiler: it never allocates a value to it, sets it
@@ -120,17 +132,17 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     const int sw01 = (4 * wave + (lrow >> 1)) & 7, sw2 = lrow >> 1;          // (row >> 1) & 7 of the rows filled
     const int xo0 = ((wave * 8 + lrow) * a.cin + ((lpc ^ sw01) << 3)) * 2;   // byte offsets inside a slab
     const int xo1 = xo0 + 64 * a.cin * 2;
-    const int xo2 = ((128 + lrow) * a.cin + ((lpc ^ sw2) << 3)) * 2;
+    const int xo2 = ((BM + lrow) * a.cin + ((lpc ^ sw2) << 3)) * 2;
     const bf16* xg = a.X + ((long long)m0 - 1 - a.Wp) * a.cin;               // first row of the kh = 0 slabs
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
     const unsigned wave_lds = __builtin_amdgcn_readfirstlane(wave * 1024);   // a scalar: it goes to M0
-    // fragment reads: row 32 (J ^ kgrp) + l32 + KW, chunk kgrp*2 + lhi
-    int rd[3][4];
+    // fragment reads: row 32 (J ^ kgrp % MB) + l32 + KW, chunk kgrp*2 + lhi
+    int rd[3][MB];
 #pragma unroll
     for (int kw = 0; kw < 3; ++kw)
 #pragma unroll
-        for (int J = 0; J < 4; ++J)
-            rd[kw][J] = (l32 + kw) * 128 + (((kgrp * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4) + (J ^ kgrp) * 4096;
+        for (int J = 0; J < MB; ++J)
+            rd[kw][J] = (l32 + kw) * 128 + (((kgrp * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4) + (J ^ (kgrp & (MB - 1))) * 4096;
 
     // The stage being fetched runs two ahead of the one being multiplied.  Its operands are
     // addressed as (scalar base, advanced once per stage) + (per-lane byte offset, fixed), which
@@ -143,7 +155,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     int w_soff = 0;                                                          // weights of the stage
     unsigned wv[3];
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) wv[kw] = (unsigned)((((nb * 9 + kw) * kfr + kgrp) * 512 + lane * 8) * 2);
+    for (int kw = 0; kw < 3; ++kw) wv[kw] = (unsigned)((((nb * 9 + kw) * kfr + kgrp) * 512 + (lane ^ row_x) * 8) * 2);
     const long long x_step = CV_BK * 2, x_row = ((long long)a.Wp * a.cin - (c_chunks - 1) * CV_BK) * 2;
     const int w_step = (CV_BK / 16) * 512 * 2, w_row = (2 * kfr + CV_BK / 16) * 512 * 2;
     int f_cc = 0;
@@ -152,11 +164,16 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 #define CV_DMA(VOFF, LDSADDR)                                                                     \
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(VOFF), "s"(xsp), \
                  "s"(LDSADDR) : "memory");
+    // (the same for lanes 0 .. 15 alone: every lane of the kernel is active here, before and behind)
+#define CV_DMA2(VOFF, LDSADDR)                                                                    \
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, 0xffff\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1" ::"v"(VOFF), \
+                 "s"(xsp), "s"(LDSADDR) : "memory");
 #define CV_LOAD_X1(BUF, I)                                                                        \
     {                                                                                             \
-        if ((I) == 0) CV_DMA(xo0, lds0 + (BUF) * XS_BYTES + wave_lds)                             \
-        if ((I) == 1) CV_DMA(xo1, lds0 + (BUF) * XS_BYTES + 8192 + wave_lds)                      \
-        if ((I) == 2 && wave == 0 && lane < 16) CV_DMA(xo2, lds0 + (BUF) * XS_BYTES + 16384)      \
+        if ((I) == 0 && (MB > 1 || wave < 4)) CV_DMA(xo0, lds0 + (BUF) * XS_BYTES + wave_lds)     \
+        if ((I) == 1 && MB == 4) CV_DMA(xo1, lds0 + (BUF) * XS_BYTES + 8192 + wave_lds)           \
+        if ((I) == 2 && MB == 4 && wave == 0 && lane < 16) CV_DMA(xo2, lds0 + (BUF) * XS_BYTES + BM * 128) \
+        if ((I) == 2 && (MB == 2 || (MB == 1 && wave < 4))) CV_DMA2(xo2, lds0 + (BUF) * XS_BYTES + BM * 128) \
     }
 #define CV_LOAD_W(SET, KW) wr[SET][KW] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv[KW], w_soff, 0);
 #define CV_READ1(DST, J, BUF, KW)                                                                 \
@@ -169,11 +186,12 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     // weights of the stage two ahead start their way into slab / set (B + 2) % 3, which the stage
     // before this one used last; the loads are spread over the stage, one after every other
     // MFMA.  Before the barrier that ends the stage every wavefront waits until its own share of
-    // the next stage's slab has landed: everything but the five (wavefront 0: six) loads issued
-    // during this stage, or simply everything when the stage issued none.
+    // the next stage's slab has landed: everything but the loads issued during this stage (three and CV_XL for the
+    // slab; wavefront 0 of 130 rows has one more), or simply everything when the stage issued none.
+    constexpr int CV_XL = 2;
 #define CV_F __builtin_amdgcn_sched_barrier(0);
 #define CV_STAGE(B, FETCH)                                                                        \
-    {                                                                                             \
+    if constexpr (MB == 4) {                                                                      \
         constexpr int N_ = ((B) + 2) % 3;                                                         \
         CV_READ1(xa, 0, B, 0) CV_READ1(xa, 1, B, 0) CV_READ1(xa, 2, B, 0) CV_READ1(xa, 3, B, 0)   \
         CV_READ1(xb, 0, B, 1) CV_F                                                                \
@@ -189,14 +207,26 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         CV_MMA1(xa, 1, B, 2) CV_F                                                                 \
         CV_MMA1(xa, 2, B, 2) CV_F                                                                 \
         CV_MMA1(xa, 3, B, 2) CV_F                                                                 \
-        if (FETCH) { CV_FETCH_NEXT CV_VMCNT(5) } else { CV_VMCNT(0) }                             \
+        if (FETCH) { CV_FETCH_NEXT CV_VMCNT(3 + CV_XL) } else { CV_VMCNT(0) }                     \
+        __syncthreads();                                                                          \
+    } else {                                                                                      \
+        constexpr int N_ = ((B) + 2) % 3, T_ = MB - 1;                                            \
+        CV_READ1(xa, 0, B, 0) if (MB == 2) CV_READ1(xa, T_, B, 0)                                 \
+        CV_READ1(xb, 0, B, 1) if (MB == 2) CV_READ1(xb, T_, B, 1)                                 \
+        CV_READ1(xc, 0, B, 2) if (MB == 2) CV_READ1(xc, T_, B, 2) CV_F                            \
+        CV_MMA1(xa, 0, B, 0) CV_F if (FETCH) CV_LOAD_W(N_, 0) CV_F                                \
+        if (MB == 2) CV_MMA1(xa, T_, B, 0) CV_F if (FETCH) CV_LOAD_W(N_, 1) CV_F                  \
+        CV_MMA1(xb, 0, B, 1) CV_F if (FETCH) CV_LOAD_W(N_, 2) CV_F                                \
+        if (MB == 2) CV_MMA1(xb, T_, B, 1) CV_F if (FETCH) CV_LOAD_X1(N_, 0) CV_F                 \
+        CV_MMA1(xc, 0, B, 2) CV_F if (FETCH) CV_LOAD_X1(N_, 2) CV_F                               \
+        if (MB == 2) CV_MMA1(xc, T_, B, 2) CV_F                                                   \
+        if (FETCH) { CV_FETCH_NEXT CV_VMCNT(3 + CV_XL) } else { CV_VMCNT(0) }                     \
         __syncthreads();                                                                          \
     }
 
-    bf16x8 xa[4], xb[4];
+    bf16x8 xa[MB], xb[MB], xc[MB];
     {
-        // (activations first: the barrier waits for those of the first stage alone, everything but the eight or nine
-        //  loads behind them)
+        // (activations first: the barrier waits for those of the first stage alone, everything but the loads behind them)
         CV_LOAD_X1(0, 0) CV_LOAD_X1(0, 1) CV_LOAD_X1(0, 2)
         CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2)
         CV_FETCH_NEXT
@@ -204,7 +234,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2)
         CV_FETCH_NEXT
         CV_F
-        CV_VMCNT(8)
+        CV_VMCNT(6 + CV_XL)
         __syncthreads();
     }
     // the number of stages is a multiple of three (three kernel rows): three stages per trip make
@@ -220,16 +250,17 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     // The last stage takes one accumulator tile behind the other, the tiles of other owners first, so that a finished tile is on its way
     // to LDS while the next one's MFMAs run.  (With the order of the first loads and the transposing reads below, launches before -> now: 90 x 160
     // cells, 256 -> 128 -> 128 13.2 -> 12.6, 9.6 -> 9.0, 9.6 -> 8.6 us; 60 x 107 11.6 -> 10.8, 8.05 -> 7.1.)
-    // (red: [owner j][wn][slot - 1][4 register groups][64 lanes][4], slot = source's K group ^ j)
-    float* red = (float*)(smem_raw + CV_SLABS_BYTES) + wn * 3072 + lane * 4;
-#define CV_HAND(S, RQ0, RQ1)                                                                      \
+    // (red: [owner's K group][wn][part - 1][NR / 4 register groups][64 lanes][4])
+    float* red = (float*)(smem_raw + ConvLds<MB>::SLABS) + wn * 3 * NR * 64 + lane * 4;
+    // register groups Q0 .. Q1 - 1 of part S: those from Q of acc[J] on
+#define CV_HAND(S, Q0, Q1)                                                                        \
     {                                                                                             \
-        float* dst_ = red + ((S) ^ kgrp) * 6144 + ((S) - 1) * 1024;                               \
-        _Pragma("unroll") for (int rq = RQ0; rq < RQ1; ++rq)                                      \
-            *(f32x4*)(dst_ + rq * 256) = f32x4{acc[S][rq * 4], acc[S][rq * 4 + 1], acc[S][rq * 4 + 2], acc[S][rq * 4 + 3]}; \
+        constexpr int J_ = (S) % MB, Q_ = (S) / MB * MB;                                          \
+        float* dst_ = red + ((S) ^ kgrp) * 6 * NR * 64 + ((S) - 1) * NR * 64;                     \
+        _Pragma("unroll") for (int q = Q0; q < Q1; ++q)                                           \
+            *(f32x4*)(dst_ + q * 256) = f32x4{acc[J_][(Q_ + q) * 4], acc[J_][(Q_ + q) * 4 + 1], acc[J_][(Q_ + q) * 4 + 2], acc[J_][(Q_ + q) * 4 + 3]}; \
     }
-    {
-        bf16x8 xc[4];
+    if constexpr (MB == 4) {
         CV_READ1(xa, 1, 2, 0) CV_READ1(xb, 1, 2, 1) CV_READ1(xc, 1, 2, 2) CV_READ1(xa, 2, 2, 0) CV_READ1(xb, 2, 2, 1) CV_READ1(xc, 2, 2, 2) CV_F
         CV_MMA1(xa, 1, 2, 0) CV_F CV_READ1(xa, 3, 2, 0) CV_F
         CV_MMA1(xb, 1, 2, 1) CV_F CV_READ1(xb, 3, 2, 1) CV_F
@@ -248,6 +279,26 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         CV_MMA1(xb, 0, 2, 1) CV_F
         CV_MMA1(xc, 0, 2, 2) CV_F
         CV_HAND(3, 0, 4)
+    } else if constexpr (MB == 2) {
+        // (parts 1 and 3 are halves of acc[1], part 2 the other half of acc[0])
+        CV_READ1(xa, 1, 2, 0) CV_READ1(xb, 1, 2, 1) CV_READ1(xc, 1, 2, 2) CV_READ1(xa, 0, 2, 0) CV_READ1(xb, 0, 2, 1) CV_READ1(xc, 0, 2, 2) CV_F
+        CV_MMA1(xa, 1, 2, 0) CV_F
+        CV_MMA1(xb, 1, 2, 1) CV_F
+        CV_MMA1(xc, 1, 2, 2) CV_F
+        CV_MMA1(xa, 0, 2, 0) CV_F
+        CV_HAND(1, 0, 2) CV_F
+        CV_MMA1(xb, 0, 2, 1) CV_F
+        CV_HAND(3, 0, 2) CV_F
+        CV_MMA1(xc, 0, 2, 2) CV_F
+        CV_HAND(2, 0, 2)
+    } else {
+        CV_READ1(xa, 0, 2, 0) CV_READ1(xb, 0, 2, 1) CV_READ1(xc, 0, 2, 2) CV_F
+        CV_MMA1(xa, 0, 2, 0)
+        CV_MMA1(xb, 0, 2, 1)
+        CV_MMA1(xc, 0, 2, 2)
+        CV_HAND(1, 0, 1)
+        CV_HAND(2, 0, 1)
+        CV_HAND(3, 0, 1)
     }
 #undef CV_HAND
 #undef CV_STAGE
@@ -255,6 +306,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 #undef CV_LOAD_X1
 #undef CV_LOAD_W
 #undef CV_DMA
+#undef CV_DMA2
 #undef CV_READ1
 #undef CV_MMA1
 #undef CV_VMCNT
@@ -263,56 +315,60 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     // ---- what the epilogue needs from memory, on its way while the partial sums are exchanged (asked for behind the
     //      exchange, it cost every launch a memory latency of its own; with the divisions of block and cell indexes as
     //      products, 8-step key frame at 90 x 160 cells 656 -> 638 us, forward at 60 x 107 27.4 -> 26.4)
-    const int p = kgrp * 32 + l32, mp = m0 + p;         // this lane's position behind the exchange
+    const int p = (kgrp & (MB - 1)) * 32 + l32, mp = m0 + p;         // this lane's position behind the exchange
     const ConvCell cell = conv_cell(a, mp, m_end);
     const bool inside = cell.inside;
-    f32x4 bias[EPI == 0 || EPI == 2 ? 4 : 1];
-    bf16x4 mk[EPI == 1 ? 4 : 1];
+    const int c_own = wn * 32 + row_x + lhi * 4;                     // and its channels: + 8 rg .. + 3, rg < MB
+    f32x4 bias[EPI == 0 || EPI == 2 ? MB : 1];
+    bf16x4 mk[EPI == 1 ? MB : 1];
     u32x4 w3f[EPI == 2 ? 4 : 1];
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-        const int c = n0 + wn * 32 + rg * 8 + lhi * 4;
+    for (int rg = 0; rg < MB; ++rg) {
+        const int c = n0 + c_own + rg * 8;
         if (EPI == 0 || EPI == 2) bias[rg] = *(const f32x4*)(a.bias + grp * a.bias_stride + c);
         if (EPI == 1) mk[rg] = *(const bf16x4*)(a.mask + (size_t)min(mp, m_end - 1) * a.cout + c);
-        // (classifier fragments: A operand, rows = classes, k = 16 channels of this tile)
-        if (EPI == 2) w3f[rg] = *(const u32x4*)(a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + n0 + lhi * 8 + rg * 16);
     }
+    // (classifier fragments: A operand, rows = classes, k = 16 channels of this tile)
+    if (EPI == 2)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            w3f[ks] = *(const u32x4*)(a.W3q + grp * a.w3_stride + (size_t)min(l32, a.n_cls - 1) * a.cout + n0 + lhi * 8 + ks * 16);
 
-    // ---- exchange of the partial sums: accumulator tile j of every wavefront has gone to the
-    //      wavefront (wn, kgrp = j), which adds the four partials in ascending source order
+    // ---- exchange of the partial sums: each part has gone to its owner, which adds the four in ascending source order
     __syncthreads();
-    f32x16 mine = acc[0];
+    float mine[NR];
     {
-        f32x16 sum;
+        // the parts of the three other K groups, in ascending order
+        const float* from = red + kgrp * 6 * NR * 64;
+        f32x4 part[3][MB];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            f32x16 term;
-            if (k == kgrp) term = mine;
-            else {
-                const float* srcp = red + kgrp * 6144 + ((k ^ kgrp) - 1) * 1024;
+        for (int i = 0; i < 3; ++i) {
+            const int k = i + (i >= kgrp ? 1 : 0);
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const f32x4 v = *(const f32x4*)(srcp + rq * 256);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) term[rq * 4 + e] = v[e];
-                }
-            }
-            if (k == 0) sum = term;
-            else
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sum[r] += term[r];
+            for (int q = 0; q < MB; ++q) part[i][q] = *(const f32x4*)(from + ((k ^ kgrp) - 1) * NR * 64 + q * 256);
         }
-        mine = sum;
+#define CV_PART(I) part[I][r >> 2][r & 3]
+        if (kgrp < 2) {         // (first or second: the same sum)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) mine[r] = ((CV_PART(0) + acc[0][r]) + CV_PART(1)) + CV_PART(2);
+        } else if (kgrp == 2) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) mine[r] = ((CV_PART(0) + CV_PART(1)) + acc[0][r]) + CV_PART(2);
+        } else {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) mine[r] = ((CV_PART(0) + CV_PART(1)) + CV_PART(2)) + acc[0][r];
+        }
+#undef CV_PART
     }
 
     if (EPI == 3) {
-        // a lane holds 16 channels of one position; for a fixed channel the 32 lanes of a half
+        // a lane holds NR channels of one position; for a fixed channel the 32 lanes of a half
         // wavefront are 32 consecutive positions, i.e. (inside one grid row) consecutive floats
         if (inside) {
             float* dst = a.dense + ((size_t)cell.img * a.dense_c * a.h + (cell.y - 1)) * a.w + (cell.x - 1);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ch = n0 + wn * 32 + (r >> 2) * 8 + lhi * 4 + (r & 3);
+            for (int r = 0; r < NR; ++r) {
+                const int ch = n0 + c_own + (r >> 2) * 8 + (r & 3);
                 if (ch < a.dense_c) dst[(size_t)ch * a.h * a.w] = mine[r];
             }
         }
@@ -321,10 +377,9 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
 
     // ---- epilogue: bias + ReLU (forward) or ReLU mask (data-gradient), zero outside the grid,
     //      round to bfloat16, stage the tile in LDS as [position][channel]
-    bf16* Os = (bf16*)smem_raw;     // [CV_BM][CV_OLD], where the slabs were
+    bf16* Os = (bf16*)smem_raw;     // [BM][CV_OLD], where the slabs were
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-        const int c = wn * 32 + rg * 8 + lhi * 4;   // channel inside the tile
+    for (int rg = 0; rg < MB; ++rg) {
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -333,10 +388,10 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
             else v = fmaxf(v + bias[rg][e], 0.f);
             o[e] = (bf16)(inside ? v : 0.f);
         }
-        *(bf16x4*)(Os + p * CV_OLD + c) = o;
+        *(bf16x4*)(Os + p * CV_OLD + c_own + rg * 8) = o;
     }
     __syncthreads();
-    if (EPI == 2 && wave < 4) {
+    if (EPI == 2 && wave < MB) {
         // D[class][position] for positions 32 wave .. +31 over the tile's 64 channels
         f32x16 zacc;
 #pragma unroll
@@ -359,7 +414,8 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     }
     if (a.Y) {
         // position-major: 16 bytes = 8 channels of one position
-        for (int q = tid; q < CV_BM * (CV_BN / 8); q += NT) {
+#pragma unroll
+        for (int q = tid; q < BM * (CV_BN / 8); q += NT) {
             const int p = q / (CV_BN / 8), part = q % (CV_BN / 8);
             if (m0 + p < m_end)
                 *(uint4*)(a.Y + (size_t)(m0 + p) * a.cout + n0 + part * 8) = *(const uint4*)(Os + p * CV_OLD + part * 8);
@@ -370,8 +426,8 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         // channels, through the transposing LDS read: in a group of 16 lanes, lane r names (position r / 4,
         // channels 4 (r % 4) .. + 3) and lane i receives channel i of four consecutive positions
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int u = wave + 8 * k, pg = (u >> 1) * 2 + lhi, c = (u & 1) * 32;
+        for (int u = wave; u < 4 * MB; u += 8) {
+            const int pg = (u >> 1) * 2 + lhi, c = (u & 1) * 32;
             const bf16* row = Os + (pg * 8 + ((lane & 15) >> 2)) * CV_OLD + c + (lane & 16) + 4 * (lane & 3);
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * CV_OLD));
@@ -403,24 +459,30 @@ void conv3x3_mfma(Ctx& c, const char* name, const Plan& p, const bf16* X, const 
     a.wq_stride = (size_t)cin * cout * 9;
     a.bias_stride = p.head_stride;
     a.w3_stride = (size_t)g.C * cout;
-    if (conv_tile(g, cin, cout).bn != CV_BN) { conv3x3_wide(c, name, a, epi, g.heads()); return; }
-    a.grp_tiles = cdiv(a.grp_pp, CV_BM);
+    const ConvTile t = conv_tile(g, cin, cout);
+    if (t.bn != CV_BN) { conv3x3_wide(c, name, a, epi, g.heads()); return; }
+    a.grp_tiles = cdiv(a.grp_pp, t.bm);
     a.m_tiles = g.heads() * a.grp_tiles;
     a.n_tiles = cout / CV_BN;
     a.by_n_tiles = fast_div(a.n_tiles); a.by_grp_tiles = fast_div(a.grp_tiles);
     const int tiles = a.m_tiles * a.n_tiles;
     a.tiles_per_xcd = cdiv(tiles, 8);
     const dim3 grid(a.tiles_per_xcd * 8);
-    const size_t smem = CV_SMEM_BYTES;
     // tag 1: layer-1 forward, 2: layer-2 forward, 3: layer-2 data-gradient, 4: layer-1 data-gradient
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel, size_t smem) {
         ensure_dynamic_lds((const void*)kernel, smem);
         ST_LAUNCH(c, name, kernel, grid, dim3(512), smem, a);
     };
-    if (epi == 3) go(k_conv3x3_mfma<3, 4>);
-    else if (epi == 1) go(k_conv3x3_mfma<1, 3>);
-    else if (epi == 2) go(k_conv3x3_mfma<2, 2>);
-    else go(k_conv3x3_mfma<0, 1>);
+    auto tiles_of = [&](auto mb) {
+        constexpr int MB = decltype(mb)::value;
+        if (epi == 3) go(k_conv3x3_mfma<3, 4, MB>, ConvLds<MB>::BYTES);
+        else if (epi == 1) go(k_conv3x3_mfma<1, 3, MB>, ConvLds<MB>::BYTES);
+        else if (epi == 2) go(k_conv3x3_mfma<2, 2, MB>, ConvLds<MB>::BYTES);
+        else go(k_conv3x3_mfma<0, 1, MB>, ConvLds<MB>::BYTES);
+    };
+    if (t.bm == 128) tiles_of(std::integral_constant<int, 4>{});
+    else if (t.bm == 64) tiles_of(std::integral_constant<int, 2>{});
+    else tiles_of(std::integral_constant<int, 1>{});
 }
 
 }  // namespace st

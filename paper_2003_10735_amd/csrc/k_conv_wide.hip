@@ -379,6 +379,15 @@ ConvTile conv_tile(const Geo& g, int cin, int cout)
         const float t = cdiv(blocks, 256) * (s.block + s.per64 * (cin / 64)) + s.launch;
         if (&s == shapes || t < best_t) { best = s.t; best_t = t; }
     }
+    // Small tiles on a chip they do not fill: quarter and half tiles, as long as each finds a compute unit of its own.  A block fetches its
+    // channels' weights whatever its positions, so its time falls less than its work, but what a stage multiplies, the exchange and
+    // the epilogue go with the positions; a second round would cost more than that saves.  us a launch, layer 1 / layer 2 with the classifier,
+    // and what 128 positions take: 16 x 24 cells, 64 -> 64 -> 64 (tiles of 32) 3.9 / 4.2, were 5.2 / 5.3; 30 x 53, 256 -> 128 -> 128 (32)
+    // 6.6 / 5.1, were 9.5 / 6.6; 60 x 107, 64 -> 64 -> 64 (32) 4.2 / 4.6, were 5.7 / 5.8; 60 x 107, 256 -> 128 -> 128 (64) 8.6 / 6.0, were
+    // 10.1 / 6.8.
+    if (best.bn == 64)
+        for (int bm : {32, 64})
+            if (g.heads() * cdiv(g.padded_positions() / g.heads(), bm) * cdiv(cout, 64) <= 256) { best.bm = bm; break; }
     return best;
 }
 

@@ -42,7 +42,7 @@ __device__ __forceinline__ ConvCell conv_cell(const ConvArgs& a, int mp, int m_e
     return c;
 }
 
-// Positions x channels of a block's tile: 64 channels name the kernel of k_conv_mfma.hip, 128 that of k_conv_wide.hip.
+// Positions x channels of a block's tile: 64 channels name the kernel of k_conv_mfma.hip (32, 64 or 128 positions), 128 that of k_conv_wide.hip.
 struct ConvTile { int bm, bn; };
 ConvTile conv_tile(const Geo& g, int cin, int cout);
 void conv3x3_wide(Ctx& c, const char* name, ConvArgs a, int epi, int heads);

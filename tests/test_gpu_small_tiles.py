@@ -1,0 +1,37 @@
+"""Half and quarter tiles of the bfloat16 convolutions: a frame alone, whose layers run on tiles of 32 or 64 positions, gives bit for bit
+what it gives in a batch of eight copies, whose layers run on tiles of 128 positions or the wide ones -- logits, and the gradient of
+the features, whose eighth (one pixel count for all frames) is exact."""
+import pytest
+
+import paper_2003_10735_amd as st
+
+pytestmark = pytest.mark.gpu
+
+
+# heads whose layers alone run tiles of 32 positions, of 64, and of both; one and a few tiles, ends inside a tile, padded channels
+@pytest.mark.parametrize("h,w,c_in,c1,c2,C", [(1, 1, 64, 64, 64, 3), (2, 6, 64, 128, 64, 9), (2, 7, 128, 64, 128, 12), (6, 22, 192, 64, 64, 19),
+                                              (16, 24, 64, 64, 64, 32), (30, 53, 256, 128, 128, 19), (45, 80, 256, 128, 128, 5),
+                                              (60, 107, 96, 128, 128, 9), (68, 118, 64, 64, 128, 21)])
+def test_a_frame_alone_is_a_frame_of_a_batch(h, w, c_in, c1, c2, C):
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(h * 1000 + w)
+    f = torch.randn((1, c_in, h, w), generator=gen, device="cuda").clamp(min=0).bfloat16()
+    lab = torch.randint(0, C, (1, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
+    params = torch.cat([torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5
+                        for r, k in ((c1, 9 * c_in), (1, c1), (c2, 9 * c1), (1, c2), (C, c2), (1, C))])
+    out = []
+    for n in (1, 8):
+        d = st.HeadDesc(n, c_in, h, w, c1, c2, C, feat_dtype=st.ST_BF16, compute=st.ST_COMPUTE_BF16)
+        ws = torch.zeros(st.st_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+        fs, ls = f.repeat(n, 1, 1, 1), lab.repeat(n, 1, 1)
+        z = torch.empty((n, C, h, w), device="cuda")
+        st.st_head_forward(d, fs, params, logits_lowres=z, workspace=ws)
+        grad = torch.zeros((n, c_in, h, w), device="cuda")
+        st.st_partial_distill(d, fs, ls, params.clone(), 1, 0.0, workspace=ws, feature_grad=grad)
+        torch.cuda.synchronize()
+        out.append((z, grad * n))
+    assert out[0][1].abs().max() > 0
+    for alone, batch in zip(*out):
+        for k in range(8):
+            assert torch.equal(alone[0], batch[k])
