@@ -19,34 +19,21 @@ void ZeroList::add(void* p, size_t bytes, int count, size_t stride_bytes)
 }
 
 // One vector out of the workspace: for the calls with loop exits, where the host decides what is handed back, and for
-// vectors of the caller that overlap (their order counts); else this rides on the last launch of a call.  Thread j walks the internal index; inside a 3x3 weight block
-//   internal (o*9 + tap)*ci + i   <->   external (o*ci + i)*9 + tap.
+// vectors of the caller that overlap (their order counts); else this rides on the last launch of a call.  Thread x walks the
+// caller's index (internal_index), so that the scattered side is the reads.
 __global__ void __launch_bounds__(256)
 k_permute_params(const float* __restrict__ src, float* __restrict__ dst, ParamOffsets po,
-                 int ci1, int ci2, size_t head_stride)
+                 FastDiv by_in1, FastDiv by_in2, size_t head_stride)
 {
-    const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= po.total) return;
+    const unsigned x = blockIdx.x * 256 + threadIdx.x;
     // one head per blockIdx.y: internal blocks head_stride floats apart, external ones back to back
-    src += blockIdx.y * head_stride;
-    dst += blockIdx.y * po.total;
-    size_t e = j;
-    if (j < po.b1) {
-        const size_t r = j - po.W1;
-        const size_t i = r % ci1, tap = (r / ci1) % 9, o = r / ((size_t)ci1 * 9);
-        e = po.W1 + (o * ci1 + i) * 9 + tap;
-    } else if (j >= po.W2 && j < po.b2) {
-        const size_t r = j - po.W2;
-        const size_t i = r % ci2, tap = (r / ci2) % 9, o = r / ((size_t)ci2 * 9);
-        e = po.W2 + (o * ci2 + i) * 9 + tap;
-    }
-    dst[e] = src[j];
+    if (x < po.total) dst[blockIdx.y * po.total + x] = src[blockIdx.y * head_stride + internal_index(po, by_in1, by_in2, x)];
 }
 
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst)
 {
     ST_LAUNCH(c, "params_from_internal", k_permute_params, dim3(cdiv(p.po.total, 256), p.g.heads()), dim3(256), 0, src, dst,
-              p.po, p.g.c_in, p.g.c1, p.head_stride);
+              p.po, fast_div(p.g.c_in), fast_div(p.g.c1), p.head_stride);
 }
 
 }  // namespace st

@@ -71,8 +71,7 @@ __device__ __forceinline__ Weight3x3 weight3x3(unsigned r, unsigned cin)
 constexpr int PAD_PER_THREAD = 4;     // runs of the padding role per thread
 
 // index in the caller's vector (3x3 weights OIHW) of the internal parameter j ([o][kh][kw][i])
-template <class A>
-__device__ __forceinline__ unsigned external_index(const A& a, unsigned j)
+__device__ __forceinline__ unsigned external_index(const UpdateArgs& a, unsigned j)
 {
     if (j < (unsigned)a.po.b1) {
         const Weight3x3 k = weight3x3(j, a.c_in);
@@ -381,10 +380,13 @@ __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 // (Optimiser state once took a launch per vector and direction: four of 5.2 us in an Adam call at 90 x 160 cells,
 //  256 -> 128 -> 128 channels.  Riding here and on the opening launch they cost 3 us together: such a call 728 -> 710 us, one with momentum at
 //  135 x 240 cells 1268 -> 1251.)
+// A thread takes a parameter of the caller's order, so that whole lines are written and the scattered side is reads (a block's 256 are
+// nine rows of 28, which the caches hold).  The other way round every line was written in nine parts, six times the bytes: the launch 8.0 us
+// and now 7.0 at 135 x 240 cells with momentum, 9.6 and now 8.7 with Adam's two moments at 90 x 160.
 struct HandBack {
     int nb_finish, nb_out;
     const float* src[3]; float* dst[3];
-    ParamOffsets po; int c_in, c1;
+    ParamOffsets po; FastDiv by_in1, by_in2;      // (channels of a row of W1, of W2)
     size_t hs_param, hs_ext;     // several heads: floats from one head's vector to the next
 };
 
@@ -396,10 +398,10 @@ __global__ void __launch_bounds__(256) k_finish_pass(HandBack a, FinishArgs f)
         return;
     }
     const int b = blockIdx.x - a.nb_finish, v = b / a.nb_out;
-    const unsigned j = (unsigned)(b - v * a.nb_out) * 256 + threadIdx.x;
+    const unsigned x = (unsigned)(b - v * a.nb_out) * 256 + threadIdx.x;
     const float* src = (v == 0 ? a.src[0] : v == 1 ? a.src[1] : a.src[2]) + blockIdx.y * a.hs_param;
     float* dst = (v == 0 ? a.dst[0] : v == 1 ? a.dst[1] : a.dst[2]) + blockIdx.y * a.hs_ext;
-    if (j < a.po.total) dst[external_index(a, j)] = src[j];
+    if (x < a.po.total) dst[x] = src[internal_index(a.po, a.by_in1, a.by_in2, x)];
 }
 
 // Zeros for the padding of the operand copies: channels beyond the caller's counts, of which the parameter role writes
@@ -680,7 +682,7 @@ void finish_pass(Ctx& c, const Plan& p, char* ws, float* loss_out, double* miou_
     int vectors = 0;
     if (ext_out) {
         a.nb_out = cdiv(p.po.total, 256);
-        a.po = p.po; a.c_in = p.g.c_in; a.c1 = p.g.c1;
+        a.po = p.po; a.by_in1 = fast_div(p.g.c_in); a.by_in2 = fast_div(p.g.c1);
         a.hs_param = p.head_stride; a.hs_ext = p.po.total;
         const size_t from[3] = {p.theta, p.vel, p.vel2};
         float* const to[3] = {ext_out, out_vel, out_vel2};

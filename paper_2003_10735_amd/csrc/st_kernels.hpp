@@ -31,6 +31,18 @@ __device__ __forceinline__ void zero_block(const ZeroList& z, int block)
         if (i < z.n16[r]) p[i] = make_uint4(0, 0, 0, 0);
     }
 }
+// Where the parameter x of the caller's vector lies in the internal one (by_in1, by_in2: c_in and c1 as divisors): inside a 3x3 weight block
+//   internal (o*9 + tap)*ci + i   <->   external (o*ci + i)*9 + tap.
+__device__ __forceinline__ unsigned internal_index(const ParamOffsets& po, FastDiv by_in1, FastDiv by_in2, unsigned x)
+{
+    const bool one = x < (unsigned)po.b1;
+    if (!one && !(x >= (unsigned)po.W2 && x < (unsigned)po.b2)) return x;
+    const unsigned base = one ? 0u : (unsigned)po.W2;
+    const FastDiv by_in = one ? by_in1 : by_in2;
+    const unsigned oi = (x - base) / 9u, tap = x - base - oi * 9u;
+    const unsigned o = (unsigned)fast_quot((int)oi, by_in), i = oi - o * by_in.d;
+    return base + (o * 9u + tap) * by_in.d + i;
+}
 void permute_params(Ctx& c, const Plan& p, const float* src, float* dst);
 
 // what the weight gradients of the 3x3 layers run on (float32: split operands, or the float32 instruction)
