@@ -381,8 +381,8 @@ __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 //  256 -> 128 -> 128 channels.  Riding here and on the opening launch they cost 3 us together: such a call 728 -> 710 us, one with momentum at
 //  135 x 240 cells 1268 -> 1251.)
 // A thread takes a parameter of the caller's order, so that whole lines are written and the scattered side is reads (a block's 256 are
-// nine rows of 28, which the caches hold).  The other way round every line was written in nine parts, six times the bytes: the launch 8.0 us
-// and now 7.0 at 135 x 240 cells with momentum, 9.6 and now 8.7 with Adam's two moments at 90 x 160.
+// nine rows of 28, which the caches hold).  The other way round every line was written in nine parts (10.9 MiB counted at 256 -> 128 -> 128
+// channels, 8.5 now): the launch 8.0 us and now 7.0 at 135 x 240 cells with momentum, 9.6 and now 8.7 with Adam's two moments at 90 x 160.
 struct HandBack {
     int nb_finish, nb_out;
     const float* src[3]; float* dst[3];
@@ -719,8 +719,8 @@ constexpr int MIOU_THREADS = 1024;
 
 // Mean IoU (Eq. 1) of a C x C table of counts, any C up to 256: 16 lanes per class add
 // that class's row and column (exact integer sums), then a single thread adds the per-class
-// ratios of the classes that occur as a label in ascending order in float64 and divides by
-// their number; 0 when there is none.  A table of up to 64 classes is fetched once, by all threads, into LDS.
+// ratios of the classes that occur as a label in ascending order in float64 (eight read at a time: read one by one they are a
+// chain of LDS latencies) and divides by their number; 0 when there is none.  A table of up to 64 classes is fetched once, by all threads, into LDS.
 __global__ void __launch_bounds__(MIOU_THREADS)
 k_miou_from_counts(const unsigned long long* __restrict__ conf, int C, double* __restrict__ out)
 {
@@ -752,8 +752,15 @@ k_miou_from_counts(const unsigned long long* __restrict__ conf, int C, double* _
     if (threadIdx.x == 0) {
         double sum = 0.0;
         int cnt = 0;
-        for (int c = 0; c < C; ++c)
-            if (present[c]) { sum += iou[c]; ++cnt; }
+        for (int c0 = 0; c0 < C; c0 += 8) {
+            double t[8];
+            int p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { t[e] = iou[min(c0 + e, C - 1)]; p[e] = present[min(c0 + e, C - 1)]; }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c0 + e < C) { sum += t[e]; cnt += p[e]; }      // (a class that does not occur adds zero)
+        }
         *out = cnt ? sum / cnt : 0.0;
     }
 }
