@@ -49,9 +49,13 @@ struct WgradArgs {
     int o_tiles, i_tiles, splits, items_per_xcd;
     FastDiv by_tiles, by_splits, by_o_tiles, by_row;      // (o_tiles * i_tiles; splits; o_tiles; Wp / 8)
     // Several heads: head k owns the positions from 8-position group k * head_groups8 on and
-    // writes its partial copies head_out_stride floats after head k - 1.  (With an odd number of rows a head's last
-    // pair reaches into the next frame's first row, or the guard: dY is zero there.)
+    // writes its partial copies head_out_stride floats after head k - 1.
     int heads, head_groups8;
+    // Groups from a head's first to the end of the one row behind its last: a border row of the next frame, or guard columns, zeros
+    // either way.  Nothing behind it is an operand: with an odd number of rows the last pair reaches two rows further with
+    // its X fragments, and there zeros are read.  (dY being zero in that pair's lower row is not enough: the rows behind
+    // are the next client's, and zero times an infinity or a NaN of that client's is a NaN.)
+    int end_groups;
     size_t head_out_stride;
 };
 
@@ -108,9 +112,9 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     const int pair0 = fast_quot(unit0, a.by_row);
     int col = unit0 - pair0 * row_groups;                      // column group of the next unit to load
     const int first = pair0 * 2 * row_groups + col, before = first - (col ? 1 : row_groups + 1);    // groups of unit0 and unit0 - 1
-    // (a descriptor ends with its channel block, whose head and tail are zeroed guard columns)
+    // (a descriptor ends at end_groups.  No load whose value is used has a scalar offset behind that end.)
     auto operand = [&](const bf16* base, int block, int group) __attribute__((always_inline)) {
-        const long long left = ((long long)NG - (g0 + group)) * 512;
+        const long long left = ((long long)a.end_groups - group) * 512;
         return __builtin_amdgcn_make_buffer_rsrc((void*)(base + (((ptrdiff_t)block * NG + g0 + group) << 8)), 0,
                                                  (int)(unsigned)(left < 0xFFFFFFFFll ? left : 0xFFFFFFFFll), 0x00020000);
     };
@@ -204,8 +208,8 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
         // unit0 - 1 (guard columns make it readable) supplies the first left neighbours and
         // unit1 the last right neighbours
         // (all loads are unconditional: a load under a branch would force the compiler to wait for every outstanding load
-        //  at the join; past the end of the range the slots hold what follows there, or zeros behind the channel block:
-        //  finite and unused)
+        //  at the join; past the end of the range the slots hold what follows there, or zeros behind the head's end: no
+        //  product takes them)
         WG_LOAD_Y(DEPTH - 1, 0)
 #pragma unroll
         for (int d = 0; d < DEPTH - 1; ++d) {
@@ -306,6 +310,7 @@ static WgradArgs wgrad_args(const Plan& p, const bf16* dYT, const bf16* XT, floa
     const int rows = p.g.n * p.g.Hp / a.heads;
     a.n_units = (rows + 1) / 2 * (p.g.Wp / 8);
     a.head_groups8 = p.g.Hp * p.g.Wp / 8;
+    a.end_groups = (rows + 1) * (p.g.Wp / 8);
     a.head_out_stride = p.grad_stride * p.grad_copies;
     a.units_per_wave = cdiv(a.n_units, splits * 4);
     a.o_tiles = cdiv(cout, 32); a.i_tiles = cdiv(cin, 32);
