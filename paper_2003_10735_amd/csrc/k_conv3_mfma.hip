@@ -104,8 +104,9 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
 #pragma unroll
     for (int k = 0; k < A2_CHUNKS; ++k) {
         const int q = tid + NT * k, p = q / (C2 / 8), part8 = q - p * (C2 / 8);
-        // (rows past the last position repeat it: d loss / d z is zero there)
-        a2v[k] = *(const u32x4*)(a2 + (size_t)min(m0 + p, PP - 1) * k2 + ch0 + part8 * 8);
+        // (Rows past this head's last position repeat it, a border cell: zeros.  That d loss / d z is zero in those rows would not do:
+        //  with several heads they are the next client's, and zero times an infinity of its activations is a NaN.)
+        a2v[k] = *(const u32x4*)(a2 + (size_t)min(m0 + p, m_end - 1) * k2 + ch0 + part8 * 8);
     }
     // W3^T fragments of this wavefront's da2 tiles: rows = channels, k = 16 classes per step
     // (the dW3 wavefronts load them too: a load under a branch would be waited for at the join)

@@ -1,4 +1,4 @@
-"""Clients of a grouped call are apart: whatever one client's features hold, infinities and NaN included, every
+"""Clients of a grouped call are apart: whatever one client's features or head hold, infinities and NaN included, every
 other client's head, optimiser state, losses, metric and class map are bit for bit what they are beside a finite neighbour."""
 import pytest
 
@@ -12,7 +12,7 @@ SHAPES = [(3, 9, 35, 64, 64, 64), (3, 3, 5, 64, 128, 64), (3, 13, 31, 64, 64, 12
           (2, 5, 300, 64, 64, 64)]
 
 
-@pytest.mark.parametrize("what", ["first row of features", "all features"])
+@pytest.mark.parametrize("what", ["first row of features", "all features", "first layer", "second layer"])
 @pytest.mark.parametrize("n,h,w,c_in,c1,c2", SHAPES)
 def test_a_client_does_not_reach_another(n, h, w, c_in, c1, c2, what):
     import torch
@@ -28,7 +28,11 @@ def test_a_client_does_not_reach_another(n, h, w, c_in, c1, c2, what):
     def run(bad):
         fs, ps, vel = f.clone(), heads.clone(), torch.zeros_like(heads)
         if bad is not None:
-            if what == "all features":
+            if what == "first layer":      # (some of its activations, of the size of 1, run to infinity)
+                ps[bad, :c1 * c_in * 9] *= 2e38
+            elif what == "second layer":
+                ps[bad, c1 * c_in * 9 + c1:c1 * c_in * 9 + c1 + c2 * c1 * 9] *= 2e38
+            elif what == "all features":
                 fs[bad] = float("nan")
             else:
                 fs[bad, :, 0] = float("inf")
