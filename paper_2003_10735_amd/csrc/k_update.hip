@@ -246,13 +246,16 @@ __device__ __forceinline__ V add_copies(V acc, const float* gp, size_t stride, i
         if (s0 + e < splits) acc = s0 + e ? acc + v[e] : v[e];
     return acc;
 }
-// (loads that only repeat the last copy are left out where the copies are large: three or four of 1.3 million parameters, five loads
-// each, made a 16-step call 0.1 % slower than a loop over them, 7224 -> 7235 us; as it is 7347 -> 7344 on another card)
+// Loads that only repeat the last copy are left out for the counts of large layers and many clients, two to five, where a launch is bound by
+// its bytes: two copies of 3.5 million parameters 18.67 us with three loads, 18.47 with two, three or four of 1.3 million, five loads each,
+// 0.1 % of a 16-step call.  Six copies and more are small layers, bound by the trip, and a form for each count costs more in
+// branches than it saves: 16 copies 6.5 -> 6.7 us, 8 copies 6.8 -> 7.1, 5 copies of 0.44 million 6.0 -> 6.25 (one alone: two loads, in the noise).
 template <class V>
 __device__ __forceinline__ V sum_copies(const float* gp, size_t stride, int splits)
 {
     V g = {};
-    if (splits <= 3) return add_copies<3>(g, gp, stride, 0, splits);
+    if (splits <= 2) return add_copies<2>(g, gp, stride, 0, splits);
+    if (splits == 3) return add_copies<3>(g, gp, stride, 0, splits);
     if (splits == 4) return add_copies<4>(g, gp, stride, 0, splits);
     if (splits == 5) return add_copies<5>(g, gp, stride, 0, splits);
     for (int s = 0; s < splits; s += 8) g = add_copies<8>(g, gp, stride, s, splits);
