@@ -81,8 +81,10 @@ void ensure_dynamic_lds(const void* kernel, size_t bytes)
 }
 
 // ------------------------------------------------------------------ validation and plan
-// Bytes that the 32-bit offsets of a wavefront of the bfloat16 weight-gradient kernel span at `splits`
-// position splits: its units, one more on either side, and two kernel rows.
+// What is kept below 2^31 so that the 32-bit offsets of a wavefront of the bfloat16 weight-gradient kernel hold: 1024 bytes for each
+// of a wavefront's positions / 16, two more, and two grid rows.  The kernel's offsets are unsigned and reach further, from the unit before a
+// wavefront's first to the second row of the pair that it is fetching seven units ahead, in pairs of rows: at most two grid rows and four
+// units more than is counted here, which stays below 2^32.
 static long long wgrad_offset_bytes(const Geo& g, int splits)
 {
     const long long units = cdiv(cdiv(g.padded_positions() / g.heads(), 16), splits * 4);
