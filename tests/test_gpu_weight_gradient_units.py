@@ -1,6 +1,8 @@
 """Weight gradients of the bfloat16 path against float64 products of the very operands the kernel reads (activations and
 back-propagated gradients, taken from the workspace), on grids whose units of eight columns x two rows end in every way:
-odd and even rows, one and two groups of columns, fewer units than the operand ring holds, many position splits, several heads."""
+odd and even rows, one and two groups of columns, fewer units than the operand ring holds, many position splits, several heads, and rows so
+wide that the last pair of an odd number of them reaches further than the guard columns.  The workspace holds NaN before the call, so that
+whatever is read beyond an operand shows."""
 import pytest
 
 import paper_2003_10735_amd as st
@@ -10,7 +12,8 @@ pytestmark = pytest.mark.gpu
 # n, h, w, c_in, c1, c2, grouped
 SHAPES = [(1, 1, 1, 64, 64, 64, 0), (1, 2, 6, 64, 64, 64, 0), (1, 3, 7, 64, 64, 64, 0), (1, 5, 14, 64, 128, 64, 0), (1, 6, 15, 128, 64, 64, 0),
           (1, 16, 24, 64, 64, 64, 0), (1, 33, 57, 128, 64, 128, 0), (1, 60, 107, 96, 48, 48, 0), (2, 9, 30, 64, 64, 64, 0),
-          (3, 12, 22, 64, 64, 128, 1), (3, 13, 31, 64, 64, 64, 1), (1, 90, 160, 256, 128, 128, 0), (1, 135, 240, 64, 64, 64, 0)]
+          (3, 12, 22, 64, 64, 128, 1), (3, 13, 31, 64, 64, 64, 1), (1, 90, 160, 256, 128, 128, 0), (1, 135, 240, 64, 64, 64, 0),
+          (1, 5, 300, 64, 64, 64, 0), (1, 9, 360, 64, 64, 64, 0), (3, 7, 270, 64, 64, 64, 0), (2, 5, 300, 64, 64, 64, 1), (1, 1, 500, 64, 64, 64, 0)]
 
 
 @pytest.mark.parametrize("n,h,w,c_in,c1,c2,grouped", SHAPES)
@@ -21,7 +24,7 @@ def test_weight_gradients_are_the_sums_of_their_operands(n, h, w, c_in, c1, c2, 
     gen.manual_seed(h * 1000 + w)
     d = st.HeadDesc(n, c_in, h, w, c1, c2, C, feat_dtype=st.ST_BF16, compute=st.ST_COMPUTE_BF16, grouped=grouped)
     heads = n if grouped else 1
-    ws = torch.zeros(st.st_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    ws = torch.full((st.st_workspace_bytes(d),), 0xFF, dtype=torch.uint8, device="cuda")
     f = torch.randn((n, c_in, h, w), generator=gen, device="cuda").clamp(min=0).bfloat16()
     lab = torch.randint(0, C, (n, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
     one = [torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5 if b == 0 else torch.zeros(r, device="cuda")
