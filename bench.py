@@ -46,26 +46,26 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # the kernel source it was measured on:
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
-    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "1251484349cb76396ddac10f94c8aeb893fd26d24bed407fd245eade9bb8c0bb", 37.02, 8.83),
+    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 37.02, 8.83),
     ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 13.74, 6.34),
     ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 6.97, 4.92),
     ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 10.70, 3.77),
-    ("720p", "upsample_ce_grad"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 4.69, 4.71),
-    ("720p", "upsample_ce"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 3.08, 1.79),
+    ("720p", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 4.69, 4.71),
+    ("720p", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 3.08, 1.79),
     ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 13.19, 9.81),
-    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "1251484349cb76396ddac10f94c8aeb893fd26d24bed407fd245eade9bb8c0bb", 79.87, 8.83),
+    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 79.87, 8.83),
     ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 23.24, 13.93),
     ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 11.78, 10.82),
     ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 20.01, 8.29),
-    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 10.02, 11.14),
-    ("1080p", "upsample_ce"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 6.45, 4.02),
+    ("1080p", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 10.02, 11.14),
+    ("1080p", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 6.45, 4.02),
     ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 27.54, 21.56),
-    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "1251484349cb76396ddac10f94c8aeb893fd26d24bed407fd245eade9bb8c0bb", 273.25, 17.88),
-    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 70.23, 54.34),
-    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 52.74, 46.79),
-    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 86.53, 30.19),
-    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 30.10, 22.19),
-    ("batch4", "upsample_ce"): ("k_loss.hip", "43961a91371909109c5e07bce18ed9547f8b7c398be70a3ebc10d6ffc67094a7", 23.43, 7.61),
+    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 273.25, 17.88),
+    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 70.19, 54.34),
+    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 53.08, 46.79),
+    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 86.74, 30.19),
+    ("batch4", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 30.10, 22.19),
+    ("batch4", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 23.43, 7.61),
     ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 71.41, 80.27),
 }
 

@@ -22,7 +22,7 @@
 // Work split: one 512-thread block per tile of 1 x LOSS_TX groups of 8 x 8 pixels, two threads
 // per pixel column (four pixels each).  A tile touches 3 x (LOSS_TX + 2) low-resolution cells;
 // its share of U^T P for those cells goes to a slot of its own, and the consumer adds the (at
-// most four) slots that meet in a cell in a fixed order.  No floating-point atomics here:
+// most six) slots that meet in a cell in a fixed order.  No floating-point atomics here:
 // results do not change from run to run.
 #include "st_kernels.hpp"
 #include "st_mfma.hpp"

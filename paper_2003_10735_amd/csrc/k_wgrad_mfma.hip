@@ -15,11 +15,12 @@
 // lane holds) instead of loading shifted windows.  9 MFMAs per 4 loads.  A bigger block would need fewer loads per MFMA but leaves
 // too few blocks to fill the chip without multiplying the partial copies.
 // Why two rows: the three X fragments of a unit then are four row pieces of 512 bytes, two of them read twice at the same time
-// and the second time out of the L1 cache.  With a unit of 16 columns of one row they were six different ones,
-// and what came from L2 -- 4 KB a unit and wavefront, 45 bytes per cycle and compute unit -- bound the kernel.  Cycles a unit,
-// before / now (288 are MFMAs): 4 x 90 x 160 cells, 320 -> 256 -> 256 391 / 317, 135 x 240, 256 -> 128 -> 128 347 / 316, 90 x 160 366 / 346 (49 units a
-// wavefront: the first operands' way counts); the first of these launches 133.6 / 121.1 us, at a clock that the power draw
-// lowers from 2.2 to 2.05 GHz.  The element that enters a shifted fragment now lies in the same lane; cross-lane
+// and the second time mostly out of the L1 cache.  With a unit of 16 columns of one row they were six different ones, and a unit and
+// wavefront took 4 KB from L2, 45 bytes per cycle and compute unit.  Read requests to L2 (TCP_TCC_READ_REQ_sum, millions a launch),
+// before / now: 4 x 90 x 160 cells, 320 -> 256 -> 256 17.9 / 14.3, 135 x 240, 256 -> 128 -> 128 3.30 / 2.75, 90 x 160 1.52 / 1.33; the launches
+// 143.9 / 130.1, 29.8 / 29.1 and 17.6 / 16.3 us (median under the profiler, one card; at 90 x 160 cells a wavefront has 49 units, and the
+// first operands' way and the reduction are half the launch).  From memory it fetches more than before, not less (90 x 160 33.8 / 37.2 MiB:
+// the rows of a pair are in two places).  The element that enters a shifted fragment now lies in the same lane; cross-lane
 // permutes fetched it from the other half of the wavefront.
 //
 // The four wavefronts of a block own the same output block and a quarter each of the block's
@@ -248,7 +249,8 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
 // launch order on whichever compute unit is free, and every partial copy is read once more by the
 // optimiser kernel.  The search simulates exactly that for every pair of split counts and keeps the
 // shortest; among equals, fewer partial copies.
-// bfloat16: units of 16 positions (9 MFMAs of 32 cycles), the fixed cost is about 22 of them.
+// bfloat16: units of 16 positions (9 MFMAs of 32 cycles), the fixed cost is about 22 of them.  (The kernel's units are pairs of rows: where
+// a head has an odd number of them, half a row more than is counted here.)
 // float32: units of 16 positions (54 MFMAs of 32 cycles); a launch takes some 10 us + 1.4 per unit, of which 4 units count as fixed (2: 120 x 200
 // cells, 256 -> 128 -> 128, 0.7 % slower; 8, 14: within 0.3 % at nine sizes from 16 x 16 cells on).  By the float32 instruction: units of 8
 // positions (36 MFMAs of 64 cycles).

@@ -95,16 +95,10 @@ inline ParamOffsets param_offsets(const Geo& g)
 
 // ------------------------------------------------------------------ loss-kernel tiling
 // The fused up-sample + cross-entropy kernel works on tiles of LOSS_TY x LOSS_TX groups of 8x8
-// frame pixels (one thread per pixel column).  A tile touches (LOSS_TY + 2) x (LOSS_TX + 2)
+// frame pixels (two threads per pixel column).  A tile touches (LOSS_TY + 2) x (LOSS_TX + 2)
 // low-resolution cells and leaves its share of d loss / d z for them in a slot of its own.
-#ifndef ST_LOSS_TX
-#define ST_LOSS_TX 32
-#endif
-constexpr int LOSS_TX = ST_LOSS_TX;     // 8-pixel column groups per tile (two threads per pixel column)
-#ifndef ST_LOSS_TY
-#define ST_LOSS_TY 1
-#endif
-constexpr int LOSS_TY = ST_LOSS_TY;     // 8-pixel row groups per tile
+constexpr int LOSS_TX = 32;             // 8-pixel column groups per tile
+constexpr int LOSS_TY = 1;              // 8-pixel row groups per tile (the kernel and the gather are written for these two)
 constexpr int LOSS_CW = LOSS_TX + 2;    // cells per tile row
 constexpr int LOSS_CH = LOSS_TY + 2;    // cell rows per tile
 

@@ -1,5 +1,6 @@
 // d loss / d z of low-resolution cells from what the loss kernel left behind: the per-tile slots of
-// U^T softmax (added in a fixed order: tile rows first), minus U^T of the one-hot labels, over N_valid.
+// U^T softmax, minus U^T of the one-hot labels, over N_valid.  The slots are added in a fixed order: tile row by tile row,
+// in each the tile column with the cell before the one beside it, be that to the left or to the right.
 #pragma once
 #include "st_common.hpp"
 
@@ -38,7 +39,7 @@ __host__ __device__ __forceinline__ GatherAt gather_at(int CP, const LossTiling&
     const long long col[2] = {(long long)((size_t)tile * tile_floats) + (LOSS_CW + in + 1),
                               (long long)((size_t)(tile + tx1 - tx) * tile_floats) + (LOSS_CW + in1 + 1)};
     // a 0/1 weight: tiles that do not exist or do not touch the cell read slot element 0 with weight 0, so that every
-    // load is unconditional
+    // load is unconditional.  (That element belongs to a cell outside the grid: zero, whatever the first frame holds.)
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
