@@ -25,6 +25,14 @@ __host__ __device__ __forceinline__ int fast_quot(int n, const FastDiv& f)
     return (int)(q + ((unsigned)n - q * f.d >= f.d ? 1u : 0u));
 }
 
+// Which of `n` tiles block `block` of n takes: blocks go to the eight XCDs in turn, and every XCD gets a run of consecutive tiles, the same
+// band of rows in every kernel that orders its tiles so.
+__host__ __device__ __forceinline__ int xcd_band(int block, int n)
+{
+    const int xcd = block & 7, rest = n & 7;
+    return (block >> 3) + xcd * (n >> 3) + (xcd < rest ? xcd : rest);
+}
+
 // ------------------------------------------------------------------ geometry
 // Activations live position-major ("NHWC") on a grid padded by one zero cell on every side, so
 // a 3x3 tap is a plain offset and needs no bounds test:

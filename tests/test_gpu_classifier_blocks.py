@@ -1,0 +1,63 @@
+"""Gradient of the classifier's weights and bias, a sum over the backward launch's blocks of 64 positions, for as many blocks as fewer than,
+exactly and more than the eight runs they are dealt out in: against float64 products of the activations the kernel read and the gradient
+of the very logits it left, and the gradient it handed on, zero wherever there is no cell."""
+import pytest
+
+import paper_2003_10735_amd as st
+
+pytestmark = pytest.mark.gpu
+
+# n, h, w, c2, grouped: 1, 1, 2, 7, 8, 9, 15, 17, 26 blocks; several heads of 2, 3 and 9
+SHAPES = [(1, 1, 1, 64, 0), (1, 2, 14, 128, 0), (1, 3, 22, 64, 0), (1, 12, 30, 64, 0), (1, 14, 30, 192, 0), (2, 4, 46, 64, 0), (1, 13, 62, 256, 0),
+          (1, 15, 62, 128, 0), (1, 24, 62, 320, 0), (3, 6, 13, 64, 1), (5, 6, 21, 128, 1), (3, 12, 38, 64, 1)]
+
+
+@pytest.mark.parametrize("n,h,w,c2,grouped", SHAPES)
+def test_classifier_gradient_is_the_sum_over_all_blocks(n, h, w, c2, grouped):
+    import torch
+    C, c_in, c1 = 7, 64, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(h * 1000 + w)
+    d = st.HeadDesc(n, c_in, h, w, c1, c2, C, feat_dtype=st.ST_BF16, compute=st.ST_COMPUTE_BF16, grouped=grouped)
+    heads = n if grouped else 1
+    ws = torch.full((st.st_workspace_bytes(d),), 0xFF, dtype=torch.uint8, device="cuda")
+    f = torch.randn((n, c_in, h, w), generator=gen, device="cuda").clamp(min=0).bfloat16()
+    lab = torch.randint(0, C, (n, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
+    one = [torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5 if b == 0 else torch.zeros(r, device="cuda")
+           for r, k in ((c1, 9 * c_in), (c2, 9 * c1), (C, c2)) for b in (0, 1)]
+    before = torch.cat(one * heads)
+    # no step: the logits that the step below starts from
+    st.st_partial_distill(d, f, lab, before.clone(), 0, 0.0, workspace=ws)
+    torch.cuda.synchronize()
+    lay = st.st_get_workspace_layout(d)
+    Wp, Hp = lay["row_pitch"], h + 2
+    z = ws[lay["z"]:lay["z"] + n * C * h * w * 4].view(torch.float32).reshape(n, C, h, w).double().cpu().requires_grad_(True)
+    up = torch.nn.functional.interpolate(z, scale_factor=8, mode="bilinear", align_corners=False)
+    loss = torch.nn.functional.cross_entropy(up, lab.long().cpu(), reduction="sum") / (n // heads * 64 * h * w)
+    g, = torch.autograd.grad(loss, z)
+    lr = 1.0
+    after = before.clone()
+    st.st_partial_distill(d, f, lab, after, 1, lr, workspace=ws)
+    torch.cuda.synchronize()
+    # (the last forward pass of that call has overwritten a2: the step before it is repeated without an update)
+    keep = before.clone()
+    st.st_partial_distill(d, f, lab, keep, 1, 0.0, workspace=ws)
+    torch.cuda.synchronize()
+    k2 = (c2 + 63) // 64 * 64
+    a2, da2 = (ws[lay[m]:lay[m] + n * Hp * Wp * k2 * 2].view(torch.bfloat16).reshape(n, Hp, Wp, k2).double().cpu() for m in ("a2", "da2"))
+    border = torch.ones(Hp, Wp, dtype=torch.bool)
+    border[1:h + 1, 1:w + 1] = False
+    assert (da2[:, border] == 0).all() and da2.abs().max() > 0
+    a2 = a2[:, 1:h + 1, 1:w + 1, :c2]
+    size = before.numel() // heads
+    # g enters the product rounded to bfloat16 (2^-9, and the float32 sums behind it far less); the new weight is rounded once
+    for k in range(heads):
+        gk, ak = (g[k:k + 1], a2[k:k + 1]) if heads > 1 else (g, a2)
+        step = (before[k * size:(k + 1) * size].double() - after[k * size:(k + 1) * size].double()).cpu() / lr
+        old = before[k * size:(k + 1) * size].double().cpu()
+        gm, am = gk.permute(0, 2, 3, 1).reshape(-1, C), ak.reshape(-1, c2)
+        at = size - C - C * c2
+        want, scale = gm.t() @ am, gm.abs().t() @ am.abs()
+        ulp = old.abs().max() * 2.0 ** -23
+        assert ((step[at:at + C * c2].reshape(C, c2) - want).abs() <= 2.0 ** -8 * scale + ulp).all(), k
+        assert ((step[size - C:] - gm.sum(0)).abs() <= 2.0 ** -8 * gm.abs().sum(0) + ulp).all(), k
