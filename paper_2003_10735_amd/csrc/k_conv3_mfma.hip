@@ -208,7 +208,7 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
-                    if (c < g.C) slot[c * k2 + ch0 + t * 32 + l32] = acc[r];    // (rows beyond the classes are never read)
+                    if (c < g.C) store_through(slot + ch0 + t * 32, (unsigned)(c * k2 + l32) * 4, acc[r]);    // (rows beyond the classes are never read)
                 }
             }
         }
@@ -219,15 +219,19 @@ k_conv3_bwd_mfma(const float* __restrict__ slots, const float* __restrict__ T,
     for (int q = tid; q < BP * (C2 / 8); q += NT) {
         const int p = q / (C2 / 8), part8 = q % (C2 / 8);
         if (m0 + p < m_end)
-            *(uint4*)(da2 + (size_t)(m0 + p) * k2 + ch0 + part8 * 8) = *(const uint4*)(Os + p * OLD + part8 * 8);
+            store_through(da2 + (size_t)m0 * k2 + ch0, (unsigned)(p * k2 + part8 * 8) * 2, *(const u32x4*)(Os + p * OLD + part8 * 8));
     }
-    for (int q = tid; q < (BP / 8) * C2; q += NT) {
-        const int o = q % C2, pg = q / C2;
-        if (m0 + pg * 8 >= m_end) continue;
-        bf16x8 ov;
+    // (through the transposing LDS read, a wavefront two groups of 32 channels: lane r of 16 names position r / 4, channels 4 (r % 4) .. + 3, and
+    //  lane i receives channel i of four consecutive positions)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ov[e] = Os[(pg * 8 + e) * OLD + o];
-        *(bf16x8*)(da2T + xt_index(ch0 + o, guard + m0 + pg * 8, PPT / 8)) = ov;
+    for (int u = wave; u < (BP / 16) * OT; u += NT / 64) {
+        const int pg = u / OT * 2 + lhi, c = u % OT * 32;
+        const bf16* row = Os + (pg * 8 + ((lane & 15) >> 2)) * OLD + c + (lane & 16) + 4 * (lane & 3);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * OLD));
+        const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        if (m0 + pg * 8 < m_end)
+            store_through(da2T + xt_index(ch0 + c, guard + m0 + u / OT * 16, PPT / 8), lhi * 512 + l32 * 16, __builtin_bit_cast(u32x4, v));
     }
 }
 

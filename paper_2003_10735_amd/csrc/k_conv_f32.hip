@@ -764,7 +764,7 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
     float* redb = red + 4 * 9 * 32 * 32;
     bsum += __shfl_xor(bsum, 32, 64);
     if (lhi == 0) redb[wave * 32 + l32] = bsum;
-    wgrad_reduce_store(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
+    wgrad_reduce_store<true>(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
     if (i0 == 0 && tid < 32 && o0 + tid < a.cout)
         a.db[(size_t)split * a.split_stride + o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
 }
@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_f32_few(Wgrad32Args a1, Wgrad3
     float* redb = red + 4 * 9 * 32 * 32;
     bsum += __shfl_xor(bsum, 32, 64);
     if (lhi == 0) redb[wave * 32 + l32] = bsum;
-    wgrad_reduce_store(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
+    wgrad_reduce_store<false>(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
     if (i0 == 0 && tid < 32 && o0 + tid < a.cout)
         a.db[(size_t)split * a.split_stride + o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
 }

@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         for (int q = tid; q < BM * (CV_BN / 8); q += NT) {
             const int p = q / (CV_BN / 8), part = q % (CV_BN / 8);
             if (m0 + p < m_end)
-                *(uint4*)(a.Y + (size_t)(m0 + p) * a.cout + n0 + part * 8) = *(const uint4*)(Os + p * CV_OLD + part * 8);
+                store_through(a.Y + (size_t)m0 * a.cout + n0, (unsigned)(p * a.cout + part * 8) * 2, *(const u32x4*)(Os + p * CV_OLD + part * 8));
         }
     }
     if (a.YT) {
@@ -432,7 +432,8 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)row);
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * CV_OLD));
             const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            if (m0 + pg * 8 < m_end) *(s16x8*)(a.YT + xt_index(n0 + c + l32, a.guard + m0 + pg * 8, a.PPT / 8)) = v;
+            if (m0 + pg * 8 < m_end)
+                store_through(a.YT + xt_index(n0 + c, a.guard + m0 + (u >> 1) * 16, a.PPT / 8), lhi * 512 + l32 * 16, __builtin_bit_cast(u32x4, v));
         }
     }
 }

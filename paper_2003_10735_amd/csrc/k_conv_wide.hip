@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
                 for (int e = 0; e < 8; ++e) o[e] = (float)m[e] > 0.f ? o[e] : (bf16)0.f;
                 *(bf16x8*)(Os + p * OLD + c) = o;
             }
-            if (a.Y && m0 + p < m_end && n0 + c < a.cout) *(bf16x8*)(a.Y + (size_t)(m0 + p) * a.cout + n0 + c) = o;
+            if (a.Y && m0 + p < m_end && n0 + c < a.cout) store_through(a.Y + (size_t)m0 * a.cout + n0, (unsigned)(p * a.cout + c) * 2, __builtin_bit_cast(u32x4, o));
         }
         if (EPI == 1) __syncthreads();
     }
@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3x3_wide(ConvArgs a)
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(row + 4 * OLD));
             const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
             if (m0 + pg * 8 < m_end && n0 + c < a.cout)
-                *(s16x8*)(a.YT + xt_index(n0 + c + l32, a.guard + m0 + pg * 8, a.PPT / 8)) = v;
+                store_through(a.YT + xt_index(n0 + c, a.guard + m0 + u / (BN / 32) * 16, a.PPT / 8), lhi * 512 + l32 * 16, __builtin_bit_cast(u32x4, v));
         }
     }
 }

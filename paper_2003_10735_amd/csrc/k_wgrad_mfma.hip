@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(256) k_wgrad3x3_mfma(WgradArgs a1, WgradArgs a
     float* red = (float*)smem_raw;
     float* redb = red + 4 * 9 * 32 * 32;           // [4][32] sums of dY over the positions
     if (want_bias && lhi == 0) redb[wave * 32 + l32] = acc[9][0];
-    wgrad_reduce_store(acc, red, a.dW + head * a.head_out_stride + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
+    wgrad_reduce_store<true>(acc, red, a.dW + head * a.head_out_stride + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
     if (want_bias && tid < 32 && o0 + tid < a.cout) {
         float* db = a.db + head * a.head_out_stride + (size_t)split * a.split_stride;
         db[o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];

@@ -12,6 +12,22 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // v_mfma_f32_32x32x16_bf16: D[32x32] += A[32x16] * B[16x32].  Lane l supplies A[l % 32][8*(l/32) .. +7]
 // and B[8*(l/32) .. +7][l % 32]; it receives D[8*(r/4) + 4*(l/32) + r%4][l % 32] in register r.
 
+// Stores at device scope (sc1): they go through the L2 cache to memory as they are made, `off` bytes behind `base`, which is the same for all
+// lanes.  A plain store stays in L2 as a dirty line until its launch ends, and the next launch waits for the write-back: 7.9 MB written by
+// 240 blocks and nothing else 2.83 us a launch, through the cache 2.32.  The reader fetches the data from memory either way (what a step
+// moves turns every L2 over between a write and its read).  For whole 128-byte lines of outputs that are large: the logits' shares, rows of
+// 80 bytes in pieces of 16, are dearer this way (4 x 90 x 160 cells 7524 -> 7610 us a call), and where everything a step writes stays in L2 a
+// plain store is the cheaper one (weight gradients of 16 x 16 cells, float32: a call 192 -> 196 us).
+// Key frame at 90 x 160 cells 612 -> 592 us, at 135 x 240 1172 -> 1139, 60 x 107 cells, 96 -> 48 -> 48 channels 210 -> 207.
+__device__ __forceinline__ void store_through(void* base, unsigned off, u32x4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000), (int)off, 0, 16);
+}
+__device__ __forceinline__ void store_through(void* base, unsigned off, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000), (int)off, 0, 16);
+}
+
 // Channel-major operand copies ("XT") feed the weight-gradient kernels, whose MFMA fragments are
 // 32 channels x 8 consecutive positions.  They are stored blocked so that such a fragment is one
 // contiguous 512-byte run and a wavefront's fragment load is fully coalesced:

@@ -13,8 +13,9 @@ constexpr size_t WGRAD_SMEM_BYTES = (size_t)(4 * 9 * 32 * 32 + 4 * 32) * sizeof(
 // so a lane holds four consecutive input channels i of one output channel o per register group: one
 // 16-byte LDS write.  Rows are 128 bytes; the 16-byte chunk c of row o is stored at chunk
 // c ^ ((o >> 1) & 7), which spreads the 16 lanes of a write (and of a read) over all banks.
-// acc[0..8]: the taps.  dW: [cout][9][cin] of this split.
-template <int N>
+// acc[0..8]: the taps.  dW: [cout][9][cin] of this split.  (A tile's 32-bit offsets: a whole one has 32 output channels, so that a row of
+// 9 cin floats is below 2^25 bytes.)  THROUGH: past the caches (store_through).
+template <bool THROUGH, int N>
 __device__ __forceinline__ void wgrad_reduce_store(const f32x16 (&acc)[N], float* red, float* dW, int o0, int i0, int cout, int cin)
 {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
@@ -40,8 +41,12 @@ __device__ __forceinline__ void wgrad_reduce_store(const f32x16 (&acc)[N], float
         const int t = q >> 8, ol = (q >> 3) & 31, part = q & 7;
         return dW + ((size_t)(o0 + ol) * 9 + t) * cin + i0 + part * 4;
     };
+    auto offset_of = [&](int q) { return (unsigned)((((q >> 3) & 31) * 9 + (q >> 8)) * cin + (q & 7) * 4) * 4u; };
     if (o0 + 32 <= cout && i0 + 32 <= cin && ((cin | (int)((uintptr_t)dW >> 2)) & 3) == 0) {
-        for (int q = tid; q < 9 * 32 * 8; q += 256) *(f32x4*)place_of(q) = sum_of(q);
+        for (int q = tid; q < 9 * 32 * 8; q += 256) {
+            if (THROUGH) store_through(dW + (size_t)o0 * 9 * cin + i0, offset_of(q), __builtin_bit_cast(u32x4, sum_of(q)));
+            else *(f32x4*)place_of(q) = sum_of(q);
+        }
     } else {
         // a tile with padded channels of a narrow head: those have no gradient to store
         for (int q = tid; q < 9 * 32 * 8; q += 256) {
