@@ -863,55 +863,78 @@ static Wgrad32Args wgrad_f32_args(const Plan& p, const float* dY, const float* X
 // ------------------------------------------------------------------ classifier backward
 //   g = d loss / d z from the loss kernel's slots (gather_g), also left in gz;
 //   da2[p][o] = [a2[p][o] > 0] * sum_c g[c][p] * W3[c][o];   dW3, db3: one slot per block (the optimiser kernel adds them)
-// A block of 256 threads takes 64 padded positions.  Bound by its chain of dependent memory round
-// trips, like the bfloat16 kernel of the same layer.
-// (Four wavefronts for da2 and four for dW3 side by side, as there: without prefetching what a role reads,
-// 16 x 16 cells 203 -> 208 us and 68 x 120 cells 901 -> 911 us a call; with it 203 -> 197 and 900 -> 893, but at
-// 204 registers, one block per compute unit.)
-constexpr int B32_BP = 64;
+// A block of 512 threads takes 64 padded positions and up to 512 channels (blockIdx.y: which).  Bound by its chain of dependent memory round
+// trips, like the bfloat16 kernel of the same layer, and laid out like it: the two products side by side, four wavefronts each, and
+// everything that does not depend on g asked for before it is: a2 on its way to LDS, where both products take it from, and the first
+// tiles of W3.  256 threads that did one product after the other, each with loads of its own behind g: 68 x 120 cells, 256 -> 128 -> 128 channels
+// 673 us a call of four steps, 664 so; 16 x 16 cells, 64 channels 192.7 and 187.0; 90 x 160 cells 1001 and 994, two frames of it 1837 and 1832;
+// 135 x 240 cells, 24 -> 32 -> 24 channels 609 and 603.
+constexpr int B32_BP = 64, B32_NT = 512, B32_TILES = 16;
+constexpr int B32_RUN = B32_BP * 32 + 160;      // bytes of a run's positions in LDS: 32 banks on behind position 31, eight banks on from run to run
 
-__global__ void __launch_bounds__(256)
+template <bool PARTS>       // PARTS: more channels than a block takes
+__global__ void __launch_bounds__(B32_NT, 1)
 k_conv3_bwd_f32(const float* __restrict__ slots, const float* __restrict__ T, const unsigned long long* __restrict__ n_valid,
-                int CP, LossTiling lt, const float* __restrict__ a2, const float* __restrict__ W3T, float* __restrict__ da2,
-                float* __restrict__ gz, float* __restrict__ part, Geo g, int PPT, int guard)
+                    int CP, LossTiling lt, const float* __restrict__ a2, const float* __restrict__ W3T, float* __restrict__ da2,
+                    float* __restrict__ gz, float* __restrict__ part, Geo g, int PPT, int guard, int blocks)
 {
     constexpr int BP = B32_BP, GP = BP + 8;     // (pitch: the two halves of a B read 32 banks apart)
     __shared__ __attribute__((aligned(16))) float g_cp[32 * GP];    // [class][position]
+    extern __shared__ __attribute__((aligned(16))) unsigned char a2s[];      // [run of eight channels][position][8], see at()
     // (what the first loads need, in one trip for the arguments)
     asm volatile("" ::"s"(slots), "s"(T), "s"(n_valid), "s"(CP), "s"(lt.tiles_x), "s"(lt.tiles_y), "s"(a2), "s"(W3T), "s"(g.n), "s"(g.h), "s"(g.w), "s"(g.Hp), "s"(g.Wp),
-                 "s"(g.C), "s"(g.k2), "s"(g.by_frame.d), "s"(g.by_frame.m), "s"(g.by_row.d), "s"(g.by_row.m));
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                 "s"(g.C), "s"(g.k2), "s"(g.by_frame.d), "s"(g.by_frame.m), "s"(g.by_row.d), "s"(g.by_row.m), "s"(blocks), "s"(PPT), "s"(guard));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
     const int PP = g.padded_positions(), hw = g.h * g.w;
-    const int m0 = blockIdx.x * BP;
-    {
-        const int pl = tid & 63, cq = tid >> 6;
-        float v[8];
-        const GatherCell cell = gather_g<8, 4>(slots, T, n_valid, CP, lt, g, m0 + pl, PP, cq, v);
+    const int bid = xcd_band(blockIdx.x, blocks), m0 = bid * BP;
+    // this block's tiles of 32 channels and runs of eight, from tile t_first on
+    const int t_first = PARTS ? blockIdx.y * B32_TILES : 0, OT = (g.c2 + 31) / 32 - t_first, G2 = (g.c2 + 7) / 8 - t_first * 4, CG = (g.C + 7) / 8;
+    const int tiles = PARTS ? min(OT, B32_TILES) : OT;
+    if (PARTS) { a2 += (size_t)t_first * 4 * PPT * 8; da2 += (size_t)t_first * 4 * PPT * 8; W3T += (size_t)t_first * 4 * 64 * 4; }
+    auto at = [](int run, int pos) __attribute__((always_inline)) { return run * B32_RUN + pos * 32 + (pos >= 32 ? 128 : 0); };
+
+    // ---- a2: 16 bytes per thread and turn, 128 of a run's 64 positions; rows behind the last position and runs behind the last one
+    //      repeat it
+    constexpr int TURNS = 4;                       // turns in registers before the gradient (c2 = 128); the others follow behind it
+    const int half = tid & 1, pos = (tid >> 1) & 63, r0 = tid >> 7;
+    const size_t col = (size_t)(guard + min(m0 + pos, PP - 1)) * 8 + half * 4;
+    f32x4 av[TURNS];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int c = cq + 4 * k;
+    for (int k = 0; k < TURNS; ++k) av[k] = *(const f32x4*)(a2 + (size_t)min(r0 + 4 * k, G2 - 1) * PPT * 8 + col);
+    // W3 of the first two tiles that a wavefront of the first product takes (all load them: see the bfloat16 kernel)
+    f32x4 wf[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) wf[k][q] = *(const f32x4*)(W3T + ((min((wave & 3) / 2 + 2 * k, tiles - 1) * 4 + q) * 64 + lane) * 4);
+    {
+        const int pl = tid & 63;
+        float v[4];
+        const GatherCell cell = gather_g<4, 8>(slots, T, n_valid, CP, lt, g, m0 + pl, PP, wave, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int c = wave + 8 * k;
             g_cp[c * GP + pl] = c < g.C ? v[k] : 0.f;
-            if (c < g.C && cell.inside) gz[((size_t)cell.img * g.C + c) * hw + cell.cy * g.w + cell.cx] = v[k];
+            if (c < g.C && cell.inside && t_first == 0) gz[((size_t)cell.img * g.C + c) * hw + cell.cy * g.w + cell.cx] = v[k];
         }
     }
+#pragma unroll
+    for (int k = 0; k < TURNS; ++k)
+        if (r0 + 4 * k < tiles * 4) *(f32x4*)(a2s + at(r0 + 4 * k, pos) + half * 16) = av[k];
+    for (int run = r0 + 4 * TURNS; run < tiles * 4; run += 4)
+        *(f32x4*)(a2s + at(run, pos) + half * 16) = *(const f32x4*)(a2 + (size_t)min(run, G2 - 1) * PPT * 8 + col);
     __syncthreads();
 
-    const int OT = (g.c2 + 31) / 32, G2 = (g.c2 + 7) / 8, CG = (g.C + 7) / 8;
-    {
+    float* slot = part + (size_t)bid * (32 * g.k2 + 32);
+    if (wave < 4) {
         const int pm = (wave & 1) * 32 + l32, mp = m0 + pm;
         float gb[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e) gb[q][e] = g_cp[(q * 8 + lhi * 4 + e) * GP + pm];
-        for (int t = wave >> 1; t < OT; t += 2) {
-            f32x4 wf[4], mk[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) wf[q] = *(const f32x4*)(W3T + ((t * 4 + q) * 64 + lane) * 4);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                mk[q] = *(const f32x4*)(a2 + ((size_t)min(t * 4 + q, G2 - 1) * PPT + guard + min(mp, PP - 1)) * 8 + lhi * 4);
+        auto tile = [&](int t, const f32x4 (&w)[4]) __attribute__((always_inline)) {
             f32x16 acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -919,46 +942,53 @@ k_conv3_bwd_f32(const float* __restrict__ slots, const float* __restrict__ T, co
             for (int q = 0; q < 4; ++q)
                 if (q < CG)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[q][e], gb[q][e], acc, 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q][e], gb[q][e], acc, 0, 0, 0);
             // (g is zero on the border, and so is da2)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (t * 4 + q < G2 && mp < PP) {
+                    const f32x4 mk = *(const f32x4*)(a2s + at(t * 4 + q, pm) + lhi * 16);
                     f32x4 v;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = mk[q][e] > 0.f ? acc[q * 4 + e] : 0.f;
+                    for (int e = 0; e < 4; ++e) v[e] = mk[e] > 0.f ? acc[q * 4 + e] : 0.f;
                     *(f32x4*)(da2 + ((size_t)(t * 4 + q) * PPT + guard + mp) * 8 + lhi * 4) = v;
                 }
+        };
+        const int t0 = wave >> 1;
+        if (t0 < tiles) tile(t0, wf[0]);
+        if (t0 + 2 < tiles) tile(t0 + 2, wf[1]);
+        for (int t = t0 + 4; t < tiles; t += 2) {
+            f32x4 w[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q] = *(const f32x4*)(W3T + ((t * 4 + q) * 64 + lane) * 4);
+            tile(t, w);
         }
-    }
-    // dW3: k = positions, the two halves of the block's 64
-    float* slot = part + (size_t)blockIdx.x * (32 * g.k2 + 32);
-    f32x4 ga[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) ga[q] = *(const f32x4*)(g_cp + l32 * GP + lhi * 32 + q * 4);
-    for (int t = wave; t < OT; t += 4) {
-        const float* ab = a2 + (size_t)min((t * 32 + l32) >> 3, G2 - 1) * PPT * 8 + (l32 & 7);
-        float av[32];
-#pragma unroll
-        for (int s = 0; s < 32; ++s) av[s] = ab[(size_t)(guard + min(m0 + lhi * 32 + s, PP - 1)) * 8];
-        f32x16 acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-        for (int s = 0; s < 32; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ga[s >> 2][s & 3], av[s], acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
-            if (c < g.C && t * 32 + l32 < g.k2) slot[c * g.k2 + t * 32 + l32] = acc[r];
-        }
-    }
-    {   // db3: eight threads per class
+        // db3: eight threads per class
         const int c = tid >> 3, q = tid & 7;
         float s = 0.f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) s += g_cp[c * GP + q * 8 + k];
         s += __shfl_xor(s, 1, 64); s += __shfl_xor(s, 2, 64); s += __shfl_xor(s, 4, 64);
-        if (q == 0 && c < g.C) slot[32 * g.k2 + c] = s;
+        if (q == 0 && c < g.C && t_first == 0) slot[32 * g.k2 + c] = s;
+    } else {
+        // dW3: k = positions, the two halves of the block's 64
+        f32x4 ga[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) ga[q] = *(const f32x4*)(g_cp + l32 * GP + lhi * 32 + q * 4);
+        for (int t = wave - 4; t < tiles; t += 4) {
+            const float* ab = (const float*)(a2s + at(min((t * 32 + l32) >> 3, G2 - 1), lhi * 32)) + (l32 & 7);
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+            for (int s = 0; s < 32; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ga[s >> 2][s & 3], ab[s * 8], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = (r >> 2) * 8 + lhi * 4 + (r & 3);
+                const int o = (t_first + t) * 32 + l32;
+                if (c < g.C && o < g.k2) slot[c * g.k2 + o] = acc[r];
+            }
+        }
     }
 }
 
@@ -976,9 +1006,14 @@ void backward_f32(Ctx& c, const Plan& p, char* ws, float* dfeat)
 {
     const Geo& g = p.g;
     auto f = [&](size_t at) { return (float*)(ws + at); };
-    ST_LAUNCH(c, "conv3_bwd_f32", k_conv3_bwd_f32, dim3(p.blocks3), dim3(256), 0, f(p.g_slots), f(p.tadj),
-              (const unsigned long long*)(ws + p.counters), (g.C + 3) / 4 * 4, p.lt, f(p.a2), f(p.wq3t), f(p.da2), f(p.gz), f(p.grad3), g,
-              p.PPT, p.guard);
+    const int tiles3 = cdiv(g.c2, 32);
+    auto classifier = [&](auto kernel) {
+        ensure_dynamic_lds((const void*)kernel, (size_t)B32_TILES * 4 * B32_RUN);
+        ST_LAUNCH(c, "conv3_bwd_f32", kernel, dim3(p.blocks3, cdiv(tiles3, B32_TILES)), dim3(B32_NT), (size_t)std::min(tiles3, B32_TILES) * 4 * B32_RUN, f(p.g_slots), f(p.tadj),
+                  (const unsigned long long*)(ws + p.counters), (g.C + 3) / 4 * 4, p.lt, f(p.a2), f(p.wq3t), f(p.da2), f(p.gz), f(p.grad3), g,
+                  p.PPT, p.guard, p.blocks3);
+    };
+    if (tiles3 <= B32_TILES) classifier(k_conv3_bwd_f32<false>); else classifier(k_conv3_bwd_f32<true>);
     conv_f32(c, "conv2_dgrad_f32", p, 1, f(p.da2), f(p.wq2t), f(p.theta) + p.po.W2, g.c2, g.c1, nullptr, f(p.a1), f(p.da1), nullptr, nullptr, nullptr);
     if (dfeat)
         conv_f32(c, "conv1_dgrad_f32", p, 3, f(p.da1), f(p.wq1t), f(p.theta) + p.po.W1, g.c1, g.c_in, nullptr, nullptr, nullptr, nullptr, nullptr, dfeat);
