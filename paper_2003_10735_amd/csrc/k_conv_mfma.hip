@@ -58,7 +58,8 @@ struct ConvLds {
     static constexpr int BM = 32 * MB, ROWS = BM + 2, SLAB = ROWS * CV_BK * 2;       // one slab: BM + 2 rows of 64 channels, unpadded
     // dynamic LDS: the activation slabs, whose room the staged output tile takes afterwards, and behind them the exchanged partial
     // sums (8 owners x 3 sources x 4 MB registers x 64 lanes, float32), which are written while the last slab is still read
-    static constexpr size_t SLABS = (size_t)CV_NBUF * SLAB, BYTES = SLABS + (size_t)8 * 3 * 4 * MB * 64 * sizeof(float);
+    static constexpr int PER = MB == 1 ? 3 : 1;           // stages between two barriers, whose slabs rotate together
+    static constexpr size_t SLABS = (size_t)CV_NBUF * PER * SLAB, BYTES = SLABS + (size_t)8 * 3 * 4 * MB * 64 * sizeof(float);
     static_assert((size_t)BM * CV_OLD * sizeof(bf16) <= SLABS && BYTES <= 160 * 1024, "LDS buffers fit");
 };
 
@@ -158,9 +159,12 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     for (int kw = 0; kw < 3; ++kw) wv[kw] = (unsigned)((((nb * 9 + kw) * kfr + kgrp) * 512 + (lane ^ row_x) * 8) * 2);
     const long long x_step = CV_BK * 2, x_row = ((long long)a.Wp * a.cin - (c_chunks - 1) * CV_BK) * 2;
     const int w_step = (CV_BK / 16) * 512 * 2, w_row = (2 * kfr + CV_BK / 16) * 512 * 2;
-    int f_cc = 0;
+    int f_cc = 0, x_cc = 0;
 #define CV_FETCH_NEXT                                                                             \
     if (++f_cc == c_chunks) { f_cc = 0; xsp += x_row; w_soff += w_row; } else { xsp += x_step; w_soff += w_step; }
+    // (small tiles, whose activations run further ahead than their weights)
+#define CV_W_NEXT if (++f_cc == c_chunks) { f_cc = 0; w_soff += w_row; } else w_soff += w_step;
+#define CV_X_NEXT if (++x_cc == c_chunks) { x_cc = 0; xsp += x_row; } else xsp += x_step;
 #define CV_DMA(VOFF, LDSADDR)                                                                     \
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(VOFF), "s"(xsp), \
                  "s"(LDSADDR) : "memory");
@@ -209,44 +213,103 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         CV_MMA1(xa, 3, B, 2) CV_F                                                                 \
         if (FETCH) { CV_FETCH_NEXT CV_VMCNT(3 + CV_XL) } else { CV_VMCNT(0) }                     \
         __syncthreads();                                                                          \
-    } else {                                                                                      \
-        constexpr int N_ = ((B) + 2) % 3, T_ = MB - 1;                                            \
-        CV_READ1(xa, 0, B, 0) if (MB == 2) CV_READ1(xa, T_, B, 0)                                 \
-        CV_READ1(xb, 0, B, 1) if (MB == 2) CV_READ1(xb, T_, B, 1)                                 \
-        CV_READ1(xc, 0, B, 2) if (MB == 2) CV_READ1(xc, T_, B, 2) CV_F                            \
+    } else if constexpr (MB == 2) {                                                               \
+        constexpr int N_ = ((B) + 2) % 3;                                                         \
+        CV_READ1(xa, 0, B, 0) CV_READ1(xa, 1, B, 0) CV_READ1(xb, 0, B, 1)                         \
+        CV_READ1(xb, 1, B, 1) CV_READ1(xc, 0, B, 2) CV_READ1(xc, 1, B, 2) CV_F                    \
         CV_MMA1(xa, 0, B, 0) CV_F if (FETCH) CV_LOAD_W(N_, 0) CV_F                                \
-        if (MB == 2) CV_MMA1(xa, T_, B, 0) CV_F if (FETCH) CV_LOAD_W(N_, 1) CV_F                  \
+        CV_MMA1(xa, 1, B, 0) CV_F if (FETCH) CV_LOAD_W(N_, 1) CV_F                                \
         CV_MMA1(xb, 0, B, 1) CV_F if (FETCH) CV_LOAD_W(N_, 2) CV_F                                \
-        if (MB == 2) CV_MMA1(xb, T_, B, 1) CV_F if (FETCH) CV_LOAD_X1(N_, 0) CV_F                 \
+        CV_MMA1(xb, 1, B, 1) CV_F if (FETCH) CV_LOAD_X1(N_, 0) CV_F                               \
         CV_MMA1(xc, 0, B, 2) CV_F if (FETCH) CV_LOAD_X1(N_, 2) CV_F                               \
-        if (MB == 2) CV_MMA1(xc, T_, B, 2) CV_F                                                   \
+        CV_MMA1(xc, 1, B, 2) CV_F                                                                 \
         if (FETCH) { CV_FETCH_NEXT CV_VMCNT(3 + CV_XL) } else { CV_VMCNT(0) }                     \
         __syncthreads();                                                                          \
     }
 
+    // The smallest tiles, three MFMAs a stage: three stages between two barriers, out of slabs cur, cur + 1, cur + 2; meanwhile the activations of
+    // the stage six ahead start their way into slab far + B, which every wavefront has left behind the barrier.  A barrier and the first
+    // reads behind it take longer than such a stage's MFMAs.  Calls, a barrier a stage -> this: 16 x 24 cells, 64 channels, 4 steps
+    // 150.5 -> 148.5 us; 30 x 53, 256 -> 128 -> 128 209.2 -> 207.9, forward 22.7 -> 22.5; 60 x 107, 96 -> 48 -> 48 206.1 -> 204.4.  (Tiles of 64
+    // positions lost 1 % that way: 60 x 107 cells, 256 -> 128 -> 128, forward 23.2 -> 23.5.  Their first barrier waits for three slabs.)
+#define CV_SMALL(B, FETCH_W, FETCH_X)                                                             \
+    {                                                                                             \
+        constexpr int N_ = ((B) + 2) % 3;                                                         \
+        CV_READ1(xa, 0, cur + B, 0) CV_READ1(xb, 0, cur + B, 1) CV_READ1(xc, 0, cur + B, 2) CV_F  \
+        CV_MMA1(xa, 0, B, 0) CV_F                                                                 \
+        if (FETCH_W) { CV_LOAD_W(N_, 0) CV_LOAD_W(N_, 1) } CV_F                                   \
+        CV_MMA1(xb, 0, B, 1) CV_F                                                                 \
+        if (FETCH_W) CV_LOAD_W(N_, 2) if (FETCH_X) CV_LOAD_X1(far + B, 0) CV_F                    \
+        CV_MMA1(xc, 0, B, 2) CV_F                                                                 \
+        if (FETCH_X) CV_LOAD_X1(far + B, 2) CV_F                                                  \
+        if (FETCH_W) { CV_W_NEXT }                                                                \
+        if (FETCH_X) { CV_X_NEXT }                                                                \
+    }
+
     bf16x8 xa[MB], xb[MB], xc[MB];
-    {
-        // (activations first: the barrier waits for those of the first stage alone, everything but the loads behind them)
-        CV_LOAD_X1(0, 0) CV_LOAD_X1(0, 1) CV_LOAD_X1(0, 2)
-        CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2)
-        CV_FETCH_NEXT
-        CV_LOAD_X1(1, 0) CV_LOAD_X1(1, 1) CV_LOAD_X1(1, 2)
-        CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2)
-        CV_FETCH_NEXT
-        CV_F
-        CV_VMCNT(6 + CV_XL)
-        __syncthreads();
-    }
-    // the number of stages is a multiple of three (three kernel rows): three stages per trip make
-    // the LDS slab and the weight register set of every stage compile-time choices.  The last
-    // three stages are written out: only the first of them still has something to fetch.
-    for (int s = 0; s + 3 < n_stages; s += 3) {
+    int cur = 0;             // first slab in use (other tiles: stays, their slabs rotate by number)
+    if constexpr (MB > 1) {
+        {
+            // (activations first: the barrier waits for those of the first stage alone, everything but the loads behind them)
+            CV_LOAD_X1(0, 0) CV_LOAD_X1(0, 1) CV_LOAD_X1(0, 2)
+            CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2)
+            CV_FETCH_NEXT
+            CV_LOAD_X1(1, 0) CV_LOAD_X1(1, 1) CV_LOAD_X1(1, 2)
+            CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2)
+            CV_FETCH_NEXT
+            CV_F
+            CV_VMCNT(6 + CV_XL)
+            __syncthreads();
+        }
+        // the number of stages is a multiple of three (three kernel rows): three stages per trip make
+        // the LDS slab and the weight register set of every stage compile-time choices.  The last
+        // three stages are written out: only the first of them still has something to fetch.
+        for (int s = 0; s + 3 < n_stages; s += 3) {
+            CV_STAGE(0, true)
+            CV_STAGE(1, true)
+            CV_STAGE(2, true)
+        }
         CV_STAGE(0, true)
-        CV_STAGE(1, true)
-        CV_STAGE(2, true)
+        CV_STAGE(1, false)
+    } else {
+        const int trips = c_chunks;       // (three stages each)
+        int far = 6;
+        {
+            CV_LOAD_X1(0, 0) CV_LOAD_X1(0, 2) CV_X_NEXT
+            CV_LOAD_X1(1, 0) CV_LOAD_X1(1, 2) CV_X_NEXT
+            CV_LOAD_X1(2, 0) CV_LOAD_X1(2, 2) CV_X_NEXT
+            CV_LOAD_W(0, 0) CV_LOAD_W(0, 1) CV_LOAD_W(0, 2) CV_W_NEXT
+            CV_LOAD_W(1, 0) CV_LOAD_W(1, 1) CV_LOAD_W(1, 2) CV_W_NEXT
+            CV_F
+            if (trips > 1) {
+                CV_LOAD_X1(3, 0) CV_LOAD_X1(3, 2) CV_X_NEXT
+                CV_LOAD_X1(4, 0) CV_LOAD_X1(4, 2) CV_X_NEXT
+                CV_LOAD_X1(5, 0) CV_LOAD_X1(5, 2) CV_X_NEXT
+                CV_VMCNT(6 + 3 * CV_XL)
+            } else { CV_VMCNT(6) }
+            __syncthreads();
+        }
+        for (int t = 0; t + 2 < trips; ++t) {
+            CV_SMALL(0, true, true)
+            CV_SMALL(1, true, true)
+            CV_SMALL(2, true, true)
+            // (what follows the next three stages' activations: nine weight fragments and three stages' activations)
+            CV_VMCNT(9 + 3 * CV_XL)
+            __syncthreads();
+            far = cur;
+            cur = cur == 6 ? 0 : cur + 3;
+        }
+        if (trips > 1) {
+            CV_SMALL(0, true, false)
+            CV_SMALL(1, true, false)
+            CV_SMALL(2, true, false)
+            CV_VMCNT(9)
+            __syncthreads();
+            cur = cur == 6 ? 0 : cur + 3;
+        }
+        CV_SMALL(0, true, false)
+        CV_SMALL(1, false, false)
     }
-    CV_STAGE(0, true)
-    CV_STAGE(1, false)
     // The last stage takes one accumulator tile behind the other, the tiles of other owners first, so that a finished tile is on its way
     // to LDS while the next one's MFMAs run.  (With the order of the first loads and the transposing reads below, launches before -> now: 90 x 160
     // cells, 256 -> 128 -> 128 13.2 -> 12.6, 9.6 -> 9.0, 9.6 -> 8.6 us; 60 x 107 11.6 -> 10.8, 8.05 -> 7.1.)
@@ -292,7 +355,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         CV_MMA1(xc, 0, 2, 2) CV_F
         CV_HAND(2, 0, 2)
     } else {
-        CV_READ1(xa, 0, 2, 0) CV_READ1(xb, 0, 2, 1) CV_READ1(xc, 0, 2, 2) CV_F
+        CV_READ1(xa, 0, cur + 2, 0) CV_READ1(xb, 0, cur + 2, 1) CV_READ1(xc, 0, cur + 2, 2) CV_F
         CV_MMA1(xa, 0, 2, 0)
         CV_MMA1(xb, 0, 2, 1)
         CV_MMA1(xc, 0, 2, 2)
@@ -302,7 +365,10 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     }
 #undef CV_HAND
 #undef CV_STAGE
+#undef CV_SMALL
 #undef CV_FETCH_NEXT
+#undef CV_W_NEXT
+#undef CV_X_NEXT
 #undef CV_LOAD_X1
 #undef CV_LOAD_W
 #undef CV_DMA

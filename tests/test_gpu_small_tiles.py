@@ -14,10 +14,10 @@ def blocks(n, h, w, bm, cout):
 
 
 # heads whose layers alone run tiles of 32 positions, of 64, and of both; one and a few tiles, ends inside a tile (1400 and 2480 positions are
-# no multiple of 32), the fewest stages, padded channels
+# no multiple of 32), the fewest stages, padded channels; on tiles of 32, whose slabs rotate three stages at a time, one to seven turns
 @pytest.mark.parametrize("h,w,c_in,c1,c2,C", [(1, 1, 64, 64, 64, 3), (33, 35, 64, 64, 64, 7), (29, 78, 64, 64, 128, 6), (33, 38, 64, 128, 64, 11), (2, 6, 64, 128, 64, 9), (2, 7, 128, 64, 128, 12), (6, 22, 192, 64, 64, 19),
                                               (16, 24, 64, 64, 64, 32), (30, 53, 256, 128, 128, 19), (45, 80, 256, 128, 128, 5),
-                                              (60, 107, 96, 128, 128, 9), (68, 118, 64, 64, 128, 21)])
+                                              (60, 107, 96, 128, 128, 9), (68, 118, 64, 64, 128, 21), (9, 22, 320, 64, 64, 4), (5, 14, 448, 384, 64, 8)])
 def test_a_frame_alone_is_a_frame_of_a_batch(h, w, c_in, c1, c2, C):
     import torch
     gen = torch.Generator(device="cuda")
