@@ -38,7 +38,9 @@ __device__ __forceinline__ unsigned internal_index(const ParamOffsets& po, FastD
     const bool one = x < (unsigned)po.b1;
     if (!one && !(x >= (unsigned)po.W2 && x < (unsigned)po.b2)) return x;
     const unsigned base = one ? 0u : (unsigned)po.W2;
-    const FastDiv by_in = one ? by_in1 : by_in2;
+    // (Chosen word by word: chosen as a whole it went through scratch memory, and the launch that closes a call took that much longer:
+    //  key frame at 90 x 160 cells 547.2 -> 545.5 us and 587.9 -> 583.2 on two cards, with Adam's state 556.7 -> 552.7 and 600.5 -> 592.5)
+    const FastDiv by_in = {one ? by_in1.d : by_in2.d, one ? by_in1.m : by_in2.m};
     const unsigned oi = (x - base) / 9u, tap = x - base - oi * 9u;
     const unsigned o = (unsigned)fast_quot((int)oi, by_in), i = oi - o * by_in.d;
     return base + (o * 9u + tap) * by_in.d + i;
