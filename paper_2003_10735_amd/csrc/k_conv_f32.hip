@@ -629,7 +629,6 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
     const Wgrad32Args& a = second ? a2 : a1;
     const int bid = second ? blockIdx.x - blocks1 : blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, lhi = lane >> 5;
     const int tiles = a.o_tiles * a.i_tiles;
     const int item = (bid % 8) * a.items_per_xcd + bid / 8;
     if (bid / 8 >= a.items_per_xcd || item >= tiles * a.splits) return;
@@ -646,12 +645,14 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
     const int u0 = (split * 4 + wave) * a.units_per_wave, u1 = min(u0 + a.units_per_wave, a.n_units);
     if (u0 < u1) {
         // (channels beyond the last group re-read it: their sums are dropped at the end)
-        const float* yp = a.dY + ((size_t)min((o0 + l32) >> 3, a.GY - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
-        const float* xp = a.X + ((size_t)min((i0 + l32) >> 3, a.GX - 1) * a.PPT + a.guard + (size_t)u0 * 16 + lhi * 8) * 8 + (l32 & 7);
+        auto operand = [&](const float* base, int c0, int runs, int lane) __attribute__((always_inline)) {
+            const int l32 = lane & 31;
+            return base + ((size_t)min((c0 + l32) >> 3, runs - 1) * a.PPT + a.guard + (size_t)u0 * 16 + (lane >> 5) * 8) * 8 + (l32 & 7);
+        };
         const ptrdiff_t xrow = (ptrdiff_t)a.Wp * 8;
         // raw values of two units: positions - 1 .. 8 of dY, 0 .. 7 of X in the three rows
         float ry[2][10], rx[2][3][8];
-        const float* yl = yp; const float* xl = xp;        // the unit in work
+        const float *yl = operand(a.dY, o0, a.GY, lane), *xl = operand(a.X, i0, a.GX, lane);        // the unit in work
         auto load_y = [&](int s, int ahead, int e) __attribute__((always_inline)) { ry[s][e] = yl[ahead * 128 + (e - 1) * 8]; };
         auto load_x = [&](int s, int ahead, int kh, int e) __attribute__((always_inline)) { rx[s][kh][e] = xl[(kh - 1) * xrow + ahead * 128 + e * 8]; };
         // Fragments: of dY for the unit in work and the next [dY at p + 1, p, p - 1][plane]; of X [kernel row][plane] for the unit in work,
@@ -759,14 +760,22 @@ __global__ void __launch_bounds__(256, 1) k_wgrad3x3_f32(Wgrad32Args a1, Wgrad32
                 acc[t][r] = (acc[t][r] + rest[t][r]) * F32_SPLIT_BACK;
                 finite = __builtin_fmaf(acc[t][r], 0.f, finite);
             }
-        if (__builtin_expect(__ballot(finite != 0.f) != 0, 0)) wgrad_f32_plain(yp, xp, xrow, u1 - u0, acc);
+        if (__builtin_expect(__ballot(finite != 0.f) != 0, 0)) {
+            // (Where the operands begin is found anew: kept over the loop it was kept in scratch memory, 52 bytes a lane.  68 x 120 cells, 256 -> 128 ->
+            //  128 channels 663.7 -> 659.6 us a call of four steps, 135 x 240 cells, 64 channels 795.6 -> 791.9)
+            int again = threadIdx.x & 63;
+            asm volatile("" : "+v"(again));
+            wgrad_f32_plain(operand(a.dY, o0, a.GY, again), operand(a.X, i0, a.GX, again), xrow, u1 - u0, acc);
+        }
     }
     float* redb = red + 4 * 9 * 32 * 32;
     bsum += __shfl_xor(bsum, 32, 64);
-    if (lhi == 0) redb[wave * 32 + l32] = bsum;
+    int tid2 = threadIdx.x;
+    asm volatile("" : "+v"(tid2));       // (the same once more)
+    if ((tid2 & 32) == 0) redb[(tid2 >> 6) * 32 + (tid2 & 31)] = bsum;
     wgrad_reduce_store<true>(acc, red, a.dW + (size_t)split * a.split_stride, o0, i0, a.cout, a.cin);
-    if (i0 == 0 && tid < 32 && o0 + tid < a.cout)
-        a.db[(size_t)split * a.split_stride + o0 + tid] = ((redb[tid] + redb[32 + tid]) + redb[64 + tid]) + redb[96 + tid];
+    if (i0 == 0 && tid2 < 32 && o0 + tid2 < a.cout)
+        a.db[(size_t)split * a.split_stride + o0 + tid2] = ((redb[tid2] + redb[32 + tid2]) + redb[64 + tid2]) + redb[96 + tid2];
 }
 
 // The same by the float32 instruction, for frames that leave a wavefront few positions: there a launch is what comes before and behind the
