@@ -50,6 +50,8 @@ struct UpdateArgs {
     // block ranges; vec: role (1) handles four parameters per thread over [0, W3).  (When a call opens, the blocks behind
     // nb_main handle [W3, total) one by one.)
     int nb_main, nb_l3, nb_finish, vec;
+    // role (1) by tiles of 32 x 32 weights under one tap (tiled_block): blocks of W1 and of W2, input-channel tiles of either
+    int tiled, nb_t1, nb_t2; FastDiv by_it1, by_it2;
     // several heads (blockIdx.y): floats / elements from one head's block to the next in the
     // parameter-like vectors (theta, vel, vel2), the caller's vectors, the partial gradients,
     // the bfloat16 copies and the layer-3 slots
@@ -187,6 +189,37 @@ __device__ __forceinline__ void apply_update(const UpdateArgs& a, unsigned j, fl
     }
 }
 
+// One step of four consecutive parameters; their new values.
+template <bool EE>
+__device__ __forceinline__ f32x4 step4(const UpdateArgs& a, unsigned j, f32x4 g, const Held<f32x4>& h)
+{
+    f32x4 w = h.w;
+    if (EE && a.save_old) *(f32x4*)(a.save_old + j) = w;
+    if (a.adam) {
+        f32x4 m, v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            m[e] = __builtin_fmaf(a.ad.beta1, h.m[e], a.ad.one_minus_beta1 * g[e]);
+            v[e] = __builtin_fmaf(a.ad.beta2, h.v[e], a.ad.one_minus_beta2 * (g[e] * g[e]));
+            w[e] = w[e] - a.ad.step_scale * m[e] / (__fsqrt_rn(v[e]) * a.ad.inv_sqrt_bc2 + a.ad.eps);
+        }
+        *(f32x4*)(a.vel + j) = m;
+        *(f32x4*)(a.vel2 + j) = v;
+    } else {
+        if (a.mu != 0.f) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(a.mu, h.m[e], g[e]);
+            *(f32x4*)(a.vel + j) = v;
+            g = v;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = __builtin_fmaf(-a.lr, g[e], w[e]);
+    }
+    *(f32x4*)(a.theta + j) = w;
+    return w;
+}
+
 // Four consecutive parameters (all block boundaries below W3 are multiples of four here, and so are
 // the channel counts: the four lie in the same block and under the same tap).
 template <bool EE, bool F32, bool OPEN>
@@ -201,30 +234,7 @@ __device__ __forceinline__ void apply_update4(const UpdateArgs& a, unsigned j, f
         if (a.ext_vel2) *(f32x4*)(a.vel2 + j) = f32x4{a.ext_vel2[x[0]], a.ext_vel2[x[1]], a.ext_vel2[x[2]], a.ext_vel2[x[3]]};
         *(f32x4*)(a.theta + j) = w;
     } else {
-        w = h.w;
-        if (EE && a.save_old) *(f32x4*)(a.save_old + j) = w;
-        if (a.adam) {
-            f32x4 m, v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                m[e] = __builtin_fmaf(a.ad.beta1, h.m[e], a.ad.one_minus_beta1 * g[e]);
-                v[e] = __builtin_fmaf(a.ad.beta2, h.v[e], a.ad.one_minus_beta2 * (g[e] * g[e]));
-                w[e] = w[e] - a.ad.step_scale * m[e] / (__fsqrt_rn(v[e]) * a.ad.inv_sqrt_bc2 + a.ad.eps);
-            }
-            *(f32x4*)(a.vel + j) = m;
-            *(f32x4*)(a.vel2 + j) = v;
-        } else {
-            if (a.mu != 0.f) {
-                f32x4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(a.mu, h.m[e], g[e]);
-                *(f32x4*)(a.vel + j) = v;
-                g = v;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = __builtin_fmaf(-a.lr, g[e], w[e]);
-        }
-        *(f32x4*)(a.theta + j) = w;
+        w = step4<EE>(a, j, g, h);
     }
     if (j < a.po.b1) copy_weights<F32>(a, 1, weight3x3(j, a.c_in), {w[0], w[1], w[2], w[3]});
     else if (j < a.po.W2) {
@@ -262,6 +272,46 @@ __device__ __forceinline__ V sum_copies(const float* gp, size_t stride, int spli
     return g;
 }
 
+// Role (1) on tiles (bfloat16 path, channel counts that are multiples of 32): a block takes 32 output x 32 input channels of a 3x3
+// layer under one tap, four input channels per thread.  A wavefront then has eight output channels' 128 bytes of every vector, and
+// leaves whole lines of both operand copies: the forward one as it is (in the order of wfrag_index eight output channels' eight
+// inputs are 128 bytes), the mirrored one, whose runs go over eight output channels, through LDS.  By consecutive parameters the
+// forward copy goes out in pieces of 16 bytes, each line's in eight wavefronts of as many XCDs, and the mirrored one in pieces of
+// two.  Bound by those lines' way to memory: 256 -> 256 -> 256 channels 10.8 -> 7.5 us a launch.
+template <bool EE>
+__device__ __forceinline__ void tiled_block(const UpdateArgs& a, int b)
+{
+    __shared__ __attribute__((aligned(16))) bf16 turn[256 * 4];
+    const int tid = threadIdx.x;
+    if (b >= a.nb_t1 + a.nb_t2) {
+        // the biases, one by one
+        const unsigned x = (unsigned)(b - a.nb_t1 - a.nb_t2) * 256 + tid;
+        if (x >= (unsigned)(a.c1 + a.c2)) return;
+        const unsigned j = x < (unsigned)a.c1 ? (unsigned)a.po.b1 + x : (unsigned)a.po.b2 + (x - a.c1);
+        const Held<float> h = held<float>(a, j);
+        apply_update<EE, false, false>(a, j, sum_copies<float>(a.grad + j, a.stride, x < (unsigned)a.c1 ? a.splits1 : a.splits2), h);
+        return;
+    }
+    const bool one = b < a.nb_t1;
+    const FastDiv by_it = {one ? a.by_it1.d : a.by_it2.d, one ? a.by_it1.m : a.by_it2.m};
+    const int t = one ? b : b - a.nb_t1, q = fast_quot(t, by_it), it = t - q * (int)by_it.d, ot = q / 9, tap = q - ot * 9;
+    const int ci = one ? a.c_in : a.c1, o = ot * 32 + (tid >> 3), i = it * 32 + (tid & 7) * 4;
+    const unsigned j = (one ? 0u : (unsigned)a.po.W2) + (unsigned)((o * 9 + tap) * ci + i);
+    const Held<f32x4> h = held<f32x4>(a, j);
+    const f32x4 w = step4<EE>(a, j, sum_copies<f32x4>(a.grad + j, a.stride, one ? a.splits1 : a.splits2), h);
+    const bf16x4 v = {(bf16)w[0], (bf16)w[1], (bf16)w[2], (bf16)w[3]};
+    *(bf16x4*)((bf16*)(one ? a.wq1 : a.wq2) + wfrag_index(o, tap, i, one ? a.ki : a.k1)) = v;
+    bf16* const bwd = (bf16*)(one ? a.wq1t : a.wq2t);
+    if (!bwd) return;
+    // (a wavefront's own 32 inputs x 8 outputs: no other touches them)
+    bf16* const mine = turn + (tid >> 6) * 256;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mine[((tid & 7) * 4 + e) * 8 + ((tid >> 3) & 7)] = v[e];
+    const int lane = tid & 63;
+    if (lane < 32)
+        *(bf16x8*)(bwd + wfrag_index(it * 32 + lane, 8 - tap, ot * 32 + (tid >> 6) * 8, one ? a.k1 : a.k2)) = *(const bf16x8*)(mine + lane * 8);
+}
+
 // Classifier's role of k_step_end: values per block, and the runs its threads split the slots into.
 constexpr int L3_VALUES = 32, L3_RUNS = 256 / L3_VALUES;
 
@@ -288,8 +338,9 @@ __device__ __forceinline__ float add_slots(float acc, const float* src, size_t s
 }
 
 // (OPEN: as a role of the launch that opens a call: parameters in, operand copies; no other roles, so that the
-//  launch carries none of their LDS)
-template <bool EE, bool F32, bool OPEN>
+//  launch carries none of their LDS.  TILED: role (1) by tiles, a kernel of its own because two kilobytes more of LDS and the
+//  longer code cost the launch that has no tiles 0.1 us)
+template <bool EE, bool F32, bool OPEN, bool TILED = false>
 __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f, int b, int head)
 {
     if (head) {
@@ -307,6 +358,7 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
         if (a.part3) a.part3 += head * a.hs_part3;
     }
     if (b < a.nb_main) {
+        if constexpr (TILED) { tiled_block<EE>(a, b); return; }
         // role (1), four parameters per thread over [0, W3): the partial gradients are added in
         // ascending order of the split, up to eight in flight
         if (a.vec) {
@@ -376,10 +428,10 @@ __device__ __forceinline__ void step_end_block(UpdateArgs a, const FinishArgs& f
     } else finish_block<EE>(f, b - a.nb_main - a.nb_l3, head);
 }
 
-template <bool EE, bool F32>
+template <bool EE, bool F32, bool TILED = false>
 __global__ void __launch_bounds__(256) k_step_end(UpdateArgs a, FinishArgs f)
 {
-    step_end_block<EE, F32, false>(a, f, blockIdx.x, blockIdx.y);
+    step_end_block<EE, F32, false, TILED>(a, f, blockIdx.x, blockIdx.y);
 }
 
 // Bookkeeping of a pass without an update and, behind it, what the call hands back: nb_out blocks per vector -- theta,
@@ -600,6 +652,14 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     // multiple of four
     a.vec = (p.g.c_in % 4 == 0 && p.g.c1 % 4 == 0 && p.g.c2 % 4 == 0) ? 1 : 0;
     a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
+    a.nb_t1 = p.g.c1 / 32 * 9 * (p.g.c_in / 32); a.nb_t2 = p.g.c2 / 32 * 9 * (p.g.c1 / 32);
+    a.by_it1 = fast_div(std::max(p.g.c_in / 32, 1)); a.by_it2 = fast_div(std::max(p.g.c1 / 32, 1));
+    // Tiles pay where they are two or more to each of the 256 CUs (720p with one head, medians in us by consecutive parameters -> by
+    // tiles, SGD unless noted): 360 tiles 5.8 -> 5.95, 504 6.05 -> 6.3, 576 8.2 -> 7.0, 864 6.7 -> 6.5 (320, 256 and 64 channels) and
+    // 8.0 -> 6.6 (192, 256, 128; Adam 9.2 -> 8.6), 1008 10.4 -> 7.1, 1152 10.8 -> 7.5 (Adam 12.9 -> 10.0), 1296 11.9 -> 9.6 (momentum
+    // 13.2 -> 11.0; four frames 19.35 -> 16.2).  Several heads of 360 tiles are not faster for being more: 14.2 -> 14.25 us with four.
+    a.tiled = do_step && p.bf16 && p.g.c_in % 32 == 0 && p.g.c1 % 32 == 0 && p.g.c2 % 32 == 0 && a.nb_t1 + a.nb_t2 >= 512;
+    if (a.tiled) a.nb_main = a.nb_t1 + a.nb_t2 + cdiv(p.g.c1 + p.g.c2, 256);
     const int nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
     a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, L3_VALUES) : 0;
     a.nb_finish = finish ? f.fph + 1 : 0;
@@ -615,7 +675,8 @@ void step_end(Ctx& c, const Plan& p, char* ws, float lr, float mu, const AdamSte
     const int blocks = step_end_args(p, ws, lr, mu, adam, true, finish, nullptr, w1t, f, a, save_old);
     const char* name = adam ? (finish ? "adam_update+finish_pass" : "adam_update") : (finish ? "sgd_update+finish_pass" : "sgd_update");
     auto go = [&](auto kernel) { ST_LAUNCH(c, name, kernel, dim3(blocks, p.g.heads()), dim3(256), 0, a, f); };
-    if (p.bf16) { if (a.save_old) go(k_step_end<true, false>); else go(k_step_end<false, false>); }
+    if (a.tiled) { if (a.save_old) go(k_step_end<true, false, true>); else go(k_step_end<false, false, true>); }
+    else if (p.bf16) { if (a.save_old) go(k_step_end<true, false>); else go(k_step_end<false, false>); }
     else { if (a.save_old) go(k_step_end<true, true>); else go(k_step_end<false, true>); }
 }
 
