@@ -138,8 +138,8 @@ struct Plan {
     bool wgrad_few;         // float32 path: those kernels by the float32 instruction
     int blocks3;            // per-block partial slots (per head) of the layer-3 backward kernel
     int grad_copies;        // max of the splits: partial gradient copies the update sums
-    size_t grad_stride;     // floats between two copies (total rounded up to 16 bytes)
-    size_t head_stride;     // floats between two heads' parameters (total rounded up to 16 bytes)
+    size_t grad_stride;     // floats between two copies (total rounded up to 128 bytes)
+    size_t head_stride;     // floats between two heads' parameters (the same)
     int guard;          // guard rows before and after every position-major activation buffer;
                         // also the number of guard columns in front of a channel-major row
     int PPT;            // row pitch (elements) of the channel-major copies; columns per run of channels (float32)
