@@ -654,11 +654,12 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
     a.nb_t1 = p.g.c1 / 32 * 9 * (p.g.c_in / 32); a.nb_t2 = p.g.c2 / 32 * 9 * (p.g.c1 / 32);
     a.by_it1 = fast_div(std::max(p.g.c_in / 32, 1)); a.by_it2 = fast_div(std::max(p.g.c1 / 32, 1));
-    // Tiles pay where they are two or more to each of the 256 CUs (720p with one head, medians in us by consecutive parameters -> by
-    // tiles, SGD unless noted): 360 tiles 5.8 -> 5.95, 504 6.05 -> 6.3, 576 8.2 -> 7.0, 864 6.7 -> 6.5 (320, 256 and 64 channels) and
+    // Tiles pay where there is one or more to each of the 256 CUs (720p, medians in us by consecutive parameters -> by tiles, SGD unless
+    // noted): 90 tiles 4.6 -> 4.6, 360 5.9 -> 5.7 (momentum 6.6 -> 6.2; four heads of 360, the whole call 1534 -> 1495), 432 8.2 -> 7.1, 504
+    // 6.0 -> 5.7; and before the partial gradients began with whole lines: 576 8.2 -> 7.0, 864 6.7 -> 6.5 (320, 256 and 64 channels) and
     // 8.0 -> 6.6 (192, 256, 128; Adam 9.2 -> 8.6), 1008 10.4 -> 7.1, 1152 10.8 -> 7.5 (Adam 12.9 -> 10.0), 1296 11.9 -> 9.6 (momentum
-    // 13.2 -> 11.0; four frames 19.35 -> 16.2).  Several heads of 360 tiles are not faster for being more: 14.2 -> 14.25 us with four.
-    a.tiled = do_step && p.bf16 && p.g.c_in % 32 == 0 && p.g.c1 % 32 == 0 && p.g.c2 % 32 == 0 && a.nb_t1 + a.nb_t2 >= 512;
+    // 13.2 -> 11.0; four frames 19.35 -> 16.2).
+    a.tiled = do_step && p.bf16 && p.g.c_in % 32 == 0 && p.g.c1 % 32 == 0 && p.g.c2 % 32 == 0 && a.nb_t1 + a.nb_t2 >= 256;
     if (a.tiled) a.nb_main = a.nb_t1 + a.nb_t2 + cdiv(p.g.c1 + p.g.c2, 256);
     const int nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);
     a.nb_l3 = do_step ? cdiv(p.g.C * p.g.c2 + p.g.C, L3_VALUES) : 0;

@@ -1,4 +1,4 @@
-"""The optimiser's launch on tiles of 32 x 32 weights (large heads whose channel counts are multiples of 32): every parameter gets its own
+"""The optimiser's launch on tiles of 32 x 32 weights (heads of 256 tiles or more whose channel counts are multiples of 32): every parameter gets its own
 gradient, once, and the products' copies of the weights are the ones that the next call's opening launch makes of the parameters."""
 import pytest
 import torch
@@ -8,9 +8,10 @@ import paper_2003_10735_amd as st
 
 pytestmark = pytest.mark.gpu
 
-# c_in, c1, c2, heads: rows of one tile, channel counts short of a fragment of 64, more output than input channels and the reverse; and, for the
-# same checks on the way by consecutive parameters, one tile row too few and a channel count that is no multiple of 32
-SHAPES = [(32, 256, 256, 1), (256, 224, 32, 1), (352, 160, 32, 1), (160, 224, 96, 1), (256, 256, 256, 1), (64, 256, 256, 3), (224, 224, 32, 1), (264, 256, 64, 1)]
+# c_in, c1, c2, heads: rows of one tile, channel counts short of a fragment of 64, more output than input channels and the reverse, 270 tiles; and,
+# for the same checks on the way by consecutive parameters, 252 tiles and a channel count that is no multiple of 32
+SHAPES = [(32, 256, 256, 1), (256, 224, 32, 1), (352, 160, 32, 1), (160, 224, 96, 1), (256, 256, 256, 1), (64, 256, 256, 3), (224, 224, 32, 1), (128, 160, 64, 1),
+          (256, 128, 128, 2), (128, 128, 96, 1), (264, 256, 64, 1)]
 
 
 @pytest.mark.parametrize("c_in,c1,c2,n", SHAPES)
