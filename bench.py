@@ -46,27 +46,27 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # the kernel source it was measured on:
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
-    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 37.02, 8.83),
-    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 13.74, 6.34),
-    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 6.97, 4.92),
-    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "23c21848a7e738fa735e6456e7b5310c0dabd0b7cb6c58b94d2361eb5b8957e2", 10.70, 3.77),
+    ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "c752d04ee658089e8af3755a287c56e17a35bf7842e802f2732b870d038bd08b", 37.01, 8.44),
+    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 13.74, 6.34),
+    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 7.72, 4.92),
+    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 10.70, 3.77),
     ("720p", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 4.69, 4.71),
     ("720p", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 3.08, 1.79),
-    ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 13.19, 9.81),
-    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 79.87, 8.83),
-    ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 23.24, 13.93),
-    ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 11.78, 10.82),
-    ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 20.01, 8.29),
+    ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "94f6403c91f21b1005d6dea0535c3a66c16126ec0879e6eb9555187c42a8242b", 8.71, 9.81),
+    ("1080p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "c752d04ee658089e8af3755a287c56e17a35bf7842e802f2732b870d038bd08b", 79.81, 8.44),
+    ("1080p", "conv1_fwd_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 23.24, 13.93),
+    ("1080p", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 12.13, 10.82),
+    ("1080p", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 20.01, 8.29),
     ("1080p", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 10.02, 11.14),
     ("1080p", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 6.45, 4.02),
-    ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 27.54, 21.56),
-    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "115f0a2eb00abbb3dc69da1578a0f14a6729d4e6bfe3e6182a1d8097dcbaf493", 273.25, 17.88),
-    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 70.19, 54.34),
-    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 53.08, 46.79),
-    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "e054b6e67bbc3037d01854d2c195332b060f718e5fa57dab255675a8e4ba0f6a", 86.74, 30.19),
+    ("1080p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "94f6403c91f21b1005d6dea0535c3a66c16126ec0879e6eb9555187c42a8242b", 19.41, 21.56),
+    ("batch4", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "c752d04ee658089e8af3755a287c56e17a35bf7842e802f2732b870d038bd08b", 271.51, 17.44),
+    ("batch4", "conv1_fwd_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 54.89, 54.34),
+    ("batch4", "conv2_fwd_logits_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 47.64, 46.79),
+    ("batch4", "conv2_dgrad_mfma"): ("k_conv_wide.hip", "dbf505eea9d1b3ebd1c062abac668479f01d3c76892a5e7a2f5c104b0024a041", 80.89, 30.19),
     ("batch4", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 30.10, 22.19),
     ("batch4", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 23.43, 7.61),
-    ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "acb4d06d14fa8f3614b7555cfbedd92da85c7a73a080c73e2c6c7b2cde7080f3", 71.41, 80.27),
+    ("batch4", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "94f6403c91f21b1005d6dea0535c3a66c16126ec0879e6eb9555187c42a8242b", 50.09, 80.27),
 }
 
 
