@@ -208,7 +208,8 @@ int st_head_forward(const st_head_desc* desc, const void* features, const float*
  * 75 MiB).  The call allocates nothing, on the device or through any library; shapes that need more are
  * refused with ST_ERR_TOO_LARGE before any GPU work.  What counts is
  *   bfloat16 heads with c_in and c1 multiples of 64 and c2 one of 64, 128, 256: st_workspace_bytes(desc),
- *     but for 4 bytes per cell row and 32 columns of every frame;
+ *     but for 4 bytes per cell row and 32 columns of every frame, and with every partial gradient and
+ *     every head's parameters rounded up to 16 bytes, where a training call has them at 128;
  *   any other head: the buffers of the forward pass on the padded channels and, where those exceed the
  *     limit too, the activations and logits at the head's own sizes,
  *     n*h*w*(c1 + c2) elements and n*(h+2)*(w+9)*(n_classes+3) floats at most: such calls run on

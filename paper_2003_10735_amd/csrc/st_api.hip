@@ -193,8 +193,10 @@ Plan make_plan(const st_head_desc& d, PlanKind kind)
     p.g_slots = train_take(loss_slot_floats(g) * 4);
     // whole lines: 32 weights of a row then begin with a line in every copy and every head, where the weight-gradient launch leaves
     // such rows past the L2 cache and the optimiser's launch reads them.  (Rounded to 16 bytes each such row lay in two lines of all copies
-    // but the first: 720p key frame 536.4 -> 532.1 us, four clients 1548 -> 1532, batch of four 7172 -> 7141.)
-    p.grad_stride = (p.po.total + 31) / 32 * 32;
+    // but the first: 720p key frame 536.4 -> 532.1 us, four clients 1548 -> 1532, batch of four 7172 -> 7141.)  A forward pass has neither
+    // reader nor writer of that kind, and its plan is what decides whether a call fits the built-in scratch: 16 bytes there.
+    const size_t floats = kind == PLAN_FULL ? 32 : 4;
+    p.grad_stride = (p.po.total + floats - 1) / floats * floats;
     p.head_stride = p.grad_stride;
     p.theta = take(off, heads * p.head_stride * 4);
     p.vel = train_take(heads * p.head_stride * 4);

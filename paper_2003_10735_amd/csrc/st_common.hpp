@@ -138,7 +138,7 @@ struct Plan {
     bool wgrad_few;         // float32 path: those kernels by the float32 instruction
     int blocks3;            // per-block partial slots (per head) of the layer-3 backward kernel
     int grad_copies;        // max of the splits: partial gradient copies the update sums
-    size_t grad_stride;     // floats between two copies (total rounded up to 128 bytes)
+    size_t grad_stride;     // floats between two copies (total rounded up to 128 bytes; plans of a forward pass: 16)
     size_t head_stride;     // floats between two heads' parameters (the same)
     int guard;          // guard rows before and after every position-major activation buffer;
                         // also the number of guard columns in front of a channel-major row
@@ -159,8 +159,9 @@ struct Plan {
     size_t total;
 };
 
-// PLAN_FORWARD: the offsets of the full plan, with those of buffers that only training needs set to 0
-// (absent), so that no kernel fills them.  PLAN_COMPACT: the same buffers without room for the others.
+// PLAN_FORWARD: room for the buffers of the full plan, with the offsets of those that only training needs set to 0
+// (absent), so that no kernel fills them; heads and partial gradients 16 bytes apart.  PLAN_COMPACT: the same buffers without room for
+// the others.
 enum PlanKind { PLAN_FULL, PLAN_FORWARD, PLAN_COMPACT };
 Plan make_plan(const st_head_desc& d, PlanKind kind = PLAN_FULL);
 

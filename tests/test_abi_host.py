@@ -212,6 +212,23 @@ def test_what_the_built_in_scratch_takes(shape, fits):
     assert st.lib().st_head_forward_noalloc(C.byref(d), dummy, dummy, None, None, None) == (st.ST_ERR_NO_DEVICE if fits else st.ST_ERR_TOO_LARGE)
 
 
+# (n, c_in, h, w, c1, c2, classes, grouped): the last shape that fits, and the first that does not -- one cell row, one head or eight columns
+# (the pitch of a row) more.  Those that fit do so by less than what their parameter vectors, rounded up to whole cache lines, would add.
+@pytest.mark.parametrize("shape,more", [
+    ((1, 256, 21, 1520, 64, 64, 7, 0), (1, 256, 21, 1528, 64, 64, 7, 0)), ((1, 128, 53, 889, 64, 64, 5, 0), (1, 128, 54, 889, 64, 64, 5, 0)),
+    ((1, 128, 3, 3438, 256, 64, 22, 0), (1, 128, 3, 3446, 256, 64, 22, 0)), ((3, 128, 31, 208, 64, 256, 10, 1), (3, 128, 32, 208, 64, 256, 10, 1)),
+    ((20, 64, 6, 11, 64, 256, 13, 1), (21, 64, 6, 11, 64, 256, 13, 1)), ((36, 64, 54, 2, 64, 64, 14, 1), (37, 64, 54, 2, 64, 64, 14, 1)),
+    ((25, 64, 20, 1, 128, 64, 10, 1), (25, 64, 21, 1, 128, 64, 10, 1))])
+def test_the_layout_of_training_does_not_move_the_scratch_limit(shape, more):
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch kernels on dummy pointers")
+    dummy = C.c_void_p(256)
+    for (n, c_in, h, w, c1, c2, classes, grouped), want in ((shape, st.ST_ERR_NO_DEVICE), (more, st.ST_ERR_TOO_LARGE)):
+        d = st.HeadDesc(n, c_in, h, w, c1, c2, classes, compute=st.ST_COMPUTE_BF16, feat_dtype=st.ST_BF16, grouped=grouped).c()
+        assert st.lib().st_head_forward_noalloc(C.byref(d), dummy, dummy, None, None, None) == want
+
+
 def test_layout_names_no_buffer_that_nothing_writes():
     """d loss / d z is assembled on the float32 path only."""
     for compute in (st.ST_COMPUTE_F32, st.ST_COMPUTE_BF16):
