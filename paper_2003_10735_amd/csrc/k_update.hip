@@ -303,10 +303,14 @@ __device__ __forceinline__ void tiled_block(const UpdateArgs& a, int b)
     *(bf16x4*)((bf16*)(one ? a.wq1 : a.wq2) + wfrag_index(o, tap, i, one ? a.ki : a.k1)) = v;
     bf16* const bwd = (bf16*)(one ? a.wq1t : a.wq2t);
     if (!bwd) return;
-    // (a wavefront's own 32 inputs x 8 outputs: no other touches them)
+    // (a wavefront's own 32 inputs x 8 outputs: no other touches them.  Its lanes read what others of them wrote, LDS serves a wavefront in
+    //  order: what lies between keeps the compiler to that order and is no instruction)
     bf16* const mine = turn + (tid >> 6) * 256;
 #pragma unroll
     for (int e = 0; e < 4; ++e) mine[((tid & 7) * 4 + e) * 8 + ((tid >> 3) & 7)] = v[e];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int lane = tid & 63;
     if (lane < 32)
         *(bf16x8*)(bwd + wfrag_index(it * 32 + lane, 8 - tap, ot * 32 + (tid >> 6) * 8, one ? a.k1 : a.k2)) = *(const bf16x8*)(mine + lane * 8);

@@ -26,10 +26,10 @@ def test_tiled_update(c_in, c1, c2, n):
     p = torch.cat([torch.randn(s, generator=gen, device="cuda").flatten() * ((2.0 / s[1:].numel()) ** 0.5 if len(s) > 1 else 0.1)
                    for _ in range(n) for s in map(torch.Size, shapes)])
 
-    def run(parts, adam):
+    def run(parts, adam, grad=None):
         x, a, b, t = p.clone(), torch.zeros_like(p), torch.zeros_like(p), 0
         for k in parts:
-            st.st_partial_distill(d, f, lab, x, k, lr, **(dict(adam=dict(m=a, v=b, t0=t)) if adam else dict(momentum=0.9, velocity=a)))
+            st.st_partial_distill(d, f, lab, x, k, lr, feature_grad=grad, **(dict(adam=dict(m=a, v=b, t0=t)) if adam else dict(momentum=0.9, velocity=a)))
             t += k
         return x, a, b
 
@@ -39,6 +39,13 @@ def test_tiled_update(c_in, c1, c2, n):
             assert torch.equal(u, v)
 
     if n == 1:
+        # the same with the gradient of the features in the last step: its product reads the mirrored copy of layer 1, which no other call has
+        for adam in (False, True):
+            two, one = (torch.zeros((n, c_in, h, w), device="cuda") for _ in range(2))
+            for u, v in zip(run((2,), adam, two), run((1, 1), adam, one)):
+                assert torch.equal(u, v)
+            assert torch.equal(two, one) and one.abs().max() > 0
+
         # with a look at the metric behind every step, which keeps the parameters before the update: the same, and the best ones are some step's
         y, a, best = p.clone(), torch.zeros_like(p), torch.empty_like(p)
         r = st.st_partial_distill(d, f, lab, y, 2, lr, momentum=0.9, velocity=a, threshold=0.9999, best_params=best)
