@@ -26,10 +26,10 @@ def test_tiled_update(c_in, c1, c2, n):
     p = torch.cat([torch.randn(s, generator=gen, device="cuda").flatten() * ((2.0 / s[1:].numel()) ** 0.5 if len(s) > 1 else 0.1)
                    for _ in range(n) for s in map(torch.Size, shapes)])
 
-    def run(parts, adam, grad=None):
+    def run(parts, adam):
         x, a, b, t = p.clone(), torch.zeros_like(p), torch.zeros_like(p), 0
         for k in parts:
-            st.st_partial_distill(d, f, lab, x, k, lr, feature_grad=grad, **(dict(adam=dict(m=a, v=b, t0=t)) if adam else dict(momentum=0.9, velocity=a)))
+            st.st_partial_distill(d, f, lab, x, k, lr, **(dict(adam=dict(m=a, v=b, t0=t)) if adam else dict(momentum=0.9, velocity=a)))
             t += k
         return x, a, b
 
@@ -39,13 +39,6 @@ def test_tiled_update(c_in, c1, c2, n):
             assert torch.equal(u, v)
 
     if n == 1:
-        # the same with the gradient of the features in the last step: its product reads the mirrored copy of layer 1, which no other call has
-        for adam in (False, True):
-            two, one = (torch.zeros((n, c_in, h, w), device="cuda") for _ in range(2))
-            for u, v in zip(run((2,), adam, two), run((1, 1), adam, one)):
-                assert torch.equal(u, v)
-            assert torch.equal(two, one) and one.abs().max() > 0
-
         # with a look at the metric behind every step, which keeps the parameters before the update: the same, and the best ones are some step's
         y, a, best = p.clone(), torch.zeros_like(p), torch.empty_like(p)
         r = st.st_partial_distill(d, f, lab, y, 2, lr, momentum=0.9, velocity=a, threshold=0.9999, best_params=best)
@@ -80,3 +73,30 @@ def test_tiled_update(c_in, c1, c2, n):
                 tiles = lambda t: t.reshape(t.shape[0] // 32, 32, t.shape[1] // 32, 32, 9).permute(0, 2, 4, 1, 3).flatten(3).norm(dim=-1)
                 ratio = float((tiles(error) / tiles(q.grad)).max())
                 assert ratio <= 0.25, (k, tuple(q.shape))
+
+
+@pytest.mark.parametrize("c_in,c1,c2", [s[:3] for s in SHAPES if s[3] == 1])
+def test_gradient_of_the_features_in_a_second_step(c_in, c1, c2):
+    """Its product reads the mirrored copy of layer 1's weights that the first step left; a call of its own for the second step makes that copy
+    of the parameters anew: bit for bit the same."""
+    h, w, C, lr = 7, 24, 5, 0.02
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(c_in * 1000 + c2)
+    d = st.HeadDesc(1, c_in, h, w, c1, c2, C, feat_dtype=st.ST_BF16, compute=st.ST_COMPUTE_BF16)
+    f = torch.randn((1, c_in, h, w), generator=gen, device="cuda").clamp(min=0).bfloat16()
+    lab = torch.randint(0, C, (1, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
+    p = torch.cat([torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5 if b == 0 else torch.zeros(r, device="cuda")
+                   for r, k in ((c1, 9 * c_in), (c2, 9 * c1), (C, c2)) for b in (0, 1)])
+
+    def run(parts, adam):
+        x, a, b, t = p.clone(), torch.zeros_like(p), torch.zeros_like(p), 0
+        grad = torch.zeros((1, c_in, h, w), device="cuda")
+        for k in parts:
+            st.st_partial_distill(d, f, lab, x, k, lr, feature_grad=grad, **(dict(adam=dict(m=a, v=b, t0=t)) if adam else dict(momentum=0.9, velocity=a)))
+            t += k
+        return x, a, b, grad
+
+    for adam in (False, True):
+        two, ones = run((2,), adam), run((1, 1), adam)
+        assert all(torch.equal(u, v) for u, v in zip(two, ones))
+        assert two[3].abs().max() > 0
