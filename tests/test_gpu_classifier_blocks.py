@@ -112,3 +112,34 @@ def test_float32_classifier_backward(n, h, w, c2, C):
     w3, s3 = gm.t() @ inner(a2), gm.abs().t() @ inner(a2).abs()
     assert ((grad[-C * c2 - C:-C].reshape(C, c2) - w3).abs() <= eps * s3 + 1e-38).all()
     assert ((grad[-C:] - gm.sum(0)).abs() <= eps * gm.abs().sum(0) + 1e-38).all()
+
+
+@pytest.mark.parametrize("n,h,w,c2,C", F32_SHAPES)
+def test_float32_classifier_backward_writes_every_cell(n, h, w, c2, C):
+    """Out of a workspace of NaNs: a border cell, a run of channels or a half of a tile that the launch left out would show (the call itself
+    clears the guard columns in front of and behind the positions, and none of these)."""
+    import torch
+    c_in, c1 = 16, 24
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(h * 1000 + w)
+    d = st.HeadDesc(n, c_in, h, w, c1, c2, C, feat_dtype=st.ST_F32, compute=st.ST_COMPUTE_F32)
+    ws = torch.full((st.st_workspace_bytes(d),), 0xFF, dtype=torch.uint8, device="cuda")
+    f = torch.randn((n, c_in, h, w), generator=gen, device="cuda").clamp(min=0)
+    lab = torch.randint(0, C, (n, 8 * h, 8 * w), generator=gen, device="cuda", dtype=torch.int32)
+    params = torch.cat([torch.randn(r * k, generator=gen, device="cuda") * (2.0 / k) ** 0.5 if b == 0 else torch.zeros(r, device="cuda")
+                        for r, k in ((c1, 9 * c_in), (c2, 9 * c1), (C, c2)) for b in (0, 1)])
+    st.st_partial_distill(d, f, lab, params.clone(), 1, 0.0, workspace=ws)
+    torch.cuda.synchronize()
+    lay = st.st_get_workspace_layout(d)
+    Wp, Hp, PP = lay["row_pitch"], h + 2, n * (h + 2) * lay["row_pitch"]
+    guard = (Wp + 2 + 256 + 7) // 8 * 8
+    run = (guard + (PP + 15) // 16 * 16 + guard) * 8
+    k = (c2 + 7) // 8
+    first = lay["da2"] // 4
+    whole = ws.view(torch.float32)
+    da2 = torch.stack([whole[first + r * run:first + r * run + PP * 8].reshape(n, Hp, Wp, 8) for r in range(k)], -2).reshape(n, Hp, Wp, k * 8)
+    assert torch.isfinite(da2).all() and da2[..., :c2].abs().max() > 0
+    border = torch.ones(Hp, Wp, dtype=torch.bool, device="cuda")
+    border[1:h + 1, 1:w + 1] = False
+    assert (da2[:, border] == 0).all()
+    assert (da2[..., c2:] == 0).all()
