@@ -47,9 +47,9 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # (workload, kernel) -> (source file, sha256 of that file at measurement, fetched MiB, written MiB)
 MEASURED_TRAFFIC = {
     ("720p", "conv12_wgrad_mfma"): ("k_wgrad_mfma.hip", "c752d04ee658089e8af3755a287c56e17a35bf7842e802f2732b870d038bd08b", 37.01, 8.44),
-    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 13.74, 6.34),
-    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 7.72, 4.92),
-    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "083b4a40eff5e17a6ab7340f430997de3fe646dacc1ac765717c9058c667c8a6", 10.70, 3.77),
+    ("720p", "conv1_fwd_mfma"): ("k_conv_mfma.hip", "6ef7ee1a0cfc54ed643e534165f644a6f308830fb294d96a09859bdbfe9370d7", 13.74, 6.34),
+    ("720p", "conv2_fwd_logits_mfma"): ("k_conv_mfma.hip", "6ef7ee1a0cfc54ed643e534165f644a6f308830fb294d96a09859bdbfe9370d7", 7.73, 4.92),
+    ("720p", "conv2_dgrad_mfma"): ("k_conv_mfma.hip", "6ef7ee1a0cfc54ed643e534165f644a6f308830fb294d96a09859bdbfe9370d7", 10.70, 3.77),
     ("720p", "upsample_ce_grad"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 4.69, 4.71),
     ("720p", "upsample_ce"): ("k_loss.hip", "3514c6cb2b780416fa86ec0e73e121941555318247c5244d07e9395cb9b2f2b1", 3.08, 1.79),
     ("720p", "conv3_bwd_mfma"): ("k_conv3_mfma.hip", "94f6403c91f21b1005d6dea0535c3a66c16126ec0879e6eb9555187c42a8242b", 8.71, 9.81),

@@ -877,9 +877,12 @@ static Wgrad32Args wgrad_f32_args(const Plan& p, const float* dY, const float* X
 // everything that does not depend on g asked for before it is: a2 on its way to LDS, where both products take it from, and the first
 // tiles of W3.  256 threads that did one product after the other, each with loads of its own behind g: 68 x 120 cells, 256 -> 128 -> 128 channels
 // 673 us a call of four steps, 664 so; 16 x 16 cells, 64 channels 192.7 and 187.0; 90 x 160 cells 1001 and 994, two frames of it 1837 and 1832;
-// 135 x 240 cells, 24 -> 32 -> 24 channels 609 and 603.
+// 135 x 240 cells, 24 -> 32 -> 24 channels 609 and 603.  Wide heads (beyond 256 channels a compute unit has room for one block): 34 x 60 cells,
+// 128 -> 128 -> 256 channels 432 and 425, -> 512 599 and 581; 68 x 120, 64 -> 64 -> 512 813 and 796, 32 -> 32 -> 1100 1349 and 1301; 34 x 60, 32 -> 32 -> 1024 669
+// and 580.  (Of all this the bands per XCD are 0.1 % of a call, at 90 x 160 cells with 64 channels 1 %.)
 constexpr int B32_BP = 64, B32_NT = 512, B32_TILES = 16;
-constexpr int B32_RUN = B32_BP * 32 + 160;      // bytes of a run's positions in LDS: 32 banks on behind position 31, eight banks on from run to run
+constexpr int B32_RUN = B32_BP * 32 + 160;      // bytes of a run's positions in LDS: 32 of the 64 banks on behind position 31, 40 on from run to
+                                                // run, so that the lanes of a dW3 read (four runs, both halves of the positions) have a bank each
 
 template <bool PARTS>       // PARTS: more channels than a block takes
 __global__ void __launch_bounds__(B32_NT, 1)

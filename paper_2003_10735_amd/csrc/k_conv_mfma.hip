@@ -31,6 +31,7 @@
 // tile's rows shifted by kh, plus one on each side) of 128 bytes, their 16-byte chunks swizzled
 // by the row number so that the fragment reads of 16 consecutive rows spread over all banks.  Three
 // slabs and three sets of weight registers rotate: loads run two stages ahead of the matrix cores.
+// (Tiles of 32 positions: nine slabs, a barrier every three stages; activations run six stages ahead, weights two.)
 //
 // A lane owns 4 consecutive output channels of one position per register group, which packs
 // into one 8-byte LDS write in the epilogue.  The epilogue stages the tile in LDS and writes it
@@ -50,7 +51,7 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int CV_BN = 64;
 constexpr int CV_BK = 64;
-constexpr int CV_NBUF = 3;          // activation slabs in LDS: one in use, two on their way
+constexpr int CV_NBUF = 3;          // sets of activation slabs in LDS (ConvLds::PER slabs each): one in use, two on their way
 constexpr int CV_OLD = CV_BN + 8;   // pitch of the staged output tile
 // Tiles of 32 MB positions: 128, or 64 or 32 where those find a compute unit each of their own (conv_tile).
 template <int MB>
@@ -72,7 +73,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     constexpr int BM = ConvLds<MB>::BM, XS_BYTES = ConvLds<MB>::SLAB;
     constexpr int NR = 4 * MB;             // registers (of 16 per 32 x 32 sums) of an owner: a wavefront's MB tiles are four parts
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    // smem_raw during the K loop: [CV_NBUF][BM + 2][128 bytes], chunks swizzled
+    // smem_raw during the K loop: [CV_NBUF * PER][BM + 2][128 bytes], chunks swizzled
 
     // (what the first loads need, in one trip for the arguments: left to itself the compiler asks for some of it only
     //  behind the question whether the block has a tile)
@@ -122,7 +123,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
     // 34 the first four) also fills the two behind BM, all with the same bytes.  (With 130 rows the eight loads cost more: key frame at 90 x 160
     // cells 641 -> 649 us.)
     // The loads are written in assembly: the compiler would order every barrier behind all
-    // outstanding loads of this kind, while the pipeline below needs two stages in flight.
+    // outstanding loads of this kind, while the pipeline below needs two stages or more in flight.
     // (M0 is a reserved register for this compiler: it never allocates a value to it, sets it
     //  right before each instruction of its own that reads it, and rejects it in an asm clobber
     //  list ("inline asm clobber list contains reserved registers: m0") -- so the statement
@@ -145,7 +146,7 @@ __global__ void __launch_bounds__(512) k_conv3x3_mfma(ConvArgs a)
         for (int J = 0; J < MB; ++J)
             rd[kw][J] = (l32 + kw) * 128 + (((kgrp * 2 + lhi) ^ (((l32 + kw) >> 1) & 7)) << 4) + (J ^ (kgrp & (MB - 1))) * 4096;
 
-    // The stage being fetched runs two ahead of the one being multiplied.  Its operands are
+    // The stage being fetched runs two ahead of the one being multiplied (activations of tiles of 32 positions: six).  Its operands are
     // addressed as (scalar base, advanced once per stage) + (per-lane byte offset, fixed), which
     // costs no vector instruction and two scalar ones per stage.
     const char* xsp = (const char*)xg;                                      // activations of the stage

@@ -658,11 +658,16 @@ static int step_end_args(const Plan& p, char* ws, float lr, float mu, const Adam
     a.nb_main = a.vec ? cdiv(p.po.W3 / 4, 256) : cdiv(p.po.W3, 256);
     a.nb_t1 = p.g.c1 / 32 * 9 * (p.g.c_in / 32); a.nb_t2 = p.g.c2 / 32 * 9 * (p.g.c1 / 32);
     a.by_it1 = fast_div(std::max(p.g.c_in / 32, 1)); a.by_it2 = fast_div(std::max(p.g.c1 / 32, 1));
-    // Tiles pay where there is one or more to each of the 256 CUs (720p, medians in us by consecutive parameters -> by tiles, SGD unless
-    // noted): 90 tiles 4.6 -> 4.6, 360 5.9 -> 5.7 (momentum 6.6 -> 6.2; four heads of 360, the whole call 1534 -> 1495), 432 8.2 -> 7.1, 504
-    // 6.0 -> 5.7; and before the partial gradients began with whole lines: 576 8.2 -> 7.0, 864 6.7 -> 6.5 (320, 256 and 64 channels) and
-    // 8.0 -> 6.6 (192, 256, 128; Adam 9.2 -> 8.6), 1008 10.4 -> 7.1, 1152 10.8 -> 7.5 (Adam 12.9 -> 10.0), 1296 11.9 -> 9.6 (momentum
-    // 13.2 -> 11.0; four frames 19.35 -> 16.2).
+    // Tiles where one head has one or more to each of the 256 CUs: there they always pay.  The launch at 720p, medians in us by consecutive
+    // parameters -> by tiles, SGD unless noted: 360 tiles 5.9 -> 5.7 (momentum 6.6 -> 6.2; four heads of 360, the whole call 1534 -> 1495), 432
+    // 8.2 -> 7.1, 504 6.0 -> 5.7.  (Larger heads were measured before partial gradients began with whole lines, which both ways gained by: 576
+    // 8.2 -> 7.0, 864 6.7 -> 6.5 with 320, 256 and 64 channels and 8.0 -> 6.6 with 192, 256 and 128, Adam 9.2 -> 8.6; 1008 10.4 -> 7.1, 1152
+    // 10.8 -> 7.5, Adam 12.9 -> 10.0; 1296 11.9 -> 9.6, momentum 13.2 -> 11.0, four frames 19.35 -> 16.2.)  Below the line they are level for one
+    // head of few tiles and worth 1 to 2 % of a call from some 130 on, or of heads that have as many together; the line does not follow that.
+    // Calls of four steps at 16 x 24 / 45 x 80 / 90 x 160 cells: 18 tiles 146.3 -> 147.1 / 173.3 -> 173.4 / 256.9 -> 255.3, 72 149.2 -> 148.5 /
+    // 177.6 -> 176.4 / 261.5 -> 260.3, 108 153.7 -> 153.9 / 184.1 -> 183.8 / 267.8 -> 267.3, 135 161.3 -> 160.3 / 200.8 -> 199.3 / 290.2 -> 288.0, 162
+    // 162.3 -> 160.2 / 204.5 -> 202.2 / 296.6 -> 294.2, 225 169.1 -> 165.8 / 210.5 -> 208.1 / 353.6 -> 351.7; 315 175.5 -> 171.2 / 219.4 -> 216.8 /
+    // 378.7 -> 378.0; eight heads of 72 166.5 -> 160.6 / 346.5 -> 338.5 / 751 -> 746.
     a.tiled = do_step && p.bf16 && p.g.c_in % 32 == 0 && p.g.c1 % 32 == 0 && p.g.c2 % 32 == 0 && a.nb_t1 + a.nb_t2 >= 256;
     if (a.tiled) a.nb_main = a.nb_t1 + a.nb_t2 + cdiv(p.g.c1 + p.g.c2, 256);
     const int nb_tail = do_step ? 0 : cdiv(p.po.total - p.po.W3, 256);

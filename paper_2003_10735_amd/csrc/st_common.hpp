@@ -25,8 +25,9 @@ __host__ __device__ __forceinline__ int fast_quot(int n, const FastDiv& f)
     return (int)(q + ((unsigned)n - q * f.d >= f.d ? 1u : 0u));
 }
 
-// Which of `n` tiles block `block` of n takes: blocks go to the eight XCDs in turn, and every XCD gets a run of consecutive tiles, the same
-// band of rows in every kernel that orders its tiles so.
+// Which of `n` tiles block `block` of n takes: blocks go to the eight XCDs in turn, and every XCD gets a run of consecutive tiles, about the
+// same band of rows in every kernel that orders its tiles so.  (The loss kernel and the convolutions deal out runs of ceil(n / 8), whose edges
+// lie a few tiles elsewhere; and with a second row of blocks in the grid, n no multiple of eight, that row begins on another XCD.)
 __host__ __device__ __forceinline__ int xcd_band(int block, int n)
 {
     const int xcd = block & 7, rest = n & 7;

@@ -18,7 +18,12 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // moves turns every L2 over between a write and its read).  For whole 128-byte lines of outputs that are large: the logits' shares, rows of
 // 80 bytes in pieces of 16, are dearer this way (4 x 90 x 160 cells 7524 -> 7610 us a call), and where everything a step writes stays in L2 a
 // plain store is the cheaper one (weight gradients of 16 x 16 cells, float32: a call 192 -> 196 us).
-// Key frame at 90 x 160 cells 612 -> 592 us, at 135 x 240 1172 -> 1139, 60 x 107 cells, 96 -> 48 -> 48 channels 210 -> 207.
+// Plain -> this, us a call: key frame at 90 x 160 cells 608 -> 585, at 135 x 240 1171 -> 1137, 4 x 90 x 160 cells, 320 -> 256 -> 256 channels
+// 7483 -> 7410, 60 x 107 cells, 96 -> 48 -> 48 channels 208.7 -> 204.9; calls of four steps at 45 x 80 cells 222.5 -> 218.1 with 128 channels and
+// 188.3 -> 187.5 with 64.  Below that the bfloat16 kernels lose a little by it: 64 channels at 30 x 53 cells 168.5 -> 169.8, 23 x 40 154.7 -> 156.6,
+// 16 x 24 147.4 -> 150.2 (128 channels 169.1 -> 170.0, 256 228.5 -> 228.1).  They have no line by size for it: with plain stores of convolution
+// outputs and classifier gradients of a megabyte or less 16 x 24 cells took 147.7 instead of 148.9, but 43 x 78 with 128 channels 204 instead
+// of 201, and asking for the size in the classifier's backward cost the large grids (135 x 240 cells, four steps 715 -> 719.5).
 __device__ __forceinline__ void store_through(void* base, unsigned off, u32x4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000), (int)off, 0, 16);
